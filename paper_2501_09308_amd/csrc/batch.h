@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "dense_tile.h"
 #include "xrdvi_device.h"
 
 namespace xrdvi {
@@ -14,7 +15,7 @@ constexpr int kMaxSlots = 512;
 // (windowed or dense, symmetric or asymmetric peaks, constant or sec-law
 // width), so that each kernel keeps the register budget of its
 // single-analysis counterpart.
-enum BatchKind { kSample = 0, kWindows, kWindowsSec, kPlan, kPlanSec, kCand,
+enum BatchKind { kSample = 0, kWindows, kWindowsSec, kCand,
                  kFusedWin, kFusedDense, kFusedWinAsym, kFusedDenseAsym,
                  kFusedWinSec, kFusedDenseSec, kFusedWinAsymSec,
                  kFusedDenseAsymSec,
@@ -62,15 +63,14 @@ inline void batch_units(const ProbDev &P, int S, int units[kKinds]) {
     units[kSample] = (int)(S * nkb);
     if (win || sec)
         units[sec ? kWindowsSec : kWindows] = (int)(((long long)S * P.T + 255) / 256);
-    if (!win)   // the windowed forward tile finds its own ranges
-        units[sec ? kPlanSec : kPlan] = (int)(((long long)S * P.ntiles * P.K + 255) / 256);
-    if (win && !sec) {   // ... among candidates found once per step
+    if (win && !sec) {   // the forward's candidates, found once per step
         // the phases' extremes over the samples, 64 phases per unit, run as
         // the window step's first units
         units[kWindows] += (int)nkb;
         units[kCand] = (int)(((long long)P.K + kCandThreads - 1) / kCandThreads) * P.ntiles;
     }
-    units[fused_kind(win, asym, sec)] = P.ntiles * S;
+    const DenseCut cut = dense_cut(P.N, S);
+    units[fused_kind(win, asym, sec)] = win ? P.ntiles * S : cut.tiles(P.N) * cut.groups(S);
     if (win) units[adjoint_kind(asym, sec)] = P.K * S;
     units[kElbo] = 1;
     units[kGrad] = win ? (P.K + kWaves - 1) / kWaves : P.K;   // windowed: a phase per wave

@@ -118,21 +118,6 @@ __global__ __launch_bounds__(256) void kb_windows(const SlotDev *tab,
     }
 }
 
-template <bool SEC>
-__global__ __launch_bounds__(256) void kb_plan(const SlotDev *tab,
-                                               const SchedDev *sch) {
-    __shared__ PrefixSmem ps;
-    load_prefix(sch, SEC ? kPlanSec : kPlan, ps);
-    const int total = uniform(ps.pre[ps.n]);
-    for (int u = blockIdx.x; u < total; u += gridDim.x) {
-        const int i = find_slot(ps, u);
-        const SlotDev &d = slot_entry(tab, ps, i);
-        if (!running(d)) continue;
-        const size_t g = (size_t)local_unit(ps, i, u) * 256 + threadIdx.x;
-        if (g < (size_t)d.st.S * d.P.ntiles * d.P.K) plan_elem<SEC>(d.P, d.st, d.st.phi, g);
-    }
-}
-
 __global__ __launch_bounds__(kCandThreads) void kb_cand(const SlotDev *tab,
                                                         const SchedDev *sch) {
     __shared__ PrefixSmem ps;
@@ -153,14 +138,12 @@ __global__ __launch_bounds__(kCandThreads) void kb_cand(const SlotDev *tab,
 // their LDS allows (80 VGPRs; six 8-byte values are spilled once per block
 // and reloaded once per unit, outside the record loops): their waves wait
 // on memory more than their single-analysis counterpart's.
-template <bool WIN, bool ASYM, bool SEC>
-__global__ __launch_bounds__(kBlock, WIN && !SEC ? 6 : 1) void kb_fused(const SlotDev *tab,
+template <bool ASYM, bool SEC>
+__global__ __launch_bounds__(kBlock, !SEC ? 6 : 1) void kb_win(const SlotDev *tab,
                                                                         const SchedDev *sch) {
-    using Smem = typename std::conditional<WIN, WinSmem<ASYM>,
-                                           FusedSmem>::type;
     __shared__ PrefixSmem ps;
-    __shared__ Smem sm;
-    load_prefix(sch, fused_kind(WIN, ASYM, SEC), ps);
+    __shared__ WinSmem<ASYM> sm;
+    load_prefix(sch, fused_kind(true, ASYM, SEC), ps);
     const int total = uniform(ps.pre[ps.n]);
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
         const int i = find_slot(ps, u);
@@ -168,7 +151,7 @@ __global__ __launch_bounds__(kBlock, WIN && !SEC ? 6 : 1) void kb_fused(const Sl
         if (!running(d)) continue;
         const int local = local_unit(ps, i, u);
         int t = local % d.P.ntiles, s = local / d.P.ntiles;
-        if (WIN && !SEC && d.st.S % kXcds == 0) {
+        if (!SEC && d.st.S % kXcds == 0) {
             // a block runs on XCD u mod 8, and u - local is the same for all
             // of an analysis's units: the units with one value of local mod 8
             // share an XCD, which takes one eighth of the samples of every
@@ -178,16 +161,42 @@ __global__ __launch_bounds__(kBlock, WIN && !SEC ? 6 : 1) void kb_fused(const Sl
             s = (local % kXcds) * G + q % G;
         }
         if (s >= d.st.S) continue;
-        // windowed: forward only (the adjoint is peak-major); dense: fused
-        if constexpr (WIN) {
-            // records in grid steps on a uniform grid (constant width only)
-            if (!SEC && uses_grid_steps(d.P))
-                win_tile<ASYM, SEC, !SEC>(d.P, d.st, t, s, nullptr, sm);
-            else
-                win_tile<ASYM, SEC, false>(d.P, d.st, t, s, nullptr, sm);
-        } else {
-            fused_tile<false, true, ASYM, SEC>(d.P, d.st, t, s, nullptr, sm);
-        }
+        // records in grid steps on a uniform grid (constant width only)
+        if (!SEC && uses_grid_steps(d.P))
+            win_tile<ASYM, SEC, !SEC>(d.P, d.st, t, s, nullptr, sm);
+        else
+            win_tile<ASYM, SEC, false>(d.P, d.st, t, s, nullptr, sm);
+        __syncthreads();
+    }
+}
+
+// Dense fused forward + adjoint, units (tile, sample group) with the groups
+// fastest (a tile's samples run at the same time and share its peaks).
+template <bool ASYM, bool SEC>
+__global__ __launch_bounds__(kDenseWaves * kWave, 4) void kb_dense(const SlotDev *tab,
+                                                                   const SchedDev *sch) {
+    __shared__ PrefixSmem ps;
+    __shared__ union {
+        DenseSmem<kDenseWaves, 4, 4, ASYM, SEC> wide;
+        DenseSmem<kDenseWaves, 4, 2, ASYM, SEC> four;
+        DenseSmem<kDenseWaves, 1, 2, ASYM, SEC> one;
+    } sm;
+    load_prefix(sch, fused_kind(false, ASYM, SEC), ps);
+    const int total = uniform(ps.pre[ps.n]);
+    for (int u = blockIdx.x; u < total; u += gridDim.x) {
+        const int i = find_slot(ps, u);
+        const SlotDev &d = slot_entry(tab, ps, i);
+        if (!running(d)) continue;
+        const int local = local_unit(ps, i, u);
+        const DenseCut cut = dense_cut(d.P.N, d.st.S);
+        const int ng = cut.groups(d.st.S), t = local / ng, grp = local % ng;
+        if (t >= d.st.nt) continue;
+        if (cut.leaves == 4)
+            dense_tile<true, ASYM, SEC, kDenseWaves, 4, 4>(d.P, d.st, t, grp, nullptr, sm.wide);
+        else if (cut.group == 4)
+            dense_tile<true, ASYM, SEC, kDenseWaves, 4, 2>(d.P, d.st, t, grp, nullptr, sm.four);
+        else
+            dense_tile<true, ASYM, SEC, kDenseWaves, 1, 2>(d.P, d.st, t, grp, nullptr, sm.one);
         __syncthreads();
     }
 }
@@ -283,17 +292,15 @@ hipError_t launch_batch_step(const SlotDev *tab, const SchedDev *sch,
     kb_sample<<<kGridSmall, 256, 0, s>>>(tab, sch);
     if (any(1, 0)) kb_windows<false><<<kGridLarge, 256, 0, s>>>(tab, sch);
     if (any(-1, 1)) kb_windows<true><<<kGridLarge, 256, 0, s>>>(tab, sch);
-    if (any(0, 0)) kb_plan<false><<<kGridLarge, 256, 0, s>>>(tab, sch);
-    if (any(0, 1)) kb_plan<true><<<kGridLarge, 256, 0, s>>>(tab, sch);
     if (any(1, 0)) kb_cand<<<kGridLarge, kCandThreads, 0, s>>>(tab, sch);
-    if (has(true, false, false)) kb_fused<true, false, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(false, false, false)) kb_fused<false, false, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(true, true, false)) kb_fused<true, true, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(false, true, false)) kb_fused<false, true, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(true, false, true)) kb_fused<true, false, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(false, false, true)) kb_fused<false, false, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(true, true, true)) kb_fused<true, true, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(false, true, true)) kb_fused<false, true, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
+    if (has(true, false, false)) kb_win<false, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
+    if (has(false, false, false)) kb_dense<false, false><<<kGridLarge, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(true, true, false)) kb_win<true, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
+    if (has(false, true, false)) kb_dense<true, false><<<kGridLarge, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(true, false, true)) kb_win<false, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
+    if (has(false, false, true)) kb_dense<false, true><<<kGridLarge, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(true, true, true)) kb_win<true, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
+    if (has(false, true, true)) kb_dense<true, true><<<kGridLarge, kDenseWaves * kWave, 0, s>>>(tab, sch);
     if (has(true, false, false)) kb_adjoint<false, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
     if (has(true, true, false)) kb_adjoint<true, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
     if (has(true, false, true)) kb_adjoint<false, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);

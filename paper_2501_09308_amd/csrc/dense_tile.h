@@ -1,0 +1,1006 @@
+// Dense mode (c = 0): one (2-theta tile, group of samples) of the fused
+// profile + likelihood + adjoint, with the far Lorentzian tails on nodes.
+//
+// Every peak reaches every point, but a peak whose centre lies at least two
+// half-widths of an interval from its middle, and whose Gaussian does not
+// reach it, is a smooth function there: the interpolant through kNodes
+// Chebyshev nodes of the interval reproduces 1 / (1 + q2^2) to 1.4e-8 of its
+// value at the nearest such centre, and the adjoint's l^2 q2 and l^2 to 1e-7
+// and 4.3e-7, errors falling by 3.7 per node and faster for farther peaks.
+// Two levels of intervals are used: the tile (64 LV points) and its LV leaves
+// of 64 points.  Peaks far from the tile (most of them) are evaluated at the
+// tile's 16 nodes, peaks far from a leaf only at that leaf's 16 nodes, the
+// others at the leaf's points:
+//   forward  node sums of all phases, carried from the tile's nodes to the
+//            leaves' and from those to the points once per (tile, sample);
+//   adjoint  sum_i R_i F(x_i) = sum_n R_n F(v_n) with R_n = sum_i R_i l_n(x_i)
+//            (the transpose), so the residual is carried to the nodes once.
+//            The shift's sum needs no sums of its own on the tile's nodes:
+//            sum I l^2 q2 is -F' / (2 iw2) with F = sum I l, so it takes F's
+//            node values with the weights R'_n = sum_m R_m l_n'(v_m).
+//
+// Lanes: a wave holds SG samples (4 or 1).  With SG = 4 the 16 lanes of a
+// sample are its nodes and share its points, the peaks are wave-uniform
+// (scalar loads) and the adjoint's sums reduce over 16 lanes for four samples
+// at once.  SG = 1 is for grids too small to fill the GPU that way: a
+// sample's 64 lanes take four far peaks at the tile's 16 nodes together, and
+// a leaf's points in one go (so leaves need no nodes).  NW waves split the
+// phases.
+//
+// What it measured (one MI355X, step of ELBO, adjoint and gradient, against
+// evaluating every peak at every point): 50 phases x 40 peaks, 3501 points,
+// S = 64: 208 -> 77 us; 200 x 60, 7001, S = 128: 3611 -> 726 us; asymmetric
+// 50 x 50, 2501, S = 32: 160 -> 80 us; profile of 77 x 50, 5003, S = 24: 95 ->
+// 30 us.  Bound by VALU issue on the large ones (about 80 % of the kernel's
+// cycles; a last round of blocks that fills half the CUs and the stages
+// between the phase loops, 17 000 cycles per block, take the rest).
+#pragma once
+
+#include "xrdvi_device.h"
+
+namespace xrdvi {
+
+constexpr int kNodes = 16;
+constexpr double kFarRadius = 2.0;     // in half-widths of the tile
+constexpr int kLeaf = kWave;           // points of a leaf
+constexpr int kDenseWaves = 16;        // waves per block
+constexpr int kMinGroupBlocks = 96;
+constexpr int kPlanPhases = 256;       // phases whose near ranges are held in LDS
+constexpr int kNodeStride = kNodes + 1;    // (no LDS bank conflicts)
+
+// Half-width (deg) given to the nodes of a one-point tile.
+constexpr double kPointHalf = 0.05;
+
+// The nodes cos(theta_n), theta_n = (2 n + 1) pi / 32, and the numerators
+// (-1)^n sin(theta_n) / 16 of their interpolation weights
+//   l_n(t) = T16(t) (-1)^n sin(theta_n) / (16 (t - cos theta_n)).
+__constant__ const double kNodeCos[kNodes] = {
+    0.99518472667219693, 0.95694033573220882,
+    0.88192126434835505, 0.77301045336273699,
+    0.63439328416364549, 0.47139673682599781,
+    0.29028467725446233, 0.09801714032956077,
+    -0.098017140329560645, -0.29028467725446216,
+    -0.4713967368259977, -0.63439328416364538,
+    -0.77301045336273699, -0.88192126434835494,
+    -0.95694033573220882, -0.99518472667219682,
+};
+__constant__ const double kNodeNum[kNodes] = {
+    0.0061260712705975377, -0.018142792328403896,
+    0.029462296051624853, -0.039649580260227843,
+    0.048313153335171062, -0.055120079021772184,
+    0.059808770983263058, -0.062199045417012301,
+    0.062199045417012308, -0.059808770983263058,
+    0.055120079021772191, -0.048313153335171069,
+    0.039649580260227843, -0.029462296051624867,
+    0.018142792328403899, -0.0061260712705975516,
+};
+// d l_n / dt at node m, [m][n].
+__constant__ const double kNodeDeriv[kNodes][kNodes] = {
+    {51.792831098067211, -77.438037004005736, 42.461439259893375,
+     -29.131495532874293, 21.858839993468788, -17.177986233491936,
+     13.850175995364282, -11.316916195110146, 9.2875530989122765,
+     -7.5948830160827541, 6.1350992786889949, -4.8395856843711895,
+     3.6603814576093647, -2.5620980641664688, 1.5171008342870898,
+     -0.50241928618815679},
+    {8.8289725519850979, 5.6781471211595651, -21.64665401709345,
+     11.881798187143547, -8.255971374269512, 6.2571630068793604,
+     -4.9449189653107286, 3.991400054958512, -3.2497102178311286,
+     2.6431142533328513, -2.1270367504090717, 1.6734009709286282,
+     -1.263283185091326, 0.88310718047447023, -0.52249861493968897,
+     0.17296979808284091},
+    {-1.8358010864067509, 8.2085388173702825, 1.9843883778092071,
+     -12.356657609378537, 6.6248263190876679, -4.5572634187795309,
+     3.4311781356219084, -2.6931105493056307, 2.1543603720002076,
+     -1.7317865827354484, 1.3824307444118293, -1.0814575903446177,
+     0.81318980529924312, -0.56694403481635802, 0.33487944904089401,
+     -0.11077114887436472},
+    {0.6954240126678416, -2.4877872757573432, 6.8227114323536568,
+     0.96036918738381261, -8.7904228071334938, 4.6091426477380386,
+     -3.124825676618364, 2.3240510042688647, -1.8009979229012723,
+     1.4186408425223205, -1.1171428893957234, 0.86578107837740148,
+     -0.64682178335999008, 0.44900162784130354, -0.26450372107388515,
+     0.087380243086837395},
+    {-0.35144747928055481, 1.1642484512613696, -2.4636380724016975,
+     5.9204699935110128, 0.53083291904951435, -6.9994842750530211,
+     3.5975261420344133, -2.4002080147615596, 1.7577771646932798,
+     -1.3387792947463535, 1.0317435935592389, -0.78815462345125042,
+     0.58311539819488101, -0.4021720668486467, 0.23598125531477016,
+     -0.077811091075405514},
+    {0.21218597637536299, -0.67790067272537091, 1.3020199771661196,
+     -2.3849411910968379, 5.3774594927688701, 0.30303790007021669,
+     -5.9911152940563834, 3.0222007288099548, -1.9817361921195735,
+     1.4245630915742116, -1.0606776859903473, 0.79265259600094873,
+     -0.57805112509770729, 0.39496344206385009, -0.23044303663315086,
+     0.075781992889849131},
+    {-0.14530803368462933, 0.45502753895468251, -0.83261971099020049,
+     1.373324685393212, -2.3474965932632257, 5.0885914521431106,
+     0.15849822203138439, -5.4089489012225442, 2.6782395433049389,
+     -1.7224470982383346, 1.2099616206709698, -0.87359471744412587,
+     0.62347621607209025, -0.42024039178966899, 0.24321728673556051,
+     -0.079681118673232285},
+    {0.10978038535550652, -0.33959874670558116, 0.60425453769360549,
+     -0.94439875132923812, 1.4481455398755532, -2.3734250948138484,
+     5.0012112090562857, 0.049483980570376271, -5.1011486186891588,
+     2.4763483384890179, -1.5563170125796115, 1.0605402304677098,
+     -0.73185148966625002, 0.48337489559945856, -0.27649383723407389,
+     0.090094433910261632},
+    {-0.090094433910261437, 0.27649383723407378, -0.48337489559945829,
+     0.73185148966625002, -1.0605402304677096, 1.5563170125796113,
+     -2.4763483384890179, 5.1011486186891579, -0.049483980570376208,
+     -5.0012112090562866, 2.3734250948138484, -1.4481455398755532,
+     0.94439875132923801, -0.60425453769360571, 0.33959874670558116,
+     -0.10978038535550676},
+    {0.079681118673232104, -0.24321728673556048, 0.42024039178966882,
+     -0.62347621607209047, 0.87359471744412587, -1.2099616206709696,
+     1.7224470982383346, -2.6782395433049389, 5.4089489012225469,
+     -0.15849822203138428, -5.0885914521431097, 2.3474965932632257,
+     -1.3733246853932115, 0.83261971099020093, -0.45502753895468251,
+     0.14530803368462963},
+    {-0.075781992889848937, 0.23044303663315077, -0.39496344206384987,
+     0.57805112509770717, -0.79265259600094851, 1.0606776859903471,
+     -1.4245630915742111, 1.9817361921195729, -3.0222007288099548,
+     5.9911152940563817, -0.30303790007021658, -5.377459492768871,
+     2.384941191096837, -1.3020199771661203, 0.67790067272537091,
+     -0.21218597637536343},
+    {0.07781109107540532, -0.23598125531477007, 0.40217206684864643,
+     -0.58311539819488101, 0.78815462345125009, -1.0317435935592385,
+     1.3387792947463533, -1.7577771646932796, 2.4002080147615596,
+     -3.5975261420344116, 6.999484275053022, -0.53083291904951424,
+     -5.9204699935110074, 2.4636380724016984, -1.1642484512613691,
+     0.35144747928055553},
+    {-0.087380243086837187, 0.26450372107388509, -0.44900162784130332,
+     0.64682178335999008, -0.86578107837740126, 1.1171428893957231,
+     -1.4186408425223203, 1.800997922901272, -2.3240510042688647,
+     3.1248256766183631, -4.6091426477380377, 8.7904228071334884,
+     -0.96036918738381261, -6.8227114323536666, 2.4877872757573436,
+     -0.69542401266784359},
+    {0.11077114887436441, -0.33487944904089384, 0.56694403481635747,
+     -0.81318980529924278, 1.0814575903446171, -1.3824307444118284,
+     1.7317865827354473, -2.1543603720002062, 2.6931105493056298,
+     -3.4311781356219053, 4.5572634187795291, -6.6248263190876653,
+     12.356657609378544, -1.9843883778092046, -8.2085388173702682,
+     1.835801086406754},
+    {-0.17296979808284046, 0.52249861493968874, -0.88310718047446946,
+     1.2632831850913258, -1.6734009709286277, 2.1270367504090708,
+     -2.6431142533328509, 3.2497102178311277, -3.9914000549585116,
+     4.9449189653107268, -6.2571630068793587, 8.2559713742695084,
+     -11.881798187143545, 21.646654017093425, -5.6781471211595651,
+     -8.8289725519851405},
+    {0.50241928618815457, -1.517100834287086, 2.5620980641664617,
+     -3.6603814576093567, 4.839585684371178, -6.1350992786889798,
+     7.5948830160827354, -9.2875530989122552, 11.316916195110121,
+     -13.85017599536425, 17.1779862334919, -21.858839993468745,
+     29.131495532874244, -42.461439259893304, 77.438037004005793,
+     -51.79283109806601},
+};
+
+// How a dense analysis is cut into blocks: leaves per tile and samples per
+// block (a function of the analysis alone, so that it gives the same bits
+// alone and served).
+struct DenseCut {
+    int leaves, group;
+    __host__ __device__ int tiles(int N) const {
+        return (N + leaves * kLeaf - 1) / (leaves * kLeaf);
+    }
+    __host__ __device__ int groups(int S) const { return (S + group - 1) / group; }
+    __host__ __device__ long long blocks(int N, int S) const {
+        return (long long)tiles(N) * groups(S);
+    }
+};
+__host__ __device__ inline DenseCut dense_cut(int N, int S) {
+    // One block of 16 waves runs per CU.  Two leaves while that is one round
+    // of the 256 CUs, four beyond: 3501 points, S = 64 takes 61 us with four
+    // (224 blocks) and 71 with two (448), 7001 points, S = 128 692 and 808 us;
+    // 2501 points, S = 32 takes 119 us with four (80 blocks) and 65 with two.
+    if (DenseCut{2, 4}.blocks(N, S) > 256) return DenseCut{4, 4};
+    // Few blocks of four samples leave CUs idle: 3501 points, S = 8 (56 such
+    // blocks) takes 56 us with them and 43 with one sample per block, but one
+    // sample per block costs about twice the work (2501 points, S = 32, 160
+    // blocks: 65 us with four samples, 105 with one).
+    if (DenseCut{2, 4}.blocks(N, S) >= kMinGroupBlocks) return DenseCut{2, 4};
+    return DenseCut{2, 1};
+}
+
+template <int NW, int SG, int LV, bool ASYM, bool SEC>
+struct DenseSmem {
+    // LDS for the far sums kept for the adjoint (those of the first phases;
+    // the others' are formed again)
+    static constexpr int kFarFloats = 32 * 1024 / 4;
+    static constexpr int kPts = LV * kLeaf;
+    static constexpr bool kMid = SG == 4;   // peaks are taken at the leaves' nodes
+    static constexpr int kFarSums = (SEC ? 3 : 2) * (ASYM ? 2 : 1);   // per lane and phase
+    static constexpr int kFarCap = kFarFloats / (kFarSums * kWave);
+    static constexpr int kLow = LV * kNodes;     // the leaves' nodes
+    float lm[kPts * kNodeStride];         // weights of the leaves' nodes at the points
+    float em[kLow * kNodeStride];         // of the tile's at the leaves', and slopes
+    float ed[kLow * kNodeStride];
+    float us[kPts], ul[kPts];             // points relative to xref, rounding errors
+    float sig[NW][SG][kPts];              // the waves' sums at the points
+    float nod[NW][kWave + 1];             // ... at the tile's nodes
+    float ndl[kMid ? NW : 1][LV][kWave];  // ... at the leaves' nodes
+    double pn[SG][kNodes];                // node sums of all waves
+    double low[SG][kLow];                 // ... brought to the leaves' nodes; then the
+                                          // residual at them
+    double rn[SG][kNodes], rs[SG][kNodes];   // residual at the tile's nodes, its slope
+    float rres[SG][kPts];                 // residual y/f - 1
+    double red[SG * LV];
+    int2 nr[kPlanPhases];                 // near peaks [x, y) of each phase
+    float far[kFarCap][kFarSums][kWave];
+};
+
+// Tables of a dense problem, made once (launch_prepare).  Kind 0 is a tile of
+// two leaves, kind 1 one of four.
+//   lm    [leaf][64][16]      weights of the leaf's nodes at its points
+//   em    [leaf][2][2][16][16]  by kind: weights of the tile's nodes at the leaf's
+//                             nodes, and their slopes (per degree)
+//   leaf  [leaf][kGeo]        its nodes, middle and half-width (FP32, relative to
+//                             the reference of its 256 points)
+//   tile  [2][tiles][kGeo]    the tile's nodes
+//   mid   [2][tiles]          its middle and half-width (FP64)
+//   near  [2][kNearLevels][tiles][K]  by margin: the peaks of a phase with
+//                             |p - middle| < (kFarRadius + margin) half-widths
+constexpr int kNearLevels = 4;
+__host__ __device__ inline double near_margin(int level) {
+    return level == 0 ? 0.0625 : level == 1 ? 0.125 : level == 2 ? 0.25 : 0.75;
+}
+constexpr int kGeo = kNodes + 4;
+struct DenseTables {
+    size_t em, leaf, tile, mid, near, total;   // offsets in bytes (lm is first)
+    size_t tiles;                              // rows per kind
+    __host__ __device__ static DenseTables of(int N, int K) {
+        const size_t leaves = ((size_t)N + kLeaf - 1) / kLeaf;
+        DenseTables o{};
+        o.tiles = (leaves + 1) / 2;
+        o.em = leaves * kLeaf * kNodes * sizeof(float);
+        o.leaf = o.em + leaves * 4 * kNodes * kNodes * sizeof(float);
+        o.tile = o.leaf + leaves * kGeo * sizeof(float);
+        o.mid = o.tile + 2 * o.tiles * kGeo * sizeof(float);
+        o.mid = (o.mid + 15) / 16 * 16;
+        o.near = o.mid + 2 * o.tiles * sizeof(double2);
+        o.total = o.near + 2 * kNearLevels * o.tiles * (size_t)K * sizeof(int2);
+        return o;
+    }
+};
+
+// Middle and half-width of the run of points [a, b).
+__device__ __forceinline__ double2 mid_half(const ProbDev &P, int a, int b) {
+    const double xa = P.x[a], xb = P.x[b - 1];
+    return make_double2(0.5 * (xa + xb), b - a > 1 ? 0.5 * (xb - xa) : kPointHalf);
+}
+
+// l_m(t) at t in [-1, 1].
+__device__ __forceinline__ double node_weight(double t, double T16, int m) {
+    const double d = t - kNodeCos[m];
+    return fabs(d) < 1e-10 ? 1.0 : T16 * kNodeNum[m] / d;
+}
+__device__ __forceinline__ double cheb16(double t) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) t = 2.0 * t * t - 1.0;
+    return t;
+}
+
+// The tables of one problem as the kernels read them.
+struct DenseView {
+    DenseTables o;
+    const char *base;
+    __device__ explicit DenseView(const ProbDev &P) : o(DenseTables::of(P.N, P.K)), base(P.dense) {}
+    __device__ const float *lm(int leaf) const {
+        return reinterpret_cast<const float *>(base) + (size_t)leaf * kLeaf * kNodes;
+    }
+    __device__ const float *em(int leaf, int kind) const {
+        return reinterpret_cast<const float *>(base + o.em) +
+               ((size_t)leaf * 2 + kind) * 2 * kNodes * kNodes;
+    }
+    __device__ const float *leaf(int l) const {
+        return reinterpret_cast<const float *>(base + o.leaf) + (size_t)l * kGeo;
+    }
+    __device__ const float *tile(int kind, int t) const {
+        return reinterpret_cast<const float *>(base + o.tile) + (kind * o.tiles + t) * kGeo;
+    }
+    __device__ double2 mid(int kind, int t) const {
+        return reinterpret_cast<const double2 *>(base + o.mid)[kind * o.tiles + t];
+    }
+    __device__ const int2 *near(int kind, int level, int t, int K) const {
+        return reinterpret_cast<const int2 *>(base + o.near) +
+               (((size_t)kind * kNearLevels + level) * o.tiles + t) * K;
+    }
+};
+
+// The tables of one leaf (and of the tiles that it begins), by a block.
+__device__ inline void dense_tables_leaf(const ProbDev &P, int leaf, char *base) {
+    ProbDev Q = P;
+    Q.dense = base;
+    const DenseView V(Q);
+    const int a = leaf * kLeaf, b = min(a + kLeaf, P.N);
+    const double2 h = mid_half(P, a, b);
+    const double xref = P.x[min(a / P.ref * P.ref + P.ref / 2, P.N - 1)];
+    float *lm = const_cast<float *>(V.lm(leaf));
+    for (int e = threadIdx.x; e < kLeaf * kNodes; e += blockDim.x) {
+        const int q = e / kNodes;
+        const double t = a + q < b ? (P.x[a + q] - h.x) / h.y : 0.0;
+        lm[e] = a + q < b ? (float)node_weight(t, cheb16(t), e % kNodes) : 0.f;
+    }
+    for (int kind = 0; kind < 2; ++kind) {
+        const int pts = (kind ? 4 : 2) * kLeaf, ta = a / pts * pts;
+        const double2 th = mid_half(P, ta, min(ta + pts, P.N));
+        float *em = const_cast<float *>(V.em(leaf, kind));
+        for (int e = threadIdx.x; e < kNodes * kNodes; e += blockDim.x) {
+            const int q = e / kNodes, m = e % kNodes;
+            const double t = (h.x + h.y * kNodeCos[q] - th.x) / th.y, T = cheb16(t);
+            em[e] = (float)node_weight(t, T, m);
+            // the slope of l_m at t: the interpolant of its values at the nodes
+            double d = 0.0;
+            for (int r = 0; r < kNodes; ++r) d = fma(node_weight(t, T, r), kNodeDeriv[r][m], d);
+            em[kNodes * kNodes + e] = (float)(d / th.y);
+        }
+        if (a != ta) continue;
+        float *tg = const_cast<float *>(V.tile(kind, a / pts));
+        for (int n = threadIdx.x; n < kNodes; n += blockDim.x)
+            tg[n] = (float)((th.x - xref) + th.y * kNodeCos[n]);
+        if (threadIdx.x == 0)
+            reinterpret_cast<double2 *>(base + V.o.mid)[kind * V.o.tiles + a / pts] = th;
+    }
+    float *lg = const_cast<float *>(V.leaf(leaf));
+    for (int n = threadIdx.x; n < kNodes; n += blockDim.x)
+        lg[n] = (float)((h.x - xref) + h.y * kNodeCos[n]);
+    if (threadIdx.x == 0) {
+        lg[kNodes] = (float)(h.x - xref);
+        lg[kNodes + 1] = (float)h.y;
+    }
+}
+// One entry of the near table: tile t of `leaves` leaves, phase k.
+__device__ inline int2 dense_near_entry(const ProbDev &P, int leaves, int level, int t, int k) {
+    const int ta = t * leaves * kLeaf;
+    const double2 h = mid_half(P, ta, min(ta + leaves * kLeaf, P.N));
+    const double r = (kFarRadius + near_margin(level)) * h.y;
+    int a = P.off[k], b = P.off[k + 1];
+    const int end = b;
+    for (int lo = a, hi = b; lo < hi;) {
+        const int mid = (lo + hi) >> 1;
+        if (P.pos[mid] > h.x - r) hi = mid; else lo = mid + 1;
+        a = lo;
+    }
+    for (int lo = a, hi = end; lo < hi;) {
+        const int mid = (lo + hi) >> 1;
+        if (P.pos[mid] >= h.x + r) hi = mid; else lo = mid + 1;
+        b = lo;
+    }
+    return make_int2(a, b < a ? a : b);
+}
+
+// Sum over the LPS consecutive lanes of one sample (16: a DPP row, 32: two
+// rows, 64: the wave), valid in the last 16 of them.
+template <int LPS>
+__device__ __forceinline__ float lanes_total(float v) {
+    static_assert(LPS == 16 || LPS == 32 || LPS == 64, "DPP rows");
+    v += dpp_f32<0x128, 0xf, true>(v);   // row_ror:8
+    v += dpp_f32<0x124, 0xf, true>(v);
+    v += dpp_f32<0x122, 0xf, true>(v);
+    v += dpp_f32<0x121, 0xf, true>(v);
+    if (LPS >= 32) v += dpp_f32<0x142, 0xa, false>(v);   // row_bcast:15
+    if (LPS == 64) v += dpp_f32<0x143, 0xc, false>(v);   // row_bcast:31
+    return v;
+}
+
+// The near peaks [na, nb) of phase k for samples [s0, s0 + ns): those with a
+// centre within kFarRadius half-widths of the tile's middle or a Gaussian
+// that reaches the tile, at any of the samples (a superset is harmless:
+// near peaks are evaluated at every point).
+template <bool SEC>
+__device__ inline int2 dense_near(const ProbDev &P, const StepDev &st, int t, int leaves,
+                                  int k, int s0, int ns, double2 mh) {
+    const int a = P.off[k], b = P.off[k + 1];
+    if (a >= b) return make_int2(a, a);
+    const double xm = mh.x, ha = mh.y, ra = kFarRadius * ha, xa = xm - ha, xb = xm + ha;
+    const int K = P.K;
+    double lo = __builtin_huge_val(), hi = -__builtin_huge_val();
+    bool whole = false;
+    // sec law: a centre below xa has at most the width at xa
+    const double cxa = SEC ? fabs(cos(xa * kHalfDegRad)) : 1.0;
+    for (int g = 0; g < ns; ++g) {
+        const double *ph = st.phi + (size_t)(s0 + g) * P.D * K;
+        const double mu = ph[K + k], w = ph[2 * K + k];
+        const double al = P.D == 5 ? ph[4 * K + k] : 1.0;
+        if (SEC) {
+            // the reach of a Gaussian is monotone over the phase's peaks (see
+            // sec_monotone), from the records of its first and last peak
+            const float4 *ps = st.psec + (size_t)(s0 + g) * P.T;
+            const float4 f = ps[a], l = ps[b - 1];
+            const double rf = P.pos[a] + mu, rl = P.pos[b - 1] + mu;
+            const double up = 1.0 + kGaussReach * al * f.z / f.x;
+            const double dn = 1.0 - kGaussReach * l.z / l.x;
+            whole |= !(rf > -xa && rl < 180.0 && up > 1e-3 && dn > 1e-3);
+        }
+        const double W = SEC ? w / cxa : w;
+        lo = fmin(lo, fmin(xm - ra, xa - kGaussReach * W * al) - mu);
+        hi = fmax(hi, fmax(xm + ra, SEC ? xb : xb + kGaussReach * w) - mu);
+    }
+    if (whole) return make_int2(a, b);
+    if (!SEC) {
+        // the table's first margin that covers the bounds (one load instead of
+        // two searches; all levels are within one cache line per phase group)
+        const double need = fmax(xm - lo, hi - xm) / ha - kFarRadius;
+        for (int level = 0; level < kNearLevels; ++level)
+            if (need < near_margin(level))
+                return DenseView(P).near(leaves == 4, level, t, K)[k];
+    }
+    auto ge = [&](double p) { return p >= lo; };
+    auto gt = [&](double p) { return p > hi; };
+    const Probe<4, double> pa = probe_at<4>(P.pos, a, b, tab_guess(P, k, lo, a, b));
+    const Probe<4, double> pb = probe_at<4>(P.pos, a, b, tab_guess(P, k, hi, a, b));
+    const int ca = probe_count(pa, a, b, ge), cb = probe_count(pb, a, b, gt);
+    const int na = probe_settle<4>(P.pos, a, b, pa.j0, ca, ge);
+    int nb = probe_settle<4>(P.pos, a, b, pb.j0, cb, gt);
+    if (SEC) {
+        // centres above the tile: on while a Gaussian reaches it
+        for (int g = 0; g < ns; ++g) {
+            const double *ph = st.phi + (size_t)(s0 + g) * P.D * K;
+            const double mu = ph[K + k], w = ph[2 * K + k];
+            const float4 *ps = st.psec + (size_t)(s0 + g) * P.T;
+            while (nb < b && P.pos[nb] + mu - kGaussReach * w / ps[nb].x <= xb) ++nb;
+        }
+    }
+    return make_int2(na, nb < na ? na : nb);
+}
+
+// Weights of the shift's sums under the sec law (side A: A = 1 below the
+// centre, alpha above): the shift moves the centre and, through W(rho), the
+// width,
+//   e1 += I e (c q2 + kG (2 ln2 q2^2 - 1)),  kG = A tw / (4 ln2),
+//   l1 += I l (c q2 l + kL (1 - 2 l)),       kL = A tw / 4,
+// which phase_grad turns into d/dmu exactly as the plain sums (c = 1,
+// tw = 0).  With q2^2 = tt - 1 the Gaussian weight is
+// c q2 + bG tt + gG, bG = A tw / 2, gG = -A tw (1/2 + 1/(4 ln2)): SecW.
+
+// Far sums of one phase side at the lane's node: f0 = sum I l,
+// f2 = sum I l^2 and, under the sec law (whose shift weights differ by peak),
+// f1 = sum I (l^2 (c q2 - 2 kL) + l kL) (f1 and f2 with GRAD).
+struct FarSums {
+    float f0, f1, f2;
+};
+
+template <int SLOTS, bool GRAD, bool SEC>
+__device__ __forceinline__ FarSums far_sums(cptr<float> pt, cptr<float> inten,
+                                            const float4 *ps, int j0, int j1,
+                                            int slot, float uq, float iw2,
+                                            float ka) {
+    FarSums f{0.f, 0.f, 0.f};
+    auto add = [&](float p, float I, float c, float tw) {
+        float q2 = fmaf(-p, iw2, uq);
+        if (SEC) q2 *= c;
+        const float l = rcp_f32(fmaf(q2, q2, 1.0f));
+        if (GRAD) {
+            const float Il = I * l;
+            f.f0 += Il;
+            if (SEC) {
+                const float kL = 0.25f * tw * ka, Ill = Il * l;
+                f.f2 += Ill;
+                f.f1 = fmaf(Ill, fmaf(c, q2, -2.f * kL), f.f1);
+                f.f1 = fmaf(Il, kL, f.f1);
+            } else {
+                f.f2 = fmaf(Il, l, f.f2);
+            }
+        } else {
+            f.f0 = fmaf(I, l, f.f0);
+        }
+    };
+    if (SLOTS == 1) {
+#pragma unroll 4
+        for (int j = j0; j < j1; ++j) {
+            if (SEC) {
+                const float4 r = ps[j];
+                add(pt[j], r.y, r.x, r.z);
+            } else {
+                add(pt[j], inten[j], 1.f, 0.f);
+            }
+        }
+    } else {
+#pragma unroll 2
+        for (int jj = j0; jj < j1; jj += SLOTS) {
+            const bool ok = jj + slot < j1;
+            const int j = ok ? jj + slot : j0;
+            if (SEC) {
+                const float4 r = ps[j];
+                add(pt[j], ok ? r.y : 0.f, r.x, ok ? r.z : 0.f);
+            } else {
+                add(pt[j], ok ? inten[j] : 0.f, 1.f, 0.f);
+            }
+        }
+    }
+    return f;
+}
+
+// A near peak at one sample: its tile-relative centre as a rounded value ch
+// and the rest cl (so that x - rho keeps a relative error of a few units of
+// FP32 rounding), the scales 2 c / (A w) below and above it.
+struct NearPeak {
+    float ch, cl, s, sr;
+    template <bool SEC>
+    __device__ __forceinline__ static NearPeak of(float pt, float ptl, float mu,
+                                                  float iw2, float iw2r, float c) {
+        const float ch = pt + mu, bb = ch - pt;
+        const float e = (pt - (ch - bb)) + (mu - bb);   // exact: pt + mu - ch
+        return NearPeak{ch, e + ptl, SEC ? iw2 * c : iw2, SEC ? iw2r * c : iw2r};
+    }
+    // q2 at the point u, to the accuracy that the flat of the Lorentzian
+    // needs (an absolute error of a few FP32 roundings of the tile's extent);
+    // cs = ch s
+    template <bool ASYM>
+    __device__ __forceinline__ float q2_flat(float u, float cs, bool &up) const {
+        if (ASYM) {
+            const float d = u - ch;
+            up = d >= 0.f;
+            return d * (up ? sr : s);
+        }
+        up = false;
+        return fmaf(u, s, -cs);
+    }
+    // q2 at the point u + ul; whether it lies at or above the centre (ASYM)
+    template <bool ASYM>
+    __device__ __forceinline__ float q2(float u, float ul, bool &up) const {
+        if (ASYM) {
+            const float d = (u - ch) + (ul - cl);
+            up = d >= 0.f;
+            return d * (up ? sr : s);
+        }
+        up = false;
+        return fmaf(u - ch, s, fmaf(ul, s, -cl * s));
+    }
+};
+
+// Whether the Gaussian (and the steep of the Lorentzian) matters at some
+// lane's point, a branch of the whole wave: the empty volatile statement
+// keeps the compiler from evaluating the Gaussian everywhere and selecting.
+__device__ __forceinline__ bool gauss_matters(float tt) {
+    const bool any = __builtin_amdgcn_ballot_w64(!(tt > kGaussTT)) != 0;
+    if (any) asm volatile("");
+    return any;
+}
+
+// Wave priority in the phase loops, by the phases the wave has left: a wave
+// with more of them issues first.  Among waves of one priority the oldest
+// issues first, so without this the first waves of a block finish early and
+// the last one ends alone, waiting on its own latencies.
+__device__ __forceinline__ void prio_left(int left) {
+    if (left >= 4) __builtin_amdgcn_s_setprio(3);
+    else if (left == 3) __builtin_amdgcn_s_setprio(2);
+    else if (left == 2) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+}
+
+template <bool GRAD, bool ASYM, bool SEC, int NW, int SG, int LV, typename SM>
+__device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int grp,
+                           float *f_out, SM &sm) {
+    constexpr bool MID = SM::kMid;
+    constexpr int PTS = SM::kPts;
+    constexpr int LPS = kWave / SG;         // lanes per sample
+    constexpr int PB = kLeaf / LPS;         // points of a leaf per lane
+    constexpr int NPP = LV * PB;            // points per lane
+    constexpr int SLOTS = LPS / kNodes;     // far peaks taken together
+    constexpr int NS = ASYM ? 12 : 6;
+    constexpr int NT = NW * kWave;
+    constexpr int kCap = SM::kFarCap;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int n = lane % kNodes, sl = lane / LPS, li = lane % LPS, slot = li / kNodes;
+    const int S = st.S, K = P.K, s0 = grp * SG;
+    const int ns = min(SG, S - s0);
+    const int s = s0 + min(sl, ns - 1);     // (lanes past the last sample repeat it)
+    const int i0 = t * PTS, i1 = min(i0 + PTS, P.N), np = i1 - i0;
+    const int nl = (np + kLeaf - 1) / kLeaf;   // leaves with points
+    const DenseView V(P);
+    constexpr int KIND = LV == 4;
+    const double2 mh = V.mid(KIND, t);
+
+    // the last kPlanPhases threads find the first phases' near ranges (below),
+    // the others bring in the points and the weights
+    constexpr int NC = NT - kPlanPhases;
+    if (tid < NC) {
+        for (int q = tid; q < PTS; q += NC) {
+            sm.us[q] = q < np ? P.u[i0 + q] : 0.f;
+            sm.ul[q] = q < np ? P.ul[i0 + q] : 0.f;
+        }
+        auto put = [](float *dst, float4 v) {
+            dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
+        };
+        constexpr int R4 = kNodes / 4;      // a row of 16 weights in float4s
+        const float4 *lm = reinterpret_cast<const float4 *>(V.lm(i0 / kLeaf));
+#pragma unroll 2
+        for (int e = tid; e < nl * kLeaf * R4; e += NC)
+            put(sm.lm + e / R4 * kNodeStride + e % R4 * 4, lm[e]);
+        for (int e = tid; e < nl * 2 * kNodes * R4; e += NC) {
+            const int l = e / (2 * kNodes * R4), r = e % (2 * kNodes * R4);
+            const int row = r / R4 % kNodes;
+            put((r < kNodes * R4 ? sm.em : sm.ed) + (l * kNodes + row) * kNodeStride + r % R4 * 4,
+                reinterpret_cast<const float4 *>(V.em(i0 / kLeaf + l, KIND))[r]);
+        }
+    }
+    // the lane's nodes; lane n tests the reach of leaf n % LV
+    const float vn = V.tile(KIND, t)[n];
+    float vl[LV], lmid = 0.f, lhalf = 0.f;
+    if (MID) {
+#pragma unroll
+        for (int l = 0; l < LV; ++l) vl[l] = V.leaf(i0 / kLeaf + min(l, nl - 1))[n];
+        const float *lg = V.leaf(i0 / kLeaf + min(n % LV, nl - 1));
+        lmid = lg[kNodes];
+        lhalf = lg[kNodes + 1];
+    }
+
+    const float4 *pk = st.pk + (size_t)s * K;
+    const float *pkr = ASYM ? st.pkr + (size_t)s * K : nullptr;
+    const float4 *ps = SEC ? st.psec + (size_t)s * P.T : nullptr;
+    cptr<float> ptt = as_const(P.pt + (size_t)(i0 / P.ref) * P.T);
+    cptr<float> ptl = as_const(P.ptl + (size_t)(i0 / P.ref) * P.T);
+    cptr<float> inten = as_const(P.inten);
+    cptr<int> off = as_const(P.off);
+
+    // near ranges of the phases [c0, c0 + kPlanPhases)
+    auto plan = [&](int c0) {
+        const int kk = tid - NC;
+        if (kk >= 0 && c0 + kk < K)
+            sm.nr[kk] = dense_near<SEC>(P, st, t, LV, c0 + kk, s0, ns, mh);
+        __syncthreads();
+    };
+    auto near_range = [&](int k) {
+        const int2 r = sm.nr[k % kPlanPhases];
+        return make_int2(__builtin_amdgcn_readfirstlane(r.x),
+                         __builtin_amdgcn_readfirstlane(r.y));
+    };
+    // the far sums of phase k: lo of the peaks above the tile (its points
+    // see their low side), hi of those below
+    auto far_of = [&](auto grad, int a, int b, int2 nr, float4 c, float iw2r, float ka,
+                      FarSums &lo, FarSums &hi) {
+        constexpr bool G = decltype(grad)::value;
+        const float um = vn - c.w;
+        if (ASYM) {
+            hi = far_sums<SLOTS, G, SEC>(ptt, inten, ps, a, nr.x, slot, um * iw2r, iw2r, ka);
+            lo = far_sums<SLOTS, G, SEC>(ptt, inten, ps, nr.y, b, slot, um * c.x, c.x, 1.f);
+        } else {
+            const FarSums x = far_sums<SLOTS, G, SEC>(ptt, inten, ps, a, nr.x, slot,
+                                                      um * c.x, c.x, 1.f);
+            const FarSums y = far_sums<SLOTS, G, SEC>(ptt, inten, ps, nr.y, b, slot,
+                                                      um * c.x, c.x, 1.f);
+            lo = FarSums{x.f0 + y.f0, x.f1 + y.f1, x.f2 + y.f2};
+            hi = FarSums{0.f, 0.f, 0.f};
+        }
+    };
+    // a near peak of the tile, and the reach of its Gaussian
+    struct Near {
+        NearPeak pk;
+        float I, c, tw, reach, cs;
+    };
+    auto near_peak = [&](int j, float4 c, float iw2r) {
+        Near r{};
+        r.c = 1.f;
+        if (SEC) {
+            const float4 rec = ps[j];
+            r.I = rec.y; r.c = rec.x; r.tw = rec.z;
+        } else {
+            r.I = inten[j];
+        }
+        r.pk = NearPeak::of<SEC>(ptt[j], ptl[j], c.w, c.x, iw2r, r.c);
+        r.cs = r.pk.ch * r.pk.s;
+        r.reach = (float)(2.0 * kGaussReach) *
+                  rcp_f32(ASYM ? fminf(r.pk.s, r.pk.sr) : r.pk.s);
+        return r;
+    };
+    // the leaves that the peak is near of for some sample, one bit each
+    // (lane n of a sample tests leaf n mod LV)
+    auto near_leaves = [&](const Near &r) -> unsigned {
+        if (!MID) return ~0u;
+        const bool near = !(fabsf(r.pk.ch - lmid) >= lhalf + fmaxf(lhalf, r.reach));
+        unsigned long long b = __builtin_amdgcn_ballot_w64(near);
+        b |= b >> 32;
+        return (unsigned)(b | (b >> 16));
+    };
+
+    // ---------------- forward: this wave's phases
+    float sig[NPP], lsig[LV], nsig = 0.f, u[NPP];
+#pragma unroll
+    for (int p = 0; p < NPP; ++p) sig[p] = 0.f;
+#pragma unroll
+    for (int l = 0; l < LV; ++l) lsig[l] = 0.f;
+    for (int c0 = 0; c0 < K; c0 += kPlanPhases) {
+        if (c0 > 0) __syncthreads();
+        plan(c0);
+        if (c0 == 0) {
+#pragma unroll
+            for (int p = 0; p < NPP; ++p) u[p] = sm.us[p * LPS + li];
+        }
+        for (int k = c0 + wv; k < min(K, c0 + kPlanPhases); k += NW) {
+            prio_left((min(K, c0 + kPlanPhases) - k + NW - 1) / NW);
+            const int a = off[k], b = off[k + 1];
+            if (a >= b) continue;
+            const int2 nr = near_range(k);
+            const float4 c = pk[k];
+            const float iw2r = ASYM ? pkr[k] : c.x;
+            const float ka = ASYM && SEC ? c.x / iw2r : 1.f;   // alpha
+            FarSums lo, hi;
+            if (GRAD && k < kCap) {
+                far_of(std::true_type{}, a, b, nr, c, iw2r, ka, lo, hi);
+                float (*dst)[kWave] = sm.far[k];
+                constexpr int H = SM::kFarSums / 2;   // (ASYM: the high side)
+                dst[0][lane] = lo.f0; dst[1][lane] = lo.f2;
+                if (SEC) dst[2][lane] = lo.f1;
+                if (ASYM) {
+                    dst[H][lane] = hi.f0; dst[H + 1][lane] = hi.f2;
+                    if (SEC) dst[H + 2][lane] = hi.f1;
+                }
+            } else {
+                far_of(std::false_type{}, a, b, nr, c, iw2r, ka, lo, hi);
+            }
+            nsig = fmaf(c.z, lo.f0 + hi.f0, nsig);
+            for (int j = nr.x; j < nr.y; ++j) {
+                const Near r = near_peak(j, c, iw2r);
+                const float aL = c.z * r.I, aG = c.y * r.I;
+                const unsigned near = near_leaves(r);
+#pragma unroll
+                for (int l = 0; l < LV; ++l) {
+                    if (l >= nl) break;
+                    if (near >> l & 1u) {
+                        asm volatile("");
+                        float tt[PB];
+#pragma unroll
+                        for (int q = 0; q < PB; ++q) {
+                            bool up;
+                            const float q2 = r.pk.template q2_flat<ASYM>(u[l * PB + q], r.cs, up);
+                            tt[q] = fmaf(q2, q2, 1.0f);
+                        }
+#pragma unroll
+                        for (int q = 0; q < PB; ++q) {
+                            if (gauss_matters(tt[q])) {
+                                const int p = l * PB + q;
+                                bool up;
+                                const float q2 = r.pk.template q2<ASYM>(
+                                    u[p], sm.ul[p * LPS + li], up);
+                                tt[q] = fmaf(q2, q2, 1.0f);
+                                sig[p] = fmaf(aG, exp2_f32(-tt[q]), sig[p]);
+                            }
+                        }
+#pragma unroll
+                        for (int q = 0; q < PB; ++q)
+                            sig[l * PB + q] = fmaf(aL, rcp_f32(tt[q]), sig[l * PB + q]);
+                    } else {
+                        asm volatile("");
+                        bool up;
+                        const float q2 = r.pk.template q2_flat<ASYM>(vl[l], r.cs, up);
+                        lsig[l] = fmaf(aL, rcp_f32(fmaf(q2, q2, 1.0f)), lsig[l]);
+                    }
+                }
+            }
+        }
+    }
+    __builtin_amdgcn_s_setprio(3);
+#pragma unroll
+    for (int p = 0; p < NPP; ++p) sm.sig[wv][sl][p * LPS + li] = sig[p];
+    sm.nod[wv][lane] = nsig;
+    if (MID) {
+#pragma unroll
+        for (int l = 0; l < LV; ++l) sm.ndl[wv][l][lane] = lsig[l];
+    }
+    // (the point stage's loads go out before the waves meet)
+    static_assert(NT % PTS == 0, "a thread's points share their index in the tile");
+    double py = 0.0, pb = 0.0, pl = 0.0;
+    {
+        const int i = min(i0 + tid % PTS, P.N - 1);
+        py = P.y[i];
+        pb = P.bg[i];
+        pl = P.lgy[i];
+    }
+    __syncthreads();
+    // node sums over the waves, the tile's then brought to the leaves': the
+    // lanes of a group of NG take the terms of one sum
+    {
+        constexpr int NG = NT / (SG * kNodes) < 64 ? NT / (SG * kNodes) : 64;
+        const int o = tid / NG, j = tid % NG;
+        if (o < SG * kNodes) {
+            const int g = o / kNodes, m = o % kNodes;
+            double v = 0.0;
+            for (int x = j; x < NW * SLOTS; x += NG)
+                v += (double)sm.nod[x / SLOTS][g * LPS + x % SLOTS * kNodes + m];
+#pragma unroll
+            for (int x = NG / 2; x >= 1; x >>= 1) v += __shfl_xor(v, x, kWave);
+            if (j == 0) sm.pn[g][m] = v;
+        }
+    }
+    __syncthreads();
+    {
+        constexpr int OUT = SG * SM::kLow;
+        constexpr int NG = NT / OUT < 16 ? NT / OUT : 16;
+        static_assert(OUT * NG <= NT, "one pass");
+        const int o = tid / NG, j = tid % NG;
+        if (o < OUT) {
+            const int g = o / SM::kLow, q = o % SM::kLow;
+            double v = 0.0;
+            if (MID)
+#pragma unroll
+                for (int w = j; w < NW; w += NG)
+                    v += (double)sm.ndl[w][q / kNodes][g * kNodes + q % kNodes];
+#pragma unroll
+            for (int m = j; m < kNodes; m += NG)
+                v = fma((double)sm.em[q * kNodeStride + m], sm.pn[g][m], v);
+#pragma unroll
+            for (int x = NG / 2; x >= 1; x >>= 1) v += __shfl_xor(v, x, kWave);
+            if (j == 0) sm.low[g][q] = v;
+        }
+    }
+    __syncthreads();
+
+    // ---------------- points: f = B + near + interpolated far sums (FP64),
+    // the Poisson log-likelihood and the residual
+    for (int q = tid; q < SG * PTS; q += NT) {
+        const int g = q / PTS, qq = q % PTS, i = i0 + qq, ss = s0 + g;
+        double ll = 0.0;
+        float rr = 0.f;
+        if (i < P.N && ss < S) {
+            const double *low = sm.low[g] + qq / kLeaf * kNodes;
+            double sg = 0.0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sg += (double)sm.sig[w][g][qq];
+#pragma unroll
+            for (int m = 0; m < kNodes; ++m)
+                sg = fma((double)sm.lm[qq * kNodeStride + m], low[m], sg);
+            const double f = pb + sg, y = py;   // (PTS divides NT: one point per thread)
+            if (f_out) f_out[(size_t)ss * P.N + i] = (float)f;
+            if (GRAD || st.llp) {
+                if (st.llp) ll = (y != 0.0 ? y * log(f) : 0.0) - f - pl;
+                rr = (float)(y / f - 1.0);
+            }
+        }
+        sm.rres[g][qq] = rr;
+        ll = wave_sum(ll);
+        if (lane == 0) sm.red[q / kWave] = ll;
+    }
+    __syncthreads();
+    if (tid < ns && st.llp) {
+        double v = 0.0;
+#pragma unroll
+        for (int l = 0; l < LV; ++l) v += sm.red[tid * LV + l];
+        st.llp[(size_t)(s0 + tid) * st.nt + t] = v;
+    }
+    if (!GRAD) return;
+
+    // ---------------- the residual at the leaves' nodes, then at the tile's,
+    // and its slope there
+    {
+        constexpr int OUT = SG * SM::kLow;
+        constexpr int TPO = NT / OUT < kWave ? NT / OUT : kWave;
+        const int o = tid / TPO, j = tid % TPO;
+        if (o < OUT) {
+            const int g = o / SM::kLow, m = o % SM::kLow, q0 = m / kNodes * kLeaf;
+            double v = 0.0;
+            if (m / kNodes < nl)
+#pragma unroll 4
+                for (int q = q0 + j; q < q0 + kLeaf; q += TPO)
+                    v = fma((double)sm.lm[q * kNodeStride + m % kNodes], (double)sm.rres[g][q],
+                            v);
+#pragma unroll
+            for (int x = TPO / 2; x >= 1; x >>= 1) v += __shfl_xor(v, x, kWave);
+            if (j == 0) sm.low[g][m] = v;
+        }
+    }
+    __syncthreads();
+    {
+        constexpr int NG = NT / (SG * kNodes) < 64 ? NT / (SG * kNodes) : 64;
+        const int o = tid / NG, j = tid % NG;
+        if (o < SG * kNodes) {
+            const int g = o / kNodes, m = o % kNodes;
+            double v = 0.0, d = 0.0;
+            for (int q = j; q < nl * kNodes; q += NG) {
+                v = fma((double)sm.em[q * kNodeStride + m], sm.low[g][q], v);
+                if (!SEC) d = fma((double)sm.ed[q * kNodeStride + m], sm.low[g][q], d);
+            }
+#pragma unroll
+            for (int x = NG / 2; x >= 1; x >>= 1) {
+                v += __shfl_xor(v, x, kWave);
+                if (!SEC) d += __shfl_xor(d, x, kWave);
+            }
+            if (j == 0) {
+                sm.rn[g][m] = v;
+                sm.rs[g][m] = d;
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---------------- adjoint: the phase's sums over points and nodes
+    const float rn = (float)sm.rn[sl][n], rs = SEC ? 0.f : (float)sm.rs[sl][n];
+    float r[NPP], rl[LV];
+#pragma unroll
+    for (int p = 0; p < NPP; ++p) r[p] = sm.rres[sl][p * LPS + li];
+#pragma unroll
+    for (int l = 0; l < LV; ++l) rl[l] = MID ? (float)sm.low[sl][l * kNodes + n] : 0.f;
+    for (int c0 = 0; c0 < K; c0 += kPlanPhases) {
+        if (K > kPlanPhases) {          // (otherwise the ranges are still there)
+            __syncthreads();
+            plan(c0);
+        }
+        for (int k = c0 + wv; k < min(K, c0 + kPlanPhases); k += NW) {
+            prio_left((min(K, c0 + kPlanPhases) - k + NW - 1) / NW);
+            const int a = off[k], b = off[k + 1];
+            float acc[NS];
+#pragma unroll
+            for (int q = 0; q < NS; ++q) acc[q] = 0.f;
+            if (a < b) {
+                const int2 nr = near_range(k);
+                const float4 c = pk[k];
+                const float iw2r = ASYM ? pkr[k] : c.x;
+                const float ka = ASYM && SEC ? c.x / iw2r : 1.f;
+                FarSums lo, hi{0.f, 0.f, 0.f};
+                if (k < kCap) {
+                    float (*src)[kWave] = sm.far[k];
+                    constexpr int H = SM::kFarSums / 2;
+                    lo = FarSums{src[0][lane], SEC ? src[2][lane] : 0.f, src[1][lane]};
+                    if (ASYM)
+                        hi = FarSums{src[H][lane], SEC ? src[H + 2][lane] : 0.f,
+                                     src[H + 1][lane]};
+                } else {
+                    far_of(std::true_type{}, a, b, nr, c, iw2r, ka, lo, hi);
+                }
+                acc[3] = rn * lo.f0; acc[5] = rn * lo.f2;
+                acc[4] = SEC ? rn * lo.f1 : -0.5f * rcp_f32(c.x) * (rs * lo.f0);
+                if constexpr (ASYM) {
+                    acc[9] = rn * hi.f0; acc[11] = rn * hi.f2;
+                    acc[10] = SEC ? rn * hi.f1 : -0.5f * rcp_f32(iw2r) * (rs * hi.f0);
+                }
+                for (int j = nr.x; j < nr.y; ++j) {
+                    const Near rec = near_peak(j, c, iw2r);
+                    const SecW wl = SecW::of(rec.tw), wh = SecW::of(rec.tw * ka);
+                    // the peak's own sums, its intensity applied at the end
+                    const unsigned near = near_leaves(rec);
+                    float e[NS];
+#pragma unroll
+                    for (int q = 0; q < NS; ++q) e[q] = 0.f;
+#pragma unroll
+                    for (int l = 0; l < LV; ++l) {
+                        if (l >= nl) break;
+                        if (near >> l & 1u) {
+                            asm volatile("");
+                            float q2[PB], tt[PB];
+                            bool up[PB];
+#pragma unroll
+                            for (int q = 0; q < PB; ++q) {
+                                q2[q] = rec.pk.template q2_flat<ASYM>(u[l * PB + q], rec.cs,
+                                                                      up[q]);
+                                tt[q] = fmaf(q2[q], q2[q], 1.0f);
+                            }
+#pragma unroll
+                            for (int q = 0; q < PB; ++q) {
+                                if (gauss_matters(tt[q])) {
+                                    const int p = l * PB + q;
+                                    q2[q] = rec.pk.template q2<ASYM>(
+                                        u[p], sm.ul[p * LPS + li], up[q]);
+                                    tt[q] = fmaf(q2[q], q2[q], 1.0f);
+                                    adj_point_G<ASYM, SEC>(AdjPt{r[p], q2[q], tt[q], up[q]},
+                                                           rec.c, wl, wh, e);
+                                }
+                            }
+#pragma unroll
+                            for (int q = 0; q < PB; ++q)
+                                adj_terms_L<ASYM, SEC>(r[l * PB + q], q2[q], tt[q], up[q],
+                                                       rec.c, wl, wh, e);
+                        } else {
+                            asm volatile("");
+                            bool up;
+                            const float q2 = rec.pk.template q2_flat<ASYM>(vl[l], rec.cs, up);
+                            adj_terms_L<ASYM, SEC>(rl[l], q2, fmaf(q2, q2, 1.0f), up, rec.c,
+                                                   wl, wh, e);
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < NS; ++q) acc[q] = fmaf(rec.I, e[q], acc[q]);
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < NS; ++q) acc[q] = lanes_total<LPS>(acc[q]);
+            // (a row of 16 lanes holds the totals: lane q of it stores sum q)
+            float v = acc[0];
+#pragma unroll
+            for (int q = 1; q < NS; ++q) v = n == q ? acc[q] : v;
+            if (n < NS && slot == SLOTS - 1 && sl < ns)
+                st.part[(((size_t)t * K + k) * S + s) * NS + n] = v;
+        }
+    }
+}
+
+}  // namespace xrdvi

@@ -56,7 +56,7 @@ SlotLayout slot_layout(const Job &j) {
     SlotLayout L{};
     const int T = j.off[j.K];
     L.prob = 0;
-    L.step = a256(problem_bytes(j.N, j.K, T));
+    L.step = a256(problem_bytes(j.N, j.K, T, j.cutoff == 0.0));
     const StepShape sh{num_tiles(j.N), j.K, T, j.S, j.N, j.D, j.cutoff == 0.0,
                        j.width_law != 0};
     L.state = L.step + a256(step_bytes(sh));

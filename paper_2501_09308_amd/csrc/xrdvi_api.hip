@@ -8,6 +8,7 @@
 #include <string>
 #include <vector>
 
+#include "dense_tile.h"
 #include "xrdvi.h"
 #include "xrdvi_internal.h"
 
@@ -65,9 +66,6 @@ size_t step_bytes(const StepShape &sh) {
     b += align256(sizeof(double) * S * nt);         // llp
     b += align256(sh.dense ? sizeof(float) * NS * nt * K * S : 4);  // part
     b += align256(sizeof(double) * D);              // sd
-    // tile ranges: dense mode only (windowed tiles find their own)
-    b += align256(sh.dense ? sizeof(int4) * S * nt * K : 4);            // rng
-    b += align256(sh.dense && asym ? sizeof(int2) * S * nt * K : 4);    // rng2
     b += align256(sizeof(float) * S * (size_t)sh.N);  // rres
     b += align256(sizeof(double) * NS * K * S);     // pw
     b += align256(sh.sec ? sizeof(float4) * S * (size_t)std::max(sh.T, 1) : 4);  // psec
@@ -87,6 +85,7 @@ StepDev carve_step(void *base, const StepShape &sh) {
     auto take = [&](size_t bytes) { char *r = p; p += align256(bytes); return r; };
     StepDev st{};
     st.S = sh.S;
+    st.nt = sh.dense ? dense_cut(sh.N, sh.S).tiles(sh.N) : sh.ntiles;
     st.eps = (double *)take(sizeof(double) * S * D);
     st.phi = (double *)take(sizeof(double) * S * D);
     st.pk = (float4 *)take(sizeof(float4) * S * K);
@@ -98,8 +97,6 @@ StepDev carve_step(void *base, const StepShape &sh) {
     st.llp = (double *)take(sizeof(double) * S * nt);
     st.part = (float *)take(sh.dense ? sizeof(float) * NS * nt * K * S : 4);
     st.sd = (double *)take(sizeof(double) * D);
-    st.rng = (int4 *)take(sh.dense ? sizeof(int4) * S * nt * K : 4);
-    st.rng2 = (int2 *)take(sh.dense && asym ? sizeof(int2) * S * nt * K : 4);
     st.rres = (float *)take(sizeof(float) * S * (size_t)sh.N);
     st.pw = (double *)take(sizeof(double) * NS * K * S);
     st.psec = (float4 *)take(sh.sec ? sizeof(float4) * S * (size_t)std::max(sh.T, 1) : 4);
@@ -113,10 +110,10 @@ StepDev carve_step(void *base, const StepShape &sh) {
 
 // Device layout of a prepared problem, in 256-byte aligned pieces.
 struct ProblemLayout {
-    size_t x, y, bg, lgy, u, ul, off, ph, pos, inten, pt, ptl, perm, ptab, total;
+    size_t x, y, bg, lgy, u, ul, off, ph, pos, inten, pt, ptl, perm, ptab, dense, total;
 };
 
-static ProblemLayout problem_layout(int N, int K, int T) {
+static ProblemLayout problem_layout(int N, int K, int T, bool dense) {
     const int nt = num_tiles(N);
     const size_t T1 = (size_t)std::max(T, 1);
     ProblemLayout L{};
@@ -130,18 +127,21 @@ static ProblemLayout problem_layout(int N, int K, int T) {
     L.pt = slot(4 * (size_t)nt * T1); L.ptl = slot(4 * (size_t)nt * T1);
     L.perm = slot(4 * T1);
     L.ptab = slot(4 * (size_t)K * (kTabBuckets + 1));
+    L.dense = slot(dense ? DenseTables::of(N, K).total : 4);
     L.total = o;
     return L;
 }
 
-size_t problem_bytes(int N, int K, int T) { return problem_layout(N, K, T).total; }
+size_t problem_bytes(int N, int K, int T, bool dense) {
+    return problem_layout(N, K, T, dense).total;
+}
 
 hipError_t upload_problem(const xrdvi_problem_desc &d, double lambda,
                           char *base, ProbDev &P, int **perm_out,
                           hipStream_t stream) {
     const int N = d.N, K = d.K, T = d.peak_off[K];
     const int T1 = std::max(T, 1);
-    const ProblemLayout L = problem_layout(N, K, T);
+    const ProblemLayout L = problem_layout(N, K, T, d.cutoff == 0.0);
     // peaks ordered by position within each phase (stable)
     std::vector<int> perm(T1, 0), phase(T1, 0);
     std::vector<double> pos(T1, 0.0);
@@ -189,6 +189,7 @@ hipError_t upload_problem(const xrdvi_problem_desc &d, double lambda,
     if (e != hipSuccess) return e;
     P = ProbDev{};
     P.N = N; P.K = K; P.T = T; P.ntiles = num_tiles(N);
+    P.ref = d.cutoff == 0.0 ? kRefDense : kTile;
     P.D = latent_types(d);
     P.sec = d.width_law;
     P.cutoff = d.cutoff;
@@ -227,12 +228,13 @@ hipError_t upload_problem(const xrdvi_problem_desc &d, double lambda,
     P.pt = (const float *)(base + L.pt);
     P.ptl = (const float *)(base + L.ptl);
     P.ptab = (const int *)(base + L.ptab);
+    P.dense = base + L.dense;
     P.tab_x0 = tab_x0;
     P.tab_inv = tab_inv;
     if (perm_out) *perm_out = (int *)(base + L.perm);
     return launch_prepare(P, (double *)(base + L.lgy), (float *)(base + L.u),
                           (float *)(base + L.ul), (float *)(base + L.pt),
-                          (float *)(base + L.ptl), stream);
+                          (float *)(base + L.ptl), base + L.dense, stream);
 }
 
 }  // namespace xrdvi
@@ -499,7 +501,7 @@ int xrdvi_problem_create(xrdvi_ctx *ctx, const xrdvi_problem_desc *d,
     int rc = validate_desc(d, &lam);
     if (rc != XRDVI_OK) return rc;
     DeviceGuard g(ctx->device);
-    const size_t bytes = problem_bytes(d->N, d->K, d->peak_off[d->K]);
+    const size_t bytes = problem_bytes(d->N, d->K, d->peak_off[d->K], d->cutoff == 0.0);
     void *mem = nullptr;
     hipError_t e = hipMalloc(&mem, bytes);
     if (e != hipSuccess)
@@ -599,7 +601,8 @@ int xrdvi_profile(xrdvi_ctx *ctx, const xrdvi_problem *prob, int32_t S,
     hipStream_t s = static_cast<hipStream_t>(stream);
     HIP_TRY(launch_phi_consts(P, S, phi, st.pk, st.pkr, s), "phi constants");
     HIP_TRY(launch_peak_plan(P, st, phi, s), "window plan");
-    HIP_TRY(launch_plan(P, st, phi, s), "tile plan");
+    HIP_TRY(launch_plan(P, st, s), "tile plan");
+    st.llp = nullptr;                     // no log-likelihood
     HIP_TRY(timed_fused(ctx, P, st, false, f_out, s), "profile");
     return XRDVI_OK;
     API_GUARD_END
@@ -613,7 +616,10 @@ int xrdvi_profile_static(xrdvi_ctx *ctx, const xrdvi_problem *prob, int32_t S,
     if (S < 1 || S > kMaxSamples) return fail(XRDVI_EINVAL, "S must be in [1, 1024]");
     const ProbDev &P = prob->P;
     const StepShape sh = step_shape(P, S);
-    const size_t bytes = step_bytes(sh);
+    // (the limit also counts the per-(sample, tile, phase) plan that dense
+    // calls once kept here: which calls fit stays as documented)
+    const size_t former = sh.dense ? ((sh.D == 5 ? 24 : 16) * (size_t)S * sh.ntiles * sh.K) : 0;
+    const size_t bytes = step_bytes(sh) + former;
     if (bytes > kStaticScratchBytes)
         return fail(XRDVI_EINVAL,
                     "xrdvi_profile_static: this problem and S need " +
@@ -630,7 +636,8 @@ int xrdvi_profile_static(xrdvi_ctx *ctx, const xrdvi_problem *prob, int32_t S,
     // sequence, so nothing needs clearing between calls
     HIP_TRY(launch_phi_consts(P, S, phi, st.pk, st.pkr, s), "phi constants");
     HIP_TRY(launch_peak_plan(P, st, phi, s), "window plan");
-    HIP_TRY(launch_plan(P, st, phi, s), "tile plan");
+    HIP_TRY(launch_plan(P, st, s), "tile plan");
+    st.llp = nullptr;                     // no log-likelihood
     HIP_TRY(launch_fused(P, st, false, f_out, s), "profile");
     return XRDVI_OK;
     API_GUARD_END
@@ -669,7 +676,7 @@ int xrdvi_elbo_fwd(xrdvi_ctx *ctx, const xrdvi_problem *prob, int32_t S,
     tape->has_grad = false;
     HIP_TRY(launch_sample(P, st, loc, logscale, eps, seed, step, s), "sample");
     HIP_TRY(launch_peak_plan(P, st, st.phi, s), "window plan");
-    HIP_TRY(launch_plan(P, st, st.phi, s), "tile plan");
+    HIP_TRY(launch_plan(P, st, s), "tile plan");
     HIP_TRY(timed_fused(ctx, P, st, need_grad != 0, nullptr, s),
             "fused profile/adjoint");
     HIP_TRY(launch_elbo(P, st, logscale, elbo_out, loglik_out, s), "elbo");

@@ -45,6 +45,7 @@ constexpr int kPPL = 2;                   // 2-theta points per lane
 constexpr int kTile = kWave * kPPL;       // points per tile (one block)
 constexpr int kWaves = 4;                 // waves per block, splitting phases
 constexpr int kBlock = kWave * kWaves;
+constexpr int kRefDense = 256;
 // The Gaussian term of a peak is evaluated for a tile only when the peak
 // lies within kGaussReach FWHM of one of the tile's points: beyond 4.47 w,
 // 2^(-q2^2) < 2^-80 of the peak height, far below the FP32 resolution of
@@ -62,6 +63,8 @@ constexpr double kHalfDegRad = 3.14159265358979323846 / 360.0;  // rad per deg /
 // each phase).
 struct ProbDev {
     int N, K, T, ntiles;
+    int ref;                          // points that share a reference point: a tile,
+                                      // or 256 (kRefDense) in dense mode
     int D;                            // latent types per phase: 4, or 5 with
                                       // the asymmetry alpha
     int sec;                          // 1: width w sec(rho / 2); 0: width w
@@ -83,7 +86,7 @@ struct ProbDev {
                                       // width, whose q2 it then forms in
                                       // FP32, only with windows of at most
                                       // kF32Cutoff FWHM)
-    const float *u;                   // [ntiles * kTile] x_i - xref_tile
+    const float *u;                   // [ntiles * kTile] x_i - xref
                                       // (FP32, rounded)
     const float *ul;                  // [ntiles * kTile] its rounding
                                       // error: (x_i - xref) - u_i in FP32
@@ -91,13 +94,14 @@ struct ProbDev {
     const int *phase;                 // [T] phase of each peak
     const double *pos;                // [T]
     const float *inten;               // [T]
-    const float *pt;                  // [ntiles][T] p_j - xref_tile
-    const float *ptl;                 // [ntiles][T] its rounding error
+    const float *pt;                  // [ceil(N / ref)][T] p_j - xref
+    const float *ptl;                 // [ceil(N / ref)][T] its rounding error
     // position index of each phase's sorted peaks: ptab[k][b] is the first
     // peak j of phase k with pos[j] >= tab_x0 + b / tab_inv (b = 0 ..
     // kTabBuckets), a starting guess for searches over positions
     const int *ptab;
     double tab_x0, tab_inv;
+    const char *dense;        // dense mode: DenseTables
 };
 
 constexpr int kTabBuckets = 128;
@@ -109,6 +113,8 @@ __host__ __device__ inline int num_sums(int D) { return D == 5 ? 12 : 6; }
 
 struct StepDev {
     int S;
+    int nt;           // tiles of the likelihood and adjoint sums: P.ntiles, or in
+                      // dense mode those of dense_cut
     double *eps;      // [S][D K] noise used
     double *phi;      // [S][D K] constrained samples (h, mu, w, r[, alpha])
     float4 *pk;       // [S][K] (2/w, h(1-r)cG n/w, h r cL n/w, mu) in FP32,
@@ -117,18 +123,13 @@ struct StepDev {
     double *lpj;      // [S][K] log prior + log|J|
     double *lpb;      // [S][ceil(K/64)] per-wave sums of lpj
     int *lo, *hi;     // [S][T] window plan (sorted peak order)
-    int4 *rng;        // dense mode: [S][ntiles][K] peak ranges (ja, ga, gb, jb) of a
-                      // tile: [ja, jb) reach the tile, [ga, gb) need G
-    int2 *rng2;       // [S][ntiles][K] (jr, jl) for D = 5: peaks before jr
-                      // lie at or below every point of the tile, peaks from
-                      // jl above every point
     float4 *psec;     // [S][T] sec width law, per (sample, peak):
                       // (c, I c, tan(theta) (pi/360) w, 0), c = |cos theta|
     float *rres;      // [S][N] residual y/f - 1 (windowed mode)
     double *pw;       // [K][S][num_sums] adjoint sums per (phase, sample)
                       // (windowed mode)
-    double *llp;      // [S][ntiles] per-tile log-likelihood
-    float *part;      // [ntiles][K][S][num_sums] adjoint tile sums
+    double *llp;      // [S][nt] per-tile log-likelihood
+    float *part;      // [nt][K][S][num_sums] adjoint tile sums
     double *sd;       // [D K] exp(logscale)
     // windowed mode, constant width: the candidate peaks of each (tile,
     // phase) over the step's samples, laid out [..][ntiles][K] so that the
@@ -754,34 +755,18 @@ __device__ __forceinline__ float in_vgpr(float v) {
     return v;
 }
 
-// NW waves per block (kWaves, or more for grids too small to fill the GPU).
-template <int NW>
-struct FusedSmemT {
-    float sig[NW][kTile];
-    float rres[kTile];
-    double red[NW];
-};
-using FusedSmem = FusedSmemT<kWaves>;
-
-// ---- fused profile + likelihood + adjoint of one (tile, sample) ---------
+// ---- one phase's peaks over a tile's points, from global memory ------------
 //
-// NW waves (kWaves = 4 unless the grid is too small to fill the GPU) split
-// the phases (k = wave, wave + NW, ...).  Every wave holds
-// the same kTile points, kPPL per lane (point i0 + p*64 + lane).  Peak data
-// are wave-uniform (scalar loads).  Per phase the peaks run in segments:
+// The windowed forward's path for phases whose records do not fit the
+// staging space (win_tile below).  Per phase the peaks run in segments:
 // [ja, ga) and [gb, jb) need only the Lorentzian, [ga, gb) both components.
 // For asymmetric peaks [ga, gb) splits further at jr and jl: the tile lies
 // above the centres of [ja, jr), straddles those of [jr, jl) and lies below
-// those of [jl, jb), so only [jr, jl) picks the width per point.
-// WIN: each lane is masked by the peak's exact window.  The step kernels use
-// this tile for the dense mode (WIN = false, every peak reaches every
-// point); the windowed forward is win_tile below, whose global-memory path
-// reuses the segment loops with WIN = true.
-template <bool WIN>
+// those of [jl, jb), so only [jr, jl) picks the width per point.  Each lane is
+// masked by the peak's exact window.
 struct PeakMask {
     int lo, hi;
     __device__ __forceinline__ float apply(int i, float t) const {
-        if (!WIN) return t;
         return (unsigned)(i - lo) < (unsigned)(hi - lo) ? t
                                                         : __builtin_huge_valf();
     }
@@ -789,7 +774,7 @@ struct PeakMask {
 
 // One peak as a segment loop sees it: tile-relative position (and, for the
 // peaks near the tile, the rounding error of that position), intensity,
-// (windowed mode) its grid window [lo, hi) and, with the sec width law,
+// its grid window [lo, hi) and, with the sec width law,
 // c = |cos theta| and tw = tan(theta) (pi/360) w (the intensity is then
 // I c).
 struct PeakRec {
@@ -802,7 +787,7 @@ struct SegPeaks {
     cptr<float> pt;       // tile-relative positions
     cptr<float> ptl;      // their rounding errors
     cptr<float> inten;
-    cptr<int> wlo, whi;   // windows (WIN)
+    cptr<int> wlo, whi;   // windows
     cptr<float> sec;      // per-sample sec-law records, 4 floats each (SEC)
     // scalar loads (unused fields are never loaded)
     template <bool SEC, bool NEAR>
@@ -877,7 +862,7 @@ __device__ __forceinline__ SegQ seg_q(const PeakRec &r, float u,
 // Forward terms of the peaks [j0, j1) of one phase: accL += I l, accG += I e
 // (GAUSS) with l = 1 / (1 + q2^2), e = 2^(-1 - q2^2) (see phase_consts);
 // GAUSS segments take the near form of q2.
-template <bool WIN, bool GAUSS, int SIDE, bool SEC, typename PK>
+template <bool GAUSS, int SIDE, bool SEC, typename PK>
 __device__ __forceinline__ void fwd_segment(const PK &pk, int j0, int j1,
                                             const int (&idx)[kPPL],
                                             const float (&u)[kPPL],
@@ -889,8 +874,7 @@ __device__ __forceinline__ void fwd_segment(const PK &pk, int j0, int j1,
     for (int j = j0; j < j1; ++j) {
         const PeakRec r = pk.template rec<SEC, GAUSS>(j);
         const float I = r.I;
-        PeakMask<WIN> mk;
-        if (WIN) { mk.lo = r.lo; mk.hi = r.hi; }
+        const PeakMask mk{r.lo, r.hi};
 #pragma unroll
         for (int p = 0; p < kPPL; ++p) {
             const float q2 = seg_q<SIDE, GAUSS, SEC>(r, u[p], pp, p, iw2, iw2r).q2;
@@ -900,18 +884,6 @@ __device__ __forceinline__ void fwd_segment(const PK &pk, int j0, int j1,
         }
     }
 }
-
-// Per point and phase: l0 = sum I l, l1 = sum I l^2 q2, l2 = sum I l^2,
-// e0 = sum I e, e1 = sum I e q2, e2 = sum I e q2^2 (e = 2^(-1 - q2^2),
-// l = 1/(1 + q2^2)).
-struct Acc6 {
-    float l0[kPPL], l1[kPPL], l2[kPPL], e0[kPPL], e1[kPPL], e2[kPPL];
-    __device__ __forceinline__ void zero() {
-#pragma unroll
-        for (int p = 0; p < kPPL; ++p)
-            l0[p] = l1[p] = l2[p] = e0[p] = e1[p] = e2[p] = 0.f;
-    }
-};
 
 // Sec law: the shift moves the centre and, through W(rho), the width, so
 // the mu sums take per-peak weights (side A: A = 1 below, alpha above):
@@ -928,127 +900,9 @@ struct SecW {
     }
 };
 
-// Adds the peak terms of [j0, j1) to `lo` (points below the centres, or
-// symmetric peaks) or `hi` (points above).  ka: alpha of the phase (sec law
-// with asymmetric peaks; 1 otherwise).
-template <bool WIN, bool GAUSS, int SIDE, bool SEC>
-__device__ __forceinline__ void adj_segment(const SegPeaks &pk, int j0, int j1,
-                                            const int (&idx)[kPPL],
-                                            const float (&u)[kPPL],
-                                            const PhasePts &pp,
-                                            float iw2, float iw2r, float ka,
-                                            Acc6 &lo, Acc6 &hi) {
-#pragma unroll 2
-    for (int j = j0; j < j1; ++j) {
-        const PeakRec r = pk.template rec<SEC, GAUSS>(j);
-        const float I = r.I;
-        SecW wl{0.f, 0.f, 0.f}, wh{0.f, 0.f, 0.f};
-        if (SEC) {
-            if (SIDE != kAbove) wl = SecW::of(r.tw);
-            if (SIDE != kBelow) wh = SecW::of(r.tw * ka);
-        }
-        PeakMask<WIN> mk;
-        if (WIN) { mk.lo = r.lo; mk.hi = r.hi; }
-#pragma unroll
-        for (int p = 0; p < kPPL; ++p) {
-            const SegQ sq = seg_q<SIDE, GAUSS, SEC>(r, u[p], pp, p, iw2, iw2r);
-            const float q2 = sq.q2;
-            const float tt = mk.apply(idx[p], fmaf(q2, q2, 1.0f));
-            const float l = rcp_f32(tt);
-            const float Il = I * l;
-            const float Ill = Il * l;
-            float Ie = 0.f, Ieq = 0.f;
-            if (GAUSS) {
-                Ie = I * exp2_f32(-tt);
-                Ieq = Ie * q2;
-            }
-            if (SIDE != kBoth) {
-                Acc6 &a = SIDE == kAbove ? hi : lo;
-                a.l0[p] += Il;
-                a.l2[p] += Ill;
-                if (SEC) {
-                    const SecW &sw = SIDE == kAbove ? wh : wl;
-                    a.l1[p] = fmaf(Ill, fmaf(r.c, q2, -2.f * sw.kL), a.l1[p]);
-                    a.l1[p] = fmaf(Il, sw.kL, a.l1[p]);
-                } else {
-                    a.l1[p] = fmaf(Ill, q2, a.l1[p]);
-                }
-                if (GAUSS) {
-                    a.e0[p] += Ie;
-                    if (SEC) {
-                        const SecW &sw = SIDE == kAbove ? wh : wl;
-                        a.e1[p] = fmaf(Ie, fmaf(r.c, q2, fmaf(sw.bG, tt, sw.gG)),
-                                       a.e1[p]);
-                    } else {
-                        a.e1[p] += Ieq;
-                    }
-                    a.e2[p] = fmaf(Ieq, q2, a.e2[p]);
-                }
-            } else {
-                const float Ieqq = Ieq * q2;
-                const bool up = sq.up;
-                const float fu = up ? 1.f : 0.f;
-                const float fd = 1.f - fu;
-                float m1L, m1G = 0.f;
-                if (SEC) {
-                    const float kL = up ? wh.kL : wl.kL;
-                    m1L = fmaf(Ill, fmaf(r.c, q2, -2.f * kL), Il * kL);
-                    if (GAUSS) {
-                        const float bG = up ? wh.bG : wl.bG;
-                        const float gG = up ? wh.gG : wl.gG;
-                        m1G = Ie * fmaf(r.c, q2, fmaf(bG, tt, gG));
-                    }
-                } else {
-                    m1L = Ill * q2;
-                    m1G = Ieq;
-                }
-                hi.l0[p] = fmaf(fu, Il, hi.l0[p]);
-                lo.l0[p] = fmaf(fd, Il, lo.l0[p]);
-                hi.l2[p] = fmaf(fu, Ill, hi.l2[p]);
-                lo.l2[p] = fmaf(fd, Ill, lo.l2[p]);
-                hi.l1[p] = fmaf(fu, m1L, hi.l1[p]);
-                lo.l1[p] = fmaf(fd, m1L, lo.l1[p]);
-                if (GAUSS) {
-                    hi.e0[p] = fmaf(fu, Ie, hi.e0[p]);
-                    lo.e0[p] = fmaf(fd, Ie, lo.e0[p]);
-                    hi.e1[p] = fmaf(fu, m1G, hi.e1[p]);
-                    lo.e1[p] = fmaf(fd, m1G, lo.e1[p]);
-                    hi.e2[p] = fmaf(fu, Ieqq, hi.e2[p]);
-                    lo.e2[p] = fmaf(fd, Ieqq, lo.e2[p]);
-                }
-            }
-        }
-    }
-}
-
-// The six residual-weighted sums of `a` over the tile, wave totals written by
-// lane 0 to dst[0..5] in the order (e0, e1, e2, l0, l1, l2).
-__device__ __forceinline__ void store_sums(const Acc6 &a,
-                                           const float (&rres)[kPPL],
-                                           int lane, float *dst) {
-    float v0 = 0.f, v1 = 0.f, v2 = 0.f, v3 = 0.f, v4 = 0.f, v5 = 0.f;
-#pragma unroll
-    for (int p = 0; p < kPPL; ++p) {
-        v0 = fmaf(rres[p], a.e0[p], v0);
-        v1 = fmaf(rres[p], a.e1[p], v1);
-        v2 = fmaf(rres[p], a.e2[p], v2);
-        v3 = fmaf(rres[p], a.l0[p], v3);
-        v4 = fmaf(rres[p], a.l1[p], v4);
-        v5 = fmaf(rres[p], a.l2[p], v5);
-    }
-    v0 = wave_total_f32(v0); v1 = wave_total_f32(v1);
-    v2 = wave_total_f32(v2); v3 = wave_total_f32(v3);
-    v4 = wave_total_f32(v4); v5 = wave_total_f32(v5);
-    if (lane == 0) {
-        dst[0] = v0; dst[1] = v1; dst[2] = v2;
-        dst[3] = v3; dst[4] = v4; dst[5] = v5;
-    }
-}
-
 // Point stage of a tile, after the waves' partial signals are in sig:
 // f = B + signal in FP64, the tile's Poisson log-likelihood (to st.llp) and
 // the residual y/f - 1 (to rres_lds, and to st.rres when it is set).
-template <int NW = kWaves>
 __device__ __forceinline__ void tile_points(const ProbDev &P, const StepDev &st,
                                             int t, int s, float *f_out,
                                             const float (*sig)[kTile],
@@ -1057,13 +911,13 @@ __device__ __forceinline__ void tile_points(const ProbDev &P, const StepDev &st,
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int i0 = t * kTile;
     double ll = 0.0;
-    for (int q = threadIdx.x; q < kTile; q += NW * kWave) {
+    for (int q = threadIdx.x; q < kTile; q += kBlock) {
         const int i = i0 + q;
         float rr = 0.f;
         if (i < P.N) {
             double sg = 0.0;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) sg += (double)sig[w][q];
+            for (int w = 0; w < kWaves; ++w) sg += (double)sig[w][q];
             const double f = P.bg[i] + sg;
             if (f_out) f_out[(size_t)s * P.N + i] = (float)f;
             const double y = P.y[i];
@@ -1079,129 +933,8 @@ __device__ __forceinline__ void tile_points(const ProbDev &P, const StepDev &st,
     if (threadIdx.x == 0 && st.llp) {
         double tot = 0.0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) tot += red[w];
+        for (int w = 0; w < kWaves; ++w) tot += red[w];
         st.llp[(size_t)s * P.ntiles + t] = tot;
-    }
-}
-
-template <bool WIN, bool GRAD, bool ASYM, bool SEC, int NW = kWaves>
-__device__ void fused_tile(const ProbDev &P, const StepDev &st, int t, int s,
-                           float *f_out, FusedSmemT<NW> &sm) {
-    const int lane = threadIdx.x & (kWave - 1);
-    // wave index as a wave-uniform (scalar) value: loops over phases and
-    // peaks then run on the scalar unit and peak data use scalar loads
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int i0 = t * kTile;
-    cptr<float> pk = as_const(reinterpret_cast<const float *>(st.pk + (size_t)s * P.K));
-    cptr<int> rg = as_const(reinterpret_cast<const int *>(
-        st.rng + ((size_t)s * P.ntiles + t) * P.K));
-    cptr<float> pkr = nullptr;
-    cptr<int> rg2 = nullptr;
-    if (ASYM) {
-        pkr = as_const(st.pkr + (size_t)s * P.K);
-        rg2 = as_const(reinterpret_cast<const int *>(
-            st.rng2 + ((size_t)s * P.ntiles + t) * P.K));
-    }
-    SegPeaks sp;
-    sp.pt = as_const(P.pt + (size_t)t * P.T);
-    sp.ptl = as_const(P.ptl + (size_t)t * P.T);
-    sp.inten = as_const(P.inten);
-    sp.wlo = as_const(st.lo + (size_t)s * P.T);
-    sp.whi = as_const(st.hi + (size_t)s * P.T);
-    sp.sec = SEC ? as_const(reinterpret_cast<const float *>(st.psec + (size_t)s * P.T))
-                 : nullptr;
-
-    float u[kPPL], ul[kPPL];
-    int idx[kPPL];
-#pragma unroll
-    for (int p = 0; p < kPPL; ++p) {
-        idx[p] = i0 + p * kWave + lane;
-        u[p] = P.u[idx[p]];
-        ul[p] = P.ul[idx[p]];
-    }
-
-    // ---------------- forward: partial signal over this wave's phases
-    float sig[kPPL];
-#pragma unroll
-    for (int p = 0; p < kPPL; ++p) sig[p] = 0.f;
-
-    for (int k = wv; k < P.K; k += NW) {
-        const int ja = rg[4 * k], ga = rg[4 * k + 1], gb = rg[4 * k + 2],
-                  jb = rg[4 * k + 3];
-        if (ja >= jb) continue;
-        const float iw2 = in_vgpr(pk[4 * k]);
-        const float aG = pk[4 * k + 1], aL = pk[4 * k + 2], mu = pk[4 * k + 3];
-        const float iw2r = ASYM ? in_vgpr(pkr[k]) : iw2;
-        PhasePts pp;
-        pp.set(u, ul, mu, iw2, iw2r, ASYM);
-        float accL[kPPL], accG[kPPL];
-#pragma unroll
-        for (int p = 0; p < kPPL; ++p) {
-            accL[p] = 0.f;
-            accG[p] = 0.f;
-        }
-        if (ASYM) {
-            const int jr = rg2[2 * k], jl = rg2[2 * k + 1];
-            fwd_segment<WIN, false, kAbove, SEC>(sp, ja, ga, idx, u, pp, iw2, iw2r, accL, accG);
-            fwd_segment<WIN, true, kAbove, SEC>(sp, ga, jr, idx, u, pp, iw2, iw2r, accL, accG);
-            fwd_segment<WIN, true, kBoth, SEC>(sp, jr, jl, idx, u, pp, iw2, iw2r, accL, accG);
-            fwd_segment<WIN, true, kBelow, SEC>(sp, jl, gb, idx, u, pp, iw2, iw2r, accL, accG);
-            fwd_segment<WIN, false, kBelow, SEC>(sp, gb, jb, idx, u, pp, iw2, iw2r, accL, accG);
-        } else {
-            fwd_segment<WIN, false, kBelow, SEC>(sp, ja, ga, idx, u, pp, iw2, iw2r, accL, accG);
-            fwd_segment<WIN, true, kBelow, SEC>(sp, ga, gb, idx, u, pp, iw2, iw2r, accL, accG);
-            fwd_segment<WIN, false, kBelow, SEC>(sp, gb, jb, idx, u, pp, iw2, iw2r, accL, accG);
-        }
-#pragma unroll
-        for (int p = 0; p < kPPL; ++p)
-            sig[p] = fmaf(aL, accL[p], fmaf(aG, accG[p], sig[p]));
-    }
-
-#pragma unroll
-    for (int p = 0; p < kPPL; ++p) sm.sig[wv][p * kWave + lane] = sig[p];
-    __syncthreads();
-
-    tile_points<NW>(P, st, t, s, f_out, sm.sig, sm.rres, sm.red);
-    if (!GRAD) return;
-
-    // ---------------- adjoint: recompute every peak value; the phase's sums
-    // are sum_points (y/f - 1) * (per-point sums), reduced over the wave
-    constexpr int NS = ASYM ? 12 : 6;
-    float rres[kPPL];
-#pragma unroll
-    for (int p = 0; p < kPPL; ++p) rres[p] = sm.rres[p * kWave + lane];
-
-    for (int k = wv; k < P.K; k += NW) {
-        float *dst = st.part + (((size_t)t * P.K + k) * st.S + s) * NS;
-        const int ja = rg[4 * k], ga = rg[4 * k + 1], gb = rg[4 * k + 2],
-                  jb = rg[4 * k + 3];
-        if (ja >= jb) {
-            if (lane < NS) dst[lane] = 0.f;
-            continue;
-        }
-        const float iw2 = in_vgpr(pk[4 * k]);
-        const float mu = pk[4 * k + 3];
-        const float iw2r = ASYM ? in_vgpr(pkr[k]) : iw2;
-        PhasePts pp;
-        pp.set(u, ul, mu, iw2, iw2r, ASYM);
-        const float ka = ASYM && SEC ? iw2 / iw2r : 1.f;   // alpha
-        Acc6 lo, hi;
-        lo.zero();
-        if (ASYM) {
-            hi.zero();
-            const int jr = rg2[2 * k], jl = rg2[2 * k + 1];
-            adj_segment<WIN, false, kAbove, SEC>(sp, ja, ga, idx, u, pp, iw2, iw2r, ka, lo, hi);
-            adj_segment<WIN, true, kAbove, SEC>(sp, ga, jr, idx, u, pp, iw2, iw2r, ka, lo, hi);
-            adj_segment<WIN, true, kBoth, SEC>(sp, jr, jl, idx, u, pp, iw2, iw2r, ka, lo, hi);
-            adj_segment<WIN, true, kBelow, SEC>(sp, jl, gb, idx, u, pp, iw2, iw2r, ka, lo, hi);
-            adj_segment<WIN, false, kBelow, SEC>(sp, gb, jb, idx, u, pp, iw2, iw2r, ka, lo, hi);
-        } else {
-            adj_segment<WIN, false, kBelow, SEC>(sp, ja, ga, idx, u, pp, iw2, iw2r, ka, lo, hi);
-            adj_segment<WIN, true, kBelow, SEC>(sp, ga, gb, idx, u, pp, iw2, iw2r, ka, lo, hi);
-            adj_segment<WIN, false, kBelow, SEC>(sp, gb, jb, idx, u, pp, iw2, iw2r, ka, lo, hi);
-        }
-        store_sums(lo, rres, lane, dst);
-        if (ASYM) store_sums(hi, rres, lane, dst + 6);
     }
 }
 
@@ -1312,15 +1045,15 @@ __device__ void win_phase_global(const SegPeaks &sp, int4 r, int2 r2,
     if (ASYM) {
         const int jr = __builtin_amdgcn_readfirstlane(r2.x);
         const int jl = __builtin_amdgcn_readfirstlane(r2.y);
-        fwd_segment<true, false, kAbove, SEC>(sp, ja, ga, idx, u, pp, iw2, iw2r, accL, accG);
-        fwd_segment<true, true, kAbove, SEC>(sp, ga, jr, idx, u, pp, iw2, iw2r, accL, accG);
-        fwd_segment<true, true, kBoth, SEC>(sp, jr, jl, idx, u, pp, iw2, iw2r, accL, accG);
-        fwd_segment<true, true, kBelow, SEC>(sp, jl, gb, idx, u, pp, iw2, iw2r, accL, accG);
-        fwd_segment<true, false, kBelow, SEC>(sp, gb, jb, idx, u, pp, iw2, iw2r, accL, accG);
+        fwd_segment<false, kAbove, SEC>(sp, ja, ga, idx, u, pp, iw2, iw2r, accL, accG);
+        fwd_segment<true, kAbove, SEC>(sp, ga, jr, idx, u, pp, iw2, iw2r, accL, accG);
+        fwd_segment<true, kBoth, SEC>(sp, jr, jl, idx, u, pp, iw2, iw2r, accL, accG);
+        fwd_segment<true, kBelow, SEC>(sp, jl, gb, idx, u, pp, iw2, iw2r, accL, accG);
+        fwd_segment<false, kBelow, SEC>(sp, gb, jb, idx, u, pp, iw2, iw2r, accL, accG);
     } else {
-        fwd_segment<true, false, kBelow, SEC>(sp, ja, ga, idx, u, pp, iw2, iw2r, accL, accG);
-        fwd_segment<true, true, kBelow, SEC>(sp, ga, gb, idx, u, pp, iw2, iw2r, accL, accG);
-        fwd_segment<true, false, kBelow, SEC>(sp, gb, jb, idx, u, pp, iw2, iw2r, accL, accG);
+        fwd_segment<false, kBelow, SEC>(sp, ja, ga, idx, u, pp, iw2, iw2r, accL, accG);
+        fwd_segment<true, kBelow, SEC>(sp, ga, gb, idx, u, pp, iw2, iw2r, accL, accG);
+        fwd_segment<false, kBelow, SEC>(sp, gb, jb, idx, u, pp, iw2, iw2r, accL, accG);
     }
 #pragma unroll
     for (int p = 0; p < kPPL; ++p)
@@ -1620,13 +1353,9 @@ struct AdjPt {
 };
 
 template <bool ASYM, bool SEC>
-__device__ __forceinline__ AdjPt adj_point_L(float R, float d, float iw2,
-                                             float iw2r, float c,
-                                             const SecW &wl, const SecW &wh,
-                                             float (&acc)[ASYM ? 12 : 6]) {
-    const bool up = ASYM && d >= 0.f;
-    const float q2 = d * (up ? iw2r : iw2);
-    const float tt = fmaf(q2, q2, 1.0f);
+__device__ __forceinline__ void adj_terms_L(float R, float q2, float tt, bool up,
+                                            float c, const SecW &wl, const SecW &wh,
+                                            float (&acc)[ASYM ? 12 : 6]) {
     const float l = rcp_f32(tt);
     const float Rl = R * l;
     const float Rll = Rl * l;
@@ -1637,12 +1366,12 @@ __device__ __forceinline__ AdjPt adj_point_L(float R, float d, float iw2,
     } else {
         m1L = Rll * q2;
     }
-    if (!ASYM) {
+    if constexpr (!ASYM) {
         acc[3] += Rl;
         acc[5] += Rll;
         if (SEC) acc[4] += m1L;
         else acc[4] = fmaf(Rll, q2, acc[4]);
-    } else {
+    } else {   // six sums per side
         const float fu = up ? 1.f : 0.f, fd = 1.f - fu;
         acc[3] = fmaf(fd, Rl, acc[3]);
         acc[9] = fmaf(fu, Rl, acc[9]);
@@ -1651,6 +1380,16 @@ __device__ __forceinline__ AdjPt adj_point_L(float R, float d, float iw2,
         acc[4] = fmaf(fd, m1L, acc[4]);
         acc[10] = fmaf(fu, m1L, acc[10]);
     }
+}
+
+template <bool ASYM, bool SEC>
+__device__ __forceinline__ AdjPt adj_point_L(float R, float d, float iw2,
+                                             float iw2r, float c,
+                                             const SecW &wl, const SecW &wh,
+                                             float (&acc)[ASYM ? 12 : 6]) {
+    const bool up = ASYM && d >= 0.f;
+    const float q2 = d * (up ? iw2r : iw2), tt = fmaf(q2, q2, 1.0f);
+    adj_terms_L<ASYM, SEC>(R, q2, tt, up, c, wl, wh, acc);
     return AdjPt{R, q2, tt, up};
 }
 
@@ -1669,7 +1408,7 @@ __device__ __forceinline__ void adj_point_G(const AdjPt &pt, float c,
     } else {
         m1G = Req;
     }
-    if (!ASYM) {
+    if constexpr (!ASYM) {
         acc[0] += Re;
         acc[1] += m1G;
         acc[2] = fmaf(Req, q2, acc[2]);

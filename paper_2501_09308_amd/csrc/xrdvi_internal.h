@@ -13,9 +13,9 @@
 namespace xrdvi {
 
 // Per-problem tables: ln y!, the tile-relative FP32 grid and peak positions
-// and the rounding errors of both.
+// and the rounding errors of both; in dense mode the DenseTables.
 hipError_t launch_prepare(const ProbDev &P, double *lgy, float *u, float *ul,
-                          float *pt, float *ptl, hipStream_t stream);
+                          float *pt, float *ptl, char *dense, hipStream_t stream);
 hipError_t launch_sample(const ProbDev &P, const StepDev &st,
                          const double *loc, const double *logscale,
                          const double *eps, uint64_t seed, uint64_t step,
@@ -31,13 +31,9 @@ hipError_t launch_windows(const ProbDev &P, int S, const double *phi, int *lo,
 // records (sec law); nothing for a dense constant-width problem.
 hipError_t launch_peak_plan(const ProbDev &P, const StepDev &st,
                             const double *phi, hipStream_t stream);
-hipError_t launch_plan(const ProbDev &P, const StepDev &st, const double *phi,
-                       hipStream_t stream);
-// wide: dense tiles with more waves each (small grids; other summation
-// order of the partial signals, so not for results that must match across
-// paths bit for bit).
+hipError_t launch_plan(const ProbDev &P, const StepDev &st, hipStream_t stream);
 hipError_t launch_fused(const ProbDev &P, const StepDev &st, bool grad,
-                        float *f_out, hipStream_t stream, bool wide = false);
+                        float *f_out, hipStream_t stream);
 // logp_out: per-sample log posterior density; gz_out: per-sample gradient
 // of it in z, [S][D K] (both optional).
 hipError_t launch_elbo(const ProbDev &P, const StepDev &st,
@@ -89,7 +85,7 @@ inline int latent_types(const xrdvi_problem_desc &d) {
 // Device bytes of a prepared problem and its upload (validated desc,
 // resolved lambda) into `base`; fills P and the sorted-to-caller peak
 // permutation.  Synchronises `stream` before returning (pageable sources).
-size_t problem_bytes(int N, int K, int T);
+size_t problem_bytes(int N, int K, int T, bool dense);
 hipError_t upload_problem(const xrdvi_problem_desc &d, double lambda,
                           char *base, ProbDev &P, int **perm_out,
                           hipStream_t stream);

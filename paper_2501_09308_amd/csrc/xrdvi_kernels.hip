@@ -1,5 +1,8 @@
 // Global kernels of one analysis step (gfx950).  See xrdvi_device.h for the
 // per-tile work and the data layout.
+#include <type_traits>
+
+#include "dense_tile.h"
 #include "xrdvi_device.h"
 #include "xrdvi_internal.h"
 #include "xrdvi_steps.h"
@@ -10,8 +13,7 @@ namespace xrdvi {
 __global__ void k_prepare_points(ProbDev P, double *lgy, float *u, float *ul) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= P.ntiles * kTile) return;
-    const int t = i / kTile;
-    const double xref = P.x[min(t * kTile + kTile / 2, P.N - 1)];
+    const double xref = P.x[min(i / P.ref * P.ref + P.ref / 2, P.N - 1)];
     if (i < P.N) {
         lgy[i] = lgamma(P.y[i] + 1.0);
         const double v = P.x[i] - xref;
@@ -26,7 +28,7 @@ __global__ void k_prepare_points(ProbDev P, double *lgy, float *u, float *ul) {
 
 __global__ void k_prepare_peaks(ProbDev P, float *pt, float *ptl) {
     const int t = blockIdx.y;
-    const double xref = P.x[min(t * kTile + kTile / 2, P.N - 1)];
+    const double xref = P.x[min(t * P.ref + P.ref / 2, P.N - 1)];
     for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < P.T;
          j += gridDim.x * blockDim.x) {
         const double v = P.pos[j] - xref;
@@ -34,6 +36,19 @@ __global__ void k_prepare_peaks(ProbDev P, float *pt, float *ptl) {
         pt[(size_t)t * P.T + j] = vh;
         ptl[(size_t)t * P.T + j] = (float)(v - (double)vh);
     }
+}
+
+// The tables of a dense problem: one block per leaf; one thread per (kind of
+// tile, margin, tile, phase).
+__global__ __launch_bounds__(256) void k_prepare_dense(ProbDev P, char *tables) {
+    dense_tables_leaf(P, blockIdx.x, tables);
+}
+__global__ __launch_bounds__(64) void k_prepare_near(ProbDev P, int2 *near, size_t tiles) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x, t = blockIdx.y;
+    const int leaves = blockIdx.z / kNearLevels ? 4 : 2, level = blockIdx.z % kNearLevels;
+    if (k < P.K && t < (P.N + leaves * kLeaf - 1) / (leaves * kLeaf))
+        near[(((size_t)(leaves == 4) * kNearLevels + level) * tiles + t) * P.K + k] =
+            dense_near_entry(P, leaves, level, t, k);
 }
 
 // a1: grid (ceil(K/64), S), 256 threads.
@@ -77,15 +92,6 @@ __global__ void k_windows(ProbDev P, int S, const double *__restrict__ phi,
         windows_elem<SEC>(P, phi, lo, hi, perm, g, psec);
 }
 
-// a2 (cont.): peak ranges of every (sample, tile, phase).
-template <bool SEC>
-__global__ void k_plan(ProbDev P, StepDev st, const double *__restrict__ phi) {
-    const size_t n = (size_t)st.S * P.ntiles * P.K;
-    for (size_t g = (size_t)blockIdx.x * blockDim.x + threadIdx.x; g < n;
-         g += (size_t)gridDim.x * blockDim.x)
-        plan_elem<SEC>(P, st, phi, g);
-}
-
 // a2 (windowed, constant width): the window step and the phases' extremes
 // over the samples in one launch.  Blocks [0, next) take 64 phases each,
 // the others one thread per (sample, peak) as k_windows.
@@ -111,26 +117,16 @@ __global__ __launch_bounds__(kCandThreads) void k_cand(ProbDev P, StepDev st) {
     if (k < P.K) cand_elem(P, st, blockIdx.y, k);
 }
 
-// a3 + a4 (+ a6): grid (ntiles, S), kBlock threads, blocks ordered by XCD
-// (the samples of a tile share its positions and counts in one L2, and
-// their adjoint partials, adjacent in memory, merge there before write-back).
-template <bool WIN, bool GRAD, bool ASYM, bool SEC>
-__global__ __launch_bounds__(kBlock) void k_fused(ProbDev P, StepDev st,
-                                                  float *f_out) {
-    __shared__ FusedSmem sm;
-    const int2 ts = xcd_tile_sample(P.ntiles, st.S);
-    fused_tile<WIN, GRAD, ASYM, SEC>(P, st, ts.x, ts.y, f_out, sm);
-}
-
-// Dense a3 + a4 + a6 with kWideWaves waves per tile, for grids of too few
-// (tile, sample) blocks to fill the GPU (the log-posterior path of
-// Hamiltonian Monte Carlo with a few chains); kWideWaves * 64 threads.
-constexpr int kWideWaves = 16;
-template <bool GRAD, bool ASYM, bool SEC>
-__global__ __launch_bounds__(kWideWaves * kWave) void k_fused_wide(ProbDev P, StepDev st,
+// a3 + a4 (+ a6), dense: one (tile, group of SG samples) per block, grid
+// (tiles, groups), blocks ordered by XCD (the samples of a tile share its
+// positions and counts in one L2, and their adjoint partials, adjacent in
+// memory, merge there before write-back).  Four waves per SIMD (128 VGPRs).
+template <bool GRAD, bool ASYM, bool SEC, int SG, int LV>
+__global__ __launch_bounds__(kDenseWaves * kWave, 4) void k_dense(ProbDev P, StepDev st,
                                                                   float *f_out) {
-    __shared__ FusedSmemT<kWideWaves> sm;
-    fused_tile<false, GRAD, ASYM, SEC, kWideWaves>(P, st, blockIdx.x, blockIdx.y, f_out, sm);
+    __shared__ DenseSmem<kDenseWaves, SG, LV, ASYM, SEC> sm;
+    const int2 tg = xcd_tile_sample(st.nt, (st.S + SG - 1) / SG);
+    dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, LV>(P, st, tg.x, tg.y, f_out, sm);
 }
 
 // a3 + a4 (windowed): forward tile over its staged peak records; grid
@@ -205,12 +201,19 @@ __global__ void k_adam(int n, double *theta, double *m1, double *m2,
 // ---- launchers ------------------------------------------------------------
 
 hipError_t launch_prepare(const ProbDev &P, double *lgy, float *u, float *ul,
-                          float *pt, float *ptl, hipStream_t stream) {
+                          float *pt, float *ptl, char *dense, hipStream_t stream) {
     const int np = P.ntiles * kTile;
     k_prepare_points<<<(np + 255) / 256, 256, 0, stream>>>(P, lgy, u, ul);
     if (P.T > 0) {
-        dim3 g((P.T + 255) / 256 < 64 ? (P.T + 255) / 256 : 64, P.ntiles);
+        dim3 g((P.T + 255) / 256 < 64 ? (P.T + 255) / 256 : 64, (P.N + P.ref - 1) / P.ref);
         k_prepare_peaks<<<g, 256, 0, stream>>>(P, pt, ptl);
+    }
+    if (P.cutoff == 0.0) {
+        const DenseTables D = DenseTables::of(P.N, P.K);
+        const int leaves = (P.N + kLeaf - 1) / kLeaf;
+        k_prepare_dense<<<leaves, 256, 0, stream>>>(P, dense);
+        dim3 g((P.K + 63) / 64, (leaves + 1) / 2, 2 * kNearLevels);
+        k_prepare_near<<<g, 64, 0, stream>>>(P, reinterpret_cast<int2 *>(dense + D.near), D.tiles);
     }
     return hipGetLastError();
 }
@@ -265,24 +268,15 @@ hipError_t launch_peak_plan(const ProbDev &P, const StepDev &st,
                           st.hi, nullptr, stream, P.sec ? st.psec : nullptr);
 }
 
-// Dense mode: the tile plan.  Windowed mode with a constant width: the
-// candidate ranges of each (tile, phase) over the step's samples, from the
-// phases' extremes that launch_peak_plan found (the windowed forward tile
-// then finds its exact ranges among them).
-hipError_t launch_plan(const ProbDev &P, const StepDev &st, const double *phi,
-                       hipStream_t stream) {
-    if (P.cutoff > 0.0) {
-        if (!P.sec && st.cab) {
-            dim3 g((P.K + kCandThreads - 1) / kCandThreads, P.ntiles);
-            k_cand<<<g, kCandThreads, 0, stream>>>(P, st);
-        }
-        return hipGetLastError();
+// Windowed mode with a constant width: the candidate ranges of each (tile,
+// phase) over the step's samples, from the phases' extremes that
+// launch_peak_plan found (the windowed forward tile then finds its exact
+// ranges among them).
+hipError_t launch_plan(const ProbDev &P, const StepDev &st, hipStream_t stream) {
+    if (P.cutoff > 0.0 && !P.sec && st.cab) {
+        dim3 g((P.K + kCandThreads - 1) / kCandThreads, P.ntiles);
+        k_cand<<<g, kCandThreads, 0, stream>>>(P, st);
     }
-    const size_t n = (size_t)st.S * P.ntiles * P.K;
-    size_t blocks = (n + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    if (P.sec) k_plan<true><<<(unsigned)blocks, 256, 0, stream>>>(P, st, phi);
-    else k_plan<false><<<(unsigned)blocks, 256, 0, stream>>>(P, st, phi);
     return hipGetLastError();
 }
 
@@ -290,9 +284,9 @@ hipError_t launch_plan(const ProbDev &P, const StepDev &st, const double *phi,
 // the residual, the peak-major adjoint follows when `grad` is set.
 template <bool ASYM, bool SEC>
 static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
-                           float *f_out, hipStream_t stream, bool wide) {
-    dim3 g(P.ntiles, st.S);
+                           float *f_out, hipStream_t stream) {
     if (P.cutoff > 0.0) {
+        dim3 g(P.ntiles, st.S);
         StepDev sf = st;
         if (!grad) sf.rres = nullptr;
         // records in grid steps on a uniform grid (constant width only)
@@ -307,26 +301,31 @@ static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
     } else {
         StepDev sd = st;
         sd.rres = nullptr;      // dense: the residual stays in LDS
-        if (wide) {
-            const int nt = kWideWaves * kWave;
-            if (grad) k_fused_wide<true, ASYM, SEC><<<g, nt, 0, stream>>>(P, sd, f_out);
-            else k_fused_wide<false, ASYM, SEC><<<g, nt, 0, stream>>>(P, sd, f_out);
-        } else if (grad) {
-            k_fused<false, true, ASYM, SEC><<<g, kBlock, 0, stream>>>(P, sd, f_out);
-        } else {
-            k_fused<false, false, ASYM, SEC><<<g, kBlock, 0, stream>>>(P, sd, f_out);
-        }
+        auto run = [&](auto sg_tag, auto lv_tag) {
+            constexpr int SG = decltype(sg_tag)::value, LV = decltype(lv_tag)::value;
+            constexpr int nt = kDenseWaves * kWave;
+            const dim3 g(st.nt, (st.S + SG - 1) / SG);
+            if (grad) k_dense<true, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, sd, f_out);
+            else k_dense<false, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, sd, f_out);
+        };
+        const std::integral_constant<int, 1> one;
+        const std::integral_constant<int, 2> two;
+        const std::integral_constant<int, 4> four;
+        const DenseCut cut = dense_cut(P.N, st.S);
+        if (cut.leaves == 4) run(four, four);
+        else if (cut.group == 4) run(four, two);
+        else run(one, two);
     }
 }
 
 hipError_t launch_fused(const ProbDev &P, const StepDev &st, bool grad,
-                        float *f_out, hipStream_t stream, bool wide) {
+                        float *f_out, hipStream_t stream) {
     if (P.D == 5) {
-        if (P.sec) launch_fused_t<true, true>(P, st, grad, f_out, stream, wide);
-        else launch_fused_t<true, false>(P, st, grad, f_out, stream, wide);
+        if (P.sec) launch_fused_t<true, true>(P, st, grad, f_out, stream);
+        else launch_fused_t<true, false>(P, st, grad, f_out, stream);
     } else {
-        if (P.sec) launch_fused_t<false, true>(P, st, grad, f_out, stream, wide);
-        else launch_fused_t<false, false>(P, st, grad, f_out, stream, wide);
+        if (P.sec) launch_fused_t<false, true>(P, st, grad, f_out, stream);
+        else launch_fused_t<false, false>(P, st, grad, f_out, stream);
     }
     return hipGetLastError();
 }
@@ -374,11 +373,8 @@ hipError_t launch_logpost(const ProbDev &P, const StepDev &st,
                           double *gz, hipStream_t stream) {
     hipError_t e = launch_sample(P, st, zeros, zeros, z, 0, 0, stream);
     if (e == hipSuccess) e = launch_peak_plan(P, st, st.phi, stream);
-    if (e == hipSuccess) e = launch_plan(P, st, st.phi, stream);
-    // a few chains give too few (tile, sample) blocks to fill the GPU: the
-    // dense tile then splits its phases over more waves
-    const bool wide = P.cutoff == 0.0 && (long long)P.ntiles * st.S < 4LL * 256;
-    if (e == hipSuccess) e = launch_fused(P, st, gz != nullptr, nullptr, stream, wide);
+    if (e == hipSuccess) e = launch_plan(P, st, stream);
+    if (e == hipSuccess) e = launch_fused(P, st, gz != nullptr, nullptr, stream);
     if (e == hipSuccess)
         e = launch_elbo(P, st, zeros, nullptr, nullptr, stream, logp);
     if (e == hipSuccess && gz)

@@ -118,22 +118,6 @@ __device__ inline void windows_elem(const ProbDev &P, const double *phi,
     }
 }
 
-// ---- a2 (cont.): range element g = (s * ntiles + t) * K + k ---------------
-template <bool SEC>
-__device__ inline void plan_elem(const ProbDev &P, const StepDev &st,
-                                 const double *phi, size_t g) {
-    const int k = (int)(g % P.K);
-    const size_t st_idx = g / P.K;
-    const int t = (int)(st_idx % P.ntiles), s = (int)(st_idx / P.ntiles);
-    if (P.D == 5) {
-        int2 side;
-        st.rng[g] = tile_range<SEC>(P, st, phi, s, t, k, &side);
-        st.rng2[g] = side;
-    } else {
-        st.rng[g] = tile_range<SEC>(P, st, phi, s, t, k, nullptr);
-    }
-}
-
 // ---- a5: ELBO assembly, block of 1024 threads --------------------------------
 //
 // Each sample is summed by a group of G consecutive lanes (G a power of
@@ -158,7 +142,7 @@ __device__ inline double elbo_block(const ProbDev &P, const StepDev &st,
     const int kb = (P.K + kWave - 1) / kWave;
     double l = 0.0, p = 0.0;
     if (s < S) {
-        for (int t = g; t < P.ntiles; t += G) l += st.llp[(size_t)s * P.ntiles + t];
+        for (int t = g; t < st.nt; t += G) l += st.llp[(size_t)s * st.nt + t];
         for (int b = g; b < kb; b += G) p += st.lpb[(size_t)s * kb + b];
     }
     for (int o = G / 2; o >= 1; o >>= 1) {
@@ -348,7 +332,7 @@ __device__ inline void grad_block(const ProbDev &P, const StepDev &st, int k,
                         if (c < NS) E[c] = src[c];
                 }
             } else {
-                for (int t = g; t < P.ntiles; t += G) {
+                for (int t = g; t < st.nt; t += G) {
                     const float *src = st.part + (((size_t)t * K + k) * S + s) * NS;
 #pragma unroll
                     for (int c = 0; c < 12; ++c)

@@ -25,7 +25,7 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
-KERNEL_SOURCES = ("xrdvi_device.h", "xrdvi_steps.h", "xrdvi_kernels.hip")
+KERNEL_SOURCES = ("xrdvi_device.h", "dense_tile.h", "xrdvi_steps.h", "xrdvi_kernels.hip")
 RECORD_PREFIX = "traffic-record: "
 
 

@@ -46,11 +46,13 @@ constexpr int kTile = kWave * kPPL;       // points per tile (one block)
 constexpr int kWaves = 4;                 // waves per block, splitting phases
 constexpr int kBlock = kWave * kWaves;
 constexpr int kRefDense = 256;
-// The Gaussian term of a peak is evaluated for a tile only when the peak
-// lies within kGaussReach FWHM of one of the tile's points: beyond 4.47 w,
-// 2^(-q2^2) < 2^-80 of the peak height, far below the FP32 resolution of
-// any profile value f >= B > 0 (the extra 0.13 w absorbs rounding).
-constexpr double kGaussReach = 4.6;
+// The Gaussian term of a peak is evaluated only within kGaussReach FWHM of its
+// centre: beyond 3.5 w, 2^(-q2^2) < 2^-49 of the peak height, below half an
+// FP32 unit of the profile (f >= B > 0) for every peak up to 3e7 times the
+// background, where the diffractogram's largest are some 1e3 times.  Against
+// 4.6 w (2^-84): 200 x 60 peaks dense, N = 7001, S = 128 726 -> 687 us;
+// 2000 x 100, N = 14001, windows of 8 FWHM 1277 -> 1261 us.
+constexpr double kGaussReach = 3.5;
 
 constexpr double kCG = 0.93943727869965133377;   // 2 sqrt(ln 2 / pi)
 constexpr double kCL = 0.63661977236758134308;   // 2 / pi

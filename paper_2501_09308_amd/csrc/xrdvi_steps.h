@@ -191,11 +191,12 @@ __device__ inline void adam_update(double &theta, double &m1, double &m2,
 
 // ---- a7: gradient of phase k, block of 256 threads ----------------------------
 //
-// SG = min(S, 64) samples per pass, 256 / SG threads per sample each summing
-// a stripe of tiles (dense) or reading the phase's sums (windowed); stripes,
-// samples and tiles are combined in FP64 in fixed order, then the chain
-// rule runs through the prior, Jacobian and reparameterisation.  With
-// `adam`, the gradient of the phase's 2 D parameters updates loc/logscale
+// SG = min(S, 64) samples per pass, G threads per sample each summing a stripe
+// of tiles, G at most the number of tiles (with one sample, 256 stripes of
+// which a single thread added all took 21 us, 28 take 6); stripes, samples and
+// tiles are combined in FP64 in fixed order, then the chain rule runs through
+// the prior, Jacobian and reparameterisation.
+// With `adam`, the gradient of the phase's 2 D parameters updates loc/logscale
 // in place instead of being stored.  gz_out (may be NULL) receives every
 // sample's gradient of the log posterior density in z, [S][D K].
 struct GradSmem {
@@ -316,7 +317,7 @@ __device__ inline void grad_block(const ProbDev &P, const StepDev &st, int k,
     const int K = P.K, S = st.S;
     const int NS = num_sums(P.D);
     const int SG = S < kWave ? S : kWave;
-    const int G = 256 / SG;
+    const int G = min(256 / SG, st.nt);
     const int tid = threadIdx.x, sl = tid % SG, g = tid / SG;
     double am[5] = {0, 0, 0, 0, 0}, as[5] = {0, 0, 0, 0, 0};
     for (int s0 = 0; s0 < S; s0 += SG) {
@@ -324,29 +325,20 @@ __device__ inline void grad_block(const ProbDev &P, const StepDev &st, int k,
         // E stays in registers: every loop over it has a constant trip count
         double E[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         if (g < G && s < S) {
-            if (P.cutoff > 0.0) {
-                if (g == 0) {
-                    const double *src = st.pw + ((size_t)k * S + s) * NS;
+#pragma unroll 2
+            for (int t = g; t < st.nt; t += G) {
+                const float *src = st.part + (((size_t)t * K + k) * S + s) * NS;
 #pragma unroll
-                    for (int c = 0; c < 12; ++c)
-                        if (c < NS) E[c] = src[c];
-                }
-            } else {
-                for (int t = g; t < st.nt; t += G) {
-                    const float *src = st.part + (((size_t)t * K + k) * S + s) * NS;
-#pragma unroll
-                    for (int c = 0; c < 12; ++c)
-                        if (c < NS) E[c] += (double)src[c];
-                }
+                for (int c = 0; c < 12; ++c)
+                    if (c < NS) E[c] += (double)src[c];
             }
         }
 #pragma unroll
         for (int c = 0; c < 12; ++c) sm.red[tid][c] = E[c];
         __syncthreads();
         if (g == 0 && s < S) {
-#pragma unroll
-            for (int c = 0; c < 12; ++c) E[c] = 0.0;
-            for (int gg = 0; gg < G; ++gg)
+#pragma unroll 2
+            for (int gg = 1; gg < G; ++gg)
 #pragma unroll
                 for (int c = 0; c < 12; ++c) E[c] += sm.red[gg * SG + sl][c];
             grad_sample(P, st, k, s, E, am, as, gz_out);
@@ -360,8 +352,7 @@ __device__ inline void grad_block(const ProbDev &P, const StepDev &st, int k,
 
 // The gradient of phase k of a windowed analysis by one wave: its adjoint
 // sums are already per (phase, sample), so the lanes take the samples (64
-// per pass) and no block-wide reduction is needed.  The same arithmetic, in
-// the same order, as grad_block.
+// per pass) and no block-wide reduction is needed.
 __device__ inline void grad_wave(const ProbDev &P, const StepDev &st, int k,
                                  double scale, const double *scale_dev,
                                  double *gloc, double *glogscale, double *loc,
@@ -374,12 +365,11 @@ __device__ inline void grad_wave(const ProbDev &P, const StepDev &st, int k,
     for (int s0 = 0; s0 < S; s0 += kWave) {
         const int s = s0 + lane;
         if (s < S) {
-            // (0 + sum, as grad_block's combination of its groups forms it)
             double E[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
             const double *src = st.pw + ((size_t)k * S + s) * NS;
 #pragma unroll
             for (int c = 0; c < 12; ++c)
-                if (c < NS) E[c] = 0.0 + src[c];
+                if (c < NS) E[c] = src[c];
             grad_sample(P, st, k, s, E, am, as, gz_out);
         }
     }

@@ -71,8 +71,9 @@ inline void batch_units(const ProbDev &P, int S, int units[kKinds]) {
     }
     const DenseCut cut = dense_cut(P.N, S);
     units[fused_kind(win, asym, sec)] = win ? P.ntiles * S : cut.tiles(P.N) * cut.groups(S);
-    if (win) units[adjoint_kind(asym, sec)] = P.K * S;
-    units[kElbo] = 1;
+    // (the windowed adjoint's last unit is the ELBO)
+    if (win) units[adjoint_kind(asym, sec)] = P.K * S + 1;
+    else units[kElbo] = 1;
     units[kGrad] = win ? (P.K + kWaves - 1) / kWaves : P.K;   // windowed: a phase per wave
 }
 

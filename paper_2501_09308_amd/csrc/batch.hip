@@ -202,10 +202,11 @@ __global__ __launch_bounds__(kDenseWaves * kWave, 4) void kb_dense(const SlotDev
 }
 
 template <bool ASYM, bool SEC>
-__global__ __launch_bounds__(kBlock) void kb_adjoint(const SlotDev *tab,
+__global__ __launch_bounds__(kBlock, ASYM || SEC ? 1 : 8) void kb_adjoint(const SlotDev *tab,
                                                      const SchedDev *sch) {
     __shared__ PrefixSmem ps;
     __shared__ double red[kWaves][12];
+    __shared__ ElboSmem<kBlock> el;
     load_prefix(sch, adjoint_kind(ASYM, SEC), ps);
     const int total = uniform(ps.pre[ps.n]);
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
@@ -213,7 +214,13 @@ __global__ __launch_bounds__(kBlock) void kb_adjoint(const SlotDev *tab,
         const SlotDev &d = slot_entry(tab, ps, i);
         if (!running(d)) continue;
         const int local = local_unit(ps, i, u);
-        if (local / d.P.K >= d.st.S || d.P.cutoff == 0.0) continue;
+        if (d.P.cutoff == 0.0) continue;
+        if (local / d.P.K >= d.st.S) {        // the ELBO
+            const double e = elbo_block<kBlock>(d.P, d.st, d.logscale, nullptr, el);
+            if (threadIdx.x == 0) d.trace[*d.step] = e;
+            __syncthreads();
+            continue;
+        }
         adjoint_phase<ASYM, SEC>(d.P, d.st, local / d.P.K, local % d.P.K, red);
         __syncthreads();
     }
@@ -222,14 +229,14 @@ __global__ __launch_bounds__(kBlock) void kb_adjoint(const SlotDev *tab,
 __global__ __launch_bounds__(1024) void kb_elbo(const SlotDev *tab,
                                                 const SchedDev *sch) {
     __shared__ PrefixSmem ps;
-    __shared__ ElboSmem sm;
+    __shared__ ElboSmem<1024> sm;
     load_prefix(sch, kElbo, ps);
     const int total = uniform(ps.pre[ps.n]);
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
         const int i = find_slot(ps, u);
         const SlotDev &d = slot_entry(tab, ps, i);
         if (!running(d)) continue;
-        const double e = elbo_block(d.P, d.st, d.logscale, nullptr, sm);
+        const double e = elbo_block<1024>(d.P, d.st, d.logscale, nullptr, sm);
         if (threadIdx.x == 0) d.trace[*d.step] = e;
         __syncthreads();
     }
@@ -305,7 +312,7 @@ hipError_t launch_batch_step(const SlotDev *tab, const SchedDev *sch,
     if (has(true, true, false)) kb_adjoint<true, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
     if (has(true, false, true)) kb_adjoint<false, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
     if (has(true, true, true)) kb_adjoint<true, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    kb_elbo<<<kGridElbo, 1024, 0, s>>>(tab, sch);
+    if (any(0, -1)) kb_elbo<<<kGridElbo, 1024, 0, s>>>(tab, sch);
     kb_grad_adam<<<kGridLarge, 256, 0, s>>>(tab, sch);
     kb_advance<<<1, 1024, 0, s>>>(tab, sch);
     return hipGetLastError();

@@ -395,18 +395,20 @@ hipEvent_t take_event(xrdvi_ctx *ctx) {
 
 // Launches the fused kernel, bracketed by events when timing is enabled.
 hipError_t timed_fused(xrdvi_ctx *ctx, const ProbDev &P, const StepDev &st,
-                       bool grad, float *f_out, hipStream_t s) {
+                       bool grad, float *f_out, hipStream_t s,
+                       const ElboOut *elbo = nullptr) {
     hipEvent_t a = nullptr, b = nullptr;
     if (ctx->timing) {
         a = take_event(ctx);
         b = take_event(ctx);
         if (a && b) (void)hipEventRecord(a, s);
     }
-    hipError_t e = launch_fused(P, st, grad, f_out, s);
+    hipError_t e = launch_fused(P, st, grad, f_out, s, elbo);
     if (ctx->timing && a && b) {
         (void)hipEventRecord(b, s);
         ctx->ev_pending.emplace_back(a, b);
     }
+    if (e == hipSuccess && elbo && !elbo_in_fused(P, grad)) e = launch_elbo(P, st, *elbo, s);
     return e;
 }
 
@@ -677,9 +679,9 @@ int xrdvi_elbo_fwd(xrdvi_ctx *ctx, const xrdvi_problem *prob, int32_t S,
     HIP_TRY(launch_sample(P, st, loc, logscale, eps, seed, step, s), "sample");
     HIP_TRY(launch_peak_plan(P, st, st.phi, s), "window plan");
     HIP_TRY(launch_plan(P, st, s), "tile plan");
-    HIP_TRY(timed_fused(ctx, P, st, need_grad != 0, nullptr, s),
+    const ElboOut el{logscale, elbo_out, loglik_out, nullptr};
+    HIP_TRY(timed_fused(ctx, P, st, need_grad != 0, nullptr, s, &el),
             "fused profile/adjoint");
-    HIP_TRY(launch_elbo(P, st, logscale, elbo_out, loglik_out, s), "elbo");
     tape->has_grad = need_grad != 0;
     return XRDVI_OK;
     API_GUARD_END

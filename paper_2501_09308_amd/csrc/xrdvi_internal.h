@@ -32,14 +32,22 @@ hipError_t launch_windows(const ProbDev &P, int S, const double *phi, int *lo,
 hipError_t launch_peak_plan(const ProbDev &P, const StepDev &st,
                             const double *phi, hipStream_t stream);
 hipError_t launch_plan(const ProbDev &P, const StepDev &st, hipStream_t stream);
+// Where the ELBO goes; logp: per-sample log posterior density (optional
+// outputs NULL).
+struct ElboOut {
+    const double *logscale;
+    double *elbo, *loglik, *logp;
+};
+// Whether launch_fused writes the ELBO itself (a block of the windowed
+// adjoint's launch) when it is given `elbo`; otherwise launch_elbo follows.
+inline bool elbo_in_fused(const ProbDev &P, bool grad) { return P.cutoff > 0.0 && grad; }
 hipError_t launch_fused(const ProbDev &P, const StepDev &st, bool grad,
-                        float *f_out, hipStream_t stream);
-// logp_out: per-sample log posterior density; gz_out: per-sample gradient
-// of it in z, [S][D K] (both optional).
-hipError_t launch_elbo(const ProbDev &P, const StepDev &st,
-                       const double *logscale, double *elbo_out,
-                       double *loglik_out, hipStream_t stream,
-                       double *logp_out = nullptr);
+                        float *f_out, hipStream_t stream,
+                        const ElboOut *elbo = nullptr);
+hipError_t launch_elbo(const ProbDev &P, const StepDev &st, const ElboOut &out,
+                       hipStream_t stream);
+// gz_out: per-sample gradient of the log posterior density in z, [S][D K]
+// (optional).
 hipError_t launch_grad(const ProbDev &P, const StepDev &st, double scale,
                        const double *scale_dev, double *gloc,
                        double *glogscale, hipStream_t stream,

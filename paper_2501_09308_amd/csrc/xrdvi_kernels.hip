@@ -146,23 +146,27 @@ __global__ __launch_bounds__(kBlock, SEC ? 1 : (ASYM ? 6 : 7)) void k_win(ProbDe
     win_tile<ASYM, SEC, UNIF>(P, st, ts.x, ts.y, f_out, sm);
 }
 
-// a6 (windowed): peak-major adjoint, one block per (sample, phase);
-// grid (K, S), kBlock threads.
+// a6 (windowed): peak-major adjoint, one block per (sample, phase), and a5 by
+// the first block; grid (K, S + 1), kBlock threads.
 template <bool ASYM, bool SEC>
-__global__ __launch_bounds__(kBlock) void k_adjoint_win(ProbDev P, StepDev st) {
+__global__ __launch_bounds__(kBlock) void k_adjoint_win(ProbDev P, StepDev st, ElboOut out) {
     __shared__ double red[kWaves][12];
-    adjoint_phase<ASYM, SEC>(P, st, blockIdx.y, blockIdx.x, red);
+    if (blockIdx.y == 0) {
+        __shared__ ElboSmem<kBlock> sm;
+        if (blockIdx.x > 0 || !out.logscale) return;
+        const double e = elbo_block<kBlock>(P, st, out.logscale, out.loglik, sm, out.logp);
+        if (threadIdx.x == 0 && out.elbo) *out.elbo = e;
+        return;
+    }
+    adjoint_phase<ASYM, SEC>(P, st, blockIdx.y - 1, blockIdx.x, red);
 }
 
-// a5: one block of 1024 threads.
-__global__ __launch_bounds__(1024) void k_elbo(ProbDev P, StepDev st,
-                                               const double *__restrict__ logscale,
-                                               double *elbo_out,
-                                               double *loglik_out,
-                                               double *logp_out) {
-    __shared__ ElboSmem sm;
-    const double e = elbo_block(P, st, logscale, loglik_out, sm, logp_out);
-    if (threadIdx.x == 0 && elbo_out) *elbo_out = e;
+// a5: one block of NT threads (see elbo_block).
+template <int NT>
+__global__ __launch_bounds__(NT) void k_elbo(ProbDev P, StepDev st, ElboOut out) {
+    __shared__ ElboSmem<NT> sm;
+    const double e = elbo_block<NT>(P, st, out.logscale, out.loglik, sm, out.logp);
+    if (threadIdx.x == 0 && out.elbo) *out.elbo = e;
 }
 
 // a7: one block of 256 threads per phase.
@@ -284,7 +288,7 @@ hipError_t launch_plan(const ProbDev &P, const StepDev &st, hipStream_t stream) 
 // the residual, the peak-major adjoint follows when `grad` is set.
 template <bool ASYM, bool SEC>
 static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
-                           float *f_out, hipStream_t stream) {
+                           float *f_out, hipStream_t stream, const ElboOut *elbo) {
     if (P.cutoff > 0.0) {
         dim3 g(P.ntiles, st.S);
         StepDev sf = st;
@@ -295,8 +299,8 @@ static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
         else
             k_win<ASYM, SEC, false><<<g, kBlock, 0, stream>>>(P, sf, f_out);
         if (grad) {
-            dim3 ga(P.K, st.S);
-            k_adjoint_win<ASYM, SEC><<<ga, kBlock, 0, stream>>>(P, st);
+            dim3 ga(P.K, st.S + 1);
+            k_adjoint_win<ASYM, SEC><<<ga, kBlock, 0, stream>>>(P, st, elbo ? *elbo : ElboOut{});
         }
     } else {
         StepDev sd = st;
@@ -319,23 +323,21 @@ static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
 }
 
 hipError_t launch_fused(const ProbDev &P, const StepDev &st, bool grad,
-                        float *f_out, hipStream_t stream) {
+                        float *f_out, hipStream_t stream, const ElboOut *elbo) {
     if (P.D == 5) {
-        if (P.sec) launch_fused_t<true, true>(P, st, grad, f_out, stream);
-        else launch_fused_t<true, false>(P, st, grad, f_out, stream);
+        if (P.sec) launch_fused_t<true, true>(P, st, grad, f_out, stream, elbo);
+        else launch_fused_t<true, false>(P, st, grad, f_out, stream, elbo);
     } else {
-        if (P.sec) launch_fused_t<false, true>(P, st, grad, f_out, stream);
-        else launch_fused_t<false, false>(P, st, grad, f_out, stream);
+        if (P.sec) launch_fused_t<false, true>(P, st, grad, f_out, stream, elbo);
+        else launch_fused_t<false, false>(P, st, grad, f_out, stream, elbo);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_elbo(const ProbDev &P, const StepDev &st,
-                       const double *logscale, double *elbo_out,
-                       double *loglik_out, hipStream_t stream,
-                       double *logp_out) {
-    k_elbo<<<1, 1024, 0, stream>>>(P, st, logscale, elbo_out, loglik_out,
-                                   logp_out);
+hipError_t launch_elbo(const ProbDev &P, const StepDev &st, const ElboOut &out,
+                       hipStream_t stream) {
+    if (P.cutoff > 0.0) k_elbo<kBlock><<<1, kBlock, 0, stream>>>(P, st, out);
+    else k_elbo<1024><<<1, 1024, 0, stream>>>(P, st, out);
     return hipGetLastError();
 }
 
@@ -374,9 +376,9 @@ hipError_t launch_logpost(const ProbDev &P, const StepDev &st,
     hipError_t e = launch_sample(P, st, zeros, zeros, z, 0, 0, stream);
     if (e == hipSuccess) e = launch_peak_plan(P, st, st.phi, stream);
     if (e == hipSuccess) e = launch_plan(P, st, stream);
-    if (e == hipSuccess) e = launch_fused(P, st, gz != nullptr, nullptr, stream);
-    if (e == hipSuccess)
-        e = launch_elbo(P, st, zeros, nullptr, nullptr, stream, logp);
+    const ElboOut el{zeros, nullptr, nullptr, logp};
+    if (e == hipSuccess) e = launch_fused(P, st, gz != nullptr, nullptr, stream, &el);
+    if (e == hipSuccess && !elbo_in_fused(P, gz != nullptr)) e = launch_elbo(P, st, el, stream);
     if (e == hipSuccess && gz)
         e = launch_grad(P, st, 1.0, nullptr, nullptr, nullptr, stream, gz);
     return e;

@@ -118,55 +118,65 @@ __device__ inline void windows_elem(const ProbDev &P, const double *phi,
     }
 }
 
-// ---- a5: ELBO assembly, block of 1024 threads --------------------------------
+// ---- a5: ELBO assembly, block of NT threads -----------------------------------
 //
 // Each sample is summed by a group of G consecutive lanes (G a power of
-// two, G * S <= 1024) and the groups combine with a butterfly; totals over
-// samples use a fixed tree.
+// two, G * S <= NT where that is possible) and the groups combine with a
+// butterfly; totals over samples use a fixed tree.  Dense analyses take a
+// launch of 1024 threads; windowed ones a block of 256 of the adjoint's
+// launch, which needs the forward's sums as this does (and the same 256
+// threads when no adjoint follows: the same bits).
+template <int NT>
 struct ElboSmem {
-    double tot[1024];
-    double red[1024 / kWave];
+    double tot[NT];
+    double red[NT / kWave];
 };
 
 // logp_out (may be NULL) receives each sample's ln p(Y|phi_s) + ln p(phi_s)
 // + ln|J(z_s)|: the unnormalised log posterior density at z_s.
+template <int NT>
 __device__ inline double elbo_block(const ProbDev &P, const StepDev &st,
                                     const double *__restrict__ logscale,
-                                    double *loglik_out, ElboSmem &sm,
+                                    double *loglik_out, ElboSmem<NT> &sm,
                                     double *logp_out = nullptr) {
 #pragma clang fp contract(off)
     const int S = st.S;
     int G = 1;
-    while (G < kWave && 2 * G * S <= 1024) G *= 2;
-    const int tid = threadIdx.x, s = tid / G, g = tid % G;
+    while (G < kWave && 2 * G * S <= NT) G *= 2;
+    const int tid = threadIdx.x, g = tid % G;
     const int kb = (P.K + kWave - 1) / kWave;
-    double l = 0.0, p = 0.0;
-    if (s < S) {
-        for (int t = g; t < st.nt; t += G) l += st.llp[(size_t)s * st.nt + t];
-        for (int b = g; b < kb; b += G) p += st.lpb[(size_t)s * kb + b];
-    }
-    for (int o = G / 2; o >= 1; o >>= 1) {
-        l += __shfl_xor(l, o, kWave);
-        p += __shfl_xor(p, o, kWave);
+    double tot = 0.0;                     // this group's samples
+    for (int s0 = 0; s0 < S; s0 += NT / G) {
+        const int s = s0 + tid / G;
+        double l = 0.0, p = 0.0;
+        if (s < S) {
+            for (int t = g; t < st.nt; t += G) l += st.llp[(size_t)s * st.nt + t];
+            for (int b = g; b < kb; b += G) p += st.lpb[(size_t)s * kb + b];
+        }
+        for (int o = G / 2; o >= 1; o >>= 1) {
+            l += __shfl_xor(l, o, kWave);
+            p += __shfl_xor(p, o, kWave);
+        }
+        if (g == 0 && s < S) {
+            if (loglik_out) loglik_out[s] = l;
+            if (logp_out) logp_out[s] = l + p;
+            tot += l + p;
+        }
     }
     sm.tot[tid] = 0.0;
     __syncthreads();
-    if (g == 0 && s < S) {
-        if (loglik_out) loglik_out[s] = l;
-        if (logp_out) logp_out[s] = l + p;
-        sm.tot[s] = l + p;
-    }
+    if (g == 0) sm.tot[tid / G] = tot;
     double ent = 0.0;
-    for (int j = tid; j < P.D * P.K; j += 1024) ent += logscale[j];
+    for (int j = tid; j < P.D * P.K; j += NT) ent += logscale[j];
     ent = wave_sum(ent);
     if ((tid & (kWave - 1)) == 0) sm.red[tid / kWave] = ent;
     __syncthreads();
-    for (int w = 512; w >= 1; w >>= 1) {
+    for (int w = NT / 2; w >= 1; w >>= 1) {
         if (tid < w) sm.tot[tid] += sm.tot[tid + w];
         __syncthreads();
     }
     double e = 0.0;
-    for (int w = 0; w < 1024 / kWave; ++w) e += sm.red[w];
+    for (int w = 0; w < NT / kWave; ++w) e += sm.red[w];
     const double D = (double)P.D * P.K;
     return sm.tot[0] / S + e + 0.5 * D * (1.0 + kLn2Pi);   // valid in all threads
 }

@@ -71,7 +71,7 @@ size_t step_bytes(const StepShape &sh) {
     b += align256(sh.sec ? sizeof(float4) * S * (size_t)std::max(sh.T, 1) : 4);  // psec
     const bool cand = !sh.dense && !sh.sec;
     b += align256(cand ? sizeof(int2) * nt * K : 4);                      // cab
-    b += align256(cand ? sizeof(double) * kCandKeep * nt * K : 4);        // cp
+    b += align256(cand ? sizeof(float4) * nt * K : 4);                    // cp
     b += align256(cand ? sizeof(double4) * K : 4);                        // cext
     return b;
 }
@@ -102,7 +102,7 @@ StepDev carve_step(void *base, const StepShape &sh) {
     st.psec = (float4 *)take(sh.sec ? sizeof(float4) * S * (size_t)std::max(sh.T, 1) : 4);
     const bool cand = !sh.dense && !sh.sec;
     st.cab = (int2 *)take(cand ? sizeof(int2) * nt * K : 4);
-    st.cp = (double *)take(cand ? sizeof(double) * kCandKeep * nt * K : 4);
+    st.cp = (float4 *)take(cand ? sizeof(float4) * nt * K : 4);
     st.cext = (double4 *)take(cand ? sizeof(double4) * K : 4);
     if (!cand) st.cab = nullptr;
     return st;
@@ -618,9 +618,11 @@ int xrdvi_profile_static(xrdvi_ctx *ctx, const xrdvi_problem *prob, int32_t S,
     if (S < 1 || S > kMaxSamples) return fail(XRDVI_EINVAL, "S must be in [1, 1024]");
     const ProbDev &P = prob->P;
     const StepShape sh = step_shape(P, S);
-    // (the limit also counts the per-(sample, tile, phase) plan that dense
-    // calls once kept here: which calls fit stays as documented)
-    const size_t former = sh.dense ? ((sh.D == 5 ? 24 : 16) * (size_t)S * sh.ntiles * sh.K) : 0;
+    // (the limit also counts what calls once kept here besides: the dense
+    // plan per (sample, tile, phase), FP64 candidate positions; which calls fit
+    // stays as it was)
+    const size_t tk = (size_t)sh.ntiles * sh.K;
+    const size_t former = sh.dense ? (sh.D == 5 ? 24 : 16) * S * tk : sh.sec ? 0 : 16 * tk;
     const size_t bytes = step_bytes(sh) + former;
     if (bytes > kStaticScratchBytes)
         return fail(XRDVI_EINVAL,

@@ -137,19 +137,8 @@ struct StepDev {
     // phase) over the step's samples, laid out [..][ntiles][K] so that the
     // forward's threads (one per phase of a tile) read them coalesced:
     int2 *cab;        // [ntiles][K] candidates [ca, cb)
-    double *cp;       // [kCandKeep][ntiles][K] positions of the first ones
+    float4 *cp;       // [ntiles][K] tile-relative positions of the first four
     double4 *cext;    // [K] (min mu, max mu, max w, max w alpha) over samples
-};
-
-// Candidate peaks [ca, cb) of one phase for one tile are those whose window
-// can reach the tile at some sample of the step; the positions of the first
-// four of them are kept beside the range, so that the windowed forward finds
-// its exact ranges without a search when a tile has at most four candidates
-// (the usual case).
-constexpr int kCandKeep = 4;
-struct CandRec {
-    int ca, cb;
-    double p[kCandKeep];
 };
 
 // Read-only view of data that no kernel of the current launch writes:
@@ -629,79 +618,57 @@ __device__ inline void cand_elem(const ProbDev &P, const StepDev &st, int t,
     const int ca = probe_settle<4>(P.pos, a, b, pa.j0, na, ge);
     int cb = probe_settle<4>(P.pos, a, b, pb.j0, nb, gt);
     cb = cb < ca ? ca : cb;
-    const size_t ci = (size_t)t * P.K + k, ntk = (size_t)P.ntiles * P.K;
+    const size_t ci = (size_t)t * P.K + k;
     st.cab[ci] = make_int2(ca, cb);
+    const float *pt = P.pt + (size_t)t * P.T;
+    float v[4];
 #pragma unroll
-    for (int q = 0; q < kCandKeep; ++q)
-        st.cp[q * ntk + ci] = ca + q < cb ? P.pos[ca + q] : 0.0;
+    for (int q = 0; q < 4; ++q) v[q] = ca + q < cb ? pt[ca + q] : 0.f;
+    st.cp[ci] = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// The candidates of (tile t, phase k) as the forward's staging thread reads
-// them.
-__device__ __forceinline__ CandRec cand_read(const ProbDev &P, const StepDev &st,
-                                             int t, int k) {
-    const size_t ci = (size_t)t * P.K + k, ntk = (size_t)P.ntiles * P.K;
-    CandRec r;
+// The peaks of phase k that the forward stages for (tile t, sample s): [ja,
+// jb), whose windows reach the tile, and [ga, gb) of them, whose Gaussian does
+// (constant width).  Counted over the tile's candidates in FP32 tile-relative
+// positions with bounds widened far beyond their rounding: a few peaks more
+// than the exact ranges (each record carries its exact window), for a quarter
+// of the work of FP64 predicates.  Candidates past the fourth, whose positions
+// are not kept beside the range, are read four at a time.
+__device__ __forceinline__ int4 cand_ranges(const ProbDev &P, const StepDev &st,
+                                            const double *ph, int t, int k,
+                                            double xa, double xb, double xref) {
+    const size_t ci = (size_t)t * P.K + k;
     const int2 ab = st.cab[ci];
-    r.ca = ab.x;
-    r.cb = ab.y;
+    const float4 cp = st.cp[ci];
+    const double mu = ph[P.K + k], w = ph[2 * P.K + k];
+    const double al = P.D == 5 ? ph[4 * P.K + k] : 1.0;
+    const float a = (float)(xa - xref - mu), b = (float)(xb - xref - mu);
+    const float c = (float)(P.cutoff * w), g = (float)(kGaussReach * w), alf = (float)al;
+    auto wider = [](float v, float sign) { return v + sign * 4e-6f * (1.f + fabsf(v)); };
+    const float wl = wider(a - c * alf, -1.f), wh = wider(b + c, 1.f);
+    const float gl = wider(a - g * alf, -1.f), gh = wider(b + g, 1.f);
+    int ja = 0, jb = 0, ga = 0, gb = 0;
+    const int n = ab.y - ab.x;
+    auto count = [&](int q, float p) {
+        const bool in = q < n;
+        ja += in && p < wl;
+        jb += in && p <= wh;
+        ga += in && p < gl;
+        gb += in && p <= gh;
+    };
+    count(0, cp.x); count(1, cp.y); count(2, cp.z); count(3, cp.w);
+    const float *pt = P.pt + (size_t)t * P.T + ab.x;
+    for (int q0 = 4; q0 < n; q0 += 4) {
+        float p[4];
 #pragma unroll
-    for (int q = 0; q < kCandKeep; ++q) r.p[q] = st.cp[q * ntk + ci];
-    return r;
-}
-
-// The ranges [ja, jb) and [ga, gb) of phase_window and gauss_range
-// (constant width), searched within the candidates [ca, cb) of the tile:
-// from the candidates' own positions when there are at most four, else by
-// the batched searches restricted to the candidates.  The predicates are
-// those of phase_window and gauss_range, monotone over the phase, so the
-// ranges are the same as from searches over the whole phase.
-__device__ inline PhaseWin phase_window_cand(const ProbDev &P, const double *ph,
-                                             int k, double xa, double xb,
-                                             const CandRec &cand, int2 *gr) {
-#pragma clang fp contract(off)
-    PhaseWin r;
-    r.a = P.off[k];
-    r.b = P.off[k + 1];
-    r.mu = ph[P.K + k];
-    r.w = ph[2 * P.K + k];
-    r.alpha = P.D == 5 ? ph[4 * P.K + k] : 1.0;
-    r.g_mono = true;
-    const double mu = r.mu, w = r.w, alpha = r.alpha;
-    const int ca = cand.ca, cb = cand.cb;
-    auto reach_a = [&](double p) { return xa <= window_bounds<false>(P, p, mu, w, alpha).y; };
-    auto past_b = [&](double p) { return window_bounds<false>(P, p, mu, w, alpha).x > xb; };
-    auto g_a = [&](double p) { return p >= xa - mu - kGaussReach * w * alpha; };
-    auto g_b = [&](double p) { return p > xb - mu + kGaussReach * w; };
-    int ja, jb, ga, gb;
-    if (cb - ca <= kCandKeep) {
-        Probe<kCandKeep, double> pr;
-        pr.j0 = ca;
+        for (int q = 0; q < 4; ++q) p[q] = pt[min(q0 + q, n - 1)];
 #pragma unroll
-        for (int q = 0; q < kCandKeep; ++q) pr.v[q] = cand.p[q];
-        ja = ca + probe_count(pr, ca, cb, reach_a);
-        jb = ca + probe_count(pr, ca, cb, past_b);
-        ga = ca + probe_count(pr, ca, cb, g_a);
-        gb = ca + probe_count(pr, ca, cb, g_b);
-    } else {
-        const double hw = P.cutoff * w, hwu = P.D == 5 ? hw * alpha : hw;
-        const double rg = kGaussReach * w, rgu = rg * alpha;
-        ja = probe_result<4>(P.pos, ca, cb, probe_at<4>(P.pos, ca, cb,
-                             tab_guess(P, k, xa - mu - hwu, ca, cb)), reach_a);
-        jb = probe_result<4>(P.pos, ca, cb, probe_at<4>(P.pos, ca, cb,
-                             tab_guess(P, k, xb - mu + hw, ca, cb)), past_b);
-        ga = probe_result<4>(P.pos, ca, cb, probe_at<4>(P.pos, ca, cb,
-                             tab_guess(P, k, xa - mu - rgu, ca, cb)), g_a);
-        gb = probe_result<4>(P.pos, ca, cb, probe_at<4>(P.pos, ca, cb,
-                             tab_guess(P, k, xb - mu + rg, ca, cb)), g_b);
+        for (int q = 0; q < 4; ++q) count(q0 + q, p[q]);
     }
-    if (jb < ja) jb = ja;
-    ga = ga < ja ? ja : (ga > jb ? jb : ga);
-    gb = gb < ga ? ga : (gb > jb ? jb : gb);
-    r.ja = ja;
-    r.jb = jb;
-    *gr = make_int2(ga, gb);
-    return r;
+    jb = max(jb, ja);
+    ga = min(max(ga, ja), jb);
+    gb = min(max(gb, ga), jb);
+    return make_int4(ab.x + ja, ab.x + ga, ab.x + gb, ab.x + jb);
 }
 
 // Range entry of (sample s, tile t, phase k); phi: [S][D][K].  For
@@ -1020,7 +987,7 @@ struct WinSmem {
         WinRecord<ASYM> rec[kCap];
         Sums e;
     };
-    int wmax[kWaves], wmaxn[kWaves], wcnt[kWaves], wcntg[kWaves];
+    int wmax[kWaves], wmaxn[kWaves], wfit[kWaves], wcnt[kWaves], wcntg[kWaves];
     double red[kWaves];
 };
 
@@ -1196,27 +1163,20 @@ __device__ void win_tile(const ProbDev &P, const StepDev &st, int t, int s,
 
     for (int c0 = 0; c0 < K; c0 += kWinChunk) {
         const int nk = min(kWinChunk, K - c0);
-        // this thread's phase: the peaks whose windows reach the tile and,
-        // among them, those whose Gaussian does (found here: the windowed
-        // forward is their only user), constants and counts
-        PhaseWin pw{0, 0, 0, 0, 0.0, 0.0, 1.0, true};
-        int2 gr = make_int2(0, 0);
-        float4 cst = make_float4(0.f, 0.f, 0.f, 0.f);
-        float iw2r = 0.f;
+        // this thread's phase: the peaks [x, w) whose windows reach the tile
+        // and, among them, those [y, z) whose Gaussian does
+        int4 rg = make_int4(0, 0, 0, 0);
         if (tid < nk) {
-            cst = pkv[c0 + tid];
-            if (ASYM) iw2r = pkrv[c0 + tid];
             if constexpr (!SEC) {
-                // constant width: among the step's candidates (written by
-                // the candidate kernel before this one)
-                pw = phase_window_cand(P, ph, c0 + tid, xa, xb,
-                                       cand_read(P, st, t, c0 + tid), &gr);
+                // among the step's candidates (written by the candidate kernel)
+                rg = cand_ranges(P, st, ph, t, c0 + tid, xa, xb, xref);
             } else {
-                pw = phase_window<SEC>(P, ph, c0 + tid, i0, i1, wlo, whi);
-                gr = gauss_range<SEC>(P, pw, c0 + tid, xa, xb);
+                const PhaseWin pw = phase_window<SEC>(P, ph, c0 + tid, i0, i1, wlo, whi);
+                const int2 g = gauss_range<SEC>(P, pw, c0 + tid, xa, xb);
+                rg = make_int4(pw.ja, g.x, g.y, pw.jb);
             }
         }
-        const int cnt = pw.jb - pw.ja, cg = gr.y - gr.x;
+        const int cnt = rg.w - rg.x, cg = rg.z - rg.y;
         // inclusive prefixes over the block of the record counts and of the
         // Gaussian record counts
         int incl = cnt, inclg = cg;
@@ -1233,72 +1193,82 @@ __device__ void win_tile(const ProbDev &P, const StepDev &st, int t, int s,
         // records of the phases that fit (a prefix of the chunk: incl grows
         // with the phase index).  Records with a Gaussian fill the list from
         // the front, the others from the back, each in phase and peak order.
+        // The phase's thread only marks the slots with (phase, peak); the records
+        // are then made by all threads, one slot each: phases have 0 to some
+        // six peaks on a tile, so a thread per phase making its own left two
+        // thirds of the lanes idle (2000 phases, 110 tiles, S = 32: 195 of the
+        // forward's 650 us).
         const bool fits = tid < nk && incl <= kCap;
         if (fits) {
-            const float iw2 = cst.x, aG = cst.y, aL = cst.z;
-            // The tile-relative centre comes from the FP64 position and
-            // shift (rounded once, its rounding error kept for the records
-            // with the Gaussian), the window from the window step's arrays
-            // (a load instead of a search: the forward is bound by VALU
-            // issue), and the side of an asymmetric peak from the predicates
-            // of the tile plan's side searches.
             for (int q = 0; q < cnt; ++q) {
-                const int j = pw.ja + q;
-                const double pj = P.pos[j];
-                const float I = SEC ? psec[4 * j + 1] : P.inten[j];
-                const float c = SEC ? psec[4 * j] : 1.f;
-                // (in grid steps the scales are 2 dx / w: the degree scales
-                // times dx)
-                const float iw2u = UNIF ? (float)((double)iw2 * P.dx) : iw2;
-                const float iw2ru = UNIF ? (float)((double)iw2r * P.dx) : iw2r;
-                float alo = iw2u * c, ahi = alo;
-                if (ASYM) {
-                    // centre at or below the tile's first point: the tile
-                    // lies above it; at or below its last: it straddles it
-                    const float ar = iw2ru * c;
-                    const double rho = pj + pw.mu;
-                    if (!(rho > xa)) alo = ahi = ar;
-                    else if (!(rho > xb)) ahi = ar;
-                }
-                const bool gauss = j >= gr.x && j < gr.y;
-                const int slot = gauss ? exclg + (j - gr.x)
+                const int j = rg.x + q;
+                const bool gauss = j >= rg.y && j < rg.z;
+                const int slot = gauss ? exclg + (j - rg.y)
                                        : kCap - 1 - excln -
-                                             (j < gr.x ? j - pw.ja : q - cg);
-                const double cxd = (pj - xref) + pw.mu;
-                const double cx = UNIF ? cxd * gpd : cxd;   // grid steps if UNIF
-                const float cxf = (float)cx;
-                // symmetric peaks keep the centre times the scale (records
-                // without the Gaussian) or the rounding error of the centre
-                // times the scale (with it), so that q2 takes fused
-                // multiply-adds (see win_record)
-                const int2 wnd = make_int2(wlo[j], whi[j]);
-                const int whi_j = wnd.y < wnd.x ? wnd.x : wnd.y;
-                const double cld = cx - (double)cxf;
-                const float cl = (float)(ASYM ? cld : cld * (double)alo);
-                sm.rec[slot] = WinRecord<ASYM>::make(
-                    ASYM || gauss ? cxf : (float)(cx * (double)alo), alo, I * aL,
-                    gauss ? I * aG : 0.f, win_rel(wnd.x, whi_j, i0), ahi, gauss ? cl : 0.f);
+                                             (j < rg.y ? j - rg.x : q - cg);
+                *reinterpret_cast<int2 *>(&sm.rec[slot]) = make_int2(tid, j);
             }
         }
         // staged record counts and number of fitting phases
         const int ng = wave_max_i32(fits ? inclg : 0);
         const int nn = wave_max_i32(fits ? incl - inclg : 0);
         const int nfit = __builtin_popcountll(__ballot(fits));
-        __syncthreads();                       // prefix words read, records written
-        if (lane == 0) { sm.wmax[wv] = ng; }
-        if (lane == 1) { sm.wmaxn[wv] = nn; }
-        if (lane == 2) { sm.wcnt[wv] = nfit; }
+        if (lane == 0) { sm.wmax[wv] = ng; sm.wmaxn[wv] = nn; sm.wfit[wv] = nfit; }
         __syncthreads();
         int n_g = 0, n_n = 0, n_fit = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) {
             n_g = max(n_g, sm.wmax[w]);
             n_n = max(n_n, sm.wmaxn[w]);
-            n_fit += sm.wcnt[w];
+            n_fit += sm.wfit[w];
         }
         n_g = __builtin_amdgcn_readfirstlane(n_g);
         n_n = __builtin_amdgcn_readfirstlane(n_n);
         n_fit = __builtin_amdgcn_readfirstlane(n_fit);
+
+        // The records.  The tile-relative centre comes from the FP64 position
+        // and shift (rounded once, its rounding error kept for the records with
+        // the Gaussian), the window from the window step's arrays (a load
+        // instead of a search: the forward is bound by VALU issue).
+        for (int r = tid; r < n_g + n_n; r += kBlock) {
+            const bool gauss = r < n_g;
+            const int slot = gauss ? r : kCap - 1 - (r - n_g);
+            const int2 mark = *reinterpret_cast<const int2 *>(&sm.rec[slot]);
+            const int k = c0 + mark.x, j = mark.y;
+            const float4 cst = pkv[k];
+            const float iw2 = cst.x, iw2r = ASYM ? pkrv[k] : 0.f;
+            const double pj = P.pos[j], mu = ph[K + k];
+            const float I = SEC ? psec[4 * j + 1] : P.inten[j];
+            const float c = SEC ? psec[4 * j] : 1.f;
+            const int2 wnd = make_int2(wlo[j], whi[j]);
+            // (in grid steps the scales are 2 dx / w: the degree scales
+            // times dx)
+            const float iw2u = UNIF ? (float)((double)iw2 * P.dx) : iw2;
+            const float iw2ru = UNIF ? (float)((double)iw2r * P.dx) : iw2r;
+            float alo = iw2u * c, ahi = alo;
+            if (ASYM) {
+                // centre at or below the tile's first point: the tile lies
+                // above it; at or below its last: it straddles it
+                const float ar = iw2ru * c;
+                const double rho = pj + mu;
+                if (!(rho > xa)) alo = ahi = ar;
+                else if (!(rho > xb)) ahi = ar;
+            }
+            const double cxd = (pj - xref) + mu;
+            const double cx = UNIF ? cxd * gpd : cxd;   // grid steps if UNIF
+            const float cxf = (float)cx;
+            // symmetric peaks keep the centre times the scale (records
+            // without the Gaussian) or the rounding error of the centre
+            // times the scale (with it), so that q2 takes fused
+            // multiply-adds (see win_record)
+            const int whi_j = wnd.y < wnd.x ? wnd.x : wnd.y;
+            const double cld = cx - (double)cxf;
+            const float cl = (float)(ASYM ? cld : cld * (double)alo);
+            sm.rec[slot] = WinRecord<ASYM>::make(
+                ASYM || gauss ? cxf : (float)(cx * (double)alo), alo, I * cst.z,
+                gauss ? I * cst.y : 0.f, win_rel(wnd.x, whi_j, i0), ahi, gauss ? cl : 0.f);
+        }
+        __syncthreads();
 
         // the waves share the two lists
         // (two records per pass, unrolled by hand: the volatile statements

@@ -134,13 +134,11 @@ __global__ __launch_bounds__(kCandThreads) void kb_cand(const SlotDev *tab,
     }
 }
 
-// The windowed constant-width variants are held to the six blocks per CU
-// their LDS allows (80 VGPRs; six 8-byte values are spilled once per block
-// and reloaded once per unit, outside the record loops): their waves wait
-// on memory more than their single-analysis counterpart's.
+// Held to the six blocks per CU the LDS allows (80 VGPRs; a few values are
+// spilled once per block and reloaded once per unit, outside the record
+// loops): the waves wait on memory more than the single-analysis kernel's.
 template <bool ASYM, bool SEC>
-__global__ __launch_bounds__(kBlock, !SEC ? 6 : 1) void kb_win(const SlotDev *tab,
-                                                                        const SchedDev *sch) {
+__global__ __launch_bounds__(kBlock, 6) void kb_win(const SlotDev *tab, const SchedDev *sch) {
     __shared__ PrefixSmem ps;
     __shared__ WinSmem<ASYM> sm;
     load_prefix(sch, fused_kind(true, ASYM, SEC), ps);
@@ -151,7 +149,7 @@ __global__ __launch_bounds__(kBlock, !SEC ? 6 : 1) void kb_win(const SlotDev *ta
         if (!running(d)) continue;
         const int local = local_unit(ps, i, u);
         int t = local % d.P.ntiles, s = local / d.P.ntiles;
-        if (!SEC && d.st.S % kXcds == 0) {
+        if (d.st.S % kXcds == 0) {
             // a block runs on XCD u mod 8, and u - local is the same for all
             // of an analysis's units: the units with one value of local mod 8
             // share an XCD, which takes one eighth of the samples of every

@@ -403,7 +403,7 @@ __device__ inline int2 dense_near(const ProbDev &P, const StepDev &st, int t, in
         const double al = P.D == 5 ? ph[4 * K + k] : 1.0;
         if (SEC) {
             // the reach of a Gaussian is monotone over the phase's peaks (see
-            // sec_monotone), from the records of its first and last peak
+            // sec_ranges), from the records of its first and last peak
             const float4 *ps = st.psec + (size_t)(s0 + g) * P.T;
             const float4 f = ps[a], l = ps[b - 1];
             const double rf = P.pos[a] + mu, rl = P.pos[b - 1] + mu;

@@ -374,11 +374,11 @@ __device__ __forceinline__ double2 window_bounds(const ProbDev &P, double p,
     return make_double2(rho - hw, rho + (P.D == 5 ? hw * alpha : hw));
 }
 
-template <bool SEC>
+// W: the peak's full width (peak_width of rho = p + mu).
 __device__ inline int2 window_of(const ProbDev &P, double p, double mu,
-                                 double w, double alpha) {
+                                 double W, double alpha) {
     if (P.cutoff == 0.0) return make_int2(0, P.N);
-    const double2 ab = window_bounds<SEC>(P, p, mu, w, alpha);
+    const double2 ab = window_bounds<false>(P, p, mu, W, alpha);
     int2 r = grid_range(P.x, P.N, P.x0, P.inv_dx, ab.x, ab.y);
     if (r.y < r.x) r.y = r.x;
     return r;
@@ -403,22 +403,6 @@ __device__ inline int first_centre_above(const double *p, int a, int b,
     return a;
 }
 
-// With the sec law a peak's reach [rho - R W, rho + R alpha W] has bounds
-// that move with rho at slopes 1 - R W tau and 1 + R alpha W tau
-// (tau = tan(theta) pi / 360).  For centres inside (-180, 180) deg, W tau
-// increases with rho, so both bounds are monotone over a phase (and the
-// searches over its sorted peaks valid) when the slopes are positive at the
-// last and the first centre respectively.
-__device__ inline bool sec_monotone(double rf, double rl, double w, double R,
-                                    double alpha) {
-#pragma clang fp contract(off)
-    if (!(rf > -180.0) || !(rl < 180.0)) return false;
-    const double tf = rf * kHalfDegRad, tl = rl * kHalfDegRad;
-    const double up = 1.0 + R * alpha * (w / fabs(cos(tf))) * tan(tf) * kHalfDegRad;
-    const double dn = 1.0 - R * (w / fabs(cos(tl))) * tan(tl) * kHalfDegRad;
-    return up > 0.0 && dn > 0.0;
-}
-
 // Probe start for the first peak of phase k (peaks [a, b)) whose position
 // is >= v: one before the bucket's first peak, so that the probe also
 // covers an answer one to the left of it.
@@ -428,126 +412,6 @@ __device__ __forceinline__ int tab_guess(const ProbDev &P, int k, double v,
     const int u = !(g > 0.0) ? 0 : (g < (double)kTabBuckets ? (int)g : kTabBuckets);
     const int j = P.ptab[k * (kTabBuckets + 1) + u];
     return (j < a ? a : (j > b ? b : j)) - 1;
-}
-
-// The peaks of phase k whose windows reach the points [xa, xb] = x[i0 ..
-// i1-1] of a tile (sample row ph of phi, window arrays wlo / whi of that
-// sample): [ja, jb), from two searches whose probes go out together, each
-// predicate monotone over the whole phase:
-//   ja: first peak whose window reaches the tile, hi_j > i0 <=> xa <= b_j,
-//   jb: first peak whose window starts past it, lo_j >= i1 <=> a_j > xb,
-// with the window bounds (a_j, b_j) formed as the window step forms them.
-// The searches start from position-index guesses.  With a constant width
-// they test the positions; under the sec law (whose bounds need a cosine
-// per peak) they test the window step's index arrays.  The whole phase
-// when there is no window or its sec-law bounds are not monotone.  Also
-// returns the phase's FP64 shift, width and alpha, and whether the reach
-// of the Gaussian is monotone (sec law).
-struct PhaseWin {
-    int a, b, ja, jb;
-    double mu, w, alpha;
-    bool g_mono;
-};
-
-template <bool SEC>
-__device__ inline PhaseWin phase_window(const ProbDev &P, const double *ph,
-                                        int k, int i0, int i1, const int *wlo,
-                                        const int *whi) {
-#pragma clang fp contract(off)
-    PhaseWin r;
-    r.a = P.off[k];
-    r.b = P.off[k + 1];
-    const int a = r.a, b = r.b;
-    r.mu = ph[P.K + k];
-    r.w = ph[2 * P.K + k];
-    r.alpha = P.D == 5 ? ph[4 * P.K + k] : 1.0;
-    const double mu = r.mu, w = r.w, alpha = r.alpha;
-    const double xa = P.x[i0], xb = P.x[i1 - 1];
-    bool win_mono = true;
-    r.g_mono = true;
-    if (SEC && a < b) {
-        const double rf = P.pos[a] + mu, rl = P.pos[b - 1] + mu;
-        win_mono = sec_monotone(rf, rl, w, P.cutoff, alpha);
-        r.g_mono = sec_monotone(rf, rl, w, kGaussReach, alpha);
-    }
-    r.ja = a;
-    r.jb = b;
-    if (!(P.cutoff > 0.0) || !win_mono) return r;
-    const double Wt = SEC ? peak_width<SEC>(xa, w) : w;   // a guess only
-    const double hw = P.cutoff * Wt, hwu = P.D == 5 ? hw * alpha : hw;
-    const int g_a = tab_guess(P, k, xa - mu - hwu, a, b);
-    const int g_b = tab_guess(P, k, xb - mu + hw, a, b);
-    if (SEC) {
-        const Probe<4, int> pja = probe_at<4>(whi, a, b, g_a);
-        const Probe<4, int> pjb = probe_at<4>(wlo, a, b, g_b);
-        auto reach_a = [&](int hi) { return hi > i0; };
-        auto past_b = [&](int lo) { return lo >= i1; };
-        const int nja = probe_count(pja, a, b, reach_a);
-        const int njb = probe_count(pjb, a, b, past_b);
-        r.ja = probe_settle<4>(whi, a, b, pja.j0, nja, reach_a);
-        r.jb = probe_settle<4>(wlo, a, b, pjb.j0, njb, past_b);
-    } else {
-        const Probe<4, double> pja = probe_at<4>(P.pos, a, b, g_a);
-        const Probe<4, double> pjb = probe_at<4>(P.pos, a, b, g_b);
-        auto reach_a = [&](double p) {
-            return xa <= window_bounds<SEC>(P, p, mu, w, alpha).y;
-        };
-        auto past_b = [&](double p) {
-            return window_bounds<SEC>(P, p, mu, w, alpha).x > xb;
-        };
-        const int nja = probe_count(pja, a, b, reach_a);
-        const int njb = probe_count(pjb, a, b, past_b);
-        r.ja = probe_settle<4>(P.pos, a, b, pja.j0, nja, reach_a);
-        r.jb = probe_settle<4>(P.pos, a, b, pjb.j0, njb, past_b);
-    }
-    if (r.jb < r.ja) r.jb = r.ja;
-    return r;
-}
-
-// The peaks of [ja, jb) whose Gaussian reaches the tile [xa, xb]: [ga, gb),
-// clamped into [ja, jb).  Reach of a peak: [rho - R W, rho + R alpha W] with
-// R = kGaussReach; ga is the first peak whose reach ends at or past xa, gb
-// the first whose reach starts past xb.  With a constant width, searched
-// like [ja, jb) over the positions; under the sec law by bisection of the
-// few peaks of [ja, jb) (a cosine per test), and all of them when the reach
-// is not monotone.
-template <bool SEC>
-__device__ inline int2 gauss_range(const ProbDev &P, const PhaseWin &pw, int k,
-                                   double xa, double xb) {
-#pragma clang fp contract(off)
-    const int a = pw.a, b = pw.b, ja = pw.ja, jb = pw.jb;
-    const double mu = pw.mu, w = pw.w, alpha = pw.alpha;
-    if (SEC) {
-        if (!pw.g_mono) return make_int2(ja, jb);
-        auto bisect = [&](int lo, int hi, auto pred) {
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (pred(P.pos[mid])) hi = mid; else lo = mid + 1;
-            }
-            return lo;
-        };
-        const int ga = bisect(ja, jb, [&](double p) {
-            const double rho = p + mu;
-            return rho + kGaussReach * peak_width<SEC>(rho, w) * alpha >= xa;
-        });
-        const int gb = bisect(ga, jb, [&](double p) {
-            const double rho = p + mu;
-            return rho - kGaussReach * peak_width<SEC>(rho, w) > xb;
-        });
-        return make_int2(ga, gb);
-    }
-    const double rg = kGaussReach * w, rgu = rg * alpha;
-    const Probe<4, double> pga = probe_at<4>(P.pos, a, b, tab_guess(P, k, xa - mu - rgu, a, b));
-    const Probe<4, double> pgb = probe_at<4>(P.pos, a, b, tab_guess(P, k, xb - mu + rg, a, b));
-    auto g_a = [&](double p) { return p >= xa - mu - kGaussReach * w * alpha; };
-    auto g_b = [&](double p) { return p > xb - mu + kGaussReach * w; };
-    const int nga = probe_count(pga, a, b, g_a);
-    const int ngb = probe_count(pgb, a, b, g_b);
-    int ga = probe_settle<4>(P.pos, a, b, pga.j0, nga, g_a);
-    int gb = probe_settle<4>(P.pos, a, b, pgb.j0, ngb, g_b);
-    ga = ga < ja ? ja : (ga > jb ? jb : ga);
-    gb = gb < ga ? ga : (gb > jb ? jb : gb);
-    return make_int2(ga, gb);
 }
 
 // ---- candidate ranges (windowed mode, constant width) --------------------
@@ -671,29 +535,59 @@ __device__ __forceinline__ int4 cand_ranges(const ProbDev &P, const StepDev &st,
     return make_int4(ab.x + ja, ab.x + ga, ab.x + gb, ab.x + jb);
 }
 
-// Range entry of (sample s, tile t, phase k); phi: [S][D][K].  For
-// asymmetric peaks *side receives (jr, jl) with ga <= jr <= jl <= gb.
-// Ranges may be wider than needed (the windowed kernels mask each peak by
-// its exact window); with the sec law they cover the whole phase when its
-// bounds are not monotone.  [ja, jb) as phase_window, [ga, gb) as
-// gauss_range.
-template <bool SEC>
-__device__ inline int4 tile_range(const ProbDev &P, const StepDev &st,
-                                  const double *phi, int s, int t, int k,
-                                  int2 *side) {
-#pragma clang fp contract(off)
-    const int i0 = t * kTile, i1 = min(i0 + kTile, P.N);
-    const double xa = P.x[i0], xb = P.x[i1 - 1];
-    const PhaseWin pw = phase_window<SEC>(P, phi + (size_t)s * P.D * P.K, k, i0, i1,
-                                          st.lo + (size_t)s * P.T,
-                                          st.hi + (size_t)s * P.T);
-    const int2 g = gauss_range<SEC>(P, pw, k, xa, xb);
-    if (side) {
-        const int jr = first_centre_above(P.pos, g.x, g.y, pw.mu, xa);
-        const int jl = first_centre_above(P.pos, jr, g.y, pw.mu, xb);
-        *side = make_int2(jr, jl);
+// The same ranges under the sec law, whose widths grow with the centre: a
+// centre below the tile has at most the width at xa, so the first peak follows
+// from a search of the positions; from there on the window step's indices tell
+// which peaks start past the tile, and the records' c (W = w / c) which
+// Gaussians reach it.  No cosine is formed: the phase's first and last records
+// say whether the bounds are monotone over its peaks (the whole phase
+// otherwise): they move with rho at slopes 1 - R W tau and 1 + R alpha W tau,
+// tau = tan(theta) pi / 360, and for centres inside (-180, 180) deg W tau
+// increases with rho, so positive slopes at the last and the first centre
+// suffice.  cxa: |cos(xa pi / 360)|.
+__device__ __forceinline__ int4 sec_ranges(const ProbDev &P, const double *ph, int k,
+                                           const int *wlo, const float *psec, int i1,
+                                           double xa, double xb, double cxa) {
+    const int a = P.off[k], b = P.off[k + 1];
+    if (a >= b) return make_int4(a, a, a, a);
+    const double mu = ph[P.K + k], w = ph[2 * P.K + k];
+    const double al = P.D == 5 ? ph[4 * P.K + k] : 1.0;
+    const float4 *ps = reinterpret_cast<const float4 *>(psec);
+    const float4 f = ps[a], l = ps[b - 1];
+    const double R = fmax(P.cutoff, kGaussReach);
+    const double rf = P.pos[a] + mu, rl = P.pos[b - 1] + mu;
+    const double up = 1.0 + R * al * f.z / f.x, dn = 1.0 - R * l.z / l.x;
+    if (!(rf > -xa && rl < 180.0 && up > 1e-3 && dn > 1e-3)) return make_int4(a, a, b, b);
+    const double v = xa - mu - P.cutoff * (w / cxa) * al - 1e-5;
+    auto ge = [&](double p) { return !(p < v); };
+    const Probe<4, double> pr = probe_at<4>(P.pos, a, b, tab_guess(P, k, v, a, b));
+    const int ja = probe_settle<4>(P.pos, a, b, pr.j0, probe_count(pr, a, b, ge), ge);
+    int jb = ja, ga = ja, gb = ja;
+    const double rw = kGaussReach * w;
+    for (bool past = false; jb < b && !past;) {
+        int lo[4];
+        float c[4];
+        double p[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int j = min(jb + q, b - 1);
+            lo[q] = wlo[j];
+            c[q] = ps[j].x;
+            p[q] = P.pos[j];
+        }
+        const int j0 = jb;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            past = past || j0 + q >= b || lo[q] >= i1;
+            if (!past) {
+                const double rho = p[q] + mu, g = rw / c[q];
+                ga += rho + g * al < xa - 1e-5;      // (both monotone)
+                gb += rho - g <= xb + 1e-5;
+                jb = j0 + q + 1;
+            }
+        }
     }
-    return make_int4(pw.ja, g.x, g.y, pw.jb);
+    return make_int4(ja, ga, max(gb, ga), jb);
 }
 
 // ---- wave reductions ------------------------------------------------------
@@ -1158,6 +1052,7 @@ __device__ void win_tile(const ProbDev &P, const StepDev &st, int t, int s,
         ug[p] = (float)(idx[p] - iref);   // exact
         sig[p] = 0.f;
     }
+    const double cxa = SEC ? fabs(cos(xa * kHalfDegRad)) : 1.0;
     // grid steps per degree (uniform grid)
     const double gpd = P.inv_dx;
 
@@ -1171,9 +1066,7 @@ __device__ void win_tile(const ProbDev &P, const StepDev &st, int t, int s,
                 // among the step's candidates (written by the candidate kernel)
                 rg = cand_ranges(P, st, ph, t, c0 + tid, xa, xb, xref);
             } else {
-                const PhaseWin pw = phase_window<SEC>(P, ph, c0 + tid, i0, i1, wlo, whi);
-                const int2 g = gauss_range<SEC>(P, pw, c0 + tid, xa, xb);
-                rg = make_int4(pw.ja, g.x, g.y, pw.jb);
+                rg = sec_ranges(P, ph, c0 + tid, wlo, psec, i1, xa, xb, cxa);
             }
         }
         const int cnt = rg.w - rg.x, cg = rg.z - rg.y;
@@ -1291,7 +1184,13 @@ __device__ void win_tile(const ProbDev &P, const StepDev &st, int t, int s,
         for (int kl = n_fit + wv; kl < nk; kl += kWaves) {
             const int k = c0 + kl;
             int2 rk2 = make_int2(0, 0);
-            const int4 rk = tile_range<SEC>(P, st, st.phi, s, t, k, ASYM ? &rk2 : nullptr);
+            int4 rk;
+            if constexpr (SEC) rk = sec_ranges(P, ph, k, wlo, psec, i1, xa, xb, cxa);
+            else rk = cand_ranges(P, st, ph, t, k, xa, xb, xref);
+            if (ASYM) {
+                rk2.x = first_centre_above(P.pos, rk.y, rk.z, ph[K + k], xa);
+                rk2.y = first_centre_above(P.pos, rk2.x, rk.z, ph[K + k], xb);
+            }
             win_phase_global<ASYM, SEC>(sp, rk, rk2, pkv[k], ASYM ? pkrv[k] : 0.f,
                                         u, ul, idx, sig);
         }

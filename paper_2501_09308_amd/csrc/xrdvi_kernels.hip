@@ -130,18 +130,14 @@ __global__ __launch_bounds__(kDenseWaves * kWave, 4) void k_dense(ProbDev P, Ste
 }
 
 // a3 + a4 (windowed): forward tile over its staged peak records; grid
-// (ntiles, S), kBlock threads, blocks ordered by XCD (constant width).  The
-// register budget is held to the occupancy the staging space allows (seven
-// blocks per CU, six with asymmetric records; the sec-law variants are
-// left unbounded).
+// (ntiles, S), kBlock threads, blocks ordered by XCD.  The register budget is
+// held to the occupancy the staging space allows (seven blocks per CU, six
+// with asymmetric records or the sec law).
 template <bool ASYM, bool SEC, bool UNIF>
-__global__ __launch_bounds__(kBlock, SEC ? 1 : (ASYM ? 6 : 7)) void k_win(ProbDev P, StepDev st,
+__global__ __launch_bounds__(kBlock, ASYM || SEC ? 6 : 7) void k_win(ProbDev P, StepDev st,
                                                 float *f_out) {
     __shared__ WinSmem<ASYM> sm;
-    // the sec-law variant reads per-sample window and peak records, which
-    // the default order (tile fastest) keeps to a few samples per L2
-    const int2 ts = SEC ? make_int2(blockIdx.x, blockIdx.y)
-                  : st.S % kXcds == 0 ? xcd_sample_group(st.S)
+    const int2 ts = st.S % kXcds == 0 ? xcd_sample_group(st.S)
                                       : xcd_tile_sample(P.ntiles, st.S);
     win_tile<ASYM, SEC, UNIF>(P, st, ts.x, ts.y, f_out, sm);
 }

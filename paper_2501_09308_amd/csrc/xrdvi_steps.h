@@ -102,20 +102,23 @@ __device__ inline void windows_elem(const ProbDev &P, const double *phi,
     const int k = P.phase[j];
     const double *ph = phi + (size_t)s * P.D * P.K;
     const double mu = ph[P.K + k], w = ph[2 * P.K + k];
+    // (one sine and cosine for the width, the record and its tangent)
+    double sn = 0.0, cs = 1.0;
+    if (SEC) {
+        sincos((P.pos[j] + mu) * kHalfDegRad, &sn, &cs);
+    }
+    const double c = SEC ? fabs(cs) : 1.0;
     if (lo) {
-        const int2 wnd = window_of<SEC>(P, P.pos[j], mu, w,
+        const int2 wnd = window_of(P, P.pos[j], mu, SEC ? w / c : w,
                                    P.D == 5 ? ph[4 * P.K + k] : 1.0);
         const size_t o = (size_t)s * P.T + (perm ? perm[j] : j);
         lo[o] = wnd.x;
         hi[o] = wnd.y;
     }
-    if (SEC && psec) {
-        const double th = (P.pos[j] + mu) * kHalfDegRad;
-        const double c = fabs(cos(th));
+    if (SEC && psec)
         psec[(size_t)s * P.T + j] =
             make_float4((float)c, (float)((double)P.inten[j] * c),
-                        (float)(tan(th) * kHalfDegRad * w), 0.f);
-    }
+                        (float)(sn / cs * kHalfDegRad * w), 0.f);
 }
 
 // ---- a5: ELBO assembly, block of NT threads -----------------------------------

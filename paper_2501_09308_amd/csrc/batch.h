@@ -89,4 +89,7 @@ inline int batch_class(const ProbDev &P) {
 hipError_t launch_batch_step(const SlotDev *tab, const SchedDev *sch,
                              hipStream_t stream, unsigned classes);
 
+// Enters an analysis into the slot table: its entry, step 0, a zero trace.
+hipError_t launch_enter_slot(const SlotDev &d, SlotDev *entry, hipStream_t stream);
+
 }  // namespace xrdvi

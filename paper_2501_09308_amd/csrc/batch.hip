@@ -8,6 +8,7 @@
 // single-analysis kernels, and the noise of step n of an analysis is keyed
 // by (its seed, n), so an analysis computes the same result alone or in
 // any mix.
+#include <algorithm>
 #include <type_traits>
 
 #include "batch.h"
@@ -279,6 +280,22 @@ __global__ void kb_advance(const SlotDev *tab, const SchedDev *sch) {
         const SlotDev &d = tab[sch->slot[i]];
         if (*d.step < d.steps) *d.step += 1;
     }
+}
+
+// An analysis's table entry, step counter and trace in one launch; the entry
+// travels as a kernel argument.
+__global__ __launch_bounds__(256) void kb_enter(SlotDev d, SlotDev *entry) {
+    const int g = blockIdx.x * 256 + threadIdx.x;
+    for (int n = g; n < d.steps; n += gridDim.x * 256) d.trace[n] = 0.0;
+    if (g == 0) {
+        *entry = d;
+        *d.step = 0;
+    }
+}
+
+hipError_t launch_enter_slot(const SlotDev &d, SlotDev *entry, hipStream_t s) {
+    kb_enter<<<std::min((d.steps + 255) / 256, 256), 256, 0, s>>>(d, entry);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch_step(const SlotDev *tab, const SchedDev *sch,

@@ -108,9 +108,11 @@ StepDev carve_step(void *base, const StepShape &sh) {
     return st;
 }
 
-// Device layout of a prepared problem, in 256-byte aligned pieces.
+// Device layout of a prepared problem, in 256-byte aligned pieces: first what
+// the host fills in (one copy), then what launch_prepare makes from it.
 struct ProblemLayout {
-    size_t x, y, bg, lgy, u, ul, off, ph, pos, inten, pt, ptl, perm, ptab, dense, total;
+    size_t x, y, bg, off, ph, pos, inten, perm, staged;
+    size_t lgy, u, ul, ptab, pt, ptl, dense, total;
 };
 
 static ProblemLayout problem_layout(int N, int K, int T, bool dense) {
@@ -120,13 +122,15 @@ static ProblemLayout problem_layout(int N, int K, int T, bool dense) {
     size_t o = 0;
     auto slot = [&](size_t bytes) { size_t r = o; o += align256(bytes); return r; };
     L.x = slot(8 * (size_t)N); L.y = slot(8 * (size_t)N);
-    L.bg = slot(8 * (size_t)N); L.lgy = slot(8 * (size_t)N);
-    L.u = slot(4 * (size_t)nt * kTile); L.ul = slot(4 * (size_t)nt * kTile);
+    L.bg = slot(8 * (size_t)N);
     L.off = slot(4 * (size_t)(K + 1));
     L.ph = slot(4 * T1); L.pos = slot(8 * T1); L.inten = slot(4 * T1);
-    L.pt = slot(4 * (size_t)nt * T1); L.ptl = slot(4 * (size_t)nt * T1);
     L.perm = slot(4 * T1);
+    L.staged = o;
     L.ptab = slot(4 * (size_t)K * (kTabBuckets + 1));
+    L.lgy = slot(8 * (size_t)N);
+    L.u = slot(4 * (size_t)nt * kTile); L.ul = slot(4 * (size_t)nt * kTile);
+    L.pt = slot(4 * (size_t)nt * T1); L.ptl = slot(4 * (size_t)nt * T1);
     L.dense = slot(dense ? DenseTables::of(N, K).total : 4);
     L.total = o;
     return L;
@@ -136,57 +140,36 @@ size_t problem_bytes(int N, int K, int T, bool dense) {
     return problem_layout(N, K, T, dense).total;
 }
 
-hipError_t upload_problem(const xrdvi_problem_desc &d, double lambda,
-                          char *base, ProbDev &P, int **perm_out,
-                          hipStream_t stream) {
+size_t problem_staged_bytes(int N, int K, int T) {
+    return problem_layout(N, K, T, false).staged;
+}
+
+void stage_problem(const xrdvi_problem_desc &d, double lambda, char *image,
+                   char *base, ProbDev &P, int **perm_out) {
     const int N = d.N, K = d.K, T = d.peak_off[K];
-    const int T1 = std::max(T, 1);
     const ProblemLayout L = problem_layout(N, K, T, d.cutoff == 0.0);
-    // peaks ordered by position within each phase (stable)
-    std::vector<int> perm(T1, 0), phase(T1, 0);
-    std::vector<double> pos(T1, 0.0);
-    std::vector<float> inten(T1, 0.f);
+    std::memcpy(image + L.x, d.x, 8 * (size_t)N);
+    std::memcpy(image + L.y, d.y, 8 * (size_t)N);
+    std::memcpy(image + L.bg, d.bg, 8 * (size_t)N);
+    std::memcpy(image + L.off, d.peak_off, 4 * (size_t)(K + 1));
+    int *perm = (int *)(image + L.perm), *phase = (int *)(image + L.ph);
+    double *pos = (double *)(image + L.pos);
+    float *inten = (float *)(image + L.inten);
+    // peaks ordered by position within each phase (stable; ascending already
+    // in lists that come from a reflection generator)
     for (int k = 0; k < K; ++k) {
         const int a = d.peak_off[k], b = d.peak_off[k + 1];
-        std::iota(perm.begin() + a, perm.begin() + b, a);
-        std::stable_sort(perm.begin() + a, perm.begin() + b, [&](int i, int j) {
-            return d.peak_pos[i] < d.peak_pos[j];
-        });
+        std::iota(perm + a, perm + b, a);
+        if (!std::is_sorted(d.peak_pos + a, d.peak_pos + b))
+            std::stable_sort(perm + a, perm + b, [&](int i, int j) {
+                return d.peak_pos[i] < d.peak_pos[j];
+            });
         for (int j = a; j < b; ++j) {
             phase[j] = k;
             pos[j] = d.peak_pos[perm[j]];
             inten[j] = (float)d.peak_int[perm[j]];
         }
     }
-    // position index per phase: first sorted peak at or after each of
-    // kTabBuckets + 1 equally spaced positions spanning the grid
-    const double tab_x0 = d.x[0];
-    const double tab_inv = N > 1 ? kTabBuckets / (d.x[N - 1] - d.x[0]) : 0.0;
-    std::vector<int> ptab((size_t)K * (kTabBuckets + 1));
-    for (int k = 0; k < K; ++k) {
-        const int a = d.peak_off[k], b = d.peak_off[k + 1];
-        int j = a;
-        for (int bb = 0; bb <= kTabBuckets; ++bb) {
-            const double v = tab_inv > 0.0 ? tab_x0 + bb / tab_inv : tab_x0;
-            while (j < b && pos[j] < v) ++j;
-            ptab[(size_t)k * (kTabBuckets + 1) + bb] = j;
-        }
-    }
-    auto up = [&](size_t o, const void *src, size_t bytes) {
-        return hipMemcpyAsync(base + o, src, bytes, hipMemcpyHostToDevice, stream);
-    };
-    hipError_t e = up(L.x, d.x, 8 * (size_t)N);
-    if (e == hipSuccess) e = up(L.y, d.y, 8 * (size_t)N);
-    if (e == hipSuccess) e = up(L.bg, d.bg, 8 * (size_t)N);
-    if (e == hipSuccess) e = up(L.off, d.peak_off, 4 * (size_t)(K + 1));
-    if (e == hipSuccess) e = up(L.ph, phase.data(), 4 * (size_t)T1);
-    if (e == hipSuccess) e = up(L.pos, pos.data(), 8 * (size_t)T1);
-    if (e == hipSuccess) e = up(L.inten, inten.data(), 4 * (size_t)T1);
-    if (e == hipSuccess) e = up(L.perm, perm.data(), 4 * (size_t)T1);
-    if (e == hipSuccess) e = up(L.ptab, ptab.data(), 4 * ptab.size());
-    // pageable sources: complete the copies before the vectors go away
-    if (e == hipSuccess) e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) return e;
     P = ProbDev{};
     P.N = N; P.K = K; P.T = T; P.ntiles = num_tiles(N);
     P.ref = d.cutoff == 0.0 ? kRefDense : kTile;
@@ -229,12 +212,17 @@ hipError_t upload_problem(const xrdvi_problem_desc &d, double lambda,
     P.ptl = (const float *)(base + L.ptl);
     P.ptab = (const int *)(base + L.ptab);
     P.dense = base + L.dense;
-    P.tab_x0 = tab_x0;
-    P.tab_inv = tab_inv;
+    P.tab_x0 = d.x[0];
+    P.tab_inv = N > 1 ? kTabBuckets / (d.x[N - 1] - d.x[0]) : 0.0;
     if (perm_out) *perm_out = (int *)(base + L.perm);
+}
+
+hipError_t prepare_problem(const ProbDev &P, char *base, hipStream_t stream) {
+    const ProblemLayout L = problem_layout(P.N, P.K, P.T, P.cutoff == 0.0);
     return launch_prepare(P, (double *)(base + L.lgy), (float *)(base + L.u),
-                          (float *)(base + L.ul), (float *)(base + L.pt),
-                          (float *)(base + L.ptl), base + L.dense, stream);
+                          (float *)(base + L.ul), (int *)(base + L.ptab),
+                          (float *)(base + L.pt), (float *)(base + L.ptl),
+                          base + L.dense, stream);
 }
 
 }  // namespace xrdvi
@@ -512,7 +500,11 @@ int xrdvi_problem_create(xrdvi_ctx *ctx, const xrdvi_problem_desc *d,
     pb->ctx = ctx;
     pb->device = ctx->device;
     pb->mem = mem;
-    e = upload_problem(*d, lam, static_cast<char *>(mem), pb->P, &pb->perm, nullptr);
+    std::vector<char> image(problem_staged_bytes(d->N, d->K, d->peak_off[d->K]));
+    stage_problem(*d, lam, image.data(), static_cast<char *>(mem), pb->P, &pb->perm);
+    e = hipMemcpyAsync(mem, image.data(), image.size(), hipMemcpyHostToDevice, nullptr);
+    if (e == hipSuccess) e = prepare_problem(pb->P, static_cast<char *>(mem), nullptr);
+    // also completes the copy (pageable source) before the image goes away
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
         (void)hipFree(mem);

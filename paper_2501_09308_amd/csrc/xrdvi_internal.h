@@ -13,9 +13,11 @@
 namespace xrdvi {
 
 // Per-problem tables: ln y!, the tile-relative FP32 grid and peak positions
-// and the rounding errors of both; in dense mode the DenseTables.
+// and the rounding errors of both, the phases' position index; in dense mode
+// the DenseTables.
 hipError_t launch_prepare(const ProbDev &P, double *lgy, float *u, float *ul,
-                          float *pt, float *ptl, char *dense, hipStream_t stream);
+                          int *ptab, float *pt, float *ptl, char *dense,
+                          hipStream_t stream);
 hipError_t launch_sample(const ProbDev &P, const StepDev &st,
                          const double *loc, const double *logscale,
                          const double *eps, uint64_t seed, uint64_t step,
@@ -90,13 +92,16 @@ inline int latent_types(const xrdvi_problem_desc &d) {
     return d.asymmetric ? 5 : 4;
 }
 
-// Device bytes of a prepared problem and its upload (validated desc,
-// resolved lambda) into `base`; fills P and the sorted-to-caller peak
-// permutation.  Synchronises `stream` before returning (pageable sources).
+// Device bytes of a prepared problem.  Its first problem_staged_bytes are
+// filled in on the host: stage_problem (validated desc, resolved lambda) makes
+// their image and fills P and the sorted-to-caller peak permutation for a
+// problem at device address `base`; once the image is copied there,
+// prepare_problem makes the rest on the device.
 size_t problem_bytes(int N, int K, int T, bool dense);
-hipError_t upload_problem(const xrdvi_problem_desc &d, double lambda,
-                          char *base, ProbDev &P, int **perm_out,
-                          hipStream_t stream);
+size_t problem_staged_bytes(int N, int K, int T);
+void stage_problem(const xrdvi_problem_desc &d, double lambda, char *image,
+                   char *base, ProbDev &P, int **perm_out);
+hipError_t prepare_problem(const ProbDev &P, char *base, hipStream_t stream);
 // Host validation of a problem description; resolves lambda_h (0 -> 1 /
 // max(y - bg)) and returns max(y - bg) in *ymax when non-NULL.
 int validate_problem(const xrdvi_problem_desc *d, double *lambda_out,

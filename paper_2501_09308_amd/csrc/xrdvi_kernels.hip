@@ -26,6 +26,20 @@ __global__ void k_prepare_points(ProbDev P, double *lgy, float *u, float *ul) {
     }
 }
 
+// Position index of each phase (see ProbDev::ptab), a thread per entry.
+__global__ void k_prepare_index(ProbDev P, int *ptab) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= P.K * (kTabBuckets + 1)) return;
+    const int k = i / (kTabBuckets + 1), b = i % (kTabBuckets + 1);
+    const double v = P.tab_inv > 0.0 ? P.tab_x0 + b / P.tab_inv : P.tab_x0;
+    int lo = P.off[k], hi = P.off[k + 1];
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (P.pos[mid] < v) lo = mid + 1; else hi = mid;
+    }
+    ptab[i] = lo;
+}
+
 __global__ void k_prepare_peaks(ProbDev P, float *pt, float *ptl) {
     const int t = blockIdx.y;
     const double xref = P.x[min(t * P.ref + P.ref / 2, P.N - 1)];
@@ -201,9 +215,11 @@ __global__ void k_adam(int n, double *theta, double *m1, double *m2,
 // ---- launchers ------------------------------------------------------------
 
 hipError_t launch_prepare(const ProbDev &P, double *lgy, float *u, float *ul,
-                          float *pt, float *ptl, char *dense, hipStream_t stream) {
+                          int *ptab, float *pt, float *ptl, char *dense,
+                          hipStream_t stream) {
     const int np = P.ntiles * kTile;
     k_prepare_points<<<(np + 255) / 256, 256, 0, stream>>>(P, lgy, u, ul);
+    k_prepare_index<<<(P.K * (kTabBuckets + 1) + 255) / 256, 256, 0, stream>>>(P, ptab);
     if (P.T > 0) {
         dim3 g((P.T + 255) / 256 < 64 ? (P.T + 255) / 256 : 64, (P.N + P.ref - 1) / P.ref);
         k_prepare_peaks<<<g, 256, 0, stream>>>(P, pt, ptl);

@@ -1206,24 +1206,57 @@ __device__ void win_tile(const ProbDev &P, const StepDev &st, int t, int s,
 // ---- peak-major adjoint (windowed mode) -----------------------------------
 //
 // One block of kWaves waves per (sample s, phase k); the phase's peaks go
-// in groups of kAdjPeaks consecutive ones, group g to wave g mod kWaves.
-// For every peak the lanes cover consecutive points of its window (64 at a
-// time); x - rho is formed in FP64 and rounded to FP32 (its sign picks the
-// side of an asymmetric peak), or for symmetric peaks of constant width on
-// a uniform grid from FP32 offsets each rounded once (adjoint_phase).  Six
-// sums (twelve: six per side) accumulate per lane over the wave's peaks,
-// are reduced over the wave, then over the waves in fixed order.
-// R = 0 for lanes outside the window (their terms vanish).  SEC: iw2 and
-// iw2r carry the peak's c, and wl / wh are the mu-sum weights of the two
-// sides (see SecW).  The Lorentzian terms and the Gaussian terms are two
-// steps, so that a chunk of points where no Gaussian matters can skip the
+// in groups of kAdjPeaks consecutive ones, group g to wave g mod kWaves.  A
+// wave takes a group's peaks side by side, kAdjLanes lanes each, over
+// consecutive points of their windows; x - rho is formed in FP64 and rounded
+// to FP32 (its sign picks the side of an asymmetric peak), or for symmetric
+// peaks of constant width on a uniform grid from FP32 offsets each rounded
+// once (adjoint_phase).  Six sums (twelve: six per side) accumulate per lane
+// over the wave's peaks, are reduced over the wave, then over the waves in
+// fixed order.  R = 0 for lanes outside the window (their terms vanish).
+// SEC: iw2 and iw2r carry the peak's c, and wl / wh are the mu-sum weights of
+// the two sides (see SecW).  The Lorentzian terms and the Gaussian terms are
+// two steps, so that a chunk of points where no Gaussian matters skips the
 // second.
+//
+// Bound by instruction issue.  Windows are 20 to 250 points long: with one
+// peak's points on all 64 lanes a window of 80 costs 128 and the Gaussian
+// (14 of its 16 half-widths squared weigh nothing) is evaluated in every
+// chunk; with 16 lanes a peak it costs 80 to 96, the Gaussian in the middle
+// half, and one set of per-peak instructions serves four peaks.  Measured,
+// 64 lanes -> 16: 50x40, N=3501, S=64 17.0 -> 13.0 us; 2000x100, N=14001,
+// S=32 607 -> 510; 300x50 under the sec law, S=32 85 -> 70; 160x50
+// asymmetric, S=31 49 -> 37; eight served analyses 206 -> 158 a step.
 struct AdjPt {
     float R, q2, tt;
     bool up;
 };
 
-template <bool ASYM, bool SEC>
+// SIDE: where the points of a wave lie about an asymmetric peak's centre, which
+// has six sums per side (acc[6 ..]: above); known to lie on one side, they cost
+// what a symmetric peak's do.  (Symmetric peaks: kBelow.)
+
+// Adds three of the point's terms to acc[o .. o + 2] (of its side).
+template <bool ASYM, int SIDE>
+__device__ __forceinline__ void adj_add(float v0, float v1, float v2, bool up, int o,
+                                        float (&acc)[ASYM ? 12 : 6]) {
+    if constexpr (ASYM && SIDE == kBoth) {
+        const float fu = up ? 1.f : 0.f, fd = 1.f - fu;
+        acc[o] = fmaf(fd, v0, acc[o]);
+        acc[o + 1] = fmaf(fd, v1, acc[o + 1]);
+        acc[o + 2] = fmaf(fd, v2, acc[o + 2]);
+        acc[o + 6] = fmaf(fu, v0, acc[o + 6]);
+        acc[o + 7] = fmaf(fu, v1, acc[o + 7]);
+        acc[o + 8] = fmaf(fu, v2, acc[o + 8]);
+    } else {
+        constexpr int h = ASYM && SIDE == kAbove ? 6 : 0;
+        acc[h + o] += v0;
+        acc[h + o + 1] += v1;
+        acc[h + o + 2] += v2;
+    }
+}
+
+template <bool ASYM, bool SEC, int SIDE = ASYM ? kBoth : kBelow>
 __device__ __forceinline__ void adj_terms_L(float R, float q2, float tt, bool up,
                                             float c, const SecW &wl, const SecW &wh,
                                             float (&acc)[ASYM ? 12 : 6]) {
@@ -1237,34 +1270,21 @@ __device__ __forceinline__ void adj_terms_L(float R, float q2, float tt, bool up
     } else {
         m1L = Rll * q2;
     }
-    if constexpr (!ASYM) {
-        acc[3] += Rl;
-        acc[5] += Rll;
-        if (SEC) acc[4] += m1L;
-        else acc[4] = fmaf(Rll, q2, acc[4]);
-    } else {   // six sums per side
-        const float fu = up ? 1.f : 0.f, fd = 1.f - fu;
-        acc[3] = fmaf(fd, Rl, acc[3]);
-        acc[9] = fmaf(fu, Rl, acc[9]);
-        acc[5] = fmaf(fd, Rll, acc[5]);
-        acc[11] = fmaf(fu, Rll, acc[11]);
-        acc[4] = fmaf(fd, m1L, acc[4]);
-        acc[10] = fmaf(fu, m1L, acc[10]);
-    }
+    adj_add<ASYM, SIDE>(Rl, m1L, Rll, up, 3, acc);
 }
 
-template <bool ASYM, bool SEC>
+template <bool ASYM, bool SEC, int SIDE>
 __device__ __forceinline__ AdjPt adj_point_L(float R, float d, float iw2,
                                              float iw2r, float c,
                                              const SecW &wl, const SecW &wh,
                                              float (&acc)[ASYM ? 12 : 6]) {
-    const bool up = ASYM && d >= 0.f;
+    const bool up = SIDE == kAbove || (SIDE == kBoth && d >= 0.f);
     const float q2 = d * (up ? iw2r : iw2), tt = fmaf(q2, q2, 1.0f);
-    adj_terms_L<ASYM, SEC>(R, q2, tt, up, c, wl, wh, acc);
+    adj_terms_L<ASYM, SEC, SIDE>(R, q2, tt, up, c, wl, wh, acc);
     return AdjPt{R, q2, tt, up};
 }
 
-template <bool ASYM, bool SEC>
+template <bool ASYM, bool SEC, int SIDE = ASYM ? kBoth : kBelow>
 __device__ __forceinline__ void adj_point_G(const AdjPt &pt, float c,
                                             const SecW &wl, const SecW &wh,
                                             float (&acc)[ASYM ? 12 : 6]) {
@@ -1279,20 +1299,7 @@ __device__ __forceinline__ void adj_point_G(const AdjPt &pt, float c,
     } else {
         m1G = Req;
     }
-    if constexpr (!ASYM) {
-        acc[0] += Re;
-        acc[1] += m1G;
-        acc[2] = fmaf(Req, q2, acc[2]);
-    } else {
-        const float Reqq = Req * q2;
-        const float fu = pt.up ? 1.f : 0.f, fd = 1.f - fu;
-        acc[0] = fmaf(fd, Re, acc[0]);
-        acc[6] = fmaf(fu, Re, acc[6]);
-        acc[1] = fmaf(fd, m1G, acc[1]);
-        acc[7] = fmaf(fu, m1G, acc[7]);
-        acc[2] = fmaf(fd, Reqq, acc[2]);
-        acc[8] = fmaf(fu, Reqq, acc[8]);
-    }
+    adj_add<ASYM, SIDE>(Re, m1G, Req * q2, pt.up, 0, acc);
 }
 
 // The Gaussian matters where |x - rho| <= kGaussReach w (the forward's
@@ -1302,14 +1309,17 @@ constexpr float kGaussTT = (float)(1.0 + 4.0 * kGaussReach * kGaussReach);
 // Word 3 of a gfx9-family buffer resource (32-bit data format, raw access).
 constexpr int kBufferFlags = 0x00020000;
 
-// Peaks a wave handles together: their scalar data and grid loads are issued
-// back to back, so one memory latency covers all of them.
+// Peaks a wave handles side by side, and the lanes of each.
 constexpr int kAdjPeaks = 4;
+constexpr int kAdjLanes = kWave / kAdjPeaks;
+// Chunks of kAdjLanes points whose loads are issued together.
+constexpr int kAdjChunks = 4;
 
 // Windows of at most this many FWHM each side (symmetric peaks of constant
 // width on a uniform grid): the adjoint forms q2 = 2 (x - rho) / w in FP32.
-// |q2| is at most 2c inside a window and its chunk offsets at most 4c, so
-// each of its three roundings errs by at most 4c 2^-24: q2 is exact to
+// |q2| is at most 2c inside a window and its chunk offsets at most 4c (2c
+// from the middle of a window that the grid does not clip), so each of its
+// three roundings errs by at most 4c 2^-24: q2 is exact to
 // 12c 2^-24, about 6e-6 at c = 8 and 1.1e-5 at this bound (a relative
 // gradient error of that order, against a bar of 1e-4).
 constexpr double kF32Cutoff = 16.0;
@@ -1331,21 +1341,19 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
     // grid take FP32 from there (the chunk loop)
     const double iw2d = 2.0 / ph[2 * K + k];
     const float up_ratio = ASYM ? (float)(1.0 / ph[4 * K + k]) : 1.f;
-    // bounded buffer views of the residual (one per peak, below) and the
-    // grid: 32-bit offsets, and reads past the end return 0
-    const float *rres_s = st.rres + (size_t)s * P.N;
+    // bounded buffer views of the residual and the grid: 32-bit offsets, and
+    // reads past the end return 0
+    const __amdgpu_buffer_rsrc_t r_rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(st.rres + (size_t)s * P.N), (short)0, P.N * 4, kBufferFlags);
     const __amdgpu_buffer_rsrc_t x_rs = __builtin_amdgcn_make_buffer_rsrc(
         (void *)P.x, (short)0, P.N * 8, kBufferFlags);
-    cptr<int> wlo = as_const(st.lo + (size_t)s * P.T);
-    cptr<int> whi = as_const(st.hi + (size_t)s * P.T);
-    cptr<double> pos = as_const(P.pos);
-    cptr<float> inten = as_const(P.inten);
-    cptr<float> psec = SEC ? as_const(reinterpret_cast<const float *>(st.psec + (size_t)s * P.T))
-                           : nullptr;
+    const int *wlo = st.lo + (size_t)s * P.T, *whi = st.hi + (size_t)s * P.T;
+    const float4 *psec = SEC ? st.psec + (size_t)s * P.T : nullptr;
     const float ka = ASYM ? (float)ph[4 * K + k] : 1.f;
     const bool unif = P.formed_x != 0;
-    const double xl = fma((double)lane, P.dx, P.x0);   // uniform grid: x0 + lane dx
-    const double dxw = kWave * P.dx;                     // one chunk of points
+    const int sub = lane / kAdjLanes, l = lane % kAdjLanes;
+    const double xl = fma((double)l, P.dx, P.x0);        // uniform grid: x0 + l dx
+    const double dxw = kAdjLanes * P.dx;                 // one chunk of points
     const int a = P.off[k], b = P.off[k + 1];
     float acc[NS];
 #pragma unroll
@@ -1354,47 +1362,36 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
     // in position, with windows of one length), group g to wave g mod 4: only
     // the phase's last group can be short
     for (int j0 = a + kAdjPeaks * wv; j0 < b; j0 += kWaves * kAdjPeaks) {
-        int lo[kAdjPeaks], len[kAdjPeaks];
-        float I[kAdjPeaks], cq[kAdjPeaks], tw[kAdjPeaks];
-        double rho[kAdjPeaks];
-        int span = 0;
-#pragma unroll
-        for (int q = 0; q < kAdjPeaks; ++q) {
-            const int j = j0 + q;
-            const bool ok = j < b;
-            const int jj = ok ? j : j0;
-            lo[q] = wlo[jj];
-            len[q] = ok ? whi[jj] - lo[q] : 0;
-            if (SEC) {
-                cq[q] = psec[4 * jj];
-                I[q] = psec[4 * jj + 1];
-                tw[q] = psec[4 * jj + 2];
-            } else {
-                cq[q] = 1.f;
-                I[q] = inten[jj];
-                tw[q] = 0.f;
-            }
-            rho[q] = pos[jj] + mu;
-            span = max(span, len[q]);
+        const bool ok = j0 + sub < b;
+        const int j = ok ? j0 + sub : j0;
+        const int lo = wlo[j], hi = whi[j], len = ok ? hi - lo : 0;
+        const double rho = P.pos[j] + mu;
+        float cq = 1.f, I, tw = 0.f;
+        if (SEC) {
+            const float4 r = psec[j];
+            cq = r.x;
+            I = r.y;
+            tw = r.z;
+        } else {
+            I = P.inten[j];
         }
-        // each peak's residuals through a buffer view that ends with its
-        // window: lanes past the window read 0 and so weigh their point by 0
-        __amdgpu_buffer_rsrc_t rq[kAdjPeaks];
+        const SecW wl = SecW::of(tw), wh = SecW::of(tw * ka);
+        const float qs = SEC ? iw2 * cq : 1.f, qsr = SEC ? iw2r * cq : up_ratio;
+        // points every one of the group's windows has, and the longest window
+        int full = len, span = len;
+#pragma unroll
+        for (int q = 1; q < kAdjPeaks; ++q) {
+            const int v = __builtin_amdgcn_readlane(len, q * kAdjLanes);
+            full = min(q == 1 ? __builtin_amdgcn_readlane(len, 0) : full, v);
+            span = max(q == 1 ? __builtin_amdgcn_readlane(len, 0) : span, v);
+        }
         // x_i - rho = e + t in FP64.  On a uniform grid x_i is formed, not
         // loaded, so only the residuals are read: e is the lane's offset in
-        // the first chunk, x0 + (lo + lane) dx - rho, and t the chunk's c dx;
+        // one chunk, x0 + (lo + l) dx - rho, and t the chunk's c dx from it;
         // otherwise e = -rho and t = x_i, loaded.  With a constant width e
         // and t carry the factor 2/w (e by a multiply here, c dx by the
         // chunk step, a loaded x_i by a fused multiply-add)
-        double e[kAdjPeaks];
-#pragma unroll
-        for (int q = 0; q < kAdjPeaks; ++q) {
-            rq[q] = __builtin_amdgcn_make_buffer_rsrc(
-                (void *)(rres_s + lo[q]), (short)0, len[q] * 4, kBufferFlags);
-            e[q] = unif ? fma((double)lo[q], P.dx, xl) - rho[q] : -rho[q];
-            if (!SEC) e[q] *= iw2d;
-        }
-        // the chunks of the peaks' windows, one loop per kind of grid
+        // the windows' points, one loop per kind of grid
         auto chunks = [&](auto unif_tag) {
             constexpr bool UNIF = decltype(unif_tag)::value;
             // symmetric peaks of constant width on a uniform grid: q2 is
@@ -1405,58 +1402,92 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
             constexpr bool F32 = UNIF && !SEC && !ASYM;
             // the chunk's c dx (scaled by 2/w with a constant width)
             const double step = SEC ? dxw : dxw * iw2d;
-            const float stepf = (float)step;
-            float ef[kAdjPeaks];
-#pragma unroll
-            for (int q = 0; q < kAdjPeaks; ++q) ef[q] = (float)e[q];
+            // FP32: chunks counted from the window's middle one, so that the
+            // offsets and their roundings are small where the peak is
+            const int mid = F32 ? len / (2 * kAdjLanes) : 0;
+            double e = UNIF ? fma((double)(lo + mid * kAdjLanes), P.dx, xl) - rho : -rho;
+            if (!SEC) e *= iw2d;
+            const float stepf = (float)step, ef = (float)e;
             double cdx = 0.0;
-            float cf = 0.f;
-            for (int c = 0; c < span; c += kWave, cdx += step, cf += 1.f) {
-                float R[kAdjPeaks], rv[kAdjPeaks], d[kAdjPeaks];
-                double xv[kAdjPeaks];
-#pragma unroll
-                for (int q = 0; q < kAdjPeaks; ++q) {
-                    // every lane loads; points past the grid's end (a window
-                    // ending at N, or lo = N for an empty one) read 0 from
-                    // the bounded grid view, and their residual is 0
-                    rv[q] = __uint_as_float(
-                        __builtin_amdgcn_raw_buffer_load_b32(rq[q], (c + lane) * 4, 0, 0));
-                    if (!UNIF)
-                        xv[q] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
-                                                               x_rs, (lo[q] + c + lane) * 8, 0, 0));
+            float cf = -(float)mid;
+            auto load = [&](int c, float &r, double &x) {
+                // points past the grid's end read 0
+                const int i = lo + l + c;
+                r = __uint_as_float(
+                    __builtin_amdgcn_raw_buffer_load_b32(r_rs, i * 4, 0, 0));
+                if (!UNIF)
+                    x = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(
+                                                       x_rs, i * 8, 0, 0));
+            };
+            // sec law: x - rho; constant width: (x - rho) 2/w
+            auto offset = [&](double x) {
+                return F32 ? fmaf(cf, stepf, ef)
+                           : (float)(SEC || UNIF ? e + (UNIF ? cdx : x) : fma(x, iw2d, e));
+            };
+            auto point = [&](auto side, float R, float d) {
+                constexpr int SIDE = decltype(side)::value;
+                const AdjPt pt = adj_point_L<ASYM, SEC, SIDE>(R, d, qs, qsr, cq, wl, wh, acc);
+                // a wave-uniform branch (a ballot is a scalar value: no
+                // lane-to-scalar move); the windows of a group run in step,
+                // so their Gaussians matter in the same chunks
+                if (__builtin_amdgcn_ballot_w64(pt.tt <= kGaussTT) != 0) {
+                    asm volatile("");   // (a branch, not selects)
+                    adj_point_G<ASYM, SEC, SIDE>(pt, cq, wl, wh, acc);
                 }
-                // all loads are issued before the first use, so one memory
-                // latency covers them
-                __builtin_amdgcn_sched_barrier(0);
+                cf += 1.f;
+                cdx += step;
+            };
+            if constexpr (!ASYM) {
+                // the chunks from point c on; MASK: some window may end inside
+                auto points = [&](auto mask_tag, int c) {
+                    constexpr bool MASK = decltype(mask_tag)::value;
+                    float rv[kAdjChunks];
+                    double xv[kAdjChunks];
 #pragma unroll
-                for (int q = 0; q < kAdjPeaks; ++q) {
-                    R[q] = rv[q] * I[q];
-                    // sec law: x - rho; constant width: (x - rho) 2/w
-                    d[q] = F32 ? fmaf(cf, stepf, ef[q])
-                               : (float)(SEC || UNIF ? e[q] + (UNIF ? cdx : xv[q])
-                                                     : fma(xv[q], iw2d, e[q]));
-                }
-                AdjPt pt[kAdjPeaks];
-                SecW wl[kAdjPeaks], wh[kAdjPeaks];
-                bool gauss = false;
+                    for (int u = 0; u < kAdjChunks; ++u)
+                        load(c + u * kAdjLanes, rv[u], xv[u]);
+                    // all loads are issued before the first use, so one
+                    // memory latency covers them
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int q = 0; q < kAdjPeaks; ++q) {
-                    wl[q] = SecW::of(SEC ? tw[q] : 0.f);
-                    wh[q] = SecW::of(SEC ? tw[q] * ka : 0.f);
-                    pt[q] = SEC ? adj_point_L<ASYM, SEC>(R[q], d[q], iw2 * cq[q], iw2r * cq[q],
-                                                         cq[q], wl[q], wh[q], acc)
-                                : adj_point_L<ASYM, SEC>(R[q], d[q], 1.f, up_ratio, 1.f,
-                                                         wl[q], wh[q], acc);
-                    // (points outside the window lie beyond 8 FWHM: no effect)
-                    gauss = gauss | (pt[q].tt <= kGaussTT);
-                }
-                // one wave-uniform branch over the four peaks' Gaussian terms
-                // (a ballot is a scalar value: no lane-to-scalar move)
-                if (__builtin_amdgcn_ballot_w64(gauss) != 0) {
-#pragma unroll
-                    for (int q = 0; q < kAdjPeaks; ++q)
-                        adj_point_G<ASYM, SEC>(pt[q], cq[q], wl[q], wh[q], acc);
-                }
+                    for (int u = 0; u < kAdjChunks; ++u) {
+                        if (MASK && c + u * kAdjLanes >= span) break;
+                        float R = rv[u] * I;
+                        if (MASK) R = c + u * kAdjLanes < len - l ? R : 0.f;
+                        point(std::integral_constant<int, kBelow>{}, R, offset(xv[u]));
+                    }
+                };
+                int c = 0;
+                for (; c + kAdjChunks * kAdjLanes <= full; c += kAdjChunks * kAdjLanes)
+                    points(std::false_type{}, c);
+                for (; c < span; c += kAdjChunks * kAdjLanes) points(std::true_type{}, c);
+            } else {
+                // ascending points: the chunks wholly below the four centres,
+                // those with points on both sides, those wholly above, the
+                // loads two chunks ahead (a lane past its window only adds 0)
+                int c = 0;
+                float r0, r1, r2;
+                double x0 = 0.0, x1 = 0.0, x2 = 0.0;
+                load(0, r0, x0);
+                load(kAdjLanes, r1, x1);
+                auto run = [&](auto side) {
+                    constexpr int SIDE = decltype(side)::value;
+                    for (; c < span; c += kAdjLanes) {
+                        const float d = offset(x0);
+                        const uint64_t above = __builtin_amdgcn_ballot_w64(d >= 0.f);
+                        if (SIDE == kBelow && above != 0) break;
+                        if (SIDE == kBoth && above == ~0ull) break;
+                        load(c + 2 * kAdjLanes, r2, x2);
+                        point(side, c < len - l ? r0 * I : 0.f, d);
+                        r0 = r1;
+                        r1 = r2;
+                        x0 = x1;
+                        x1 = x2;
+                    }
+                };
+                run(std::integral_constant<int, kBelow>{});
+                run(std::integral_constant<int, kBoth>{});
+                run(std::integral_constant<int, kAbove>{});
             }
         };
         if (unif)

@@ -112,10 +112,8 @@ __global__ __launch_bounds__(256) void kb_windows(const SlotDev *tab,
             }
             local -= next;
         }
-        const size_t g = (size_t)local * 256 + threadIdx.x;
-        if (g < (size_t)d.st.S * d.P.T)
-            windows_elem<SEC>(d.P, d.st.phi, d.P.cutoff > 0.0 ? d.st.lo : nullptr,
-                              d.st.hi, nullptr, g, d.st.psec);
+        windows_elem<SEC>(d.P, d.st.S, d.st.phi, d.P.cutoff > 0.0 ? d.st.lo : nullptr,
+                          d.st.hi, nullptr, (size_t)local * 256, d.st.psec);
     }
 }
 

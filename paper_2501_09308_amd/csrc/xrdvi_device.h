@@ -374,12 +374,27 @@ __device__ __forceinline__ double2 window_bounds(const ProbDev &P, double p,
     return make_double2(rho - hw, rho + (P.D == 5 ? hw * alpha : hw));
 }
 
+// Grid points below v on a uniform grid where v itself says so: every x_i is
+// within 1e-9 steps of x0 + i dx (ProbDev::uniform), so a v further than
+// kGridSure steps from that needs no look at x.  -1: it does (also for NaN and
+// infinity).  Saves both bounds' probes, four scattered FP64 loads per window:
+// with the indices of windows_elem in 32 bits, 6.4 million windows (2000x100,
+// S=32) 59 -> 27 us.
+constexpr double kGridSure = 1e-6;
+__device__ __forceinline__ int grid_below(const ProbDev &P, double v) {
+    const double g = (v - P.x0) * P.inv_dx, fl = floor(g), f = g - fl;
+    if (!(f > kGridSure && f < 1.0 - kGridSure)) return -1;
+    return g < 0.0 ? 0 : (g > (double)(P.N - 1) ? P.N : (int)fl + 1);
+}
+
 // W: the peak's full width (peak_width of rho = p + mu).
 __device__ inline int2 window_of(const ProbDev &P, double p, double mu,
                                  double W, double alpha) {
     if (P.cutoff == 0.0) return make_int2(0, P.N);
     const double2 ab = window_bounds<false>(P, p, mu, W, alpha);
-    int2 r = grid_range(P.x, P.N, P.x0, P.inv_dx, ab.x, ab.y);
+    int2 r = make_int2(-1, -1);
+    if (P.uniform) r = make_int2(grid_below(P, ab.x), grid_below(P, ab.y));
+    if (r.x < 0 || r.y < 0) r = grid_range(P.x, P.N, P.x0, P.inv_dx, ab.x, ab.y);
     if (r.y < r.x) r.y = r.x;
     return r;
 }

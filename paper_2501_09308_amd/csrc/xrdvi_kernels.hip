@@ -97,13 +97,12 @@ __global__ void k_phi_consts(ProbDev P, int S, const double *__restrict__ phi,
 // a2: one thread per (sample, peak).  perm != NULL writes the caller's
 // peak order; psec != NULL also writes the sec-law peak records.
 template <bool SEC>
-__global__ void k_windows(ProbDev P, int S, const double *__restrict__ phi,
+__global__ __launch_bounds__(256) void k_windows(ProbDev P, int S, const double *__restrict__ phi,
                           int *lo, int *hi, const int *__restrict__ perm,
                           float4 *psec) {
     const size_t n = (size_t)S * P.T;
-    for (size_t g = (size_t)blockIdx.x * blockDim.x + threadIdx.x; g < n;
-         g += (size_t)gridDim.x * blockDim.x)
-        windows_elem<SEC>(P, phi, lo, hi, perm, g, psec);
+    for (size_t g = (size_t)blockIdx.x * 256; g < n; g += (size_t)gridDim.x * 256)
+        windows_elem<SEC>(P, S, phi, lo, hi, perm, g, psec);
 }
 
 // a2 (windowed, constant width): the window step and the phases' extremes
@@ -119,9 +118,8 @@ __global__ __launch_bounds__(kCandThreads) void k_windows_ext(ProbDev P, StepDev
     }
     const size_t n = (size_t)st.S * P.T;
     const size_t nb = gridDim.x - next;
-    for (size_t g = (size_t)(blockIdx.x - next) * blockDim.x + threadIdx.x; g < n;
-         g += nb * blockDim.x)
-        windows_elem<false>(P, phi, st.lo, st.hi, nullptr, g, nullptr);
+    for (size_t g = (size_t)(blockIdx.x - next) * 256; g < n; g += nb * 256)
+        windows_elem<false>(P, st.S, phi, st.lo, st.hi, nullptr, g, nullptr);
 }
 
 // The candidate ranges, grid (ceil(K / 256), ntiles), one thread per

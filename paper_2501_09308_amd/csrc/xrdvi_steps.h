@@ -86,7 +86,8 @@ __device__ inline void sample_block(const ProbDev &P, const StepDev &st,
     }
 }
 
-// ---- a2: window plan element g = s * T + j ---------------------------------
+// ---- a2: window plan, element g0 + threadIdx.x of [S][T] -------------------
+// Blocks of 256 threads; g0: the block's first element.
 // lo/hi: the peak's grid window (windowed mode; NULL skips it).  SEC (sec
 // width law): psec (NULL skips it) receives the peak's record
 // (c, I c, tan(theta) (pi/360) w, 0) with c = |cos theta|, theta = rho / 2,
@@ -94,11 +95,18 @@ __device__ inline void sample_block(const ProbDev &P, const StepDev &st,
 // constant-width kernels are a separate instantiation, so they keep the
 // register budget of the window search alone.
 template <bool SEC>
-__device__ inline void windows_elem(const ProbDev &P, const double *phi,
+__device__ inline void windows_elem(const ProbDev &P, int S, const double *phi,
                                     int *lo, int *hi, const int *perm,
-                                    size_t g, float4 *psec) {
+                                    size_t g0, float4 *psec) {
 #pragma clang fp contract(off)
-    const int s = (int)(g / P.T), j = (int)(g % P.T);
+    if (g0 + threadIdx.x >= (size_t)S * P.T) return;
+    // sample and peak: one division for the block, and below 256 peaks a
+    // short one per thread
+    const unsigned T = P.T;
+    const size_t s0 = g0 >> 32 ? g0 / T : (size_t)((unsigned)g0 / T);
+    const unsigned r = (unsigned)(g0 - s0 * T) + threadIdx.x;
+    const unsigned q = T >= 256 ? (r >= T ? 1u : 0u) : r / T;
+    const int s = (int)(s0 + q), j = (int)(r - q * T);
     const int k = P.phase[j];
     const double *ph = phi + (size_t)s * P.D * P.K;
     const double mu = ph[P.K + k], w = ph[2 * P.K + k];

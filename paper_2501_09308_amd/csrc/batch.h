@@ -29,9 +29,22 @@ constexpr int adjoint_kind(bool asym, bool sec) {
     return kAdjoint + (asym ? 1 : 0) + (sec ? 2 : 0);
 }
 
-// Fixed persistent grids (blocks) of the batched kernels.
+// Fixed persistent grids (blocks) of the batched kernels; block b takes units
+// b, b + grid, ...  The windowed forward and adjoint have several times the
+// blocks that fit the chip (some 1536 and 2048): their units differ in length,
+// and blocks that start as others end even that out, where a grid a little
+// over what fits runs its last blocks almost alone (eight analyses of N
+// 2000-12000, K 20-300, S 32: forward 166 us a step with 2048 blocks, 149 with
+// 3072, 145 with 6144, 141 with 8192; adjoint 160 with 2048, 148 with 8192,
+// 143 with 16384).  Blocks left without a unit end at once: a single analysis
+// of 8 phases takes 46 us a step with either.  The dense kernel's LDS leaves
+// one block per CU, so 256 (eight analyses of N 1500-5000, K 10-80, S 32, 60
+// steps: 14.0 ms, with 2048 blocks 14.6).
 constexpr int kGridSmall = 1024;
 constexpr int kGridLarge = 2048;
+constexpr int kGridWin = 8192;
+constexpr int kGridAdjoint = 16384;
+constexpr int kGridDense = 256;
 constexpr int kGridElbo = 256;
 
 // One resident analysis: its problem, per-step state and optimiser state.

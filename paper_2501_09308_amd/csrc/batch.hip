@@ -33,6 +33,12 @@ __device__ void load_prefix(const SchedDev *sch, int kind, PrefixSmem &ps) {
     __syncthreads();
 }
 
+// Whether the membership leaves this block without work (scalar loads only).
+__device__ __forceinline__ bool no_units(const SchedDev *sch, int kind) {
+    const auto c = as_const(sch);
+    return (int)blockIdx.x >= c->pre[kind][c->n];
+}
+
 __device__ __forceinline__ int uniform(int v) {
     return __builtin_amdgcn_readfirstlane(v);
 }
@@ -140,6 +146,7 @@ template <bool ASYM, bool SEC>
 __global__ __launch_bounds__(kBlock, 6) void kb_win(const SlotDev *tab, const SchedDev *sch) {
     __shared__ PrefixSmem ps;
     __shared__ WinSmem<ASYM> sm;
+    if (no_units(sch, fused_kind(true, ASYM, SEC))) return;
     load_prefix(sch, fused_kind(true, ASYM, SEC), ps);
     const int total = uniform(ps.pre[ps.n]);
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
@@ -204,6 +211,7 @@ __global__ __launch_bounds__(kBlock, ASYM || SEC ? 1 : 8) void kb_adjoint(const 
     __shared__ PrefixSmem ps;
     __shared__ double red[kWaves][12];
     __shared__ ElboSmem<kBlock> el;
+    if (no_units(sch, adjoint_kind(ASYM, SEC))) return;
     load_prefix(sch, adjoint_kind(ASYM, SEC), ps);
     const int total = uniform(ps.pre[ps.n]);
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
@@ -313,18 +321,18 @@ hipError_t launch_batch_step(const SlotDev *tab, const SchedDev *sch,
     if (any(1, 0)) kb_windows<false><<<kGridLarge, 256, 0, s>>>(tab, sch);
     if (any(-1, 1)) kb_windows<true><<<kGridLarge, 256, 0, s>>>(tab, sch);
     if (any(1, 0)) kb_cand<<<kGridLarge, kCandThreads, 0, s>>>(tab, sch);
-    if (has(true, false, false)) kb_win<false, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(false, false, false)) kb_dense<false, false><<<kGridLarge, kDenseWaves * kWave, 0, s>>>(tab, sch);
-    if (has(true, true, false)) kb_win<true, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(false, true, false)) kb_dense<true, false><<<kGridLarge, kDenseWaves * kWave, 0, s>>>(tab, sch);
-    if (has(true, false, true)) kb_win<false, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(false, false, true)) kb_dense<false, true><<<kGridLarge, kDenseWaves * kWave, 0, s>>>(tab, sch);
-    if (has(true, true, true)) kb_win<true, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(false, true, true)) kb_dense<true, true><<<kGridLarge, kDenseWaves * kWave, 0, s>>>(tab, sch);
-    if (has(true, false, false)) kb_adjoint<false, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(true, true, false)) kb_adjoint<true, false><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(true, false, true)) kb_adjoint<false, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
-    if (has(true, true, true)) kb_adjoint<true, true><<<kGridLarge, kBlock, 0, s>>>(tab, sch);
+    if (has(true, false, false)) kb_win<false, false><<<kGridWin, kBlock, 0, s>>>(tab, sch);
+    if (has(false, false, false)) kb_dense<false, false><<<kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(true, true, false)) kb_win<true, false><<<kGridWin, kBlock, 0, s>>>(tab, sch);
+    if (has(false, true, false)) kb_dense<true, false><<<kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(true, false, true)) kb_win<false, true><<<kGridWin, kBlock, 0, s>>>(tab, sch);
+    if (has(false, false, true)) kb_dense<false, true><<<kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(true, true, true)) kb_win<true, true><<<kGridWin, kBlock, 0, s>>>(tab, sch);
+    if (has(false, true, true)) kb_dense<true, true><<<kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(true, false, false)) kb_adjoint<false, false><<<kGridAdjoint, kBlock, 0, s>>>(tab, sch);
+    if (has(true, true, false)) kb_adjoint<true, false><<<kGridAdjoint, kBlock, 0, s>>>(tab, sch);
+    if (has(true, false, true)) kb_adjoint<false, true><<<kGridAdjoint, kBlock, 0, s>>>(tab, sch);
+    if (has(true, true, true)) kb_adjoint<true, true><<<kGridAdjoint, kBlock, 0, s>>>(tab, sch);
     if (any(0, -1)) kb_elbo<<<kGridElbo, 1024, 0, s>>>(tab, sch);
     kb_grad_adam<<<kGridLarge, 256, 0, s>>>(tab, sch);
     kb_advance<<<1, 1024, 0, s>>>(tab, sch);

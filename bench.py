@@ -28,8 +28,11 @@ METRIC = ("ELBO fwd+bwd peak-point evals/s; analyses/s + p99 latency vs "
           "plain, K=50")
 WORKLOAD = "paper50"
 SEED = 2000
-# Algorithmic FP32 work of one fused peak-point: forward 10 flops + adjoint
-# 26 flops (plus 4 transcendentals, not counted).
+# FP32 work of one peak-point where every peak is evaluated at every point:
+# forward 10 flops + adjoint 26 flops (plus 4 transcendentals, not counted).
+# The dense kernel evaluates most peaks at a few nodes of each tile instead, so
+# this model work over its time is no rate of the machine; the roofline takes
+# the flops it executes (profiles/).
 FLOPS_PER_PEAK_POINT = 36
 PEAK_FP32_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
@@ -477,7 +480,9 @@ def main(argv=None):
     ms_step = dense["wall_s"] / a.steps * 1e3
     value = sum(dense["points"]) / dense["wall_s"]
     pts_launch = dense["points"][0]
-    achieved = FLOPS_PER_PEAK_POINT * pts_launch / (dense["kernel_ms"] * 1e-3) / 1e12
+    model_tflops = FLOPS_PER_PEAK_POINT * pts_launch / (dense["kernel_ms"] * 1e-3) / 1e12
+    counters = counter_rates(profsummary.recorded(DENSE_KERNEL), dense["kernel_ms"])
+    achieved = counters["executed_tflops"] if counters else None
     out = {
         "metric": METRIC,
         "value": value,
@@ -503,14 +508,14 @@ def main(argv=None):
             "achieved": achieved,
             "peak": PEAK_FP32_TFLOPS,
             "unit": "TFLOP/s",
-            "frac": achieved / PEAK_FP32_TFLOPS,
+            "frac": achieved / PEAK_FP32_TFLOPS if counters else None,
             "traffic": profsummary.recorded_traffic(DENSE_KERNEL),
             "kernel": DENSE_KERNEL,
             "kernel_ms": dense["kernel_ms"],
-            "flops_per_peak_point": FLOPS_PER_PEAK_POINT,
+            "model_flops_per_peak_point": FLOPS_PER_PEAK_POINT,
+            "model_tflops": model_tflops,
             "peak_points_per_launch": pts_launch,
-            "counters": counter_rates(profsummary.recorded(DENSE_KERNEL),
-                                      dense["kernel_ms"]),
+            "counters": counters,
         },
         "windowed_c8": {
             "value": sum(win["points"]) / win["wall_s"],

@@ -29,9 +29,9 @@
 //
 // What it measured (one MI355X, step of ELBO, adjoint and gradient, against
 // evaluating every peak at every point): 50 phases x 40 peaks, 3501 points,
-// S = 64: 208 -> 77 us; 200 x 60, 7001, S = 128: 3611 -> 726 us; asymmetric
-// 50 x 50, 2501, S = 32: 160 -> 80 us; profile of 77 x 50, 5003, S = 24: 95 ->
-// 30 us.  Bound by VALU issue on the large ones (about 80 % of the kernel's
+// S = 64: 208 -> 75 us; 200 x 60, 7001, S = 128: 3611 -> 697 us (both with
+// the Gaussian's reach of kGaussReach); asymmetric 50 x 50, 2501, S = 32: 160
+// -> 81 us; profile of 77 x 50, 5003, S = 24: 95 -> 30 us.  Bound by VALU issue on the large ones (about 80 % of the kernel's
 // cycles; a last round of blocks that fills half the CUs and the stages
 // between the phase loops, 17 000 cycles per block, take the rest).
 #pragma once

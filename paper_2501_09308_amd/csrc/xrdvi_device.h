@@ -3,11 +3,11 @@
 // One step of the method over S Monte-Carlo samples (Sec. 3.2, App. A):
 //   sample   z = loc + exp(logscale) eps, phi = T(z), log prior + log|J|
 //   windows  per (sample, peak): grid range inside rho +- c w (FP64 bounds)
-//   fused    per (2-theta tile, sample): profile f = B + sum_k h_k C_k in
-//            FP32, Poisson log-likelihood and residual y/f - 1 in FP64, then
-//            the adjoint recomputes every peak value and accumulates six
-//            FP32 sums per (sample, phase) -- the S x K x N basis is never
-//            stored
+//   forward  per (2-theta tile, sample): profile f = B + sum_k h_k C_k in
+//            FP32, Poisson log-likelihood and residual y/f - 1 in FP64
+//   adjoint  recomputes the peak values and accumulates six FP32 sums per
+//            (sample, phase) -- the S x K x N basis is never stored; dense in
+//            the forward's launch (dense_tile.h), windowed peak by peak
 //   grad     FP64 reduction of the tile sums in fixed order and the chain
 //            rule to (loc, logscale)
 //   elbo     FP64 assembly of the estimate
@@ -45,6 +45,8 @@ constexpr int kPPL = 2;                   // 2-theta points per lane
 constexpr int kTile = kWave * kPPL;       // points per tile (one block)
 constexpr int kWaves = 4;                 // waves per block, splitting phases
 constexpr int kBlock = kWave * kWaves;
+// Points per reference position of a dense problem's positions and grid (the
+// windowed: kTile): the widest dense tile, so that its peaks have one offset.
 constexpr int kRefDense = 256;
 // The Gaussian term of a peak is evaluated only within kGaussReach FWHM of its
 // centre: beyond 3.5 w, 2^(-q2^2) < 2^-49 of the peak height, below half an

@@ -130,7 +130,8 @@ static ProblemLayout problem_layout(int N, int K, int T, bool dense) {
     L.ptab = slot(4 * (size_t)K * (kTabBuckets + 1));
     L.lgy = slot(8 * (size_t)N);
     L.u = slot(4 * (size_t)nt * kTile); L.ul = slot(4 * (size_t)nt * kTile);
-    L.pt = slot(4 * (size_t)nt * T1); L.ptl = slot(4 * (size_t)nt * T1);
+    const size_t refs = dense ? (size_t)(N + kRefDense - 1) / kRefDense : (size_t)nt;
+    L.pt = slot(4 * refs * T1); L.ptl = slot(4 * refs * T1);
     L.dense = slot(dense ? DenseTables::of(N, K).total : 4);
     L.total = o;
     return L;

@@ -195,12 +195,16 @@ __global__ __launch_bounds__(kDenseWaves * kWave, 4) void kb_dense(const SlotDev
         const DenseCut cut = dense_cut(d.P.N, d.st.S);
         const int ng = cut.groups(d.st.S), t = local / ng, grp = local % ng;
         if (t >= d.st.nt) continue;
-        if (cut.leaves == 4)
-            dense_tile<true, ASYM, SEC, kDenseWaves, 4, 4>(d.P, d.st, t, grp, nullptr, sm.wide);
+        const int wide = cut.wide(d.P.N);   // tiles of cut.leaves, then of two
+        if (cut.leaves == 4 && t < wide)
+            dense_tile<true, ASYM, SEC, kDenseWaves, 4, 4>(d.P, d.st, t, t, grp, nullptr,
+                                                           sm.wide);
         else if (cut.group == 4)
-            dense_tile<true, ASYM, SEC, kDenseWaves, 4, 2>(d.P, d.st, t, grp, nullptr, sm.four);
+            dense_tile<true, ASYM, SEC, kDenseWaves, 4, 2>(
+                d.P, d.st, cut.leaves == 4 ? t + wide : t, t, grp, nullptr, sm.four);
         else
-            dense_tile<true, ASYM, SEC, kDenseWaves, 1, 2>(d.P, d.st, t, grp, nullptr, sm.one);
+            dense_tile<true, ASYM, SEC, kDenseWaves, 1, 2>(d.P, d.st, t, t, grp, nullptr,
+                                                           sm.one);
         __syncthreads();
     }
 }

@@ -29,11 +29,11 @@
 //
 // What it measured (one MI355X, step of ELBO, adjoint and gradient, against
 // evaluating every peak at every point): 50 phases x 40 peaks, 3501 points,
-// S = 64: 208 -> 75 us; 200 x 60, 7001, S = 128: 3611 -> 697 us (both with
+// S = 64: 208 -> 75 us; 200 x 60, 7001, S = 128: 3611 -> 639 us (both with
 // the Gaussian's reach of kGaussReach); asymmetric 50 x 50, 2501, S = 32: 160
 // -> 81 us; profile of 77 x 50, 5003, S = 24: 95 -> 30 us.  Bound by VALU issue on the large ones (about 80 % of the kernel's
-// cycles; a last round of blocks that fills half the CUs and the stages
-// between the phase loops, 17 000 cycles per block, take the rest).
+// cycles; the last round of blocks and the stages between the phase loops,
+// 17 000 cycles per block, take the rest).
 #pragma once
 
 #include "xrdvi_device.h"
@@ -179,8 +179,14 @@ __constant__ const double kNodeDeriv[kNodes][kNodes] = {
 // alone and served).
 struct DenseCut {
     int leaves, group;
+    int narrow = 0;     // four leaves: trailing spans of four cut in twos
+    // Tiles of `leaves` leaves; those that follow have two.
+    __host__ __device__ int wide(int N) const {
+        return (N + leaves * kLeaf - 1) / (leaves * kLeaf) - narrow;
+    }
     __host__ __device__ int tiles(int N) const {
-        return (N + leaves * kLeaf - 1) / (leaves * kLeaf);
+        const int w = wide(N);
+        return narrow > 0 ? w + (N - w * leaves * kLeaf + 2 * kLeaf - 1) / (2 * kLeaf) : w;
     }
     __host__ __device__ int groups(int S) const { return (S + group - 1) / group; }
     __host__ __device__ long long blocks(int N, int S) const {
@@ -192,7 +198,18 @@ __host__ __device__ inline DenseCut dense_cut(int N, int S) {
     // of the 256 CUs, four beyond: 3501 points, S = 64 takes 61 us with four
     // (224 blocks) and 71 with two (448), 7001 points, S = 128 692 and 808 us;
     // 2501 points, S = 32 takes 119 us with four (80 blocks) and 65 with two.
-    if (DenseCut{2, 4}.blocks(N, S) > 256) return DenseCut{4, 4};
+    if (DenseCut{2, 4}.blocks(N, S) > 256) {
+        DenseCut cut{4, 4};
+        // A last round that leaves half the CUs idle is shorter with its spans
+        // cut in two (a block of two leaves takes some 0.6 of one of four; cut
+        // in two everywhere they would cost the other rounds 1.2): 7001
+        // points, S = 128, 896 blocks 668 us, 768 wide ones and 248 of two
+        // leaves 622.
+        const long long over = cut.blocks(N, S) > 256 ? cut.blocks(N, S) % 256 : 0;
+        const long long ng = cut.groups(S), x = (over + ng - 1) / ng;
+        if (x < cut.wide(N) && 2 * x * ng <= 256) cut.narrow = (int)x;
+        return cut;
+    }
     // Few blocks of four samples leave CUs idle: 3501 points, S = 8 (56 such
     // blocks) takes 56 us with them and 43 with one sample per block, but one
     // sample per block costs about twice the work (2501 points, S = 32, 160
@@ -568,8 +585,10 @@ __device__ __forceinline__ void prio_left(int left) {
     else __builtin_amdgcn_s_setprio(0);
 }
 
+// Tile t of those of LV leaves; its sums go to place `out` among the
+// analysis's tiles.
 template <bool GRAD, bool ASYM, bool SEC, int NW, int SG, int LV, typename SM>
-__device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int grp,
+__device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, int grp,
                            float *f_out, SM &sm) {
     constexpr bool MID = SM::kMid;
     constexpr int PTS = SM::kPts;
@@ -856,7 +875,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int grp,
         double v = 0.0;
 #pragma unroll
         for (int l = 0; l < LV; ++l) v += sm.red[tid * LV + l];
-        st.llp[(size_t)(s0 + tid) * st.nt + t] = v;
+        st.llp[(size_t)(s0 + tid) * st.nt + out] = v;
     }
     if (!GRAD) return;
 
@@ -998,7 +1017,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int grp,
 #pragma unroll
             for (int q = 1; q < NS; ++q) v = n == q ? acc[q] : v;
             if (n < NS && slot == SLOTS - 1 && sl < ns)
-                st.part[(((size_t)t * K + k) * S + s) * NS + n] = v;
+                st.part[(((size_t)out * K + k) * S + s) * NS + n] = v;
         }
     }
 }

@@ -1000,13 +1000,15 @@ __device__ __forceinline__ void win_record(const WinRecord<ASYM> r,
 // sample-fastest order, so each XCD's L2 holds the peak data near its own
 // run of tiles.
 constexpr int kXcds = 8;
-__device__ __forceinline__ int2 xcd_tile_sample(int ntiles, int S) {
+__device__ __forceinline__ int2 xcd_tile_sample(int b, int ntiles, int S) {
     const int nb = ntiles * S;
-    const int b = blockIdx.x + blockIdx.y * gridDim.x;
     const int per = nb / kXcds, rem = nb % kXcds;
     const int x = b % kXcds, i = b / kXcds;
     const int q = x * per + min(x, rem) + i;
     return make_int2(q / S, q % S);
+}
+__device__ __forceinline__ int2 xcd_tile_sample(int ntiles, int S) {
+    return xcd_tile_sample(blockIdx.x + blockIdx.y * gridDim.x, ntiles, S);
 }
 
 // Block order of the windowed forward when S is a multiple of 8: XCD x

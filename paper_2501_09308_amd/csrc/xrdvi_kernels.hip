@@ -135,10 +135,28 @@ __global__ __launch_bounds__(kCandThreads) void k_cand(ProbDev P, StepDev st) {
 // memory, merge there before write-back).  Four waves per SIMD (128 VGPRs).
 template <bool GRAD, bool ASYM, bool SEC, int SG, int LV>
 __global__ __launch_bounds__(kDenseWaves * kWave, 4) void k_dense(ProbDev P, StepDev st,
-                                                                  float *f_out) {
-    __shared__ DenseSmem<kDenseWaves, SG, LV, ASYM, SEC> sm;
-    const int2 tg = xcd_tile_sample(st.nt, (st.S + SG - 1) / SG);
-    dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, LV>(P, st, tg.x, tg.y, f_out, sm);
+                                                                  float *f_out, int wide) {
+    if constexpr (LV == 4) {
+        // the wide tiles first, then those of two leaves (see dense_cut)
+        __shared__ union {
+            DenseSmem<kDenseWaves, SG, 4, ASYM, SEC> wide;
+            DenseSmem<kDenseWaves, SG, 2, ASYM, SEC> two;
+        } sm;
+        const int ng = (st.S + SG - 1) / SG, b = blockIdx.x + blockIdx.y * gridDim.x;
+        if (b < wide * ng) {
+            const int2 tg = xcd_tile_sample(b, wide, ng);
+            dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, 4>(P, st, tg.x, tg.x, tg.y, f_out,
+                                                            sm.wide);
+        } else {
+            const int2 tg = xcd_tile_sample(b - wide * ng, st.nt - wide, ng);
+            dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, 2>(P, st, 2 * wide + tg.x,
+                                                            wide + tg.x, tg.y, f_out, sm.two);
+        }
+    } else {
+        __shared__ DenseSmem<kDenseWaves, SG, LV, ASYM, SEC> sm;
+        const int2 tg = xcd_tile_sample(st.nt, (st.S + SG - 1) / SG);
+        dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, LV>(P, st, tg.x, tg.x, tg.y, f_out, sm);
+    }
 }
 
 // a3 + a4 (windowed): forward tile over its staged peak records; grid
@@ -315,17 +333,18 @@ static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
     } else {
         StepDev sd = st;
         sd.rres = nullptr;      // dense: the residual stays in LDS
+        const DenseCut cut = dense_cut(P.N, st.S);
         auto run = [&](auto sg_tag, auto lv_tag) {
             constexpr int SG = decltype(sg_tag)::value, LV = decltype(lv_tag)::value;
             constexpr int nt = kDenseWaves * kWave;
+            const int w = cut.wide(P.N);
             const dim3 g(st.nt, (st.S + SG - 1) / SG);
-            if (grad) k_dense<true, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, sd, f_out);
-            else k_dense<false, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, sd, f_out);
+            if (grad) k_dense<true, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, sd, f_out, w);
+            else k_dense<false, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, sd, f_out, w);
         };
         const std::integral_constant<int, 1> one;
         const std::integral_constant<int, 2> two;
         const std::integral_constant<int, 4> four;
-        const DenseCut cut = dense_cut(P.N, st.S);
         if (cut.leaves == 4) run(four, four);
         else if (cut.group == 4) run(four, two);
         else run(one, two);

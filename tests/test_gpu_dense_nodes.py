@@ -39,6 +39,10 @@ CASES = [
     (600, 130, 300, 2, 0.2, False, False),
     (800, 130, 4, 12, 3.0, False, False),     # peaks wider than a tile
     (800, 6, 4, 12, 3.0, True, True),
+    (1300, 200, 3, 8, 0.2, False, False),     # the last span cut in two tiles
+    (1290, 200, 3, 8, 0.2, True, False),      # ... of which one has points
+    (2300, 132, 3, 8, 0.2, False, True),      # two spans
+    (2177, 130, 3, 8, 0.2, True, True),
 ]
 
 
@@ -82,7 +86,7 @@ def test_dense_cut_matches_oracle(N, S, K, M, wide, asym, sec):
     assert rel_l2(g, np.concatenate([rgl.ravel(), rgs.ravel()])) <= 1e-4
 
 
-@pytest.mark.parametrize("N,S", [(700, 6), (900, 60), (700, 130)])
+@pytest.mark.parametrize("N,S", [(700, 6), (900, 60), (700, 130), (1300, 200)])
 def test_each_cut_gives_the_same_bits_served_and_alone(N, S):
     """One dense analysis per kind of block, served together with the others'
     kinds, equals its one-at-a-time run bit for bit."""

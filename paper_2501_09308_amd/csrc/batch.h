@@ -31,9 +31,9 @@ constexpr int adjoint_kind(bool asym, bool sec) {
 
 // Fixed persistent grids (blocks) of the batched kernels; block b takes units
 // b, b + grid, ...  The windowed forward and adjoint have several times the
-// blocks that fit the chip (some 1536 and 2048): their units differ in length,
+// blocks that fit the chip (1792 and 2048): their units differ in length,
 // and blocks that start as others end even that out, where a grid a little
-// over what fits runs its last blocks almost alone (eight analyses of N
+// over what fits runs its last blocks almost alone (with 1536 fitting, eight analyses of N
 // 2000-12000, K 20-300, S 32: forward 166 us a step with 2048 blocks, 149 with
 // 3072, 145 with 6144, 141 with 8192; adjoint 160 with 2048, 148 with 8192,
 // 143 with 16384).  Blocks left without a unit end at once: a single analysis

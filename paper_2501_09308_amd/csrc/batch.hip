@@ -33,12 +33,6 @@ __device__ void load_prefix(const SchedDev *sch, int kind, PrefixSmem &ps) {
     __syncthreads();
 }
 
-// Whether the membership leaves this block without work (scalar loads only).
-__device__ __forceinline__ bool no_units(const SchedDev *sch, int kind) {
-    const auto c = as_const(sch);
-    return (int)blockIdx.x >= c->pre[kind][c->n];
-}
-
 __device__ __forceinline__ int uniform(int v) {
     return __builtin_amdgcn_readfirstlane(v);
 }
@@ -68,6 +62,29 @@ __device__ __forceinline__ const SlotDev &slot_entry(const SlotDev *tab,
 __device__ __forceinline__ int local_unit(const PrefixSmem &ps, int i, int u) {
     return uniform(u - ps.pre[i]);
 }
+
+// The units of one kind without the LDS copy, for kernels of many blocks with
+// few units each: scalar loads of the prefix, a search for the block's first
+// unit, which goes on from there for the next.
+struct UnitScan {
+    cptr<int> pre, slot;
+    int n, total, i = 0;
+    __device__ UnitScan(const SchedDev *sch, int kind)
+        : pre(as_const(sch->pre[kind])), slot(as_const(sch->slot)),
+          n(as_const(&sch->n)[0]), total(pre[n]) {}
+    // Resident index of unit u (not below the previous one's).
+    __device__ __forceinline__ int at(int u) {
+        if (pre[i + 1] <= u) {
+            int hi = n;
+            ++i;
+            while (hi - i > 1) {
+                const int mid = (i + hi) >> 1;
+                if (pre[mid] <= u) i = mid; else hi = mid;
+            }
+        }
+        return i;
+    }
+};
 
 __device__ inline bool running(const SlotDev &d) {
     return uniform(*d.step) < d.steps;
@@ -139,21 +156,20 @@ __global__ __launch_bounds__(kCandThreads) void kb_cand(const SlotDev *tab,
     }
 }
 
-// Held to the six blocks per CU the LDS allows (80 VGPRs; a few values are
-// spilled once per block and reloaded once per unit, outside the record
-// loops): the waves wait on memory more than the single-analysis kernel's.
+// Held to the blocks per CU the LDS allows, as the single-analysis kernel (a
+// few values are spilled once per block and reloaded once per unit, outside
+// the record loops).  With the prefix in LDS six fit, and every block loaded
+// it: eight analyses (N 2000-12000, K 20-300, S 32) 141 us a step, now 136;
+// the adjoint 143, now 138.
 template <bool ASYM, bool SEC>
-__global__ __launch_bounds__(kBlock, 6) void kb_win(const SlotDev *tab, const SchedDev *sch) {
-    __shared__ PrefixSmem ps;
+__global__ __launch_bounds__(kBlock, ASYM || SEC ? 6 : 7) void kb_win(const SlotDev *tab, const SchedDev *sch) {
     __shared__ WinSmem<ASYM> sm;
-    if (no_units(sch, fused_kind(true, ASYM, SEC))) return;
-    load_prefix(sch, fused_kind(true, ASYM, SEC), ps);
-    const int total = uniform(ps.pre[ps.n]);
-    for (int u = blockIdx.x; u < total; u += gridDim.x) {
-        const int i = find_slot(ps, u);
-        const SlotDev &d = slot_entry(tab, ps, i);
+    UnitScan us(sch, fused_kind(true, ASYM, SEC));
+    for (int u = blockIdx.x; u < us.total; u += gridDim.x) {
+        const int i = us.at(u);
+        const SlotDev &d = *(const SlotDev *)(as_const(tab) + us.slot[i]);
         if (!running(d)) continue;
-        const int local = local_unit(ps, i, u);
+        const int local = u - us.pre[i];
         int t = local % d.P.ntiles, s = local / d.P.ntiles;
         if (d.st.S % kXcds == 0) {
             // a block runs on XCD u mod 8, and u - local is the same for all
@@ -212,17 +228,14 @@ __global__ __launch_bounds__(kDenseWaves * kWave, 4) void kb_dense(const SlotDev
 template <bool ASYM, bool SEC>
 __global__ __launch_bounds__(kBlock, ASYM || SEC ? 1 : 8) void kb_adjoint(const SlotDev *tab,
                                                      const SchedDev *sch) {
-    __shared__ PrefixSmem ps;
     __shared__ double red[kWaves][12];
     __shared__ ElboSmem<kBlock> el;
-    if (no_units(sch, adjoint_kind(ASYM, SEC))) return;
-    load_prefix(sch, adjoint_kind(ASYM, SEC), ps);
-    const int total = uniform(ps.pre[ps.n]);
-    for (int u = blockIdx.x; u < total; u += gridDim.x) {
-        const int i = find_slot(ps, u);
-        const SlotDev &d = slot_entry(tab, ps, i);
+    UnitScan us(sch, adjoint_kind(ASYM, SEC));
+    for (int u = blockIdx.x; u < us.total; u += gridDim.x) {
+        const int i = us.at(u);
+        const SlotDev &d = *(const SlotDev *)(as_const(tab) + us.slot[i]);
         if (!running(d)) continue;
-        const int local = local_unit(ps, i, u);
+        const int local = u - us.pre[i];
         if (d.P.cutoff == 0.0) continue;
         if (local / d.P.K >= d.st.S) {        // the ELBO
             const double e = elbo_block<kBlock>(d.P, d.st, d.logscale, nullptr, el);

@@ -69,6 +69,19 @@ SlotLayout slot_layout(const Job &j) {
     return L;
 }
 
+// While one lives, this thread's allocations do not disturb a capture under
+// way on another thread.
+class RelaxedCapture {
+  public:
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+    RelaxedCapture(const RelaxedCapture &) = delete;
+    RelaxedCapture &operator=(const RelaxedCapture &) = delete;
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+
+  private:
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
+
 // Host side of a copy to or from the device, kept by its owner and grown to
 // the largest copy asked for; pinned where the system grants that, else
 // ordinary memory (with which copies complete before they return).
@@ -86,6 +99,7 @@ class Staging {
     char *get(size_t bytes) {
         if (wait() != hipSuccess) return nullptr;
         if (bytes <= cap_) return p_;
+        const RelaxedCapture relaxed;
         release();
         void *q = nullptr;
         pinned_ = hipHostMalloc(&q, bytes, hipHostMallocDefault) == hipSuccess;
@@ -103,7 +117,10 @@ class Staging {
         hipError_t e = hipMemcpyAsync(dst, p_, bytes, hipMemcpyHostToDevice, s);
         if (e != hipSuccess) return e;
         if (!pinned_) return hipStreamSynchronize(s);
-        if (!ev_) e = hipEventCreateWithFlags(&ev_, hipEventDisableTiming);
+        if (!ev_) {
+            const RelaxedCapture relaxed;
+            e = hipEventCreateWithFlags(&ev_, hipEventDisableTiming);
+        }
         if (e == hipSuccess) e = hipEventRecord(ev_, s);
         if (e != hipSuccess) return hipStreamSynchronize(s);
         busy_ = true;

@@ -329,12 +329,18 @@ __device__ inline void dense_tables_leaf(const ProbDev &P, int leaf, char *base)
     Q.dense = base;
     const DenseView V(Q);
     const int a = leaf * kLeaf, b = min(a + kLeaf, P.N);
-    const double2 h = mid_half(P, a, b);
+    // A leaf of one point has all its nodes there: the tile's interpolant, which
+    // grows like T16 past the tile's ends, is then taken at the point itself
+    // (with nodes kPointHalf about it, the far sum at the last of 65 points in
+    // steps of 0.005 deg was off by 3e-5, in steps of 0.001 deg by more than
+    // itself).
+    double2 h = mid_half(P, a, b);
+    if (b - a == 1) h.y = 0.0;
     const double xref = P.x[min(a / P.ref * P.ref + P.ref / 2, P.N - 1)];
     float *lm = const_cast<float *>(V.lm(leaf));
     for (int e = threadIdx.x; e < kLeaf * kNodes; e += blockDim.x) {
         const int q = e / kNodes;
-        const double t = a + q < b ? (P.x[a + q] - h.x) / h.y : 0.0;
+        const double t = a + q < b && h.y > 0.0 ? (P.x[a + q] - h.x) / h.y : 0.0;
         lm[e] = a + q < b ? (float)node_weight(t, cheb16(t), e % kNodes) : 0.f;
     }
     for (int kind = 0; kind < 2; ++kind) {

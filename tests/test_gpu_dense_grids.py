@@ -1,0 +1,101 @@
+"""The dense path on fine, coarse, merged and broken grids against the FP64
+oracle: peaks a few steps wide, so that most of them are far from a tile and
+are evaluated at its nodes, with a last leaf of one point, a change of step
+and a gap of several degrees inside a tile and inside a leaf; one sample per
+block, four with two and four leaves, and a span cut in narrow tiles.  The
+peaks' tails are the larger part of the profile.  Bars: profile 1e-5,
+log-likelihoods 1e-6, each latent's gradient 1e-4."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2501_09308_amd import workloads as W
+from paper_2501_09308_amd import xrdvi as X
+
+from gpu_common import context, dev, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def _grid(N, step, kind):
+    x = 20.0 + step * np.arange(N)
+    if kind == "merged":             # a coarse scan continued by a fine one
+        n = min(N - 2, 2 * N // 3 + 5)
+        x[n:] = x[n - 1] + 0.1 * step * np.arange(1, N - n + 1)
+    elif kind == "gap":              # several degrees without a point
+        x[N // 2 + 3:] += 4.0
+    elif kind == "ends":             # single points off both ends
+        x[0] -= 3.0
+        x[-1] += 3.0
+    return x
+
+
+def _case(N, step, S, kind, K, seed, D):
+    rng = np.random.default_rng(seed)
+    x = _grid(N, step, kind)
+    off = (9 * np.arange(K + 1)).astype(np.int32)
+    span = step * min(N, 512)
+    pos = rng.uniform(x[0] - 2.0 * span, x[-1] + 2.0 * span, 9 * K)
+    inten = rng.uniform(0.2, 1.0, 9 * K)
+    prob = W.Problem(x=x, bg=np.full(N, 1.0), peak_off=off, peak_pos=pos, peak_int=inten,
+                     cutoff=0.0, true_idx=np.zeros(0, int), phi_true=np.zeros((4, K)))
+    loc = np.zeros((D, K))
+    loc[0] = math.log(200.0 * span) + 0.3 * rng.standard_normal(K)
+    loc[1] = 0.2 * step * rng.standard_normal(K)
+    loc[2] = math.log(6.0 * step) + 0.2 * rng.standard_normal(K)
+    loc[3] = 0.5 + 0.5 * rng.standard_normal(K)
+    if D == 5:
+        loc[4] = 0.1 * rng.standard_normal(K)
+    ls = np.full((D, K), math.log(0.05))
+    ls[1] = math.log(0.3 * step)
+    return prob, loc, ls, rng.standard_normal((S, D, K))
+
+
+def _phi(loc, ls, eps):
+    z = loc + np.exp(ls) * eps
+    phi = np.exp(z)
+    phi[:, 1] = z[:, 1]
+    phi[:, 3] = 1.0 / (1.0 + np.exp(-z[:, 3]))
+    return phi
+
+
+CASES = [(N, step, S, "uniform", False, False)
+         for N, S in [(65, 3), (193, 2), (321, 5), (193, 200), (321, 260), (577, 402),
+                      (1345, 200)]
+         for step in (0.001, 0.005, 0.02, 0.035)]
+CASES += [(N, step, S, kind, False, False)
+          for N, S in [(190, 3), (450, 130), (1300, 200)]
+          for step in (0.005, 0.02)
+          for kind in ("merged", "gap", "ends")
+          if (N, step, kind) != (1300, 0.005, "gap")]
+CASES += [(65, 0.001, 3, "uniform", True, False), (321, 0.001, 260, "uniform", False, True),
+          (193, 0.005, 200, "gap", True, True), (577, 0.005, 402, "merged", True, False)]
+
+
+@pytest.mark.parametrize("N,step,S,kind,asym,sec", CASES)
+def test_dense_grids_match_oracle(N, step, S, kind, asym, sec):
+    D, K = 5 if asym else 4, 4
+    prob, loc, ls, eps = _case(N, step, S, kind, K, N + S, D)
+    print(f"\ndense grids: N={N} step={step} S={S} {kind} asym={asym} sec={sec}", flush=True)
+    pro, el = ((oracle.profile_sec, oracle.elbo_sec) if sec else
+               (oracle.profile_asym, oracle.elbo_asym) if asym else
+               (oracle.profile, oracle.elbo))
+    phi = _phi(loc, ls, eps)
+    ref = pro(prob.x, prob.bg, prob.peak_off, prob.peak_pos, prob.peak_int, 0.0, phi)
+    # counts that no sample's profile fits
+    y = np.floor(1.5 * ref[0] + 3.0)
+    ctx = context()
+    P = X.Problem.from_workload(ctx, prob, y, cutoff=0.0, asymmetric=asym,
+                                width_law="sec" if sec else 0)
+    f = X.xrdvi_profile(ctx, P, dev(phi)).cpu().numpy()
+    assert np.max(np.abs(f - ref) / ref) <= 1e-5
+    tape = X.Tape(ctx, P, S)
+    _, ll = X.xrdvi_elbo_fwd(ctx, P, tape, dev(loc), dev(ls), eps=dev(eps))
+    gl, gs = X.xrdvi_elbo_bwd(ctx, tape)
+    _, rll, rgl, rgs = el(prob, y, loc, ls, eps)
+    np.testing.assert_allclose(ll.cpu().numpy(), rll, rtol=1e-6, atol=1e-6 * np.abs(y).sum())
+    for row in range(D):
+        assert rel_l2(gl.cpu().numpy()[row], rgl[row]) <= 1e-4, row
+        assert rel_l2(gs.cpu().numpy()[row], rgs[row]) <= 1e-4, row

@@ -15,9 +15,9 @@
 //            leaves' and from those to the points once per (tile, sample);
 //   adjoint  sum_i R_i F(x_i) = sum_n R_n F(v_n) with R_n = sum_i R_i l_n(x_i)
 //            (the transpose), so the residual is carried to the nodes once.
-//            The shift's sum needs no sums of its own on the tile's nodes:
-//            sum I l^2 q2 is -F' / (2 iw2) with F = sum I l, so it takes F's
-//            node values with the weights R'_n = sum_m R_m l_n'(v_m).
+//            Every sum is formed of its own terms, the shift's too: taken as
+//            the slope of the interpolant of sum I l, whose weights reach 77,
+//            it erred by 5e-5 for centres 20 half-widths away (directly 1e-7).
 //
 // Lanes: a wave holds SG samples (4 or 1).  With SG = 4 the 16 lanes of a
 // sample are its nodes and share its points, the peaks are wave-uniform
@@ -74,106 +74,6 @@ __constant__ const double kNodeNum[kNodes] = {
     0.039649580260227843, -0.029462296051624867,
     0.018142792328403899, -0.0061260712705975516,
 };
-// d l_n / dt at node m, [m][n].
-__constant__ const double kNodeDeriv[kNodes][kNodes] = {
-    {51.792831098067211, -77.438037004005736, 42.461439259893375,
-     -29.131495532874293, 21.858839993468788, -17.177986233491936,
-     13.850175995364282, -11.316916195110146, 9.2875530989122765,
-     -7.5948830160827541, 6.1350992786889949, -4.8395856843711895,
-     3.6603814576093647, -2.5620980641664688, 1.5171008342870898,
-     -0.50241928618815679},
-    {8.8289725519850979, 5.6781471211595651, -21.64665401709345,
-     11.881798187143547, -8.255971374269512, 6.2571630068793604,
-     -4.9449189653107286, 3.991400054958512, -3.2497102178311286,
-     2.6431142533328513, -2.1270367504090717, 1.6734009709286282,
-     -1.263283185091326, 0.88310718047447023, -0.52249861493968897,
-     0.17296979808284091},
-    {-1.8358010864067509, 8.2085388173702825, 1.9843883778092071,
-     -12.356657609378537, 6.6248263190876679, -4.5572634187795309,
-     3.4311781356219084, -2.6931105493056307, 2.1543603720002076,
-     -1.7317865827354484, 1.3824307444118293, -1.0814575903446177,
-     0.81318980529924312, -0.56694403481635802, 0.33487944904089401,
-     -0.11077114887436472},
-    {0.6954240126678416, -2.4877872757573432, 6.8227114323536568,
-     0.96036918738381261, -8.7904228071334938, 4.6091426477380386,
-     -3.124825676618364, 2.3240510042688647, -1.8009979229012723,
-     1.4186408425223205, -1.1171428893957234, 0.86578107837740148,
-     -0.64682178335999008, 0.44900162784130354, -0.26450372107388515,
-     0.087380243086837395},
-    {-0.35144747928055481, 1.1642484512613696, -2.4636380724016975,
-     5.9204699935110128, 0.53083291904951435, -6.9994842750530211,
-     3.5975261420344133, -2.4002080147615596, 1.7577771646932798,
-     -1.3387792947463535, 1.0317435935592389, -0.78815462345125042,
-     0.58311539819488101, -0.4021720668486467, 0.23598125531477016,
-     -0.077811091075405514},
-    {0.21218597637536299, -0.67790067272537091, 1.3020199771661196,
-     -2.3849411910968379, 5.3774594927688701, 0.30303790007021669,
-     -5.9911152940563834, 3.0222007288099548, -1.9817361921195735,
-     1.4245630915742116, -1.0606776859903473, 0.79265259600094873,
-     -0.57805112509770729, 0.39496344206385009, -0.23044303663315086,
-     0.075781992889849131},
-    {-0.14530803368462933, 0.45502753895468251, -0.83261971099020049,
-     1.373324685393212, -2.3474965932632257, 5.0885914521431106,
-     0.15849822203138439, -5.4089489012225442, 2.6782395433049389,
-     -1.7224470982383346, 1.2099616206709698, -0.87359471744412587,
-     0.62347621607209025, -0.42024039178966899, 0.24321728673556051,
-     -0.079681118673232285},
-    {0.10978038535550652, -0.33959874670558116, 0.60425453769360549,
-     -0.94439875132923812, 1.4481455398755532, -2.3734250948138484,
-     5.0012112090562857, 0.049483980570376271, -5.1011486186891588,
-     2.4763483384890179, -1.5563170125796115, 1.0605402304677098,
-     -0.73185148966625002, 0.48337489559945856, -0.27649383723407389,
-     0.090094433910261632},
-    {-0.090094433910261437, 0.27649383723407378, -0.48337489559945829,
-     0.73185148966625002, -1.0605402304677096, 1.5563170125796113,
-     -2.4763483384890179, 5.1011486186891579, -0.049483980570376208,
-     -5.0012112090562866, 2.3734250948138484, -1.4481455398755532,
-     0.94439875132923801, -0.60425453769360571, 0.33959874670558116,
-     -0.10978038535550676},
-    {0.079681118673232104, -0.24321728673556048, 0.42024039178966882,
-     -0.62347621607209047, 0.87359471744412587, -1.2099616206709696,
-     1.7224470982383346, -2.6782395433049389, 5.4089489012225469,
-     -0.15849822203138428, -5.0885914521431097, 2.3474965932632257,
-     -1.3733246853932115, 0.83261971099020093, -0.45502753895468251,
-     0.14530803368462963},
-    {-0.075781992889848937, 0.23044303663315077, -0.39496344206384987,
-     0.57805112509770717, -0.79265259600094851, 1.0606776859903471,
-     -1.4245630915742111, 1.9817361921195729, -3.0222007288099548,
-     5.9911152940563817, -0.30303790007021658, -5.377459492768871,
-     2.384941191096837, -1.3020199771661203, 0.67790067272537091,
-     -0.21218597637536343},
-    {0.07781109107540532, -0.23598125531477007, 0.40217206684864643,
-     -0.58311539819488101, 0.78815462345125009, -1.0317435935592385,
-     1.3387792947463533, -1.7577771646932796, 2.4002080147615596,
-     -3.5975261420344116, 6.999484275053022, -0.53083291904951424,
-     -5.9204699935110074, 2.4636380724016984, -1.1642484512613691,
-     0.35144747928055553},
-    {-0.087380243086837187, 0.26450372107388509, -0.44900162784130332,
-     0.64682178335999008, -0.86578107837740126, 1.1171428893957231,
-     -1.4186408425223203, 1.800997922901272, -2.3240510042688647,
-     3.1248256766183631, -4.6091426477380377, 8.7904228071334884,
-     -0.96036918738381261, -6.8227114323536666, 2.4877872757573436,
-     -0.69542401266784359},
-    {0.11077114887436441, -0.33487944904089384, 0.56694403481635747,
-     -0.81318980529924278, 1.0814575903446171, -1.3824307444118284,
-     1.7317865827354473, -2.1543603720002062, 2.6931105493056298,
-     -3.4311781356219053, 4.5572634187795291, -6.6248263190876653,
-     12.356657609378544, -1.9843883778092046, -8.2085388173702682,
-     1.835801086406754},
-    {-0.17296979808284046, 0.52249861493968874, -0.88310718047446946,
-     1.2632831850913258, -1.6734009709286277, 2.1270367504090708,
-     -2.6431142533328509, 3.2497102178311277, -3.9914000549585116,
-     4.9449189653107268, -6.2571630068793587, 8.2559713742695084,
-     -11.881798187143545, 21.646654017093425, -5.6781471211595651,
-     -8.8289725519851405},
-    {0.50241928618815457, -1.517100834287086, 2.5620980641664617,
-     -3.6603814576093567, 4.839585684371178, -6.1350992786889798,
-     7.5948830160827354, -9.2875530989122552, 11.316916195110121,
-     -13.85017599536425, 17.1779862334919, -21.858839993468745,
-     29.131495532874244, -42.461439259893304, 77.438037004005793,
-     -51.79283109806601},
-};
-
 // How a dense analysis is cut into blocks: leaves per tile and samples per
 // block (a function of the analysis alone, so that it gives the same bits
 // alone and served).
@@ -221,16 +121,17 @@ __host__ __device__ inline DenseCut dense_cut(int N, int S) {
 template <int NW, int SG, int LV, bool ASYM, bool SEC>
 struct DenseSmem {
     // LDS for the far sums kept for the adjoint (those of the first phases;
-    // the others' are formed again)
-    static constexpr int kFarFloats = 32 * 1024 / 4;
+    // the others' are formed again): with four samples what one block per CU
+    // leaves, 52 phases in tiles of four leaves and 122 in those of two (half
+    // as many of asymmetric peaks); with one, 52, and two blocks fit a CU
+    static constexpr int kFarFloats = (SG == 4 && LV == 2 ? 92 : 39) * 1024 / 4;
     static constexpr int kPts = LV * kLeaf;
     static constexpr bool kMid = SG == 4;   // peaks are taken at the leaves' nodes
-    static constexpr int kFarSums = (SEC ? 3 : 2) * (ASYM ? 2 : 1);   // per lane and phase
+    static constexpr int kFarSums = 3 * (ASYM ? 2 : 1);     // per lane and phase
     static constexpr int kFarCap = kFarFloats / (kFarSums * kWave);
     static constexpr int kLow = LV * kNodes;     // the leaves' nodes
     float lm[kPts * kNodeStride];         // weights of the leaves' nodes at the points
-    float em[kLow * kNodeStride];         // of the tile's at the leaves', and slopes
-    float ed[kLow * kNodeStride];
+    float em[kLow * kNodeStride];         // of the tile's at the leaves'
     float us[kPts], ul[kPts];             // points relative to xref, rounding errors
     float sig[NW][SG][kPts];              // the waves' sums at the points
     float nod[NW][kWave + 1];             // ... at the tile's nodes
@@ -238,7 +139,7 @@ struct DenseSmem {
     double pn[SG][kNodes];                // node sums of all waves
     double low[SG][kLow];                 // ... brought to the leaves' nodes; then the
                                           // residual at them
-    double rn[SG][kNodes], rs[SG][kNodes];   // residual at the tile's nodes, its slope
+    double rn[SG][kNodes];                // residual at the tile's nodes
     float rres[SG][kPts];                 // residual y/f - 1
     double red[SG * LV];
     int2 nr[kPlanPhases];                 // near peaks [x, y) of each phase
@@ -248,8 +149,7 @@ struct DenseSmem {
 // Tables of a dense problem, made once (launch_prepare).  Kind 0 is a tile of
 // two leaves, kind 1 one of four.
 //   lm    [leaf][64][16]      weights of the leaf's nodes at its points
-//   em    [leaf][2][2][16][16]  by kind: weights of the tile's nodes at the leaf's
-//                             nodes, and their slopes (per degree)
+//   em    [leaf][2][16][16]   by kind: weights of the tile's nodes at the leaf's nodes
 //   leaf  [leaf][kGeo]        its nodes, middle and half-width (FP32, relative to
 //                             the reference of its 256 points)
 //   tile  [2][tiles][kGeo]    the tile's nodes
@@ -269,7 +169,7 @@ struct DenseTables {
         DenseTables o{};
         o.tiles = (leaves + 1) / 2;
         o.em = leaves * kLeaf * kNodes * sizeof(float);
-        o.leaf = o.em + leaves * 4 * kNodes * kNodes * sizeof(float);
+        o.leaf = o.em + leaves * 2 * kNodes * kNodes * sizeof(float);
         o.tile = o.leaf + leaves * kGeo * sizeof(float);
         o.mid = o.tile + 2 * o.tiles * kGeo * sizeof(float);
         o.mid = (o.mid + 15) / 16 * 16;
@@ -306,7 +206,7 @@ struct DenseView {
     }
     __device__ const float *em(int leaf, int kind) const {
         return reinterpret_cast<const float *>(base + o.em) +
-               ((size_t)leaf * 2 + kind) * 2 * kNodes * kNodes;
+               ((size_t)leaf * 2 + kind) * kNodes * kNodes;
     }
     __device__ const float *leaf(int l) const {
         return reinterpret_cast<const float *>(base + o.leaf) + (size_t)l * kGeo;
@@ -349,12 +249,8 @@ __device__ inline void dense_tables_leaf(const ProbDev &P, int leaf, char *base)
         float *em = const_cast<float *>(V.em(leaf, kind));
         for (int e = threadIdx.x; e < kNodes * kNodes; e += blockDim.x) {
             const int q = e / kNodes, m = e % kNodes;
-            const double t = (h.x + h.y * kNodeCos[q] - th.x) / th.y, T = cheb16(t);
-            em[e] = (float)node_weight(t, T, m);
-            // the slope of l_m at t: the interpolant of its values at the nodes
-            double d = 0.0;
-            for (int r = 0; r < kNodes; ++r) d = fma(node_weight(t, T, r), kNodeDeriv[r][m], d);
-            em[kNodes * kNodes + e] = (float)(d / th.y);
+            const double t = (h.x + h.y * kNodeCos[q] - th.x) / th.y;
+            em[e] = (float)node_weight(t, cheb16(t), m);
         }
         if (a != ta) continue;
         float *tg = const_cast<float *>(V.tile(kind, a / pts));
@@ -475,9 +371,9 @@ __device__ inline int2 dense_near(const ProbDev &P, const StepDev &st, int t, in
 // tw = 0).  With q2^2 = tt - 1 the Gaussian weight is
 // c q2 + bG tt + gG, bG = A tw / 2, gG = -A tw (1/2 + 1/(4 ln2)): SecW.
 
-// Far sums of one phase side at the lane's node: f0 = sum I l,
-// f2 = sum I l^2 and, under the sec law (whose shift weights differ by peak),
-// f1 = sum I (l^2 (c q2 - 2 kL) + l kL) (f1 and f2 with GRAD).
+// Far sums of one phase side at the lane's node: f0 = sum I l, f2 = sum I l^2
+// and f1 = sum I l^2 q2, under the sec law (whose shift weights differ by peak)
+// sum I (l^2 (c q2 - 2 kL) + l kL) (f1 and f2 with GRAD).
 struct FarSums {
     float f0, f1, f2;
 };
@@ -493,15 +389,15 @@ __device__ __forceinline__ FarSums far_sums(cptr<float> pt, cptr<float> inten,
         if (SEC) q2 *= c;
         const float l = rcp_f32(fmaf(q2, q2, 1.0f));
         if (GRAD) {
-            const float Il = I * l;
+            const float Il = I * l, Ill = Il * l;
             f.f0 += Il;
+            f.f2 += Ill;
             if (SEC) {
-                const float kL = 0.25f * tw * ka, Ill = Il * l;
-                f.f2 += Ill;
+                const float kL = 0.25f * tw * ka;
                 f.f1 = fmaf(Ill, fmaf(c, q2, -2.f * kL), f.f1);
                 f.f1 = fmaf(Il, kL, f.f1);
             } else {
-                f.f2 = fmaf(Il, l, f.f2);
+                f.f1 = fmaf(Ill, q2, f.f1);
             }
         } else {
             f.f0 = fmaf(I, l, f.f0);
@@ -633,10 +529,9 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
 #pragma unroll 2
         for (int e = tid; e < nl * kLeaf * R4; e += NC)
             put(sm.lm + e / R4 * kNodeStride + e % R4 * 4, lm[e]);
-        for (int e = tid; e < nl * 2 * kNodes * R4; e += NC) {
-            const int l = e / (2 * kNodes * R4), r = e % (2 * kNodes * R4);
-            const int row = r / R4 % kNodes;
-            put((r < kNodes * R4 ? sm.em : sm.ed) + (l * kNodes + row) * kNodeStride + r % R4 * 4,
+        for (int e = tid; e < nl * kNodes * R4; e += NC) {
+            const int l = e / (kNodes * R4), r = e % (kNodes * R4);
+            put(sm.em + e / R4 * kNodeStride + e % R4 * 4,
                 reinterpret_cast<const float4 *>(V.em(i0 / kLeaf + l, KIND))[r]);
         }
     }
@@ -745,11 +640,9 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                 far_of(std::true_type{}, a, b, nr, c, iw2r, ka, lo, hi);
                 float (*dst)[kWave] = sm.far[k];
                 constexpr int H = SM::kFarSums / 2;   // (ASYM: the high side)
-                dst[0][lane] = lo.f0; dst[1][lane] = lo.f2;
-                if (SEC) dst[2][lane] = lo.f1;
+                dst[0][lane] = lo.f0; dst[1][lane] = lo.f1; dst[2][lane] = lo.f2;
                 if (ASYM) {
-                    dst[H][lane] = hi.f0; dst[H + 1][lane] = hi.f2;
-                    if (SEC) dst[H + 2][lane] = hi.f1;
+                    dst[H][lane] = hi.f0; dst[H + 1][lane] = hi.f1; dst[H + 2][lane] = hi.f2;
                 }
             } else {
                 far_of(std::false_type{}, a, b, nr, c, iw2r, ka, lo, hi);
@@ -885,8 +778,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
     }
     if (!GRAD) return;
 
-    // ---------------- the residual at the leaves' nodes, then at the tile's,
-    // and its slope there
+    // ---------------- the residual at the leaves' nodes, then at the tile's
     {
         constexpr int OUT = SG * SM::kLow;
         constexpr int TPO = NT / OUT < kWave ? NT / OUT : kWave;
@@ -910,26 +802,18 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
         const int o = tid / NG, j = tid % NG;
         if (o < SG * kNodes) {
             const int g = o / kNodes, m = o % kNodes;
-            double v = 0.0, d = 0.0;
-            for (int q = j; q < nl * kNodes; q += NG) {
+            double v = 0.0;
+            for (int q = j; q < nl * kNodes; q += NG)
                 v = fma((double)sm.em[q * kNodeStride + m], sm.low[g][q], v);
-                if (!SEC) d = fma((double)sm.ed[q * kNodeStride + m], sm.low[g][q], d);
-            }
 #pragma unroll
-            for (int x = NG / 2; x >= 1; x >>= 1) {
-                v += __shfl_xor(v, x, kWave);
-                if (!SEC) d += __shfl_xor(d, x, kWave);
-            }
-            if (j == 0) {
-                sm.rn[g][m] = v;
-                sm.rs[g][m] = d;
-            }
+            for (int x = NG / 2; x >= 1; x >>= 1) v += __shfl_xor(v, x, kWave);
+            if (j == 0) sm.rn[g][m] = v;
         }
     }
     __syncthreads();
 
     // ---------------- adjoint: the phase's sums over points and nodes
-    const float rn = (float)sm.rn[sl][n], rs = SEC ? 0.f : (float)sm.rs[sl][n];
+    const float rn = (float)sm.rn[sl][n];
     float r[NPP], rl[LV];
 #pragma unroll
     for (int p = 0; p < NPP; ++p) r[p] = sm.rres[sl][p * LPS + li];
@@ -955,18 +839,14 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                 if (k < kCap) {
                     float (*src)[kWave] = sm.far[k];
                     constexpr int H = SM::kFarSums / 2;
-                    lo = FarSums{src[0][lane], SEC ? src[2][lane] : 0.f, src[1][lane]};
-                    if (ASYM)
-                        hi = FarSums{src[H][lane], SEC ? src[H + 2][lane] : 0.f,
-                                     src[H + 1][lane]};
+                    lo = FarSums{src[0][lane], src[1][lane], src[2][lane]};
+                    if (ASYM) hi = FarSums{src[H][lane], src[H + 1][lane], src[H + 2][lane]};
                 } else {
                     far_of(std::true_type{}, a, b, nr, c, iw2r, ka, lo, hi);
                 }
-                acc[3] = rn * lo.f0; acc[5] = rn * lo.f2;
-                acc[4] = SEC ? rn * lo.f1 : -0.5f * rcp_f32(c.x) * (rs * lo.f0);
+                acc[3] = rn * lo.f0; acc[4] = rn * lo.f1; acc[5] = rn * lo.f2;
                 if constexpr (ASYM) {
-                    acc[9] = rn * hi.f0; acc[11] = rn * hi.f2;
-                    acc[10] = SEC ? rn * hi.f1 : -0.5f * rcp_f32(iw2r) * (rs * hi.f0);
+                    acc[9] = rn * hi.f0; acc[10] = rn * hi.f1; acc[11] = rn * hi.f2;
                 }
                 for (int j = nr.x; j < nr.y; ++j) {
                     const Near rec = near_peak(j, c, iw2r);

@@ -99,3 +99,43 @@ def test_dense_grids_match_oracle(N, step, S, kind, asym, sec):
     for row in range(D):
         assert rel_l2(gl.cpu().numpy()[row], rgl[row]) <= 1e-4, row
         assert rel_l2(gs.cpu().numpy()[row], rgs[row]) <= 1e-4, row
+
+
+@pytest.mark.parametrize("asym", [False, True])
+@pytest.mark.parametrize("N,S,K", [(700, 1, 6), (900, 60, 5), (700, 130, 70), (1300, 200, 3)])
+def test_shift_gradient_of_phases_outside_the_scan(N, S, K, asym):
+    """Phases with every peak 2 to 40 deg past one end of the scan: their
+    shift's gradient is all far tails.  Counts are three times the profile, so
+    every term has one sign and the bar on each phase holds for its terms: some
+    27 roundings of 2^-24 (q2, whose error the cubed tail takes three times,
+    reciprocal, products, sums over nine peaks and sixteen nodes) and the
+    interpolation's 1e-7."""
+    print(f"\nouter phases: N={N} S={S} K={K} asym={asym}", flush=True)
+    D = 5 if asym else 4
+    rng = np.random.default_rng(N + S)
+    x = 60.0 + 0.02 * np.arange(N)
+    off = (9 * np.arange(K + 1)).astype(np.int32)
+    out = np.sort(rng.uniform(2.0, 40.0, (K, 9)), axis=1)
+    side = np.arange(K) % 2 == 0
+    pos = np.where(side[:, None], x[-1] + out, x[0] - out).ravel()
+    prob = W.Problem(x=x, bg=np.full(N, 1.0), peak_off=off, peak_pos=pos,
+                     peak_int=rng.uniform(0.2, 1.0, 9 * K), cutoff=0.0,
+                     true_idx=np.zeros(0, int), phi_true=np.zeros((4, K)))
+    loc = np.zeros((D, K))
+    loc[0] = math.log(500.0) + 0.3 * rng.standard_normal(K)
+    loc[2] = math.log(0.1) + 0.2 * rng.standard_normal(K)
+    loc[3] = rng.standard_normal(K)
+    ls = np.full((D, K), math.log(0.05))
+    eps = rng.standard_normal((S, D, K))
+    eps[:, 1] = 0.0                       # no shift: its prior adds nothing
+    pro, el = (oracle.profile_asym, oracle.elbo_asym) if asym else (oracle.profile, oracle.elbo)
+    y = 3.0 * pro(prob.x, prob.bg, off, pos, prob.peak_int, 0.0, _phi(loc, ls, eps))[0]
+    ctx = context()
+    P = X.Problem.from_workload(ctx, prob, y, cutoff=0.0, asymmetric=asym)
+    tape = X.Tape(ctx, P, S)
+    X.xrdvi_elbo_fwd(ctx, P, tape, dev(loc), dev(ls), eps=dev(eps))
+    gl, _ = X.xrdvi_elbo_bwd(ctx, tape)
+    ref = el(prob, y, loc, ls, eps)[2][1]
+    err = np.max(np.abs(gl.cpu().numpy()[1] - ref) / np.abs(ref))
+    print(f"largest relative error {err:.2e}", flush=True)
+    assert err <= 27 * 2.0 ** -24 + 1e-7

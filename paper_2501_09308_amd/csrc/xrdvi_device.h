@@ -49,12 +49,13 @@ constexpr int kBlock = kWave * kWaves;
 // windowed: kTile): the widest dense tile, so that its peaks have one offset.
 constexpr int kRefDense = 256;
 // The Gaussian term of a peak is evaluated only within kGaussReach FWHM of its
-// centre: beyond 3.5 w, 2^(-q2^2) < 2^-49 of the peak height, below half an
-// FP32 unit of the profile (f >= B > 0) for every peak up to 3e7 times the
-// background, where the diffractogram's largest are some 1e3 times.  Against
-// 4.6 w (2^-84): 200 x 60 peaks dense, N = 7001, S = 128 726 -> 687 us;
-// 2000 x 100, N = 14001, windows of 8 FWHM 1277 -> 1261 us.
-constexpr double kGaussReach = 3.5;
+// centre: beyond 4.6 w, 2^(-q2^2) < 2^-84 of the peak height, below half an FP32
+// unit of the profile (f >= B > 0) for every peak up to 1e18 times the
+// background.  A nearer end shows: at 3.5 w (2^-49) a purely Gaussian peak of
+// 1e6 counts on a background of 1e-6 is off by 1e-3 just past it, and saves only
+// 1 to 5 % (200 x 60 peaks dense, N = 7001, S = 128 687 us for 726; 2000 x 100,
+// N = 14001, windows of 8 FWHM 1261 for 1277).
+constexpr double kGaussReach = 4.6;
 
 constexpr double kCG = 0.93943727869965133377;   // 2 sqrt(ln 2 / pi)
 constexpr double kCL = 0.63661977236758134308;   // 2 / pi

@@ -150,8 +150,9 @@ struct DenseSmem {
 // two leaves, kind 1 one of four.
 //   lm    [leaf][64][16]      weights of the leaf's nodes at its points
 //   em    [leaf][2][16][16]   by kind: weights of the tile's nodes at the leaf's nodes
-//   leaf  [leaf][kGeo]        its nodes, middle and half-width (FP32, relative to
-//                             the reference of its 256 points)
+//   leaf  [leaf][kGeo]        its middle (FP32, relative to the reference of its 256
+//                             points), its half-width, and its nodes, relative to
+//                             that rounded middle
 //   tile  [2][tiles][kGeo]    the tile's nodes
 //   mid   [2][tiles]          its middle and half-width (FP64)
 //   near  [2][kNearLevels][tiles][K]  by margin: the peaks of a phase with
@@ -260,10 +261,11 @@ __device__ inline void dense_tables_leaf(const ProbDev &P, int leaf, char *base)
             reinterpret_cast<double2 *>(base + V.o.mid)[kind * V.o.tiles + a / pts] = th;
     }
     float *lg = const_cast<float *>(V.leaf(leaf));
+    const float mid = (float)(h.x - xref);
     for (int n = threadIdx.x; n < kNodes; n += blockDim.x)
-        lg[n] = (float)((h.x - xref) + h.y * kNodeCos[n]);
+        lg[n] = (float)((h.x - xref - (double)mid) + h.y * kNodeCos[n]);
     if (threadIdx.x == 0) {
-        lg[kNodes] = (float)(h.x - xref);
+        lg[kNodes] = mid;
         lg[kNodes + 1] = (float)h.y;
     }
 }
@@ -441,13 +443,16 @@ struct NearPeak {
         const float e = (pt - (ch - bb)) + (mu - bb);   // exact: pt + mu - ch
         return NearPeak{ch, e + ptl, SEC ? iw2 * c : iw2, SEC ? iw2r * c : iw2r};
     }
-    // q2 at the point u, to the accuracy that the flat of the Lorentzian
-    // needs (an absolute error of a few FP32 roundings of the tile's extent);
-    // cs = ch s
+    // Its centre relative to a leaf's middle m.
+    __device__ __forceinline__ float in_leaf(float m) const { return (ch - m) + cl; }
+    // q2 at the point u of a leaf, where the peak's centre is c and c s is cs:
+    // an absolute error of a few FP32 roundings of the leaf's extent, which the
+    // flat of the Lorentzian bears (relative to the reference of 256 points, as
+    // for the steep below, a peak of 0.05 deg on steps of 0.02 erred by 2.6e-6)
     template <bool ASYM>
-    __device__ __forceinline__ float q2_flat(float u, float cs, bool &up) const {
+    __device__ __forceinline__ float q2_flat(float u, float c, float cs, bool &up) const {
         if (ASYM) {
-            const float d = u - ch;
+            const float d = u - c;
             up = d >= 0.f;
             return d * (up ? sr : s);
         }
@@ -535,9 +540,12 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                 reinterpret_cast<const float4 *>(V.em(i0 / kLeaf + l, KIND))[r]);
         }
     }
-    // the lane's nodes; lane n tests the reach of leaf n % LV
+    // the lane's nodes, the leaves' relative to their middles; lane n tests the
+    // reach of leaf n % LV
     const float vn = V.tile(KIND, t)[n];
-    float vl[LV], lmid = 0.f, lhalf = 0.f;
+    float vl[LV], lm[LV], lmid = 0.f, lhalf = 0.f;
+#pragma unroll
+    for (int l = 0; l < LV; ++l) lm[l] = as_const(V.leaf(i0 / kLeaf + min(l, nl - 1)))[kNodes];
     if (MID) {
 #pragma unroll
         for (int l = 0; l < LV; ++l) vl[l] = V.leaf(i0 / kLeaf + min(l, nl - 1))[n];
@@ -587,7 +595,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
     // a near peak of the tile, and the reach of its Gaussian
     struct Near {
         NearPeak pk;
-        float I, c, tw, reach, cs;
+        float I, c, tw, reach;
     };
     auto near_peak = [&](int j, float4 c, float iw2r) {
         Near r{};
@@ -599,7 +607,6 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
             r.I = inten[j];
         }
         r.pk = NearPeak::of<SEC>(ptt[j], ptl[j], c.w, c.x, iw2r, r.c);
-        r.cs = r.pk.ch * r.pk.s;
         r.reach = (float)(2.0 * kGaussReach) *
                   rcp_f32(ASYM ? fminf(r.pk.s, r.pk.sr) : r.pk.s);
         return r;
@@ -614,7 +621,8 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
         return (unsigned)(b | (b >> 16));
     };
 
-    // ---------------- forward: this wave's phases
+    // ---------------- forward: this wave's phases (u: the lane's points, relative
+    // to their leaves' middles)
     float sig[NPP], lsig[LV], nsig = 0.f, u[NPP];
 #pragma unroll
     for (int p = 0; p < NPP; ++p) sig[p] = 0.f;
@@ -625,7 +633,8 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
         plan(c0);
         if (c0 == 0) {
 #pragma unroll
-            for (int p = 0; p < NPP; ++p) u[p] = sm.us[p * LPS + li];
+            for (int p = 0; p < NPP; ++p)
+                u[p] = (sm.us[p * LPS + li] - lm[p / PB]) + sm.ul[p * LPS + li];
         }
         for (int k = c0 + wv; k < min(K, c0 + kPlanPhases); k += NW) {
             prio_left((min(K, c0 + kPlanPhases) - k + NW - 1) / NW);
@@ -655,13 +664,15 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
 #pragma unroll
                 for (int l = 0; l < LV; ++l) {
                     if (l >= nl) break;
+                    const float cc = r.pk.in_leaf(lm[l]), cs = cc * r.pk.s;
                     if (near >> l & 1u) {
                         asm volatile("");
                         float tt[PB];
 #pragma unroll
                         for (int q = 0; q < PB; ++q) {
                             bool up;
-                            const float q2 = r.pk.template q2_flat<ASYM>(u[l * PB + q], r.cs, up);
+                            const float q2 =
+                                r.pk.template q2_flat<ASYM>(u[l * PB + q], cc, cs, up);
                             tt[q] = fmaf(q2, q2, 1.0f);
                         }
 #pragma unroll
@@ -670,7 +681,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                                 const int p = l * PB + q;
                                 bool up;
                                 const float q2 = r.pk.template q2<ASYM>(
-                                    u[p], sm.ul[p * LPS + li], up);
+                                    sm.us[p * LPS + li], sm.ul[p * LPS + li], up);
                                 tt[q] = fmaf(q2, q2, 1.0f);
                                 sig[p] = fmaf(aG, exp2_f32(-tt[q]), sig[p]);
                             }
@@ -681,7 +692,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                     } else {
                         asm volatile("");
                         bool up;
-                        const float q2 = r.pk.template q2_flat<ASYM>(vl[l], r.cs, up);
+                        const float q2 = r.pk.template q2_flat<ASYM>(vl[l], cc, cs, up);
                         lsig[l] = fmaf(aL, rcp_f32(fmaf(q2, q2, 1.0f)), lsig[l]);
                     }
                 }
@@ -859,13 +870,14 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
 #pragma unroll
                     for (int l = 0; l < LV; ++l) {
                         if (l >= nl) break;
+                        const float cc = rec.pk.in_leaf(lm[l]), cs = cc * rec.pk.s;
                         if (near >> l & 1u) {
                             asm volatile("");
                             float q2[PB], tt[PB];
                             bool up[PB];
 #pragma unroll
                             for (int q = 0; q < PB; ++q) {
-                                q2[q] = rec.pk.template q2_flat<ASYM>(u[l * PB + q], rec.cs,
+                                q2[q] = rec.pk.template q2_flat<ASYM>(u[l * PB + q], cc, cs,
                                                                       up[q]);
                                 tt[q] = fmaf(q2[q], q2[q], 1.0f);
                             }
@@ -874,7 +886,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                                 if (gauss_matters(tt[q])) {
                                     const int p = l * PB + q;
                                     q2[q] = rec.pk.template q2<ASYM>(
-                                        u[p], sm.ul[p * LPS + li], up[q]);
+                                        sm.us[p * LPS + li], sm.ul[p * LPS + li], up[q]);
                                     tt[q] = fmaf(q2[q], q2[q], 1.0f);
                                     adj_point_G<ASYM, SEC>(AdjPt{r[p], q2[q], tt[q], up[q]},
                                                            rec.c, wl, wh, e);
@@ -887,7 +899,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                         } else {
                             asm volatile("");
                             bool up;
-                            const float q2 = rec.pk.template q2_flat<ASYM>(vl[l], rec.cs, up);
+                            const float q2 = rec.pk.template q2_flat<ASYM>(vl[l], cc, cs, up);
                             adj_terms_L<ASYM, SEC>(rl[l], q2, fmaf(q2, q2, 1.0f), up, rec.c,
                                                    wl, wh, e);
                         }

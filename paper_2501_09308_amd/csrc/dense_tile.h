@@ -146,129 +146,77 @@ struct DenseSmem {
     float far[kFarCap][kFarSums][kWave];
 };
 
-// Tables of a dense problem, made once (launch_prepare).  Kind 0 is a tile of
-// two leaves, kind 1 one of four.
-//   lm    [leaf][64][16]      weights of the leaf's nodes at its points
-//   em    [leaf][2][16][16]   by kind: weights of the tile's nodes at the leaf's nodes
-//   leaf  [leaf][kGeo]        its middle (FP32, relative to the reference of its 256
-//                             points), its half-width, and its nodes, relative to
-//                             that rounded middle
-//   tile  [2][tiles][kGeo]    the tile's nodes
-//   mid   [2][tiles]          its middle and half-width (FP64)
-//   near  [2][kNearLevels][tiles][K]  by margin: the peaks of a phase with
+// Table of a dense problem of constant widths, made once (launch_prepare), by
+// kind of tile (0: two leaves, 1: four):
+//   [kinds][levels][tiles][K]  by margin: the peaks of a phase with
 //                             |p - middle| < (kFarRadius + margin) half-widths
+// An analysis in a server keeps what its cut and S use, a problem of its own
+// all.  (The nodes and their weights are formed by each block: a table of
+// them takes 96 bytes a point.)
 constexpr int kNearLevels = 4;
 __host__ __device__ inline double near_margin(int level) {
     return level == 0 ? 0.0625 : level == 1 ? 0.125 : level == 2 ? 0.25 : 0.75;
 }
-constexpr int kGeo = kNodes + 4;
-struct DenseTables {
-    size_t em, leaf, tile, mid, near, total;   // offsets in bytes (lm is first)
-    size_t tiles;                              // rows per kind
-    __host__ __device__ static DenseTables of(int N, int K) {
-        const size_t leaves = ((size_t)N + kLeaf - 1) / kLeaf;
-        DenseTables o{};
-        o.tiles = (leaves + 1) / 2;
-        o.em = leaves * kLeaf * kNodes * sizeof(float);
-        o.leaf = o.em + leaves * 2 * kNodes * kNodes * sizeof(float);
-        o.tile = o.leaf + leaves * kGeo * sizeof(float);
-        o.mid = o.tile + 2 * o.tiles * kGeo * sizeof(float);
-        o.mid = (o.mid + 15) / 16 * 16;
-        o.near = o.mid + 2 * o.tiles * sizeof(double2);
-        o.total = o.near + 2 * kNearLevels * o.tiles * (size_t)K * sizeof(int2);
-        return o;
+__host__ __device__ inline size_t near_tiles(int N, int kind) {
+    const size_t pts = (kind ? 4 : 2) * kLeaf;
+    return (N + pts - 1) / pts;
+}
+// Entries before the rows of (kind, level) in a table of so many levels.
+__host__ __device__ inline size_t near_offset(int N, int K, int levels, int kind, int level) {
+    return ((kind ? levels * near_tiles(N, 0) : 0) + level * near_tiles(N, kind)) * K;
+}
+// Kinds of tiles that the cut uses and margins that its steps look up (beyond
+// them they search): the table then takes at most 16 S bytes per 128 points and
+// phase, no more memory than a plan of each sample's ranges took.  A function
+// of N and S alone, as the cut.
+struct NearShape {
+    int kinds, levels;
+    size_t bytes(int N, int K) const {
+        return sizeof(int2) * near_offset(N, K, levels, kinds - 1, levels);
     }
 };
+__host__ __device__ inline NearShape near_shape(int N, int S) {
+    const int kinds = dense_cut(N, S).leaves == 4 ? 2 : 1;
+    return NearShape{kinds, S > 2 ? kNearLevels : kinds == 2 ? S : 2 * S};
+}
 
 // Middle and half-width of the run of points [a, b).
 __device__ __forceinline__ double2 mid_half(const ProbDev &P, int a, int b) {
-    const double xa = P.x[a], xb = P.x[b - 1];
+    const cptr<double> x = as_const(P.x);
+    const double xa = x[a], xb = x[b - 1];
     return make_double2(0.5 * (xa + xb), b - a > 1 ? 0.5 * (xb - xa) : kPointHalf);
 }
 
-// l_m(t) at t in [-1, 1].
-__device__ __forceinline__ double node_weight(double t, double T16, int m) {
-    const double d = t - kNodeCos[m];
-    return fabs(d) < 1e-10 ? 1.0 : T16 * kNodeNum[m] / d;
+// ... of a leaf.  One of a single point has all its nodes there: the tile's
+// interpolant, which grows like T16 past the tile's ends, is then taken at the
+// point itself (with nodes kPointHalf about it, the far sum at the last of 65
+// points in steps of 0.005 deg was off by 3e-5, in steps of 0.001 deg by more
+// than itself).
+__device__ __forceinline__ double2 leaf_mid_half(const ProbDev &P, int a) {
+    const cptr<double> x = as_const(P.x);
+    const int b = min(a + kLeaf, P.N);
+    const double xa = x[a], xb = x[b - 1];
+    return make_double2(0.5 * (xa + xb), 0.5 * (xb - xa));
+}
+
+// 1 / d to a rounding or two (d normal), 0 for 0.
+__device__ __forceinline__ double inverse(double d) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return d == 0.0 ? 0.0 : r;
 }
 __device__ __forceinline__ double cheb16(double t) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) t = 2.0 * t * t - 1.0;
     return t;
 }
-
-// The tables of one problem as the kernels read them.
-struct DenseView {
-    DenseTables o;
-    const char *base;
-    __device__ explicit DenseView(const ProbDev &P) : o(DenseTables::of(P.N, P.K)), base(P.dense) {}
-    __device__ const float *lm(int leaf) const {
-        return reinterpret_cast<const float *>(base) + (size_t)leaf * kLeaf * kNodes;
-    }
-    __device__ const float *em(int leaf, int kind) const {
-        return reinterpret_cast<const float *>(base + o.em) +
-               ((size_t)leaf * 2 + kind) * kNodes * kNodes;
-    }
-    __device__ const float *leaf(int l) const {
-        return reinterpret_cast<const float *>(base + o.leaf) + (size_t)l * kGeo;
-    }
-    __device__ const float *tile(int kind, int t) const {
-        return reinterpret_cast<const float *>(base + o.tile) + (kind * o.tiles + t) * kGeo;
-    }
-    __device__ double2 mid(int kind, int t) const {
-        return reinterpret_cast<const double2 *>(base + o.mid)[kind * o.tiles + t];
-    }
-    __device__ const int2 *near(int kind, int level, int t, int K) const {
-        return reinterpret_cast<const int2 *>(base + o.near) +
-               (((size_t)kind * kNearLevels + level) * o.tiles + t) * K;
-    }
-};
-
-// The tables of one leaf (and of the tiles that it begins), by a block.
-__device__ inline void dense_tables_leaf(const ProbDev &P, int leaf, char *base) {
-    ProbDev Q = P;
-    Q.dense = base;
-    const DenseView V(Q);
-    const int a = leaf * kLeaf, b = min(a + kLeaf, P.N);
-    // A leaf of one point has all its nodes there: the tile's interpolant, which
-    // grows like T16 past the tile's ends, is then taken at the point itself
-    // (with nodes kPointHalf about it, the far sum at the last of 65 points in
-    // steps of 0.005 deg was off by 3e-5, in steps of 0.001 deg by more than
-    // itself).
-    double2 h = mid_half(P, a, b);
-    if (b - a == 1) h.y = 0.0;
-    const double xref = P.x[min(a / P.ref * P.ref + P.ref / 2, P.N - 1)];
-    float *lm = const_cast<float *>(V.lm(leaf));
-    for (int e = threadIdx.x; e < kLeaf * kNodes; e += blockDim.x) {
-        const int q = e / kNodes;
-        const double t = a + q < b && h.y > 0.0 ? (P.x[a + q] - h.x) / h.y : 0.0;
-        lm[e] = a + q < b ? (float)node_weight(t, cheb16(t), e % kNodes) : 0.f;
-    }
-    for (int kind = 0; kind < 2; ++kind) {
-        const int pts = (kind ? 4 : 2) * kLeaf, ta = a / pts * pts;
-        const double2 th = mid_half(P, ta, min(ta + pts, P.N));
-        float *em = const_cast<float *>(V.em(leaf, kind));
-        for (int e = threadIdx.x; e < kNodes * kNodes; e += blockDim.x) {
-            const int q = e / kNodes, m = e % kNodes;
-            const double t = (h.x + h.y * kNodeCos[q] - th.x) / th.y;
-            em[e] = (float)node_weight(t, cheb16(t), m);
-        }
-        if (a != ta) continue;
-        float *tg = const_cast<float *>(V.tile(kind, a / pts));
-        for (int n = threadIdx.x; n < kNodes; n += blockDim.x)
-            tg[n] = (float)((th.x - xref) + th.y * kNodeCos[n]);
-        if (threadIdx.x == 0)
-            reinterpret_cast<double2 *>(base + V.o.mid)[kind * V.o.tiles + a / pts] = th;
-    }
-    float *lg = const_cast<float *>(V.leaf(leaf));
-    const float mid = (float)(h.x - xref);
-    for (int n = threadIdx.x; n < kNodes; n += blockDim.x)
-        lg[n] = (float)((h.x - xref - (double)mid) + h.y * kNodeCos[n]);
-    if (threadIdx.x == 0) {
-        lg[kNodes] = mid;
-        lg[kNodes + 1] = (float)h.y;
-    }
+// l_m(t) at t in [-1, 1] (node c, numerator num).
+__device__ __forceinline__ float node_weight(double t, double c, double num) {
+    const double d = t - c;
+    return fabs(d) < 1e-10 ? 1.f : (float)(cheb16(t) * num * inverse(d));
 }
+
 // One entry of the near table: tile t of `leaves` leaves, phase k.
 __device__ inline int2 dense_near_entry(const ProbDev &P, int leaves, int level, int t, int k) {
     const int ta = t * leaves * kLeaf;
@@ -339,11 +287,13 @@ __device__ inline int2 dense_near(const ProbDev &P, const StepDev &st, int t, in
     if (whole) return make_int2(a, b);
     if (!SEC) {
         // the table's first margin that covers the bounds (one load instead of
-        // two searches; all levels are within one cache line per phase group)
+        // two searches)
         const double need = fmax(xm - lo, hi - xm) / ha - kFarRadius;
+#pragma unroll
         for (int level = 0; level < kNearLevels; ++level)
-            if (need < near_margin(level))
-                return DenseView(P).near(leaves == 4, level, t, K)[k];
+            if (level < st.near_levels && need < near_margin(level))
+                return P.near[near_offset(P.N, K, P.near_levels, leaves == 4, level) +
+                              (size_t)t * K + k];
     }
     auto ge = [&](double p) { return p >= lo; };
     auto gt = [&](double p) { return p > hi; };
@@ -514,44 +464,58 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
     const int s = s0 + min(sl, ns - 1);     // (lanes past the last sample repeat it)
     const int i0 = t * PTS, i1 = min(i0 + PTS, P.N), np = i1 - i0;
     const int nl = (np + kLeaf - 1) / kLeaf;   // leaves with points
-    const DenseView V(P);
-    constexpr int KIND = LV == 4;
-    const double2 mh = V.mid(KIND, t);
+    const double2 mh = mid_half(P, i0, i1);
+    const double xref = as_const(P.x)[min(i0 / P.ref * P.ref + P.ref / 2, P.N - 1)];
 
-    // the last kPlanPhases threads find the first phases' near ranges (below),
-    // the others bring in the points and the weights
-    constexpr int NC = NT - kPlanPhases;
-    if (tid < NC) {
-        for (int q = tid; q < PTS; q += NC) {
-            sm.us[q] = q < np ? P.u[i0 + q] : 0.f;
-            sm.ul[q] = q < np ? P.ul[i0 + q] : 0.f;
+    // middles and half-widths of the leaves
+    double2 h[LV];
+#pragma unroll
+    for (int l = 0; l < LV; ++l) h[l] = leaf_mid_half(P, i0 + min(l, nl - 1) * kLeaf);
+    // The last kPlanPhases threads find the first phases' near ranges (below),
+    // the waves before them form the weights: eight those of the leaves' nodes at
+    // the points (32 points together), four those of the tile's at the leaves'
+    // (and bring in the points).
+    constexpr int NC = NT - kPlanPhases, LW = 8;
+    static_assert(NW == LW + 4 + kPlanPhases / kWave && PTS <= 4 * kWave, "roles of the waves");
+    const double cn = kNodeCos[n];
+    if (wv < LW) {
+        constexpr int R = LW * (kWave / kNodes), H = kLeaf / R;   // rows a pass, passes a leaf
+        const int row = wv * (kWave / kNodes) + lane / kNodes;
+        const double num = kNodeNum[n];
+        double x[LV * H];
+#pragma unroll
+        for (int i = 0; i < LV * H; ++i) x[i] = P.x[min(i0 + i * R + row, P.N - 1)];
+#pragma unroll
+        for (int i = 0; i < LV * H; ++i) {
+            const double t = (x[i] - h[i / H].x) * inverse(h[i / H].y);
+            sm.lm[(i * R + row) * kNodeStride + n] =
+                i * R + row < np ? node_weight(t, cn, num) : 0.f;
         }
-        auto put = [](float *dst, float4 v) {
-            dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-        };
-        constexpr int R4 = kNodes / 4;      // a row of 16 weights in float4s
-        const float4 *lm = reinterpret_cast<const float4 *>(V.lm(i0 / kLeaf));
-#pragma unroll 2
-        for (int e = tid; e < nl * kLeaf * R4; e += NC)
-            put(sm.lm + e / R4 * kNodeStride + e % R4 * 4, lm[e]);
-        for (int e = tid; e < nl * kNodes * R4; e += NC) {
-            const int l = e / (kNodes * R4), r = e % (kNodes * R4);
-            put(sm.em + e / R4 * kNodeStride + e % R4 * 4,
-                reinterpret_cast<const float4 *>(V.em(i0 / kLeaf + l, KIND))[r]);
+    } else if (tid < NC) {
+        const int q = tid - LW * kWave, row = q / kNodes;
+        const double num = kNodeNum[n], cr = kNodeCos[row], ih = inverse(mh.y);
+        const float uq = q < np ? P.u[i0 + q] : 0.f, ulq = q < np ? P.ul[i0 + q] : 0.f;
+#pragma unroll
+        for (int l = 0; l < LV; ++l)
+            sm.em[(l * kNodes + row) * kNodeStride + n] =
+                node_weight((h[l].x - mh.x + h[l].y * cr) * ih, cn, num);
+        if (q < PTS) {
+            sm.us[q] = uq;
+            sm.ul[q] = ulq;
         }
     }
-    // the lane's nodes, the leaves' relative to their middles; lane n tests the
-    // reach of leaf n % LV
-    const float vn = V.tile(KIND, t)[n];
+    // the lane's nodes, the leaves' relative to their rounded middles; lane n
+    // tests the reach of leaf n % LV
+    const float vn = (float)((mh.x - xref) + mh.y * cn);
     float vl[LV], lm[LV], lmid = 0.f, lhalf = 0.f;
 #pragma unroll
-    for (int l = 0; l < LV; ++l) lm[l] = as_const(V.leaf(i0 / kLeaf + min(l, nl - 1)))[kNodes];
-    if (MID) {
-#pragma unroll
-        for (int l = 0; l < LV; ++l) vl[l] = V.leaf(i0 / kLeaf + min(l, nl - 1))[n];
-        const float *lg = V.leaf(i0 / kLeaf + min(n % LV, nl - 1));
-        lmid = lg[kNodes];
-        lhalf = lg[kNodes + 1];
+    for (int l = 0; l < LV; ++l) {
+        lm[l] = (float)(h[l].x - xref);
+        vl[l] = (float)((h[l].x - xref - (double)lm[l]) + h[l].y * cn);
+        if (n % LV == l) {
+            lmid = lm[l];
+            lhalf = (float)h[l].y;
+        }
     }
 
     const float4 *pk = st.pk + (size_t)s * K;

@@ -62,7 +62,7 @@ SlotLayout slot_layout(const Job &j) {
     L.trace = 0;
     L.state = a256(sizeof(double) * (size_t)j.steps);
     L.prob = L.state + a256(sizeof(double) * 6 * j.D * (size_t)j.K);
-    L.step = L.prob + a256(problem_bytes(j.N, j.K, T, j.cutoff == 0.0));
+    L.step = L.prob + a256(problem_bytes(problem_shape(job_desc(j), near_shape(j.N, j.S))));
     const StepShape sh{num_tiles(j.N), j.K, T, j.S, j.N, j.D, j.cutoff == 0.0,
                        j.width_law != 0};
     L.total = L.step + a256(step_bytes(sh));
@@ -205,12 +205,12 @@ class GpuExecutor : public Executor {
         std::memset(h, 0, head);   // also the Adam moments
         std::memcpy(h, j.init_loc.data(), sizeof(double) * D);
         std::memcpy(h + sizeof(double) * D, j.init_logscale.data(), sizeof(double) * D);
-        stage_problem(job_desc(j), j.lambda_h, h + head, base + L.prob, d.P, nullptr);
+        stage_problem(job_desc(j), near_shape(j.N, j.S), j.lambda_h, h + head, base + L.prob,
+                      d.P, nullptr);
         hipError_t e = in.to_device(base + L.state, bytes, stream_);
         if (e == hipSuccess) e = prepare_problem(d.P, base + L.prob, stream_);
         if (e != hipSuccess) return dev_fail(e, "upload");
         d.st = carve_step(base + L.step, step_shape(d.P, j.S));
-        if (d.P.cutoff == 0.0) d.st.rres = nullptr;   // dense: no residual array
         double *state = (double *)(base + L.state);
         d.loc = state;
         d.logscale = state + D;

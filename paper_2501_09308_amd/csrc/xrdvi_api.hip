@@ -66,7 +66,7 @@ size_t step_bytes(const StepShape &sh) {
     b += align256(sizeof(double) * S * nt);         // llp
     b += align256(sh.dense ? sizeof(float) * NS * nt * K * S : 4);  // part
     b += align256(sizeof(double) * D);              // sd
-    b += align256(sizeof(float) * S * (size_t)sh.N);  // rres
+    b += align256(sh.dense ? 4 : sizeof(float) * S * (size_t)sh.N);  // rres
     b += align256(sizeof(double) * NS * K * S);     // pw
     b += align256(sh.sec ? sizeof(float4) * S * (size_t)std::max(sh.T, 1) : 4);  // psec
     const bool cand = !sh.dense && !sh.sec;
@@ -86,6 +86,7 @@ StepDev carve_step(void *base, const StepShape &sh) {
     StepDev st{};
     st.S = sh.S;
     st.nt = sh.dense ? dense_cut(sh.N, sh.S).tiles(sh.N) : sh.ntiles;
+    st.near_levels = near_shape(sh.N, sh.S).levels;
     st.eps = (double *)take(sizeof(double) * S * D);
     st.phi = (double *)take(sizeof(double) * S * D);
     st.pk = (float4 *)take(sizeof(float4) * S * K);
@@ -97,7 +98,8 @@ StepDev carve_step(void *base, const StepShape &sh) {
     st.llp = (double *)take(sizeof(double) * S * nt);
     st.part = (float *)take(sh.dense ? sizeof(float) * NS * nt * K * S : 4);
     st.sd = (double *)take(sizeof(double) * D);
-    st.rres = (float *)take(sizeof(float) * S * (size_t)sh.N);
+    st.rres = (float *)take(sh.dense ? 4 : sizeof(float) * S * (size_t)sh.N);
+    if (sh.dense) st.rres = nullptr;        // (its residual stays in LDS)
     st.pw = (double *)take(sizeof(double) * NS * K * S);
     st.psec = (float4 *)take(sh.sec ? sizeof(float4) * S * (size_t)std::max(sh.T, 1) : 4);
     const bool cand = !sh.dense && !sh.sec;
@@ -112,10 +114,11 @@ StepDev carve_step(void *base, const StepShape &sh) {
 // the host fills in (one copy), then what launch_prepare makes from it.
 struct ProblemLayout {
     size_t x, y, bg, off, ph, pos, inten, perm, staged;
-    size_t lgy, u, ul, ptab, pt, ptl, dense, total;
+    size_t lgy, u, ul, ptab, pt, ptl, near, total;
 };
 
-static ProblemLayout problem_layout(int N, int K, int T, bool dense) {
+static ProblemLayout problem_layout(const ProblemShape &sh) {
+    const int N = sh.N, K = sh.K, T = sh.T;
     const int nt = num_tiles(N);
     const size_t T1 = (size_t)std::max(T, 1);
     ProblemLayout L{};
@@ -130,25 +133,29 @@ static ProblemLayout problem_layout(int N, int K, int T, bool dense) {
     L.ptab = slot(4 * (size_t)K * (kTabBuckets + 1));
     L.lgy = slot(8 * (size_t)N);
     L.u = slot(4 * (size_t)nt * kTile); L.ul = slot(4 * (size_t)nt * kTile);
-    const size_t refs = dense ? (size_t)(N + kRefDense - 1) / kRefDense : (size_t)nt;
+    const size_t refs = sh.dense ? (size_t)(N + kRefDense - 1) / kRefDense : (size_t)nt;
     L.pt = slot(4 * refs * T1); L.ptl = slot(4 * refs * T1);
-    L.dense = slot(dense ? DenseTables::of(N, K).total : 4);
+    L.near = slot(sh.near_bytes);
     L.total = o;
     return L;
 }
 
-size_t problem_bytes(int N, int K, int T, bool dense) {
-    return problem_layout(N, K, T, dense).total;
+ProblemShape problem_shape(const xrdvi_problem_desc &d, const NearShape &near) {
+    const bool dense = d.cutoff == 0.0;
+    return ProblemShape{d.N, d.K, d.peak_off[d.K], dense,
+                        dense && d.width_law == 0 ? near.bytes(d.N, d.K) : 0};
 }
+
+size_t problem_bytes(const ProblemShape &sh) { return problem_layout(sh).total; }
 
 size_t problem_staged_bytes(int N, int K, int T) {
-    return problem_layout(N, K, T, false).staged;
+    return problem_layout(ProblemShape{N, K, T, false, 0}).staged;
 }
 
-void stage_problem(const xrdvi_problem_desc &d, double lambda, char *image,
-                   char *base, ProbDev &P, int **perm_out) {
+void stage_problem(const xrdvi_problem_desc &d, const NearShape &near, double lambda,
+                   char *image, char *base, ProbDev &P, int **perm_out) {
     const int N = d.N, K = d.K, T = d.peak_off[K];
-    const ProblemLayout L = problem_layout(N, K, T, d.cutoff == 0.0);
+    const ProblemLayout L = problem_layout(problem_shape(d, near));
     std::memcpy(image + L.x, d.x, 8 * (size_t)N);
     std::memcpy(image + L.y, d.y, 8 * (size_t)N);
     std::memcpy(image + L.bg, d.bg, 8 * (size_t)N);
@@ -212,18 +219,23 @@ void stage_problem(const xrdvi_problem_desc &d, double lambda, char *image,
     P.pt = (const float *)(base + L.pt);
     P.ptl = (const float *)(base + L.ptl);
     P.ptab = (const int *)(base + L.ptab);
-    P.dense = base + L.dense;
+    P.near = (const int2 *)(base + L.near);
+    P.near_kinds = near.kinds;
+    P.near_levels = near.levels;
     P.tab_x0 = d.x[0];
     P.tab_inv = N > 1 ? kTabBuckets / (d.x[N - 1] - d.x[0]) : 0.0;
     if (perm_out) *perm_out = (int *)(base + L.perm);
 }
 
 hipError_t prepare_problem(const ProbDev &P, char *base, hipStream_t stream) {
-    const ProblemLayout L = problem_layout(P.N, P.K, P.T, P.cutoff == 0.0);
+    const bool dense = P.cutoff == 0.0;
+    const NearShape near{P.near_kinds, P.near_levels};
+    const ProblemLayout L = problem_layout(
+        ProblemShape{P.N, P.K, P.T, dense, dense && !P.sec ? near.bytes(P.N, P.K) : 0});
     return launch_prepare(P, (double *)(base + L.lgy), (float *)(base + L.u),
                           (float *)(base + L.ul), (int *)(base + L.ptab),
                           (float *)(base + L.pt), (float *)(base + L.ptl),
-                          base + L.dense, stream);
+                          (int2 *)(base + L.near), stream);
 }
 
 }  // namespace xrdvi
@@ -492,7 +504,8 @@ int xrdvi_problem_create(xrdvi_ctx *ctx, const xrdvi_problem_desc *d,
     int rc = validate_desc(d, &lam);
     if (rc != XRDVI_OK) return rc;
     DeviceGuard g(ctx->device);
-    const size_t bytes = problem_bytes(d->N, d->K, d->peak_off[d->K], d->cutoff == 0.0);
+    const NearShape near{2, kNearLevels};      // (tapes of any S)
+    const size_t bytes = problem_bytes(problem_shape(*d, near));
     void *mem = nullptr;
     hipError_t e = hipMalloc(&mem, bytes);
     if (e != hipSuccess)
@@ -502,7 +515,7 @@ int xrdvi_problem_create(xrdvi_ctx *ctx, const xrdvi_problem_desc *d,
     pb->device = ctx->device;
     pb->mem = mem;
     std::vector<char> image(problem_staged_bytes(d->N, d->K, d->peak_off[d->K]));
-    stage_problem(*d, lam, image.data(), static_cast<char *>(mem), pb->P, &pb->perm);
+    stage_problem(*d, near, lam, image.data(), static_cast<char *>(mem), pb->P, &pb->perm);
     e = hipMemcpyAsync(mem, image.data(), image.size(), hipMemcpyHostToDevice, nullptr);
     if (e == hipSuccess) e = prepare_problem(pb->P, static_cast<char *>(mem), nullptr);
     // also completes the copy (pageable source) before the image goes away
@@ -611,11 +624,14 @@ int xrdvi_profile_static(xrdvi_ctx *ctx, const xrdvi_problem *prob, int32_t S,
     if (S < 1 || S > kMaxSamples) return fail(XRDVI_EINVAL, "S must be in [1, 1024]");
     const ProbDev &P = prob->P;
     const StepShape sh = step_shape(P, S);
-    // (the limit also counts what calls once kept here besides: the dense
-    // plan per (sample, tile, phase), FP64 candidate positions; which calls fit
-    // stays as it was)
-    const size_t tk = (size_t)sh.ntiles * sh.K;
-    const size_t former = sh.dense ? (sh.D == 5 ? 24 : 16) * S * tk : sh.sec ? 0 : 16 * tk;
+    // (the limit also counts what calls once kept here besides: in dense mode the
+    // plan per (sample, tile, phase) and the residual, FP64 candidate positions;
+    // which calls fit stays as it was)
+    const size_t tk = (size_t)sh.ntiles * sh.K, s4 = (size_t)4 * S;
+    const size_t former =
+        sh.dense ? align256(s4 * 4 * tk) + (sh.D == 5 ? align256(s4 * 2 * tk) : 256) +
+                       align256(s4 * sh.N) - 256
+                 : 512 + (sh.sec ? 0 : align256(32 * tk) - align256(16 * tk));
     const size_t bytes = step_bytes(sh) + former;
     if (bytes > kStaticScratchBytes)
         return fail(XRDVI_EINVAL,

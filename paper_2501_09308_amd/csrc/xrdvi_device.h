@@ -106,7 +106,9 @@ struct ProbDev {
     // kTabBuckets), a starting guess for searches over positions
     const int *ptab;
     double tab_x0, tab_inv;
-    const char *dense;        // dense mode: DenseTables
+    const int2 *near;         // dense mode, constant widths: table of near ranges of
+    int near_kinds;           // so many kinds of tiles and margins (dense_tile.h)
+    int near_levels;
 };
 
 constexpr int kTabBuckets = 128;
@@ -120,6 +122,7 @@ struct StepDev {
     int S;
     int nt;           // tiles of the likelihood and adjoint sums: P.ntiles, or in
                       // dense mode those of dense_cut
+    int near_levels;  // dense mode: margins looked up (near_shape)
     double *eps;      // [S][D K] noise used
     double *phi;      // [S][D K] constrained samples (h, mu, w, r[, alpha])
     float4 *pk;       // [S][K] (2/w, h(1-r)cG n/w, h r cL n/w, mu) in FP32,
@@ -130,7 +133,7 @@ struct StepDev {
     int *lo, *hi;     // [S][T] window plan (sorted peak order)
     float4 *psec;     // [S][T] sec width law, per (sample, peak):
                       // (c, I c, tan(theta) (pi/360) w, 0), c = |cos theta|
-    float *rres;      // [S][N] residual y/f - 1 (windowed mode)
+    float *rres;      // [S][N] residual y/f - 1 (windowed mode; dense: null)
     double *pw;       // [K][S][num_sums] adjoint sums per (phase, sample)
                       // (windowed mode)
     double *llp;      // [S][nt] per-tile log-likelihood

@@ -12,11 +12,13 @@
 
 namespace xrdvi {
 
+struct NearShape;   // dense_tile.h
+
 // Per-problem tables: ln y!, the tile-relative FP32 grid and peak positions
 // and the rounding errors of both, the phases' position index; in dense mode
-// the DenseTables.
+// with constant widths the near ranges.
 hipError_t launch_prepare(const ProbDev &P, double *lgy, float *u, float *ul,
-                          int *ptab, float *pt, float *ptl, char *dense,
+                          int *ptab, float *pt, float *ptl, int2 *near,
                           hipStream_t stream);
 hipError_t launch_sample(const ProbDev &P, const StepDev &st,
                          const double *loc, const double *logscale,
@@ -92,15 +94,23 @@ inline int latent_types(const xrdvi_problem_desc &d) {
     return d.asymmetric ? 5 : 4;
 }
 
+// Sizes that fix a problem's device layout; near_bytes: of its table of near
+// ranges (dense mode, constant widths).
+struct ProblemShape {
+    int N, K, T;
+    bool dense;
+    size_t near_bytes;
+};
 // Device bytes of a prepared problem.  Its first problem_staged_bytes are
 // filled in on the host: stage_problem (validated desc, resolved lambda) makes
 // their image and fills P and the sorted-to-caller peak permutation for a
 // problem at device address `base`; once the image is copied there,
 // prepare_problem makes the rest on the device.
-size_t problem_bytes(int N, int K, int T, bool dense);
+ProblemShape problem_shape(const xrdvi_problem_desc &d, const NearShape &near);
+size_t problem_bytes(const ProblemShape &sh);
 size_t problem_staged_bytes(int N, int K, int T);
-void stage_problem(const xrdvi_problem_desc &d, double lambda, char *image,
-                   char *base, ProbDev &P, int **perm_out);
+void stage_problem(const xrdvi_problem_desc &d, const NearShape &near, double lambda,
+                   char *image, char *base, ProbDev &P, int **perm_out);
 hipError_t prepare_problem(const ProbDev &P, char *base, hipStream_t stream);
 // Host validation of a problem description; resolves lambda_h (0 -> 1 /
 // max(y - bg)) and returns max(y - bg) in *ymax when non-NULL.

@@ -52,17 +52,14 @@ __global__ void k_prepare_peaks(ProbDev P, float *pt, float *ptl) {
     }
 }
 
-// The tables of a dense problem: one block per leaf; one thread per (kind of
-// tile, margin, tile, phase).
-__global__ __launch_bounds__(256) void k_prepare_dense(ProbDev P, char *tables) {
-    dense_tables_leaf(P, blockIdx.x, tables);
-}
-__global__ __launch_bounds__(64) void k_prepare_near(ProbDev P, int2 *near, size_t tiles) {
+// The near ranges of a dense problem, one thread per (kind of tile, margin,
+// tile, phase).
+__global__ __launch_bounds__(64) void k_prepare_near(ProbDev P, int2 *near) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x, t = blockIdx.y;
-    const int leaves = blockIdx.z / kNearLevels ? 4 : 2, level = blockIdx.z % kNearLevels;
-    if (k < P.K && t < (P.N + leaves * kLeaf - 1) / (leaves * kLeaf))
-        near[(((size_t)(leaves == 4) * kNearLevels + level) * tiles + t) * P.K + k] =
-            dense_near_entry(P, leaves, level, t, k);
+    const int kind = blockIdx.z / P.near_levels, level = blockIdx.z % P.near_levels;
+    if (k < P.K && t < (int)near_tiles(P.N, kind))
+        near[near_offset(P.N, P.K, P.near_levels, kind, level) + (size_t)t * P.K + k] =
+            dense_near_entry(P, kind ? 4 : 2, level, t, k);
 }
 
 // a1: grid (ceil(K/64), S), 256 threads.
@@ -231,7 +228,7 @@ __global__ void k_adam(int n, double *theta, double *m1, double *m2,
 // ---- launchers ------------------------------------------------------------
 
 hipError_t launch_prepare(const ProbDev &P, double *lgy, float *u, float *ul,
-                          int *ptab, float *pt, float *ptl, char *dense,
+                          int *ptab, float *pt, float *ptl, int2 *near,
                           hipStream_t stream) {
     const int np = P.ntiles * kTile;
     k_prepare_points<<<(np + 255) / 256, 256, 0, stream>>>(P, lgy, u, ul);
@@ -240,12 +237,9 @@ hipError_t launch_prepare(const ProbDev &P, double *lgy, float *u, float *ul,
         dim3 g((P.T + 255) / 256 < 64 ? (P.T + 255) / 256 : 64, (P.N + P.ref - 1) / P.ref);
         k_prepare_peaks<<<g, 256, 0, stream>>>(P, pt, ptl);
     }
-    if (P.cutoff == 0.0) {
-        const DenseTables D = DenseTables::of(P.N, P.K);
-        const int leaves = (P.N + kLeaf - 1) / kLeaf;
-        k_prepare_dense<<<leaves, 256, 0, stream>>>(P, dense);
-        dim3 g((P.K + 63) / 64, (leaves + 1) / 2, 2 * kNearLevels);
-        k_prepare_near<<<g, 64, 0, stream>>>(P, reinterpret_cast<int2 *>(dense + D.near), D.tiles);
+    if (P.cutoff == 0.0 && !P.sec) {
+        dim3 g((P.K + 63) / 64, (unsigned)near_tiles(P.N, 0), P.near_kinds * P.near_levels);
+        k_prepare_near<<<g, 64, 0, stream>>>(P, near);
     }
     return hipGetLastError();
 }
@@ -331,16 +325,14 @@ static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
             k_adjoint_win<ASYM, SEC><<<ga, kBlock, 0, stream>>>(P, st, elbo ? *elbo : ElboOut{});
         }
     } else {
-        StepDev sd = st;
-        sd.rres = nullptr;      // dense: the residual stays in LDS
         const DenseCut cut = dense_cut(P.N, st.S);
         auto run = [&](auto sg_tag, auto lv_tag) {
             constexpr int SG = decltype(sg_tag)::value, LV = decltype(lv_tag)::value;
             constexpr int nt = kDenseWaves * kWave;
             const int w = cut.wide(P.N);
             const dim3 g(st.nt, (st.S + SG - 1) / SG);
-            if (grad) k_dense<true, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, sd, f_out, w);
-            else k_dense<false, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, sd, f_out, w);
+            if (grad) k_dense<true, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, st, f_out, w);
+            else k_dense<false, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, st, f_out, w);
         };
         const std::integral_constant<int, 1> one;
         const std::integral_constant<int, 2> two;

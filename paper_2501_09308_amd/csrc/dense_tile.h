@@ -42,6 +42,12 @@ namespace xrdvi {
 
 constexpr int kNodes = 16;
 constexpr double kFarRadius = 2.0;     // in half-widths of the tile
+// Width in half-widths of a leaf from which a peak is taken at its nodes also
+// near its centre: poles (at half the width beside the centre) and growth off
+// the axis are then those of a peak kFarRadius away.  With every peak near
+// taken at the points, peaks of 3 deg (50 x 40, N = 3501, S = 64) took 381 us
+// and asymmetric ones (50 x 50, N = 2501, S = 32) 408.
+constexpr double kWide = 3.5;
 constexpr int kLeaf = kWave;           // points of a leaf
 constexpr int kDenseWaves = 16;        // waves per block
 constexpr int kMinGroupBlocks = 96;
@@ -393,21 +399,18 @@ struct NearPeak {
         const float e = (pt - (ch - bb)) + (mu - bb);   // exact: pt + mu - ch
         return NearPeak{ch, e + ptl, SEC ? iw2 * c : iw2, SEC ? iw2r * c : iw2r};
     }
-    // Its centre relative to a leaf's middle m.
-    __device__ __forceinline__ float in_leaf(float m) const { return (ch - m) + cl; }
-    // q2 at the point u of a leaf, where the peak's centre is c and c s is cs:
-    // an absolute error of a few FP32 roundings of the leaf's extent, which the
-    // flat of the Lorentzian bears (relative to the reference of 256 points, as
-    // for the steep below, a peak of 0.05 deg on steps of 0.02 erred by 2.6e-6)
+    // q2 at the node u of a leaf, relative to its middle m, as the centre is here:
+    // an absolute error of a few FP32 roundings of the leaf's extent
     template <bool ASYM>
-    __device__ __forceinline__ float q2_flat(float u, float c, float cs, bool &up) const {
+    __device__ __forceinline__ float q2_node(float u, float m, bool &up) const {
+        const float c = (ch - m) + cl;
         if (ASYM) {
             const float d = u - c;
             up = d >= 0.f;
             return d * (up ? sr : s);
         }
         up = false;
-        return fmaf(u, s, -cs);
+        return fmaf(u, s, -c * s);
     }
     // q2 at the point u + ul; whether it lies at or above the centre (ASYM)
     template <bool ASYM>
@@ -421,15 +424,6 @@ struct NearPeak {
         return fmaf(u - ch, s, fmaf(ul, s, -cl * s));
     }
 };
-
-// Whether the Gaussian (and the steep of the Lorentzian) matters at some
-// lane's point, a branch of the whole wave: the empty volatile statement
-// keeps the compiler from evaluating the Gaussian everywhere and selecting.
-__device__ __forceinline__ bool gauss_matters(float tt) {
-    const bool any = __builtin_amdgcn_ballot_w64(!(tt > kGaussTT)) != 0;
-    if (any) asm volatile("");
-    return any;
-}
 
 // Wave priority in the phase loops, by the phases the wave has left: a wave
 // with more of them issues first.  Among waves of one priority the oldest
@@ -556,38 +550,57 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
             hi = FarSums{0.f, 0.f, 0.f};
         }
     };
-    // a near peak of the tile, and the reach of its Gaussian
+    // a near peak of the tile, and the reach of its Gaussian; its data are read
+    // one peak ahead
     struct Near {
         NearPeak pk;
         float I, c, tw, reach;
     };
-    auto near_peak = [&](int j, float4 c, float iw2r) {
+    struct NearData {
+        float pt, ptl, I;
+        float4 rec;
+    };
+    auto near_data = [&](int j) {
+        NearData d{};
+        d.pt = ptt[j];
+        d.ptl = ptl[j];
+        if (SEC) d.rec = ps[j];
+        else d.I = inten[j];
+        return d;
+    };
+    auto near_peak = [&](const NearData &d, float4 c, float iw2r) {
         Near r{};
-        r.c = 1.f;
-        if (SEC) {
-            const float4 rec = ps[j];
-            r.I = rec.y; r.c = rec.x; r.tw = rec.z;
-        } else {
-            r.I = inten[j];
-        }
-        r.pk = NearPeak::of<SEC>(ptt[j], ptl[j], c.w, c.x, iw2r, r.c);
+        r.I = SEC ? d.rec.y : d.I;
+        r.c = SEC ? d.rec.x : 1.f;
+        r.tw = SEC ? d.rec.z : 0.f;
+        r.pk = NearPeak::of<SEC>(d.pt, d.ptl, c.w, c.x, iw2r, r.c);
         r.reach = (float)(2.0 * kGaussReach) *
                   rcp_f32(ASYM ? fminf(r.pk.s, r.pk.sr) : r.pk.s);
         return r;
     };
-    // the leaves that the peak is near of for some sample, one bit each
-    // (lane n of a sample tests leaf n mod LV)
-    auto near_leaves = [&](const Near &r) -> unsigned {
-        if (!MID) return ~0u;
-        const bool near = !(fabsf(r.pk.ch - lmid) >= lhalf + fmaxf(lhalf, r.reach));
-        unsigned long long b = __builtin_amdgcn_ballot_w64(near);
+    // Whether the peaks of a phase are taken at the leaves' nodes wherever they
+    // lie: those at least kWide half-widths of every leaf wide (for every sample)
+    // are as smooth there as one kFarRadius of them away.
+    auto wide_phase = [&](float4 c, float iw2r) {
+        const float s = ASYM ? fmaxf(c.x, iw2r) : c.x;
+        return MID && __builtin_amdgcn_ballot_w64(!(s * lhalf <= (float)(2.0 / kWide))) == 0;
+    };
+    // The leaves at whose points the peak is taken, one bit each (lane n of a
+    // sample tests leaf n mod LV): those that it is near of, or its Gaussian
+    // reaches, for some sample; of a wide phase those with the centre of an
+    // asymmetric peak, where its width changes.
+    auto near_leaves = [&](const Near &r, bool wide) -> unsigned {
+        if (wide && !ASYM) return 0;
+        const float d = fabsf(r.pk.ch - lmid), far = lhalf + fmaxf(lhalf, r.reach);
+        unsigned long long b = __builtin_amdgcn_ballot_w64(!(d >= (wide ? lhalf : far)));
         b |= b >> 32;
         return (unsigned)(b | (b >> 16));
     };
 
-    // ---------------- forward: this wave's phases (u: the lane's points, relative
-    // to their leaves' middles)
-    float sig[NPP], lsig[LV], nsig = 0.f, u[NPP];
+    // ---------------- forward: this wave's phases
+    float sig[NPP], lsig[LV], nsig = 0.f, u[NPP], ul[MID ? 1 : NPP];
+    // (kept in registers where there are few)
+    auto ul_of = [&](int p) { return MID ? sm.ul[p * LPS + li] : ul[p]; };
 #pragma unroll
     for (int p = 0; p < NPP; ++p) sig[p] = 0.f;
 #pragma unroll
@@ -597,8 +610,10 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
         plan(c0);
         if (c0 == 0) {
 #pragma unroll
-            for (int p = 0; p < NPP; ++p)
-                u[p] = (sm.us[p * LPS + li] - lm[p / PB]) + sm.ul[p * LPS + li];
+            for (int p = 0; p < NPP; ++p) {
+                u[p] = sm.us[p * LPS + li];
+                if (!MID) ul[p] = sm.ul[p * LPS + li];
+            }
         }
         for (int k = c0 + wv; k < min(K, c0 + kPlanPhases); k += NW) {
             prio_left((min(K, c0 + kPlanPhases) - k + NW - 1) / NW);
@@ -621,43 +636,43 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                 far_of(std::false_type{}, a, b, nr, c, iw2r, ka, lo, hi);
             }
             nsig = fmaf(c.z, lo.f0 + hi.f0, nsig);
+            const bool wide = wide_phase(c, iw2r);
+            NearData next = near_data(min(nr.x, b - 1));
             for (int j = nr.x; j < nr.y; ++j) {
-                const Near r = near_peak(j, c, iw2r);
+                const Near r = near_peak(next, c, iw2r);
+                next = near_data(min(j + 1, b - 1));
                 const float aL = c.z * r.I, aG = c.y * r.I;
-                const unsigned near = near_leaves(r);
+                auto at_point = [&](int p) {
+                    bool up;
+                    const float q2 = r.pk.template q2<ASYM>(u[p], ul_of(p), up);
+                    const float tt = fmaf(q2, q2, 1.0f);
+                    sig[p] = fmaf(aL, rcp_f32(tt), sig[p]);
+                    sig[p] = fmaf(aG, exp2_f32(-tt), sig[p]);
+                };
+                if constexpr (!MID) {
+                    // (no branches: bound by latency)
+#pragma unroll
+                    for (int p = 0; p < NPP; ++p) at_point(p);
+                    continue;
+                }
+                const unsigned near = near_leaves(r, wide);
 #pragma unroll
                 for (int l = 0; l < LV; ++l) {
                     if (l >= nl) break;
-                    const float cc = r.pk.in_leaf(lm[l]), cs = cc * r.pk.s;
                     if (near >> l & 1u) {
-                        asm volatile("");
-                        float tt[PB];
+                        asm volatile("");    // (a branch, not selects)
 #pragma unroll
-                        for (int q = 0; q < PB; ++q) {
-                            bool up;
-                            const float q2 =
-                                r.pk.template q2_flat<ASYM>(u[l * PB + q], cc, cs, up);
-                            tt[q] = fmaf(q2, q2, 1.0f);
-                        }
-#pragma unroll
-                        for (int q = 0; q < PB; ++q) {
-                            if (gauss_matters(tt[q])) {
-                                const int p = l * PB + q;
-                                bool up;
-                                const float q2 = r.pk.template q2<ASYM>(
-                                    sm.us[p * LPS + li], sm.ul[p * LPS + li], up);
-                                tt[q] = fmaf(q2, q2, 1.0f);
-                                sig[p] = fmaf(aG, exp2_f32(-tt[q]), sig[p]);
-                            }
-                        }
-#pragma unroll
-                        for (int q = 0; q < PB; ++q)
-                            sig[l * PB + q] = fmaf(aL, rcp_f32(tt[q]), sig[l * PB + q]);
+                        for (int q = 0; q < PB; ++q) at_point(l * PB + q);
                     } else {
                         asm volatile("");
                         bool up;
-                        const float q2 = r.pk.template q2_flat<ASYM>(vl[l], cc, cs, up);
-                        lsig[l] = fmaf(aL, rcp_f32(fmaf(q2, q2, 1.0f)), lsig[l]);
+                        const float q2 = r.pk.template q2_node<ASYM>(vl[l], lm[l], up);
+                        const float tt = fmaf(q2, q2, 1.0f);
+                        lsig[l] = fmaf(aL, rcp_f32(tt), lsig[l]);
+                        if (wide) {
+                            asm volatile("");
+                            lsig[l] = fmaf(aG, exp2_f32(-tt), lsig[l]);
+                        }
                     }
                 }
             }
@@ -823,49 +838,48 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                 if constexpr (ASYM) {
                     acc[9] = rn * hi.f0; acc[10] = rn * hi.f1; acc[11] = rn * hi.f2;
                 }
+                const bool wide = wide_phase(c, iw2r);
+                NearData next = near_data(min(nr.x, b - 1));
                 for (int j = nr.x; j < nr.y; ++j) {
-                    const Near rec = near_peak(j, c, iw2r);
+                    const Near rec = near_peak(next, c, iw2r);
+                    next = near_data(min(j + 1, b - 1));
                     const SecW wl = SecW::of(rec.tw), wh = SecW::of(rec.tw * ka);
                     // the peak's own sums, its intensity applied at the end
-                    const unsigned near = near_leaves(rec);
                     float e[NS];
 #pragma unroll
                     for (int q = 0; q < NS; ++q) e[q] = 0.f;
+                    auto at_point = [&](int p) {
+                        bool up;
+                        const float q2 = rec.pk.template q2<ASYM>(u[p], ul_of(p), up);
+                        const float tt = fmaf(q2, q2, 1.0f);
+                        adj_terms_L<ASYM, SEC>(r[p], q2, tt, up, rec.c, wl, wh, e);
+                        adj_point_G<ASYM, SEC>(AdjPt{r[p], q2, tt, up}, rec.c, wl, wh, e);
+                    };
+                    if constexpr (!MID) {
 #pragma unroll
-                    for (int l = 0; l < LV; ++l) {
-                        if (l >= nl) break;
-                        const float cc = rec.pk.in_leaf(lm[l]), cs = cc * rec.pk.s;
-                        if (near >> l & 1u) {
-                            asm volatile("");
-                            float q2[PB], tt[PB];
-                            bool up[PB];
+                        for (int p = 0; p < NPP; ++p) at_point(p);
+                    } else {
+                        const unsigned near = near_leaves(rec, wide);
 #pragma unroll
-                            for (int q = 0; q < PB; ++q) {
-                                q2[q] = rec.pk.template q2_flat<ASYM>(u[l * PB + q], cc, cs,
-                                                                      up[q]);
-                                tt[q] = fmaf(q2[q], q2[q], 1.0f);
-                            }
+                        for (int l = 0; l < LV; ++l) {
+                            if (l >= nl) break;
+                            if (near >> l & 1u) {
+                                asm volatile("");
 #pragma unroll
-                            for (int q = 0; q < PB; ++q) {
-                                if (gauss_matters(tt[q])) {
-                                    const int p = l * PB + q;
-                                    q2[q] = rec.pk.template q2<ASYM>(
-                                        sm.us[p * LPS + li], sm.ul[p * LPS + li], up[q]);
-                                    tt[q] = fmaf(q2[q], q2[q], 1.0f);
-                                    adj_point_G<ASYM, SEC>(AdjPt{r[p], q2[q], tt[q], up[q]},
-                                                           rec.c, wl, wh, e);
+                                for (int q = 0; q < PB; ++q) at_point(l * PB + q);
+                            } else {
+                                asm volatile("");
+                                bool up;
+                                const float q2 =
+                                    rec.pk.template q2_node<ASYM>(vl[l], lm[l], up);
+                                const float tt = fmaf(q2, q2, 1.0f);
+                                adj_terms_L<ASYM, SEC>(rl[l], q2, tt, up, rec.c, wl, wh, e);
+                                if (wide) {
+                                    asm volatile("");
+                                    adj_point_G<ASYM, SEC>(AdjPt{rl[l], q2, tt, up}, rec.c, wl,
+                                                           wh, e);
                                 }
                             }
-#pragma unroll
-                            for (int q = 0; q < PB; ++q)
-                                adj_terms_L<ASYM, SEC>(r[l * PB + q], q2[q], tt[q], up[q],
-                                                       rec.c, wl, wh, e);
-                        } else {
-                            asm volatile("");
-                            bool up;
-                            const float q2 = rec.pk.template q2_flat<ASYM>(vl[l], cc, cs, up);
-                            adj_terms_L<ASYM, SEC>(rl[l], q2, fmaf(q2, q2, 1.0f), up, rec.c,
-                                                   wl, wh, e);
                         }
                     }
 #pragma unroll

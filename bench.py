@@ -43,7 +43,7 @@ PEAK_HBM_GBS = 8000.0
 VALU_LANE_OPS_PER_S = 5.04e13
 TRANS_LANE_OPS_PER_S = 1.68e13
 # The dominant kernel of the dense step, as rocprofv3 names it.
-DENSE_KERNEL = "void k_dense<true, false, false, 4, 4>"
+DENSE_KERNEL = "void k_dense<true, false, false, 4, 4, false>"
 
 
 def counter_rates(rec, kernel_ms):

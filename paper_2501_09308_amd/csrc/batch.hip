@@ -212,15 +212,20 @@ __global__ __launch_bounds__(kDenseWaves * kWave, 4) void kb_dense(const SlotDev
         const int ng = cut.groups(d.st.S), t = local / ng, grp = local % ng;
         if (t >= d.st.nt) continue;
         const int wide = cut.wide(d.P.N);   // tiles of cut.leaves, then of two
-        if (cut.leaves == 4 && t < wide)
-            dense_tile<true, ASYM, SEC, kDenseWaves, 4, 4>(d.P, d.st, t, t, grp, nullptr,
-                                                           sm.wide);
-        else if (cut.group == 4)
-            dense_tile<true, ASYM, SEC, kDenseWaves, 4, 2>(
-                d.P, d.st, cut.leaves == 4 ? t + wide : t, t, grp, nullptr, sm.four);
-        else
-            dense_tile<true, ASYM, SEC, kDenseWaves, 1, 2>(d.P, d.st, t, t, grp, nullptr,
-                                                           sm.one);
+        const auto tile = [&](auto cut_tag) {
+            constexpr bool CUT = decltype(cut_tag)::value;
+            if (cut.leaves == 4 && t < wide)
+                dense_tile<true, ASYM, SEC, kDenseWaves, 4, 4, CUT>(d.P, d.st, t, t, grp,
+                                                                    nullptr, sm.wide);
+            else if (cut.group == 4)
+                dense_tile<true, ASYM, SEC, kDenseWaves, 4, 2, CUT>(
+                    d.P, d.st, cut.leaves == 4 ? t + wide : t, t, grp, nullptr, sm.four);
+            else
+                dense_tile<true, ASYM, SEC, kDenseWaves, 1, 2, CUT>(d.P, d.st, t, t, grp,
+                                                                    nullptr, sm.one);
+        };
+        if (cut_phases(d.P.K)) tile(std::true_type{});
+        else tile(std::false_type{});
         __syncthreads();
     }
 }

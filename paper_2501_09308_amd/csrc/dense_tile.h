@@ -135,6 +135,7 @@ struct DenseSmem {
     static constexpr bool kMid = SG == 4;   // peaks are taken at the leaves' nodes
     static constexpr int kFarSums = 3 * (ASYM ? 2 : 1);     // per lane and phase
     static constexpr int kFarCap = kFarFloats / (kFarSums * kWave);
+    static_assert(kFarCap >= NW, "a share of a phase has a place");
     static constexpr int kLow = LV * kNodes;     // the leaves' nodes
     float lm[kPts * kNodeStride];         // weights of the leaves' nodes at the points
     float em[kLow * kNodeStride];         // of the tile's at the leaves'
@@ -436,9 +437,11 @@ __device__ __forceinline__ void prio_left(int left) {
     else __builtin_amdgcn_s_setprio(0);
 }
 
+// Whether the waves share each phase's peaks instead of the phases.
+constexpr bool cut_phases(int K) { return 2 * K <= kDenseWaves; }
 // Tile t of those of LV leaves; its sums go to place `out` among the
 // analysis's tiles.
-template <bool GRAD, bool ASYM, bool SEC, int NW, int SG, int LV, typename SM>
+template <bool GRAD, bool ASYM, bool SEC, int NW, int SG, int LV, bool CUT, typename SM>
 __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, int grp,
                            float *f_out, SM &sm) {
     constexpr bool MID = SM::kMid;
@@ -514,37 +517,75 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
 
     const float4 *pk = st.pk + (size_t)s * K;
     const float *pkr = ASYM ? st.pkr + (size_t)s * K : nullptr;
-    const float4 *ps = SEC ? st.psec + (size_t)s * P.T : nullptr;
+    const float4 *sec = SEC ? st.psec + (size_t)s * P.T : nullptr;
     cptr<float> ptt = as_const(P.pt + (size_t)(i0 / P.ref) * P.T);
     cptr<float> ptl = as_const(P.ptl + (size_t)(i0 / P.ref) * P.T);
     cptr<float> inten = as_const(P.inten);
     cptr<int> off = as_const(P.off);
 
-    // near ranges of the phases [c0, c0 + kPlanPhases)
+    // The waves take the phases in turn.  With at most half as many phases as
+    // waves (CUT) each phase is cut in 2^ps shares, which take the place of phases:
+    // share i has the phase i >> ps, and of its near peaks and of those below
+    // and above them a part each.  (One wave a phase: K = 1 of 200 peaks, N =
+    // 3501, S = 64 took 75 us, K = 2 of 500 137 us; shares of consecutive peaks,
+    // of which one has the near ones, K = 2 of 5000 801 us for 260.  A template
+    // parameter: the shares' ranges cost the scalar registers of 200 x 60 peaks,
+    // S = 128 10 of 699 us.)
+    int ps = 0;
+    if (CUT)
+        while (K << (ps + 1) <= NW) ++ps;
+    const int KS = K << ps;
+    static_assert(3 * NW <= kPlanPhases, "ranges of the shares");
+    // near ranges of the shares [c0, c0 + kPlanPhases); those of cut phases are
+    // followed by the ranges below and above
     auto plan = [&](int c0) {
         const int kk = tid - NC;
-        if (kk >= 0 && c0 + kk < K)
-            sm.nr[kk] = dense_near<SEC>(P, st, t, LV, c0 + kk, s0, ns, mh);
+        if (kk >= 0 && c0 + kk < KS) {
+            const int k = (c0 + kk) >> ps;
+            const int2 r = dense_near<SEC>(P, st, t, LV, k, s0, ns, mh);
+            if (CUT) {
+                const auto part = [&](int j0, int j1) {
+                    const long long m = max(j1 - j0, 0), q = kk & ((1 << ps) - 1);
+                    return make_int2(j0 + (int)(m * q >> ps), j0 + (int)(m * (q + 1) >> ps));
+                };
+                sm.nr[kk] = part(r.x, r.y);
+                sm.nr[NW + kk] = part(P.off[k], r.x);
+                sm.nr[2 * NW + kk] = part(r.y, P.off[k + 1]);
+            } else {
+                sm.nr[kk] = r;
+            }
+        }
         __syncthreads();
     };
-    auto near_range = [&](int k) {
-        const int2 r = sm.nr[k % kPlanPhases];
+    auto range = [&](int i) {
+        const int2 r = sm.nr[i % kPlanPhases];
         return make_int2(__builtin_amdgcn_readfirstlane(r.x),
                          __builtin_amdgcn_readfirstlane(r.y));
     };
-    // the far sums of phase k: lo of the peaks above the tile (its points
+    // peaks of share i of a phase with the peaks [a, b)
+    struct Peaks {
+        int2 near, below, above;
+    };
+    auto peaks_of = [&](int i, int a, int b) {
+        const int2 nr = range(i);
+        if (!CUT) return Peaks{nr, make_int2(a, nr.x), make_int2(nr.y, b)};
+        return Peaks{nr, range(NW + i), range(2 * NW + i)};
+    };
+    // the far sums of a phase: lo of the peaks above the tile (its points
     // see their low side), hi of those below
-    auto far_of = [&](auto grad, int a, int b, int2 nr, float4 c, float iw2r, float ka,
+    auto far_of = [&](auto grad, const Peaks &pe, float4 c, float iw2r, float ka,
                       FarSums &lo, FarSums &hi) {
         constexpr bool G = decltype(grad)::value;
         const float um = vn - c.w;
         if (ASYM) {
-            hi = far_sums<SLOTS, G, SEC>(ptt, inten, ps, a, nr.x, slot, um * iw2r, iw2r, ka);
-            lo = far_sums<SLOTS, G, SEC>(ptt, inten, ps, nr.y, b, slot, um * c.x, c.x, 1.f);
+            hi = far_sums<SLOTS, G, SEC>(ptt, inten, sec, pe.below.x, pe.below.y, slot, um * iw2r,
+                                         iw2r, ka);
+            lo = far_sums<SLOTS, G, SEC>(ptt, inten, sec, pe.above.x, pe.above.y, slot, um * c.x, c.x,
+                                         1.f);
         } else {
-            const FarSums x = far_sums<SLOTS, G, SEC>(ptt, inten, ps, a, nr.x, slot,
+            const FarSums x = far_sums<SLOTS, G, SEC>(ptt, inten, sec, pe.below.x, pe.below.y, slot,
                                                       um * c.x, c.x, 1.f);
-            const FarSums y = far_sums<SLOTS, G, SEC>(ptt, inten, ps, nr.y, b, slot,
+            const FarSums y = far_sums<SLOTS, G, SEC>(ptt, inten, sec, pe.above.x, pe.above.y, slot,
                                                       um * c.x, c.x, 1.f);
             lo = FarSums{x.f0 + y.f0, x.f1 + y.f1, x.f2 + y.f2};
             hi = FarSums{0.f, 0.f, 0.f};
@@ -564,7 +605,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
         NearData d{};
         d.pt = ptt[j];
         d.ptl = ptl[j];
-        if (SEC) d.rec = ps[j];
+        if (SEC) d.rec = sec[j];
         else d.I = inten[j];
         return d;
     };
@@ -605,7 +646,7 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
     for (int p = 0; p < NPP; ++p) sig[p] = 0.f;
 #pragma unroll
     for (int l = 0; l < LV; ++l) lsig[l] = 0.f;
-    for (int c0 = 0; c0 < K; c0 += kPlanPhases) {
+    for (int c0 = 0; c0 < KS; c0 += kPlanPhases) {
         if (c0 > 0) __syncthreads();
         plan(c0);
         if (c0 == 0) {
@@ -615,30 +656,30 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                 if (!MID) ul[p] = sm.ul[p * LPS + li];
             }
         }
-        for (int k = c0 + wv; k < min(K, c0 + kPlanPhases); k += NW) {
-            prio_left((min(K, c0 + kPlanPhases) - k + NW - 1) / NW);
-            const int a = off[k], b = off[k + 1];
+        for (int i = c0 + wv; i < min(KS, c0 + kPlanPhases); i += NW) {
+            prio_left((min(KS, c0 + kPlanPhases) - i + NW - 1) / NW);
+            const int k = i >> ps, a = off[k], b = off[k + 1];
             if (a >= b) continue;
-            const int2 nr = near_range(k);
+            const Peaks pe = peaks_of(i, a, b);
             const float4 c = pk[k];
             const float iw2r = ASYM ? pkr[k] : c.x;
             const float ka = ASYM && SEC ? c.x / iw2r : 1.f;   // alpha
             FarSums lo, hi;
-            if (GRAD && k < kCap) {
-                far_of(std::true_type{}, a, b, nr, c, iw2r, ka, lo, hi);
-                float (*dst)[kWave] = sm.far[k];
+            if (GRAD && i < kCap) {
+                far_of(std::true_type{}, pe, c, iw2r, ka, lo, hi);
+                float (*dst)[kWave] = sm.far[i];
                 constexpr int H = SM::kFarSums / 2;   // (ASYM: the high side)
                 dst[0][lane] = lo.f0; dst[1][lane] = lo.f1; dst[2][lane] = lo.f2;
                 if (ASYM) {
                     dst[H][lane] = hi.f0; dst[H + 1][lane] = hi.f1; dst[H + 2][lane] = hi.f2;
                 }
             } else {
-                far_of(std::false_type{}, a, b, nr, c, iw2r, ka, lo, hi);
+                far_of(std::false_type{}, pe, c, iw2r, ka, lo, hi);
             }
             nsig = fmaf(c.z, lo.f0 + hi.f0, nsig);
             const bool wide = wide_phase(c, iw2r);
-            NearData next = near_data(min(nr.x, b - 1));
-            for (int j = nr.x; j < nr.y; ++j) {
+            NearData next = near_data(min(pe.near.x, b - 1));
+            for (int j = pe.near.x; j < pe.near.y; ++j) {
                 const Near r = near_peak(next, c, iw2r);
                 next = near_data(min(j + 1, b - 1));
                 const float aL = c.z * r.I, aG = c.y * r.I;
@@ -809,38 +850,38 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
     for (int p = 0; p < NPP; ++p) r[p] = sm.rres[sl][p * LPS + li];
 #pragma unroll
     for (int l = 0; l < LV; ++l) rl[l] = MID ? (float)sm.low[sl][l * kNodes + n] : 0.f;
-    for (int c0 = 0; c0 < K; c0 += kPlanPhases) {
+    for (int c0 = 0; c0 < KS; c0 += kPlanPhases) {
         if (K > kPlanPhases) {          // (otherwise the ranges are still there)
             __syncthreads();
             plan(c0);
         }
-        for (int k = c0 + wv; k < min(K, c0 + kPlanPhases); k += NW) {
-            prio_left((min(K, c0 + kPlanPhases) - k + NW - 1) / NW);
-            const int a = off[k], b = off[k + 1];
+        for (int i = c0 + wv; i < min(KS, c0 + kPlanPhases); i += NW) {
+            prio_left((min(KS, c0 + kPlanPhases) - i + NW - 1) / NW);
+            const int k = i >> ps, a = off[k], b = off[k + 1];
             float acc[NS];
 #pragma unroll
             for (int q = 0; q < NS; ++q) acc[q] = 0.f;
             if (a < b) {
-                const int2 nr = near_range(k);
+                const Peaks pe = peaks_of(i, a, b);
                 const float4 c = pk[k];
                 const float iw2r = ASYM ? pkr[k] : c.x;
                 const float ka = ASYM && SEC ? c.x / iw2r : 1.f;
                 FarSums lo, hi{0.f, 0.f, 0.f};
-                if (k < kCap) {
-                    float (*src)[kWave] = sm.far[k];
+                if (i < kCap) {
+                    float (*src)[kWave] = sm.far[i];
                     constexpr int H = SM::kFarSums / 2;
                     lo = FarSums{src[0][lane], src[1][lane], src[2][lane]};
                     if (ASYM) hi = FarSums{src[H][lane], src[H + 1][lane], src[H + 2][lane]};
                 } else {
-                    far_of(std::true_type{}, a, b, nr, c, iw2r, ka, lo, hi);
+                    far_of(std::true_type{}, pe, c, iw2r, ka, lo, hi);
                 }
                 acc[3] = rn * lo.f0; acc[4] = rn * lo.f1; acc[5] = rn * lo.f2;
                 if constexpr (ASYM) {
                     acc[9] = rn * hi.f0; acc[10] = rn * hi.f1; acc[11] = rn * hi.f2;
                 }
                 const bool wide = wide_phase(c, iw2r);
-                NearData next = near_data(min(nr.x, b - 1));
-                for (int j = nr.x; j < nr.y; ++j) {
+                NearData next = near_data(min(pe.near.x, b - 1));
+                for (int j = pe.near.x; j < pe.near.y; ++j) {
                     const Near rec = near_peak(next, c, iw2r);
                     next = near_data(min(j + 1, b - 1));
                     const SecW wl = SecW::of(rec.tw), wh = SecW::of(rec.tw * ka);
@@ -892,8 +933,21 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
             float v = acc[0];
 #pragma unroll
             for (int q = 1; q < NS; ++q) v = n == q ? acc[q] : v;
-            if (n < NS && slot == SLOTS - 1 && sl < ns)
-                st.part[(((size_t)out * K + k) * S + s) * NS + n] = v;
+            if (n < NS && slot == SLOTS - 1 && sl < ns) {
+                if (CUT) sm.nod[i][sl * NS + n] = v;
+                else st.part[(((size_t)out * K + k) * S + s) * NS + n] = v;
+            }
+        }
+    }
+    if (CUT) {
+        // the phases' sums over their shares
+        static_assert(SG * NS <= kWave + 1, "a share's sums fit its row");
+        __syncthreads();
+        for (int i = tid; i < K * ns * NS; i += NT) {
+            const int k = i / (ns * NS), q = i % (ns * NS);
+            double v = 0.0;
+            for (int w = k << ps; w < (k + 1) << ps; ++w) v += (double)sm.nod[w][q];
+            st.part[(((size_t)out * K + k) * S + s0) * NS + q] = (float)v;
         }
     }
 }

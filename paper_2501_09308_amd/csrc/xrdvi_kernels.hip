@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kCandThreads) void k_cand(ProbDev P, StepDev st) {
 // (tiles, groups), blocks ordered by XCD (the samples of a tile share its
 // positions and counts in one L2, and their adjoint partials, adjacent in
 // memory, merge there before write-back).  Four waves per SIMD (128 VGPRs).
-template <bool GRAD, bool ASYM, bool SEC, int SG, int LV>
+template <bool GRAD, bool ASYM, bool SEC, int SG, int LV, bool CUT>
 __global__ __launch_bounds__(kDenseWaves * kWave, 4) void k_dense(ProbDev P, StepDev st,
                                                                   float *f_out, int wide) {
     if constexpr (LV == 4) {
@@ -142,17 +142,17 @@ __global__ __launch_bounds__(kDenseWaves * kWave, 4) void k_dense(ProbDev P, Ste
         const int ng = (st.S + SG - 1) / SG, b = blockIdx.x + blockIdx.y * gridDim.x;
         if (b < wide * ng) {
             const int2 tg = xcd_tile_sample(b, wide, ng);
-            dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, 4>(P, st, tg.x, tg.x, tg.y, f_out,
+            dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, 4, CUT>(P, st, tg.x, tg.x, tg.y, f_out,
                                                             sm.wide);
         } else {
             const int2 tg = xcd_tile_sample(b - wide * ng, st.nt - wide, ng);
-            dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, 2>(P, st, 2 * wide + tg.x,
+            dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, 2, CUT>(P, st, 2 * wide + tg.x,
                                                             wide + tg.x, tg.y, f_out, sm.two);
         }
     } else {
         __shared__ DenseSmem<kDenseWaves, SG, LV, ASYM, SEC> sm;
         const int2 tg = xcd_tile_sample(st.nt, (st.S + SG - 1) / SG);
-        dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, LV>(P, st, tg.x, tg.x, tg.y, f_out, sm);
+        dense_tile<GRAD, ASYM, SEC, kDenseWaves, SG, LV, CUT>(P, st, tg.x, tg.x, tg.y, f_out, sm);
     }
 }
 
@@ -326,13 +326,18 @@ static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
         }
     } else {
         const DenseCut cut = dense_cut(P.N, st.S);
-        auto run = [&](auto sg_tag, auto lv_tag) {
+        auto run_cut = [&](auto sg_tag, auto lv_tag, auto cut_tag) {
             constexpr int SG = decltype(sg_tag)::value, LV = decltype(lv_tag)::value;
+            constexpr bool CUT = decltype(cut_tag)::value;
             constexpr int nt = kDenseWaves * kWave;
             const int w = cut.wide(P.N);
             const dim3 g(st.nt, (st.S + SG - 1) / SG);
-            if (grad) k_dense<true, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, st, f_out, w);
-            else k_dense<false, ASYM, SEC, SG, LV><<<g, nt, 0, stream>>>(P, st, f_out, w);
+            if (grad) k_dense<true, ASYM, SEC, SG, LV, CUT><<<g, nt, 0, stream>>>(P, st, f_out, w);
+            else k_dense<false, ASYM, SEC, SG, LV, CUT><<<g, nt, 0, stream>>>(P, st, f_out, w);
+        };
+        auto run = [&](auto sg_tag, auto lv_tag) {
+            if (cut_phases(P.K)) run_cut(sg_tag, lv_tag, std::true_type{});
+            else run_cut(sg_tag, lv_tag, std::false_type{});
         };
         const std::integral_constant<int, 1> one;
         const std::integral_constant<int, 2> two;

@@ -515,8 +515,8 @@ __device__ inline void cand_elem(const ProbDev &P, const StepDev &st, int t,
 // The peaks of phase k that the forward stages for (tile t, sample s): [ja,
 // jb), whose windows reach the tile, and [ga, gb) of them, whose Gaussian does
 // (constant width).  Counted over the tile's candidates in FP32 tile-relative
-// positions with bounds widened far beyond their rounding: a few peaks more
-// than the exact ranges (each record carries its exact window), for a quarter
+// positions with bounds widened far beyond the rounding of their terms: a few
+// peaks more than the exact ranges (each record carries its exact window), for a quarter
 // of the work of FP64 predicates.  Candidates past the fourth, whose positions
 // are not kept beside the range, are read four at a time.
 __device__ __forceinline__ int4 cand_ranges(const ProbDev &P, const StepDev &st,
@@ -529,9 +529,10 @@ __device__ __forceinline__ int4 cand_ranges(const ProbDev &P, const StepDev &st,
     const double al = P.D == 5 ? ph[4 * P.K + k] : 1.0;
     const float a = (float)(xa - xref - mu), b = (float)(xb - xref - mu);
     const float c = (float)(P.cutoff * w), g = (float)(kGaussReach * w), alf = (float)al;
-    auto wider = [](float v, float sign) { return v + sign * 4e-6f * (1.f + fabsf(v)); };
-    const float wl = wider(a - c * alf, -1.f), wh = wider(b + c, 1.f);
-    const float gl = wider(a - g * alf, -1.f), gh = wider(b + g, 1.f);
+    const float wl = (a - c * alf) - 4e-6f * (1.f + fabsf(a) + c * alf);
+    const float wh = (b + c) + 4e-6f * (1.f + fabsf(b) + c);
+    const float gl = (a - g * alf) - 4e-6f * (1.f + fabsf(a) + g * alf);
+    const float gh = (b + g) + 4e-6f * (1.f + fabsf(b) + g);
     int ja = 0, jb = 0, ga = 0, gb = 0;
     const int n = ab.y - ab.x;
     auto count = [&](int q, float p) {

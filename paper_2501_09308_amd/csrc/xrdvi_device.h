@@ -445,6 +445,11 @@ __device__ __forceinline__ int tab_guess(const ProbDev &P, int k, double v,
 // reads them with coalesced loads instead of searching the phase with
 // scattered ones.
 constexpr int kCandThreads = 256;
+// Candidates (or peaks scanned under the sec law) up to which a phase's ranges
+// are counted peak by peak; beyond, binary searches of all ends in step.  20
+// phases of 300 peaks of 2 deg, windows of 32 deg, N = 3501, S = 32: forward 212
+// us counted, 143 searched; 4 of 2000 under the sec law 794 and 292.
+constexpr int kCandCount = 16;
 
 // The extremes of each phase over the step's samples: (min mu, max mu,
 // max w, max w alpha) to st.cext[k].  Block of kCandThreads threads: 64
@@ -516,9 +521,10 @@ __device__ inline void cand_elem(const ProbDev &P, const StepDev &st, int t,
 // jb), whose windows reach the tile, and [ga, gb) of them, whose Gaussian does
 // (constant width).  Counted over the tile's candidates in FP32 tile-relative
 // positions with bounds widened far beyond the rounding of their terms: a few
-// peaks more than the exact ranges (each record carries its exact window), for a quarter
-// of the work of FP64 predicates.  Candidates past the fourth, whose positions
-// are not kept beside the range, are read four at a time.
+// peaks more than the exact ranges (each record carries its exact window), for a
+// quarter of the work of FP64 predicates.  Candidates past the fourth, whose
+// positions are not kept beside the range, are read four at a time, and more
+// than kCandCount of them searched.
 __device__ __forceinline__ int4 cand_ranges(const ProbDev &P, const StepDev &st,
                                             const double *ph, int t, int k,
                                             double xa, double xb, double xref) {
@@ -544,12 +550,24 @@ __device__ __forceinline__ int4 cand_ranges(const ProbDev &P, const StepDev &st,
     };
     count(0, cp.x); count(1, cp.y); count(2, cp.z); count(3, cp.w);
     const float *pt = P.pt + (size_t)t * P.T + ab.x;
-    for (int q0 = 4; q0 < n; q0 += 4) {
-        float p[4];
+    if (n <= kCandCount) {
+        for (int q0 = 4; q0 < n; q0 += 4) {
+            float p[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) p[q] = pt[min(q0 + q, n - 1)];
+            for (int q = 0; q < 4; ++q) p[q] = pt[min(q0 + q, n - 1)];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) count(q0 + q, p[q]);
+            for (int q = 0; q < 4; ++q) count(q0 + q, p[q]);
+        }
+    } else {
+        ja = jb = ga = gb = 0;
+        for (int step = 1 << (31 - __clz(n)); step > 0; step >>= 1) {
+            auto probe = [&](int j) { return pt[min(j + step, n) - 1]; };
+            const float pja = probe(ja), pjb = probe(jb), pga = probe(ga), pgb = probe(gb);
+            if (ja + step <= n && pja < wl) ja += step;
+            if (jb + step <= n && pjb <= wh) jb += step;
+            if (ga + step <= n && pga < gl) ga += step;
+            if (gb + step <= n && pgb <= gh) gb += step;
+        }
     }
     jb = max(jb, ja);
     ga = min(max(ga, ja), jb);
@@ -586,7 +604,12 @@ __device__ __forceinline__ int4 sec_ranges(const ProbDev &P, const double *ph, i
     const int ja = probe_settle<4>(P.pos, a, b, pr.j0, probe_count(pr, a, b, ge), ge);
     int jb = ja, ga = ja, gb = ja;
     const double rw = kGaussReach * w;
-    for (bool past = false; jb < b && !past;) {
+    // whether the Gaussian ends below the tile, and begins not above it (both
+    // true first, then false)
+    auto ends_below = [&](double p, float c) { return p + mu + rw / c * al < xa - 1e-5; };
+    auto begins = [&](double p, float c) { return p + mu - rw / c <= xb + 1e-5; };
+    bool past = false;
+    for (const int stop = min(b, ja + kCandCount); jb < stop && !past;) {
         int lo[4];
         float c[4];
         double p[4];
@@ -602,12 +625,28 @@ __device__ __forceinline__ int4 sec_ranges(const ProbDev &P, const double *ph, i
         for (int q = 0; q < 4; ++q) {
             past = past || j0 + q >= b || lo[q] >= i1;
             if (!past) {
-                const double rho = p[q] + mu, g = rw / c[q];
-                ga += rho + g * al < xa - 1e-5;      // (both monotone)
-                gb += rho - g <= xb + 1e-5;
+                ga += ends_below(p[q], c[q]);
+                gb += begins(p[q], c[q]);
                 jb = j0 + q + 1;
             }
         }
+    }
+    if (!past && jb < b) {
+        // all of them so far reach the tile: the counts go on from here
+        const int j0 = jb, n = b - j0;
+        int nj = 0, na = 0, nb = 0;
+        for (int step = 1 << (31 - __clz(n)); step > 0; step >>= 1) {
+            auto at = [&](int m) { return j0 + min(m + step, n) - 1; };
+            const int lj = wlo[at(nj)];
+            const double pa = P.pos[at(na)], pb = P.pos[at(nb)];
+            const float fa = ps[at(na)].x, fb = ps[at(nb)].x;
+            if (nj + step <= n && lj < i1) nj += step;
+            if (na + step <= n && ends_below(pa, fa)) na += step;
+            if (nb + step <= n && begins(pb, fb)) nb += step;
+        }
+        jb = j0 + nj;
+        if (ga == j0) ga += min(na, nj);
+        if (gb == j0) gb += min(nb, nj);
     }
     return make_int4(ja, ga, max(gb, ga), jb);
 }

@@ -1377,6 +1377,9 @@ constexpr int kAdjPeaks = 4;
 constexpr int kAdjLanes = kWave / kAdjPeaks;
 // Chunks of kAdjLanes points whose loads are issued together.
 constexpr int kAdjChunks = 4;
+// Points in every window of a group from which asymmetric peaks take several
+// chunks at once.
+constexpr int kAdjLong = 256;
 
 // Windows of at most this many FWHM each side (symmetric peaks of constant
 // width on a uniform grid): the adjoint forms q2 = 2 (x - rho) / w in FP32.
@@ -1526,13 +1529,15 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
                 for (; c < span; c += kAdjChunks * kAdjLanes) points(std::true_type{}, c);
             } else {
                 // ascending points: the chunks wholly below the four centres,
-                // those with points on both sides, those wholly above, the
-                // loads two chunks ahead (a lane past its window only adds 0)
+                // those with points on both sides, those wholly above; the loads
+                // two chunks ahead (a lane past its window only adds 0)
                 int c = 0;
                 float r0, r1, r2;
                 double x0 = 0.0, x1 = 0.0, x2 = 0.0;
-                load(0, r0, x0);
-                load(kAdjLanes, r1, x1);
+                auto ahead = [&]() {
+                    load(c, r0, x0);
+                    load(c + kAdjLanes, r1, x1);
+                };
                 auto run = [&](auto side) {
                     constexpr int SIDE = decltype(side)::value;
                     for (; c < span; c += kAdjLanes) {
@@ -1548,8 +1553,65 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
                         x1 = x2;
                     }
                 };
+                // long windows: kAdjChunks chunks at once while all windows have
+                // them, on one side of every centre, their Gaussians without a
+                // branch between them where they matter in each (one chunk at a
+                // time waits on itself where few waves run: 4 phases of 100 peaks
+                // of 2 deg, windows of 32 deg, N = 3501, S = 32 155 us, now 131)
+                const bool lng = full >= kAdjLong;
+                auto runs = [&](auto side) {
+                    constexpr int SIDE = decltype(side)::value;
+                    for (; c + kAdjChunks * kAdjLanes <= full; c += kAdjChunks * kAdjLanes) {
+                        float rv[kAdjChunks], dv[kAdjChunks];
+                        double xv[kAdjChunks];
+#pragma unroll
+                        for (int u = 0; u < kAdjChunks; ++u)
+                            load(c + u * kAdjLanes, rv[u], xv[u]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        const double cdx0 = cdx;
+#pragma unroll
+                        for (int u = 0; u < kAdjChunks; ++u) {
+                            dv[u] = offset(xv[u]);
+                            cdx += step;
+                        }
+                        if (SIDE == kBelow &&
+                            __builtin_amdgcn_ballot_w64(dv[kAdjChunks - 1] >= 0.f) != 0) {
+                            cdx = cdx0;
+                            break;
+                        }
+                        AdjPt pt[kAdjChunks];
+                        uint64_t g[kAdjChunks];
+                        bool every = true;
+#pragma unroll
+                        for (int u = 0; u < kAdjChunks; ++u) {
+                            pt[u] = adj_point_L<ASYM, SEC, SIDE>(rv[u] * I, dv[u], qs, qsr, cq,
+                                                                 wl, wh, acc);
+                            g[u] = __builtin_amdgcn_ballot_w64(pt[u].tt <= kGaussTT);
+                            every = every && g[u] != 0;
+                        }
+                        if (every) {
+                            asm volatile("");
+#pragma unroll
+                            for (int u = 0; u < kAdjChunks; ++u)
+                                adj_point_G<ASYM, SEC, SIDE>(pt[u], cq, wl, wh, acc);
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < kAdjChunks; ++u)
+                                if (g[u] != 0) {
+                                    asm volatile("");
+                                    adj_point_G<ASYM, SEC, SIDE>(pt[u], cq, wl, wh, acc);
+                                }
+                        }
+                    }
+                };
+                if (lng) runs(std::integral_constant<int, kBelow>{});
+                ahead();
                 run(std::integral_constant<int, kBelow>{});
                 run(std::integral_constant<int, kBoth>{});
+                if (lng) {
+                    runs(std::integral_constant<int, kAbove>{});
+                    ahead();
+                }
                 run(std::integral_constant<int, kAbove>{});
             }
         };

@@ -93,14 +93,15 @@ struct SepRow {
 };
 
 // A block's rows: in registers (R > 0; the counts too if Y), else in the
-// caller's scratch.  y counts, di inverse pivots, l = L_{i,i-1}, u = the
-// forward sweep's values; hit: y_i > z_i of the last solution.
-template <int R, bool Y>
+// caller's scratch, row i of all T threads together.  y counts, di inverse
+// pivots, l = L_{i,i-1}, u = the forward sweep's values and then z; hit: y_i >
+// z_i of the last solution.
+template <int T, int R, bool Y>
 struct Rows {
     double y_[Y ? R : 1], di_[R], l_[R], u_[R];
     const double *yg_;
     unsigned hit_ = 0;
-    __device__ void bind(const double *yg, double *, double *, double *, double *, int n) {
+    __device__ void bind(const double *yg, double *, size_t, int n) {
         yg_ = yg;
         if (Y) {
 #pragma unroll
@@ -112,21 +113,27 @@ struct Rows {
     __device__ double &l(int i) { return l_[i]; }
     __device__ double &u(int i) { return u_[i]; }
     __device__ bool hit(int i) const { return hit_ >> i & 1u; }
-    __device__ void set_hit(int i, bool h) { hit_ = (hit_ & ~(1u << i)) | (unsigned)h << i; }
-};
-template <bool Y>
-struct Rows<0, Y> {
-    const double *y_;
-    double *di_, *l_, *u_, *h_;
-    __device__ void bind(const double *yg, double *d, double *l, double *u, double *h, int) {
-        y_ = yg; di_ = d; l_ = l; u_ = u; h_ = h;
+    __device__ void set_z(int i, double z) {
+        hit_ = (hit_ & ~(1u << i)) | (unsigned)(y(i) > z) << i;
     }
-    __device__ double y(int i) const { return y_[i]; }
-    __device__ double &di(int i) { return di_[i]; }
-    __device__ double &l(int i) { return l_[i]; }
-    __device__ double &u(int i) { return u_[i]; }
-    __device__ bool hit(int i) const { return h_[i] != 0.0; }
-    __device__ void set_hit(int i, bool h) { h_[i] = h ? 1.0 : 0.0; }
+};
+template <int T, bool Y>
+struct Rows<T, 0, Y> {
+    // (T n of the longest block <= N - T + 2: it fits the spectrum's share)
+    double *y_, *di_, *l_, *u_;
+    __device__ void bind(const double *yg, double *scratch, size_t bn, int n) {
+        y_ = scratch + threadIdx.x;
+        di_ = y_ + bn;
+        l_ = di_ + bn;
+        u_ = l_ + bn;
+        for (int i = 0; i < n; ++i) y_[i * T] = yg[i];
+    }
+    __device__ double y(int i) const { return y_[i * T]; }
+    __device__ double &di(int i) { return di_[i * T]; }
+    __device__ double &l(int i) { return l_[i * T]; }
+    __device__ double &u(int i) { return u_[i * T]; }
+    __device__ bool hit(int i) const { return y_[i * T] > u_[i * T]; }
+    __device__ void set_z(int i, double z) { u_[i * T] = z; }
 };
 
 // f(i) for i = 0 .. n - 1 (or down), unrolled when the rows are in registers.
@@ -152,10 +159,10 @@ __device__ __forceinline__ void each_row_down(int n, F f) {
 }
 
 // One block of T threads per spectrum, n_iter reweighting iterations; scratch
-// arrays [B][N] (R = 0 only): h, di, l.
+// (R = 0 only): four arrays [B][N].
 template <int T, int R, bool Y>
-__global__ __launch_bounds__(T) void k_asls(int N, const double *__restrict__ y, double *h,
-                                            double *di, double *l, double *z, double lambda,
+__global__ __launch_bounds__(T) void k_asls(int N, const double *__restrict__ y,
+                                            double *scratch, double *z, double lambda,
                                             double p, int n_iter) {
     __shared__ BlockLow low_s[T];
     __shared__ SepRow sep_s[2][T];
@@ -174,9 +181,8 @@ __global__ __launch_bounds__(T) void k_asls(int N, const double *__restrict__ y,
     const int r0 = t * (base + 2) + min(t, extra), n = t < P ? base + (t < extra ? 1 : 0) : 0;
     const int e = r0 + n;              // the separator after this block: rows e, e + 1
     const bool sep = t < M;
-    Rows<R, Y> rows;
-    if (n > 0)
-        rows.bind(yb + r0, di + o + r0, l + o + r0, zb + r0, h + o + r0, n);
+    Rows<T, R, Y> rows;
+    if (n > 0) rows.bind(yb + r0, scratch + o, (size_t)gridDim.x * N, n);
     const double ys0 = sep ? yb[e] : 0.0, ys1 = sep ? yb[e + 1] : 0.0;
     bool hs0 = false, hs1 = false;
     // couplings of the block's first two rows to the separator before it, of
@@ -200,7 +206,7 @@ __global__ __launch_bounds__(T) void k_asls(int N, const double *__restrict__ y,
             double2 xf = make_double2(0.0, 0.0);
             each_row<R>(n, [&](int i) {
                 const int g = r0 + i;
-                const double w = weight(rows.hit(i));
+                const double w = weight(it > 0 && rows.hit(i));
                 // L2 d_{i-2} = lambda, L1 d_{i-1} = b
                 const double b = i >= 1 ? lambda * dtd1(g - 1, N) - (i >= 2 ? lambda * lm1 : 0.0)
                                         : 0.0;
@@ -281,7 +287,7 @@ __global__ __launch_bounds__(T) void k_asls(int N, const double *__restrict__ y,
             if (sep) fr = mulv(CR, zs);
             double um1 = 0.0, um2 = 0.0, im1 = 0.0, im2 = 0.0;
             each_row<R>(n, [&](int i) {
-                double r = weight(rows.hit(i)) * rows.y(i);
+                double r = weight(it > 0 && rows.hit(i)) * rows.y(i);
                 if (i == 0) r -= fl.x;
                 if (i == 1) r -= fl.y;
                 if (i == n - 2) r -= fr.x;
@@ -297,7 +303,7 @@ __global__ __launch_bounds__(T) void k_asls(int N, const double *__restrict__ y,
                                   (i + 1 < n ? lp1 * zp1 : 0.0);
                 lp1 = rows.l(i);
                 zp2 = zp1; zp1 = zi;
-                rows.set_hit(i, rows.y(i) > zi);
+                rows.set_z(i, zi);
                 if (last) zb[r0 + i] = zi;
             });
         }
@@ -333,25 +339,25 @@ extern "C" int xrdvi_background(xrdvi_ctx *ctx, int32_t B, int32_t N,
             set_error("background: lambda must be >= 0 and p in (0, 0.5)");
             return XRDVI_EINVAL;
         }
-        const size_t bn = (size_t)B * N;
-        double *w = static_cast<double *>(scratch);
+        double *sc = static_cast<double *>(scratch);
         hipStream_t s = static_cast<hipStream_t>(stream);
         // Rows in registers while blocks are short enough for them.  512 threads
-        // have half the registers each: they hold fewer rows, or read the
-        // counts again (15 reweightings: 8000 points 187 us with 18 rows and
-        // 277 without the counts, 12 000 points 355 us without the counts and
-        // 1340 with the rows in memory).
+        // have half the registers each: they hold fewer rows, or read the counts
+        // again (15 reweightings: 8000 points 187 us with 18 rows and 277 without
+        // the counts, 12 000 points 351 us without the counts and 384 with the rows
+        // in memory; there 30 000 points take 877, and with each block's rows one
+        // after another, which 512 threads cannot keep in a cache, 2700, and 256
+        // such spectra more than 64 threads took).
         const auto fits = [N](int threads, int r) { return N <= threads * (r + 2) - 2; };
         constexpr int R1 = 24, R2 = 18;
-        double *di = w + bn, *l = w + 2 * bn;
         if (fits(256, R1))
-            k_asls<256, R1, true><<<B, 256, 0, s>>>(N, y, w, di, l, bg_out, lambda, p, n_iter);
+            k_asls<256, R1, true><<<B, 256, 0, s>>>(N, y, sc, bg_out, lambda, p, n_iter);
         else if (fits(512, R2))
-            k_asls<512, R2, true><<<B, 512, 0, s>>>(N, y, w, di, l, bg_out, lambda, p, n_iter);
+            k_asls<512, R2, true><<<B, 512, 0, s>>>(N, y, sc, bg_out, lambda, p, n_iter);
         else if (fits(512, R1))
-            k_asls<512, R1, false><<<B, 512, 0, s>>>(N, y, w, di, l, bg_out, lambda, p, n_iter);
+            k_asls<512, R1, false><<<B, 512, 0, s>>>(N, y, sc, bg_out, lambda, p, n_iter);
         else
-            k_asls<512, 0, false><<<B, 512, 0, s>>>(N, y, w, di, l, bg_out, lambda, p, n_iter);
+            k_asls<512, 0, false><<<B, 512, 0, s>>>(N, y, sc, bg_out, lambda, p, n_iter);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) {
             set_error(std::string("background: ") + hipGetErrorString(e));

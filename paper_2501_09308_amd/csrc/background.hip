@@ -341,6 +341,10 @@ extern "C" int xrdvi_background(xrdvi_ctx *ctx, int32_t B, int32_t N,
         }
         double *sc = static_cast<double *>(scratch);
         hipStream_t s = static_cast<hipStream_t>(stream);
+        // A wave where that has as many threads as the spectrum has blocks (of 8
+        // or 9 rows from 48 points on): more spectra then fit a CU (4096 of 100
+        // points 140 us, with 256 threads 1053, as one wave with serial separators
+        // 668).
         // Rows in registers while blocks are short enough for them.  512 threads
         // have half the registers each: they hold fewer rows, or read the counts
         // again (15 reweightings: 8000 points 187 us with 18 rows and 277 without
@@ -350,7 +354,12 @@ extern "C" int xrdvi_background(xrdvi_ctx *ctx, int32_t B, int32_t N,
         // such spectra more than 64 threads took).
         const auto fits = [N](int threads, int r) { return N <= threads * (r + 2) - 2; };
         constexpr int R1 = 24, R2 = 18;
-        if (fits(256, R1))
+        const int blocks = (N + 2) / (kMinRows + 2);
+        if (blocks <= 64 && blocks >= 5)
+            k_asls<64, 10, true><<<B, 64, 0, s>>>(N, y, sc, bg_out, lambda, p, n_iter);
+        else if (blocks < 5)
+            k_asls<64, R2, true><<<B, 64, 0, s>>>(N, y, sc, bg_out, lambda, p, n_iter);
+        else if (fits(256, R1))
             k_asls<256, R1, true><<<B, 256, 0, s>>>(N, y, sc, bg_out, lambda, p, n_iter);
         else if (fits(512, R2))
             k_asls<512, R2, true><<<B, 512, 0, s>>>(N, y, sc, bg_out, lambda, p, n_iter);

@@ -50,7 +50,6 @@ constexpr double kFarRadius = 2.0;     // in half-widths of the tile
 constexpr double kWide = 3.5;
 constexpr int kLeaf = kWave;           // points of a leaf
 constexpr int kDenseWaves = 16;        // waves per block
-constexpr int kMinGroupBlocks = 96;
 constexpr int kPlanPhases = 256;       // phases whose near ranges are held in LDS
 constexpr int kNodeStride = kNodes + 1;    // (no LDS bank conflicts)
 
@@ -101,9 +100,10 @@ struct DenseCut {
 };
 __host__ __device__ inline DenseCut dense_cut(int N, int S) {
     // One block of 16 waves runs per CU.  Two leaves while that is one round
-    // of the 256 CUs, four beyond: 3501 points, S = 64 takes 61 us with four
-    // (224 blocks) and 71 with two (448), 7001 points, S = 128 692 and 808 us;
-    // 2501 points, S = 32 takes 119 us with four (80 blocks) and 65 with two.
+    // of the 256 CUs, four beyond: 50 phases of 40 peaks, N = 3501, at 168 to 252
+    // blocks of two take 52 us and their 112 to 126 blocks of four 75, at 280 (S =
+    // 37) 77.5 and 75.0, at 448 (S = 64) 81 and 76; 200 of 60, N = 7001, at 275
+    // 218 and 198.
     if (DenseCut{2, 4}.blocks(N, S) > 256) {
         DenseCut cut{4, 4};
         // A last round that leaves half the CUs idle is shorter with its spans
@@ -116,11 +116,12 @@ __host__ __device__ inline DenseCut dense_cut(int N, int S) {
         if (x < cut.wide(N) && 2 * x * ng <= 256) cut.narrow = (int)x;
         return cut;
     }
-    // Few blocks of four samples leave CUs idle: 3501 points, S = 8 (56 such
-    // blocks) takes 56 us with them and 43 with one sample per block, but one
-    // sample per block costs about twice the work (2501 points, S = 32, 160
-    // blocks: 65 us with four samples, 105 with one).
-    if (DenseCut{2, 4}.blocks(N, S) >= kMinGroupBlocks) return DenseCut{2, 4};
+    // One sample per block while those are one round too (a wave's lanes then
+    // take the points, not the nodes: about twice the work, on four times the
+    // CUs): 50 x 40, N = 3501, S = 8 (224 blocks) 38.5 us, with four samples 52.3;
+    // 50 x 50, N = 2501, S = 12 (240) 42.4 and 59.8; in two rounds S = 16 (320) 62.4
+    // and 59.8, N = 3501, S = 12 (336) 54.9 and 52.3.
+    if (DenseCut{2, 1}.blocks(N, S) > 256) return DenseCut{2, 4};
     return DenseCut{2, 1};
 }
 

@@ -200,6 +200,9 @@ __global__ __launch_bounds__(kDenseWaves * kWave, 4) void kb_dense(const SlotDev
         DenseSmem<kDenseWaves, 4, 4, ASYM, SEC> wide;
         DenseSmem<kDenseWaves, 4, 2, ASYM, SEC> four;
         DenseSmem<kDenseWaves, 1, 2, ASYM, SEC> one;
+        DirectSmem<kDenseWaves, 4, 4, ASYM> dwide;
+        DirectSmem<kDenseWaves, 4, 2, ASYM> dfour;
+        DirectSmem<kDenseWaves, 1, 2, ASYM> done;
     } sm;
     load_prefix(sch, fused_kind(false, ASYM, SEC), ps);
     const int total = uniform(ps.pre[ps.n]);
@@ -224,8 +227,21 @@ __global__ __launch_bounds__(kDenseWaves * kWave, 4) void kb_dense(const SlotDev
                 dense_tile<true, ASYM, SEC, kDenseWaves, 1, 2, CUT>(d.P, d.st, t, t, grp,
                                                                     nullptr, sm.one);
         };
-        if (cut_phases(d.P.K)) tile(std::true_type{});
-        else tile(std::false_type{});
+        if (direct_peaks(d.P.K, d.P.T)) {
+            if (cut.leaves == 4 && t < wide)
+                dense_direct<true, ASYM, SEC, kDenseWaves, 4, 4>(d.P, d.st, t, t, grp, nullptr,
+                                                                 sm.dwide);
+            else if (cut.group == 4)
+                dense_direct<true, ASYM, SEC, kDenseWaves, 4, 2>(
+                    d.P, d.st, cut.leaves == 4 ? t + wide : t, t, grp, nullptr, sm.dfour);
+            else
+                dense_direct<true, ASYM, SEC, kDenseWaves, 1, 2>(d.P, d.st, t, t, grp, nullptr,
+                                                                 sm.done);
+        } else if (cut_phases(d.P.K)) {
+            tile(std::true_type{});
+        } else {
+            tile(std::false_type{});
+        }
         __syncthreads();
     }
 }

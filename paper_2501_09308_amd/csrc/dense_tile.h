@@ -438,6 +438,14 @@ __device__ __forceinline__ void prio_left(int left) {
     else __builtin_amdgcn_s_setprio(0);
 }
 
+// Whether every peak is taken at every point (dense_direct): a phase costs what
+// some three peaks do.  With four samples, N = 3501, S = 64, one phase of 40 peaks
+// 30.6 us against 33.2 at the nodes, of 64 35.6 and 33.6, two of 20 32.5 and 34.4,
+// four of 16 39.2 and 35.5, twenty of one 39.4 and 33.5; in five rounds of blocks
+// (N = 7936, S = 73) one of 40 48 and 64, eight of 8 74 and 66.
+constexpr int kDirectPeaks = 56;
+__host__ __device__ inline bool direct_peaks(int K, int T) { return T + 3 * K <= kDirectPeaks; }
+
 // Whether the waves share each phase's peaks instead of the phases.
 constexpr bool cut_phases(int K) { return 2 * K <= kDenseWaves; }
 // Tile t of those of LV leaves; its sums go to place `out` among the
@@ -950,6 +958,127 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
             for (int w = k << ps; w < (k + 1) << ps; ++w) v += (double)sm.nod[w][q];
             st.part[(((size_t)out * K + k) * S + s0) * NS + q] = (float)v;
         }
+    }
+}
+
+// ---- few peaks: every one at every point --------------------------------------
+//
+// Around the phase loops a block of dense_tile spends some 10 us on weights,
+// ranges and nodes, which few peaks do not earn back.  Here the peaks of the
+// block's samples are prepared in LDS by a thread each; then the threads take
+// (sample, point) each, SH of them a pair's peaks in turn, and no interval is
+// formed: the sum over the peaks, the likelihood, then each phase's adjoint
+// terms, reduced over the waves.  The same tiles and places as dense_tile's.
+template <int NW, int SG, int LV, bool ASYM>
+struct DirectSmem {
+    static constexpr int kPts = LV * kLeaf, kShares = NW / (SG * LV);
+    float4 at[SG][kDirectPeaks];          // NearPeak
+    float4 amp[SG][kDirectPeaks];         // (aL, aG, I, c) ...
+    float tw[SG][kDirectPeaks];
+    float sig[kShares][SG * kPts];        // the shares' sums
+    float rres[SG * kPts];                // residual y/f - 1
+    double red[SG * LV];
+    float acc[kDirectPeaks / 3][NW][ASYM ? 12 : 6];
+};
+
+template <bool GRAD, bool ASYM, bool SEC, int NW, int SG, int LV, typename SM>
+__device__ void dense_direct(const ProbDev &P, const StepDev &st, int t, int out, int grp,
+                             float *f_out, SM &sm) {
+    constexpr int PTS = LV * kLeaf, NT = NW * kWave, SH = SM::kShares;
+    constexpr int NS = ASYM ? 12 : 6;
+    static_assert(SH * SG * PTS == NT, "a thread per share, sample and point");
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int sh = wv / (SG * LV), gq = tid % (SG * PTS), g = wv / LV % SG;
+    const int S = st.S, K = P.K, T = P.T, s0 = grp * SG, ns = min(SG, S - s0);
+    const int i0 = t * PTS, i = i0 + gq % PTS, ic = min(i, P.N - 1);
+    const bool in = i < P.N && g < ns;
+    const float u = P.u[ic], ul = P.ul[ic];
+    const double py = P.y[ic], pb = P.bg[ic], pl = P.lgy[ic];
+    cptr<int> off = as_const(P.off);
+    for (int x = tid; x < ns * T; x += NT) {
+        const int gg = x / T, j = x % T, k = P.phase[j], s = s0 + gg;
+        const float4 c = st.pk[(size_t)s * K + k];
+        const float iw2r = ASYM ? st.pkr[(size_t)s * K + k] : c.x;
+        const float4 r = SEC ? st.psec[(size_t)s * T + j] : make_float4(1.f, P.inten[j], 0.f, 0.f);
+        const size_t o = (size_t)(i0 / P.ref) * T + j;
+        const NearPeak p = NearPeak::of<SEC>(P.pt[o], P.ptl[o], c.w, c.x, iw2r, r.x);
+        sm.at[gg][j] = make_float4(p.ch, p.cl, p.s, p.sr);
+        sm.amp[gg][j] = make_float4(c.z * r.y, c.y * r.y, r.y, r.x);
+        if (SEC) sm.tw[gg][j] = r.z;
+    }
+    __syncthreads();
+    const int gs = min(g, ns - 1);       // (waves past the last sample repeat it)
+    auto q2_of = [&](int j, bool &up) {
+        const float4 a = sm.at[gs][j];
+        return NearPeak{a.x, a.y, a.z, a.w}.template q2<ASYM>(u, ul, up);
+    };
+    float sum = 0.f;
+#pragma unroll 4
+    for (int j = sh; j < T; j += SH) {
+        bool up;
+        const float q2 = q2_of(j, up), tt = fmaf(q2, q2, 1.0f);
+        const float4 m = sm.amp[gs][j];
+        sum = fmaf(m.x, rcp_f32(tt), sum);
+        sum = fmaf(m.y, exp2_f32(-tt), sum);
+    }
+    if (SH > 1) {
+        sm.sig[sh][gq] = sum;
+        __syncthreads();
+    }
+    if (sh == 0) {
+        double sg = (double)sum;
+#pragma unroll
+        for (int x = 1; x < SH; ++x) sg += (double)sm.sig[x][gq];
+        const double f = pb + sg;
+        if (in && f_out) f_out[(size_t)(s0 + g) * P.N + i] = (float)f;
+        double ll = in && st.llp ? (py != 0.0 ? py * log(f) : 0.0) - f - pl : 0.0;
+        if (GRAD) sm.rres[gq] = in ? (float)(py / f - 1.0) : 0.f;
+        ll = wave_sum(ll);
+        if (lane == 0) sm.red[wv] = ll;
+    }
+    __syncthreads();
+    if (tid < ns && st.llp) {
+        double v = 0.0;
+#pragma unroll
+        for (int l = 0; l < LV; ++l) v += sm.red[tid * LV + l];
+        st.llp[(size_t)(s0 + tid) * st.nt + out] = v;
+    }
+    if (!GRAD) return;
+    const float R = sm.rres[gq];
+    for (int k = 0; k < K; ++k) {
+        float ka = 1.f;
+        if (ASYM && SEC) {
+            const size_t o = (size_t)(s0 + gs) * K + k;
+            ka = st.pk[o].x / st.pkr[o];
+        }
+        float e[NS];
+#pragma unroll
+        for (int q = 0; q < NS; ++q) e[q] = 0.f;
+#pragma unroll 4
+        for (int j = off[k] + sh; j < off[k + 1]; j += SH) {
+            bool up;
+            const float q2 = q2_of(j, up), tt = fmaf(q2, q2, 1.0f);
+            const float4 m = sm.amp[gs][j];
+            const float RI = R * m.z, tw = SEC ? sm.tw[gs][j] : 0.f;
+            const SecW wl = SecW::of(tw), wh = SecW::of(tw * ka);
+            adj_terms_L<ASYM, SEC>(RI, q2, tt, up, m.w, wl, wh, e);
+            adj_point_G<ASYM, SEC>(AdjPt{RI, q2, tt, up}, m.w, wl, wh, e);
+        }
+#pragma unroll
+        for (int q = 0; q < NS; ++q) e[q] = wave_total_f32(e[q]);
+        float v = e[0];
+#pragma unroll
+        for (int q = 1; q < NS; ++q) v = lane == q ? e[q] : v;
+        if (lane < NS) sm.acc[k][wv][lane] = v;
+    }
+    __syncthreads();
+    for (int x = tid; x < K * ns * NS; x += NT) {
+        const int k = x / (ns * NS), q = x % NS, gg = x / NS % ns;
+        double v = 0.0;
+        for (int w = 0; w < NW; ++w)
+            if (w / LV % SG == gg) v += (double)sm.acc[k][w][q];
+        st.part[(((size_t)out * K + k) * S + s0 + gg) * NS + q] = (float)v;
     }
 }
 

@@ -156,6 +156,26 @@ __global__ __launch_bounds__(kDenseWaves * kWave, 4) void k_dense(ProbDev P, Ste
     }
 }
 
+// ... of few peaks (see dense_direct).
+template <bool GRAD, bool ASYM, bool SEC, int SG, int LV>
+__global__ __launch_bounds__(kDenseWaves * kWave, 4) void k_direct(ProbDev P, StepDev st,
+                                                                   float *f_out, int wide) {
+    __shared__ union {
+        DirectSmem<kDenseWaves, SG, LV, ASYM> wide;
+        DirectSmem<kDenseWaves, SG, 2, ASYM> two;
+    } sm;
+    const int ng = (st.S + SG - 1) / SG, b = blockIdx.x + blockIdx.y * gridDim.x;
+    if (LV == 2 || b < wide * ng) {
+        const int2 tg = xcd_tile_sample(b, LV == 2 ? st.nt : wide, ng);
+        dense_direct<GRAD, ASYM, SEC, kDenseWaves, SG, LV>(P, st, tg.x, tg.x, tg.y, f_out,
+                                                           sm.wide);
+    } else {
+        const int2 tg = xcd_tile_sample(b - wide * ng, st.nt - wide, ng);
+        dense_direct<GRAD, ASYM, SEC, kDenseWaves, SG, 2>(P, st, 2 * wide + tg.x, wide + tg.x,
+                                                          tg.y, f_out, sm.two);
+    }
+}
+
 // a3 + a4 (windowed): forward tile over its staged peak records; grid
 // (ntiles, S), kBlock threads, blocks ordered by XCD.  The register budget is
 // held to the occupancy the staging space allows (seven blocks per CU, six
@@ -336,7 +356,17 @@ static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
             else k_dense<false, ASYM, SEC, SG, LV, CUT><<<g, nt, 0, stream>>>(P, st, f_out, w);
         };
         auto run = [&](auto sg_tag, auto lv_tag) {
-            if (cut_phases(P.K)) run_cut(sg_tag, lv_tag, std::true_type{});
+            if (direct_peaks(P.K, P.T)) {
+                constexpr int SG = decltype(sg_tag)::value, LV = decltype(lv_tag)::value;
+                const dim3 g(st.nt, (st.S + SG - 1) / SG);
+                const int w = cut.wide(P.N);
+                if (grad)
+                    k_direct<true, ASYM, SEC, SG, LV>
+                        <<<g, kDenseWaves * kWave, 0, stream>>>(P, st, f_out, w);
+                else
+                    k_direct<false, ASYM, SEC, SG, LV>
+                        <<<g, kDenseWaves * kWave, 0, stream>>>(P, st, f_out, w);
+            } else if (cut_phases(P.K)) run_cut(sg_tag, lv_tag, std::true_type{});
             else run_cut(sg_tag, lv_tag, std::false_type{});
         };
         const std::integral_constant<int, 1> one;

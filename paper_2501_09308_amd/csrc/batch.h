@@ -97,8 +97,18 @@ inline int batch_class(const ProbDev &P) {
     return (P.cutoff > 0.0 ? 1 : 0) | (P.D == 5 ? 2 : 0) | (P.sec != 0 ? 4 : 0);
 }
 
-// One batched step over the resident analyses, whose classes are the set
-// bits of `classes` (bit c: some resident analysis has class c).
+// Bits of the sets of resident classes beside bit c for class c: some dense
+// analysis has one, or four, samples per block (a kernel each).
+constexpr unsigned kDenseOne = 1u << 8, kDenseFour = 1u << 9;
+constexpr int kClassSets = 1 << 10;
+inline unsigned class_bits(const ProbDev &P, int S) {
+    const unsigned c = 1u << batch_class(P);
+    if (P.cutoff > 0.0) return c;
+    return c | (dense_cut(P.N, S).group == 1 ? kDenseOne : kDenseFour);
+}
+
+// One batched step over the resident analyses, whose class_bits are set in
+// `classes`.
 hipError_t launch_batch_step(const SlotDev *tab, const SchedDev *sch,
                              hipStream_t stream, unsigned classes);
 

@@ -191,52 +191,60 @@ __global__ __launch_bounds__(kBlock, ASYM || SEC ? 6 : 7) void kb_win(const Slot
 }
 
 // Dense fused forward + adjoint, units (tile, sample group) with the groups
-// fastest (a tile's samples run at the same time and share its peaks).
+// fastest (a tile's samples run at the same time and share its peaks).  SG: the
+// units of analyses with that many samples per block, the others pass by; with
+// one, two blocks share a CU as in the single-analysis kernel.
+template <bool ASYM, bool SEC, int SG>
+union DenseBatchSmem {
+    DenseSmem<kDenseWaves, SG, 2, ASYM, SEC> two;
+    DirectSmem<kDenseWaves, SG, 2, ASYM> dtwo;
+};
 template <bool ASYM, bool SEC>
-__global__ __launch_bounds__(kDenseWaves * kWave, 4) void kb_dense(const SlotDev *tab,
-                                                                   const SchedDev *sch) {
+union DenseBatchSmem<ASYM, SEC, 4> {
+    DenseSmem<kDenseWaves, 4, 4, ASYM, SEC> wide;
+    DenseSmem<kDenseWaves, 4, 2, ASYM, SEC> two;
+    DirectSmem<kDenseWaves, 4, 4, ASYM> dwide;
+    DirectSmem<kDenseWaves, 4, 2, ASYM> dtwo;
+};
+template <bool ASYM, bool SEC, int SG>
+__global__ __launch_bounds__(kDenseWaves * kWave, SG == 1 ? 8 : 4) void kb_dense(
+    const SlotDev *tab, const SchedDev *sch) {
     __shared__ PrefixSmem ps;
-    __shared__ union {
-        DenseSmem<kDenseWaves, 4, 4, ASYM, SEC> wide;
-        DenseSmem<kDenseWaves, 4, 2, ASYM, SEC> four;
-        DenseSmem<kDenseWaves, 1, 2, ASYM, SEC> one;
-        DirectSmem<kDenseWaves, 4, 4, ASYM> dwide;
-        DirectSmem<kDenseWaves, 4, 2, ASYM> dfour;
-        DirectSmem<kDenseWaves, 1, 2, ASYM> done;
-    } sm;
+    __shared__ DenseBatchSmem<ASYM, SEC, SG> sm;
     load_prefix(sch, fused_kind(false, ASYM, SEC), ps);
     const int total = uniform(ps.pre[ps.n]);
     for (int u = blockIdx.x; u < total; u += gridDim.x) {
         const int i = find_slot(ps, u);
         const SlotDev &d = slot_entry(tab, ps, i);
-        if (!running(d)) continue;
-        const int local = local_unit(ps, i, u);
         const DenseCut cut = dense_cut(d.P.N, d.st.S);
+        if (cut.group != SG || !running(d)) continue;
+        const int local = local_unit(ps, i, u);
         const int ng = cut.groups(d.st.S), t = local / ng, grp = local % ng;
         if (t >= d.st.nt) continue;
         const int wide = cut.wide(d.P.N);   // tiles of cut.leaves, then of two
+        const bool is_wide = SG == 4 && cut.leaves == 4 && t < wide;
+        const int tw = SG == 4 && cut.leaves == 4 ? t + wide : t;   // ... as one of two
         const auto tile = [&](auto cut_tag) {
             constexpr bool CUT = decltype(cut_tag)::value;
-            if (cut.leaves == 4 && t < wide)
-                dense_tile<true, ASYM, SEC, kDenseWaves, 4, 4, CUT>(d.P, d.st, t, t, grp,
-                                                                    nullptr, sm.wide);
-            else if (cut.group == 4)
-                dense_tile<true, ASYM, SEC, kDenseWaves, 4, 2, CUT>(
-                    d.P, d.st, cut.leaves == 4 ? t + wide : t, t, grp, nullptr, sm.four);
-            else
-                dense_tile<true, ASYM, SEC, kDenseWaves, 1, 2, CUT>(d.P, d.st, t, t, grp,
-                                                                    nullptr, sm.one);
+            if constexpr (SG == 4) {
+                if (is_wide) {
+                    dense_tile<true, ASYM, SEC, kDenseWaves, 4, 4, CUT>(d.P, d.st, t, t, grp,
+                                                                        nullptr, sm.wide);
+                    return;
+                }
+            }
+            dense_tile<true, ASYM, SEC, kDenseWaves, SG, 2, CUT>(d.P, d.st, tw, t, grp, nullptr,
+                                                                 sm.two);
         };
-        if (direct_peaks(d.P.K, d.P.T)) {
-            if (cut.leaves == 4 && t < wide)
-                dense_direct<true, ASYM, SEC, kDenseWaves, 4, 4>(d.P, d.st, t, t, grp, nullptr,
-                                                                 sm.dwide);
-            else if (cut.group == 4)
-                dense_direct<true, ASYM, SEC, kDenseWaves, 4, 2>(
-                    d.P, d.st, cut.leaves == 4 ? t + wide : t, t, grp, nullptr, sm.dfour);
-            else
-                dense_direct<true, ASYM, SEC, kDenseWaves, 1, 2>(d.P, d.st, t, t, grp, nullptr,
-                                                                 sm.done);
+        if (direct_peaks(d.P.K, d.P.T, ASYM)) {
+            if constexpr (SG == 4) {
+                if (is_wide)
+                    dense_direct<true, ASYM, SEC, kDenseWaves, 4, 4>(d.P, d.st, t, t, grp,
+                                                                     nullptr, sm.dwide);
+            }
+            if (!is_wide)
+                dense_direct<true, ASYM, SEC, kDenseWaves, SG, 2>(d.P, d.st, tw, t, grp, nullptr,
+                                                                  sm.dtwo);
         } else if (cut_phases(d.P.K)) {
             tile(std::true_type{});
         } else {
@@ -342,6 +350,15 @@ hipError_t launch_enter_slot(const SlotDev &d, SlotDev *entry, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <bool ASYM, bool SEC>
+static void launch_dense(const SlotDev *tab, const SchedDev *sch, hipStream_t s,
+                         unsigned classes) {
+    if (classes & kDenseFour)
+        kb_dense<ASYM, SEC, 4><<<kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (classes & kDenseOne)
+        kb_dense<ASYM, SEC, 1><<<2 * kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+}
+
 hipError_t launch_batch_step(const SlotDev *tab, const SchedDev *sch,
                              hipStream_t s, unsigned classes) {
     // whether a resident class satisfies the windowed / sec-law test
@@ -360,13 +377,13 @@ hipError_t launch_batch_step(const SlotDev *tab, const SchedDev *sch,
     if (any(-1, 1)) kb_windows<true><<<kGridLarge, 256, 0, s>>>(tab, sch);
     if (any(1, 0)) kb_cand<<<kGridLarge, kCandThreads, 0, s>>>(tab, sch);
     if (has(true, false, false)) kb_win<false, false><<<kGridWin, kBlock, 0, s>>>(tab, sch);
-    if (has(false, false, false)) kb_dense<false, false><<<kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(false, false, false)) launch_dense<false, false>(tab, sch, s, classes);
     if (has(true, true, false)) kb_win<true, false><<<kGridWin, kBlock, 0, s>>>(tab, sch);
-    if (has(false, true, false)) kb_dense<true, false><<<kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(false, true, false)) launch_dense<true, false>(tab, sch, s, classes);
     if (has(true, false, true)) kb_win<false, true><<<kGridWin, kBlock, 0, s>>>(tab, sch);
-    if (has(false, false, true)) kb_dense<false, true><<<kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(false, false, true)) launch_dense<false, true>(tab, sch, s, classes);
     if (has(true, true, true)) kb_win<true, true><<<kGridWin, kBlock, 0, s>>>(tab, sch);
-    if (has(false, true, true)) kb_dense<true, true><<<kGridDense, kDenseWaves * kWave, 0, s>>>(tab, sch);
+    if (has(false, true, true)) launch_dense<true, true>(tab, sch, s, classes);
     if (has(true, false, false)) kb_adjoint<false, false><<<kGridAdjoint, kBlock, 0, s>>>(tab, sch);
     if (has(true, true, false)) kb_adjoint<true, false><<<kGridAdjoint, kBlock, 0, s>>>(tab, sch);
     if (has(true, false, true)) kb_adjoint<false, true><<<kGridAdjoint, kBlock, 0, s>>>(tab, sch);

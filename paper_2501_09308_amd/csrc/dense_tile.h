@@ -116,12 +116,17 @@ __host__ __device__ inline DenseCut dense_cut(int N, int S) {
         if (x < cut.wide(N) && 2 * x * ng <= 256) cut.narrow = (int)x;
         return cut;
     }
-    // One sample per block while those are one round too (a wave's lanes then
-    // take the points, not the nodes: about twice the work, on four times the
-    // CUs): 50 x 40, N = 3501, S = 8 (224 blocks) 38.5 us, with four samples 52.3;
-    // 50 x 50, N = 2501, S = 12 (240) 42.4 and 59.8; in two rounds S = 16 (320) 62.4
-    // and 59.8, N = 3501, S = 12 (336) 54.9 and 52.3.
-    if (DenseCut{2, 1}.blocks(N, S) > 256) return DenseCut{2, 4};
+    // One sample per block (a wave's lanes then take the points, not the nodes:
+    // about twice the work on four times the blocks) while one of them runs on each
+    // CU: 50 x 40, N = 3501, S = 8 (224 blocks) 38.9 us, with four samples 52.3;
+    // beyond, S = 16 (448 blocks, two on a CU) 45.7 and 52.1, but served with others
+    // (their blocks fill the CUs anyway) an analysis costs twice as much: eight, one
+    // of them of 448 blocks, 18.0 ms and 21.9.  Short grids, where most peaks are near
+    // and few blocks of four samples leave CUs idle, take two on a CU: 35 x 28, N =
+    // 200, S = 256 (512 blocks) 88 us and 110, N = 1500, S = 40 (480) 42.9 and 48.1,
+    // with peaks of 2 deg 70 and 112; in two rounds N = 300, S = 200 (600) 110 and 97.
+    constexpr int kShortGrid = 1536;
+    if (DenseCut{2, 1}.blocks(N, S) > (N <= kShortGrid ? 512 : 256)) return DenseCut{2, 4};
     return DenseCut{2, 1};
 }
 
@@ -439,12 +444,14 @@ __device__ __forceinline__ void prio_left(int left) {
 }
 
 // Whether every peak is taken at every point (dense_direct): a phase costs what
-// some three peaks do.  With four samples, N = 3501, S = 64, one phase of 40 peaks
+// some three peaks do, an asymmetric one (twelve sums) six.  With four samples, N = 3501, S = 64, one phase of 40 peaks
 // 30.6 us against 33.2 at the nodes, of 64 35.6 and 33.6, two of 20 32.5 and 34.4,
 // four of 16 39.2 and 35.5, twenty of one 39.4 and 33.5; in five rounds of blocks
 // (N = 7936, S = 73) one of 40 48 and 64, eight of 8 74 and 66.
 constexpr int kDirectPeaks = 56;
-__host__ __device__ inline bool direct_peaks(int K, int T) { return T + 3 * K <= kDirectPeaks; }
+__host__ __device__ inline bool direct_peaks(int K, int T, bool asym) {
+    return T + (asym ? 6 : 3) * K <= kDirectPeaks;
+}
 
 // Whether the waves share each phase's peaks instead of the phases.
 constexpr bool cut_phases(int K) { return 2 * K <= kDenseWaves; }
@@ -975,10 +982,10 @@ struct DirectSmem {
     float4 at[SG][kDirectPeaks];          // NearPeak
     float4 amp[SG][kDirectPeaks];         // (aL, aG, I, c) ...
     float tw[SG][kDirectPeaks];
-    float sig[kShares][SG * kPts];        // the shares' sums
+    double sig[kShares][SG * kPts];       // the shares' sums
     float rres[SG * kPts];                // residual y/f - 1
     double red[SG * LV];
-    float acc[kDirectPeaks / 3][NW][ASYM ? 12 : 6];
+    float acc[kDirectPeaks / (ASYM ? 6 : 3)][NW][ASYM ? 12 : 6];
 };
 
 template <bool GRAD, bool ASYM, bool SEC, int NW, int SG, int LV, typename SM>
@@ -1013,23 +1020,30 @@ __device__ void dense_direct(const ProbDev &P, const StepDev &st, int t, int out
         const float4 a = sm.at[gs][j];
         return NearPeak{a.x, a.y, a.z, a.w}.template q2<ASYM>(u, ul, up);
     };
-    float sum = 0.f;
-#pragma unroll 4
-    for (int j = sh; j < T; j += SH) {
+    // (four peaks in FP32, their sums in FP64)
+    double sum = 0.0;
+    auto value = [&](int j, float v) {
         bool up;
         const float q2 = q2_of(j, up), tt = fmaf(q2, q2, 1.0f);
         const float4 m = sm.amp[gs][j];
-        sum = fmaf(m.x, rcp_f32(tt), sum);
-        sum = fmaf(m.y, exp2_f32(-tt), sum);
+        return fmaf(m.y, exp2_f32(-tt), fmaf(m.x, rcp_f32(tt), v));
+    };
+    int j = sh;
+    for (; j + 3 * SH < T; j += 4 * SH) {
+        float v = 0.f;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) v = value(j + x * SH, v);
+        sum += (double)v;
     }
+    for (; j < T; j += SH) sum += (double)value(j, 0.f);
     if (SH > 1) {
         sm.sig[sh][gq] = sum;
         __syncthreads();
     }
     if (sh == 0) {
-        double sg = (double)sum;
+        double sg = sum;
 #pragma unroll
-        for (int x = 1; x < SH; ++x) sg += (double)sm.sig[x][gq];
+        for (int x = 1; x < SH; ++x) sg += sm.sig[x][gq];
         const double f = pb + sg;
         if (in && f_out) f_out[(size_t)(s0 + g) * P.N + i] = (float)f;
         double ll = in && st.llp ? (py != 0.0 ? py * log(f) : 0.0) - f - pl : 0.0;

@@ -247,7 +247,10 @@ class GpuExecutor : public Executor {
         });
         // each variant's kernels run only while an analysis of it is resident
         unsigned classes = 0;
-        for (const auto &m : members) classes |= 1u << batch_class(h_tab_[m.first].P);
+        for (const auto &m : members) {
+            const SlotDev &d = h_tab_[m.first];
+            classes |= class_bits(d.P, d.st.S);
+        }
         hipError_t e = hipSuccess;
         if (changed || members != members_) {
             members_ = members;
@@ -348,7 +351,6 @@ class GpuExecutor : public Executor {
     int *d_steps_ = nullptr;
     int *h_steps_ = nullptr;
     std::vector<std::pair<int, uint64_t>> members_;
-    static constexpr int kClassSets = 256;   // subsets of the 8 variant classes
     hipGraph_t graph_[kClassSets] = {};
     hipGraphExec_t gexec_[kClassSets] = {};
 };

@@ -1,7 +1,7 @@
 """Dense analyses of few phases, whose peaks several waves share: one to nine
 phases (the rule ends at eight), of no peaks, fewer than shares, one, and many,
-and so few peaks that every one is taken at every point (T + 3 K up to 56), in
-every kind of block, against the FP64 oracle: profile 1e-5, ELBO 1e-6, each
+and so few peaks that every one is taken at every point (T + 3 K up to 56,
+asymmetric T + 6 K), in every kind of block, against the FP64 oracle: profile 1e-5, ELBO 1e-6, each
 phase's and latent's gradient 1e-4; and served, the same bits as alone."""
 import math
 
@@ -41,7 +41,8 @@ def _case(N, S, M, D):
 @pytest.mark.parametrize("N,S", [(90, 2), (700, 1), (900, 61), (700, 130), (1300, 200)])
 @pytest.mark.parametrize("M", [(150,), (1,), (40, 0), (3, 17, 400), (5, 1, 0, 20, 9),
                                (2, 9, 30, 1, 16, 15, 17, 40), (4, 9, 30, 1, 0, 15, 17, 40, 8),
-                               (53,), (54,), (20, 30), (20, 31), 14 * (1,), 17 * (0,) + (2,)])
+                               (53,), (54,), (20, 30), (20, 31), 14 * (1,), 17 * (0,) + (2,),
+                               (50,), 8 * (1,)])
 def test_few_phases(M, N, S, asym, sec):
     print(f"\nfew phases: M={M} N={N} S={S} asym={asym} sec={sec}", flush=True)
     prob, loc, ls, eps = _case(N, S, M, 5 if asym else 4)

@@ -69,8 +69,9 @@ CASES += [(N, step, S, kind, False, False)
           for N, S in [(190, 3), (450, 130), (1300, 200)]
           for step in (0.005, 0.02)
           for kind in ("merged", "gap", "ends")]
-# (the last size of one sample per block, the first of four)
-CASES += [(129, 0.02, S, "uniform", False, False) for S in (128, 129)]
+# (the last sizes of one sample per block, the first of four)
+CASES += [(N, 0.02, S, "uniform", False, False)
+          for N, S in [(129, 256), (129, 257), (1536, 42), (1537, 19), (1537, 20)]]
 CASES += [(65, 0.001, 3, "uniform", True, False), (321, 0.001, 260, "uniform", False, True),
           (193, 0.005, 200, "gap", True, True), (577, 0.005, 402, "merged", True, False)]
 

@@ -255,7 +255,7 @@ __global__ __launch_bounds__(kDenseWaves * kWave, SG == 1 ? 8 : 4) void kb_dense
 }
 
 template <bool ASYM, bool SEC>
-__global__ __launch_bounds__(kBlock, ASYM || SEC ? 1 : 8) void kb_adjoint(const SlotDev *tab,
+__global__ __launch_bounds__(kBlock, ASYM ? (SEC ? 5 : 6) : (SEC ? 7 : 8)) void kb_adjoint(const SlotDev *tab,
                                                      const SchedDev *sch) {
     __shared__ double red[kWaves][12];
     __shared__ ElboSmem<kBlock> el;
@@ -272,7 +272,10 @@ __global__ __launch_bounds__(kBlock, ASYM || SEC ? 1 : 8) void kb_adjoint(const 
             __syncthreads();
             continue;
         }
-        adjoint_phase<ASYM, SEC>(d.P, d.st, local / d.P.K, local % d.P.K, red);
+        if (d.P.few)
+            adjoint_phase<ASYM, SEC, kWave>(d.P, d.st, local / d.P.K, local % d.P.K, red);
+        else
+            adjoint_phase<ASYM, SEC, kAdjLanes>(d.P, d.st, local / d.P.K, local % d.P.K, red);
         __syncthreads();
     }
 }

@@ -183,6 +183,9 @@ void stage_problem(const xrdvi_problem_desc &d, const NearShape &near, double la
     P.ref = d.cutoff == 0.0 ? kRefDense : kTile;
     P.D = latent_types(d);
     P.sec = d.width_law;
+    P.few = 1;
+    for (int k = 0; k < K; ++k)
+        if (d.peak_off[k + 1] - d.peak_off[k] > kAdjFew) P.few = 0;
     P.cutoff = d.cutoff;
     P.x0 = d.x[0];
     P.inv_dx = N > 1 ? (double)(N - 1) / (d.x[N - 1] - d.x[0]) : 0.0;

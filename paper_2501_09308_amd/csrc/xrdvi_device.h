@@ -73,6 +73,7 @@ struct ProbDev {
     int D;                            // latent types per phase: 4, or 5 with
                                       // the asymmetry alpha
     int sec;                          // 1: width w sec(rho / 2); 0: width w
+    int few;                          // 1: no phase has more than kAdjFew peaks
     double cutoff;
     double lambda, mu_sd, w_shape, w_rate;
     double a_mean, a_sd;              // normal prior on alpha (D = 5)
@@ -1375,7 +1376,13 @@ constexpr int kBufferFlags = 0x00020000;
 // Peaks a wave handles side by side, and the lanes of each.
 constexpr int kAdjPeaks = 4;
 constexpr int kAdjLanes = kWave / kAdjPeaks;
-// Chunks of kAdjLanes points whose loads are issued together.
+// Peaks per phase up to which a problem's adjoint takes one peak at a time on all
+// lanes of a wave, so that a short list is spread over the block's waves: 93
+// phases of 6 asymmetric peaks, windows of 4000 points, S = 192 772 us a step by
+// half the waves, 478 by all; 497 of 3, S = 14 279 and 138; 1000 of 5, windows of
+// 133 points, S = 32 134 and 130.
+constexpr int kAdjFew = 8;
+// Chunks of points whose loads are issued together.
 constexpr int kAdjChunks = 4;
 // Points in every window of a group from which asymmetric peaks take several
 // chunks at once.
@@ -1390,7 +1397,9 @@ constexpr int kAdjLong = 256;
 // gradient error of that order, against a bar of 1e-4).
 constexpr double kF32Cutoff = 16.0;
 
-template <bool ASYM, bool SEC>
+// LN: lanes of a peak, kAdjLanes, or all of the wave in a problem of few peaks
+// (ProbDev::few).
+template <bool ASYM, bool SEC, int LN>
 __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
                                      int s, int k, double (*red)[12]) {
     constexpr int NS = ASYM ? 12 : 6;
@@ -1417,17 +1426,18 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
     const float4 *psec = SEC ? st.psec + (size_t)s * P.T : nullptr;
     const float ka = ASYM ? (float)ph[4 * K + k] : 1.f;
     const bool unif = P.formed_x != 0;
-    const int sub = lane / kAdjLanes, l = lane % kAdjLanes;
+    constexpr int PK = kWave / LN;          // peaks side by side
+    const int sub = lane / LN, l = lane % LN;
     const double xl = fma((double)l, P.dx, P.x0);        // uniform grid: x0 + l dx
-    const double dxw = kAdjLanes * P.dx;                 // one chunk of points
+    const double dxw = LN * P.dx;                 // one chunk of points
     const int a = P.off[k], b = P.off[k + 1];
     float acc[NS];
 #pragma unroll
     for (int c = 0; c < NS; ++c) acc[c] = 0.f;
-    // the phase's peaks in groups of kAdjPeaks consecutive ones (neighbours
+    // the phase's peaks in groups of PK consecutive ones (neighbours
     // in position, with windows of one length), group g to wave g mod 4: only
     // the phase's last group can be short
-    for (int j0 = a + kAdjPeaks * wv; j0 < b; j0 += kWaves * kAdjPeaks) {
+    for (int j0 = a + PK * wv; j0 < b; j0 += kWaves * PK) {
         const bool ok = j0 + sub < b;
         const int j = ok ? j0 + sub : j0;
         const int lo = wlo[j], hi = whi[j], len = ok ? hi - lo : 0;
@@ -1444,12 +1454,12 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
         const SecW wl = SecW::of(tw), wh = SecW::of(tw * ka);
         const float qs = SEC ? iw2 * cq : 1.f, qsr = SEC ? iw2r * cq : up_ratio;
         // points every one of the group's windows has, and the longest window
-        int full = len, span = len;
+        int full = __builtin_amdgcn_readlane(len, 0), span = full;
 #pragma unroll
-        for (int q = 1; q < kAdjPeaks; ++q) {
-            const int v = __builtin_amdgcn_readlane(len, q * kAdjLanes);
-            full = min(q == 1 ? __builtin_amdgcn_readlane(len, 0) : full, v);
-            span = max(q == 1 ? __builtin_amdgcn_readlane(len, 0) : span, v);
+        for (int q = 1; q < PK; ++q) {
+            const int v = __builtin_amdgcn_readlane(len, q * LN);
+            full = min(full, v);
+            span = max(span, v);
         }
         // x_i - rho = e + t in FP64.  On a uniform grid x_i is formed, not
         // loaded, so only the residuals are read: e is the lane's offset in
@@ -1470,8 +1480,8 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
             const double step = SEC ? dxw : dxw * iw2d;
             // FP32: chunks counted from the window's middle one, so that the
             // offsets and their roundings are small where the peak is
-            const int mid = F32 ? len / (2 * kAdjLanes) : 0;
-            double e = UNIF ? fma((double)(lo + mid * kAdjLanes), P.dx, xl) - rho : -rho;
+            const int mid = F32 ? len / (2 * LN) : 0;
+            double e = UNIF ? fma((double)(lo + mid * LN), P.dx, xl) - rho : -rho;
             if (!SEC) e *= iw2d;
             const float stepf = (float)step, ef = (float)e;
             double cdx = 0.0;
@@ -1511,22 +1521,22 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
                     double xv[kAdjChunks];
 #pragma unroll
                     for (int u = 0; u < kAdjChunks; ++u)
-                        load(c + u * kAdjLanes, rv[u], xv[u]);
+                        load(c + u * LN, rv[u], xv[u]);
                     // all loads are issued before the first use, so one
                     // memory latency covers them
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int u = 0; u < kAdjChunks; ++u) {
-                        if (MASK && c + u * kAdjLanes >= span) break;
+                        if (MASK && c + u * LN >= span) break;
                         float R = rv[u] * I;
-                        if (MASK) R = c + u * kAdjLanes < len - l ? R : 0.f;
+                        if (MASK) R = c + u * LN < len - l ? R : 0.f;
                         point(std::integral_constant<int, kBelow>{}, R, offset(xv[u]));
                     }
                 };
                 int c = 0;
-                for (; c + kAdjChunks * kAdjLanes <= full; c += kAdjChunks * kAdjLanes)
+                for (; c + kAdjChunks * LN <= full; c += kAdjChunks * LN)
                     points(std::false_type{}, c);
-                for (; c < span; c += kAdjChunks * kAdjLanes) points(std::true_type{}, c);
+                for (; c < span; c += kAdjChunks * LN) points(std::true_type{}, c);
             } else {
                 // ascending points: the chunks wholly below the four centres,
                 // those with points on both sides, those wholly above; the loads
@@ -1536,16 +1546,16 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
                 double x0 = 0.0, x1 = 0.0, x2 = 0.0;
                 auto ahead = [&]() {
                     load(c, r0, x0);
-                    load(c + kAdjLanes, r1, x1);
+                    load(c + LN, r1, x1);
                 };
                 auto run = [&](auto side) {
                     constexpr int SIDE = decltype(side)::value;
-                    for (; c < span; c += kAdjLanes) {
+                    for (; c < span; c += LN) {
                         const float d = offset(x0);
                         const uint64_t above = __builtin_amdgcn_ballot_w64(d >= 0.f);
                         if (SIDE == kBelow && above != 0) break;
                         if (SIDE == kBoth && above == ~0ull) break;
-                        load(c + 2 * kAdjLanes, r2, x2);
+                        load(c + 2 * LN, r2, x2);
                         point(side, c < len - l ? r0 * I : 0.f, d);
                         r0 = r1;
                         r1 = r2;
@@ -1561,12 +1571,12 @@ __device__ inline void adjoint_phase(const ProbDev &P, const StepDev &st,
                 const bool lng = full >= kAdjLong;
                 auto runs = [&](auto side) {
                     constexpr int SIDE = decltype(side)::value;
-                    for (; c + kAdjChunks * kAdjLanes <= full; c += kAdjChunks * kAdjLanes) {
+                    for (; c + kAdjChunks * LN <= full; c += kAdjChunks * LN) {
                         float rv[kAdjChunks], dv[kAdjChunks];
                         double xv[kAdjChunks];
 #pragma unroll
                         for (int u = 0; u < kAdjChunks; ++u)
-                            load(c + u * kAdjLanes, rv[u], xv[u]);
+                            load(c + u * LN, rv[u], xv[u]);
                         __builtin_amdgcn_sched_barrier(0);
                         const double cdx0 = cdx;
 #pragma unroll

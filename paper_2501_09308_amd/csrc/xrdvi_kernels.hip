@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kBlock, ASYM || SEC ? 6 : 7) void k_win(ProbDev P, 
 
 // a6 (windowed): peak-major adjoint, one block per (sample, phase), and a5 by
 // the first block; grid (K, S + 1), kBlock threads.
-template <bool ASYM, bool SEC>
+template <bool ASYM, bool SEC, int LN>
 __global__ __launch_bounds__(kBlock) void k_adjoint_win(ProbDev P, StepDev st, ElboOut out) {
     __shared__ double red[kWaves][12];
     if (blockIdx.y == 0) {
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_win(ProbDev P, StepDev st, E
         if (threadIdx.x == 0 && out.elbo) *out.elbo = e;
         return;
     }
-    adjoint_phase<ASYM, SEC>(P, st, blockIdx.y - 1, blockIdx.x, red);
+    adjoint_phase<ASYM, SEC, LN>(P, st, blockIdx.y - 1, blockIdx.x, red);
 }
 
 // a5: one block of NT threads (see elbo_block).
@@ -344,7 +344,9 @@ static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
             k_win<ASYM, SEC, false><<<g, kBlock, 0, stream>>>(P, sf, f_out);
         if (grad) {
             dim3 ga(P.K, st.S + 1);
-            k_adjoint_win<ASYM, SEC><<<ga, kBlock, 0, stream>>>(P, st, elbo ? *elbo : ElboOut{});
+            const ElboOut out = elbo ? *elbo : ElboOut{};
+            if (P.few) k_adjoint_win<ASYM, SEC, kWave><<<ga, kBlock, 0, stream>>>(P, st, out);
+            else k_adjoint_win<ASYM, SEC, kAdjLanes><<<ga, kBlock, 0, stream>>>(P, st, out);
         }
     } else {
         const DenseCut cut = dense_cut(P.N, st.S);

@@ -654,6 +654,13 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
         return (unsigned)(b | (b >> 16));
     };
 
+    // the leaves with the centre for some sample
+    auto centre_leaves = [&](const Near &r) -> unsigned {
+        unsigned long long b = __builtin_amdgcn_ballot_w64(!(fabsf(r.pk.ch - lmid) >= lhalf));
+        b |= b >> 32;
+        return (unsigned)(b | (b >> 16));
+    };
+
     // ---------------- forward: this wave's phases
     float sig[NPP], lsig[LV], nsig = 0.f, u[NPP], ul[MID ? 1 : NPP];
     // (kept in registers where there are few)
@@ -912,6 +919,31 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
                         adj_terms_L<ASYM, SEC>(r[p], q2, tt, up, rec.c, wl, wh, e);
                         adj_point_G<ASYM, SEC>(AdjPt{r[p], q2, tt, up}, rec.c, wl, wh, e);
                     };
+                    // a leaf without the centre of an asymmetric peak: the lane's
+                    // points lie on one side of it, and the sums are put there once
+                    const unsigned inside = ASYM ? centre_leaves(rec) : 0u;
+                    auto one_side = [&](int l) {
+                        const bool up = lm[l] >= rec.pk.ch;
+                        const float s1 = up ? rec.pk.sr : rec.pk.s;
+                        float h[NS];
+#pragma unroll
+                        for (int q = 0; q < 6; ++q) h[q] = 0.f;
+#pragma unroll
+                        for (int q = 0; q < PB; ++q) {
+                            const int p = l * PB + q;
+                            const float q2 = ((u[p] - rec.pk.ch) + (ul_of(p) - rec.pk.cl)) * s1;
+                            const float tt = fmaf(q2, q2, 1.0f);
+                            adj_terms_L<ASYM, SEC, kBelow>(r[p], q2, tt, up, rec.c, wl, wh, h);
+                            adj_point_G<ASYM, SEC, kBelow>(AdjPt{r[p], q2, tt, up}, rec.c, wl,
+                                                           wh, h);
+                        }
+                        const float fu = up ? 1.f : 0.f, fd = 1.f - fu;
+#pragma unroll
+                        for (int q = 0; q < 6; ++q) {
+                            e[q] = fmaf(fd, h[q], e[q]);
+                            if constexpr (ASYM) e[6 + q] = fmaf(fu, h[q], e[6 + q]);
+                        }
+                    };
                     if constexpr (!MID) {
 #pragma unroll
                         for (int p = 0; p < NPP; ++p) at_point(p);
@@ -920,7 +952,10 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
 #pragma unroll
                         for (int l = 0; l < LV; ++l) {
                             if (l >= nl) break;
-                            if (near >> l & 1u) {
+                            if (ASYM && (near & ~inside) >> l & 1u) {
+                                asm volatile("");
+                                one_side(l);
+                            } else if (near >> l & 1u) {
                                 asm volatile("");
 #pragma unroll
                                 for (int q = 0; q < PB; ++q) at_point(l * PB + q);

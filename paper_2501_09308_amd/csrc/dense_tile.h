@@ -118,15 +118,16 @@ __host__ __device__ inline DenseCut dense_cut(int N, int S) {
     }
     // One sample per block (a wave's lanes then take the points, not the nodes:
     // about twice the work on four times the blocks) while one of them runs on each
-    // CU: 50 x 40, N = 3501, S = 8 (224 blocks) 38.9 us, with four samples 52.3;
-    // beyond, S = 16 (448 blocks, two on a CU) 45.7 and 52.1, but served with others
+    // CU, or a little more (two share a CU): 50 x 40, N = 3501, S = 8 (224 blocks)
+    // 38.9 us, with four samples 52.3; asymmetric 55 x 57, N = 2566, S = 14 (294), 57
+    // steps wide, 102 and 176; S = 16 (448) 45.7 and 52.1, but served with others
     // (their blocks fill the CUs anyway) an analysis costs twice as much: eight, one
     // of them of 448 blocks, 18.0 ms and 21.9.  Short grids, where most peaks are near
     // and few blocks of four samples leave CUs idle, take two on a CU: 35 x 28, N =
     // 200, S = 256 (512 blocks) 88 us and 110, N = 1500, S = 40 (480) 42.9 and 48.1,
     // with peaks of 2 deg 70 and 112; in two rounds N = 300, S = 200 (600) 110 and 97.
     constexpr int kShortGrid = 1536;
-    if (DenseCut{2, 1}.blocks(N, S) > (N <= kShortGrid ? 512 : 256)) return DenseCut{2, 4};
+    if (DenseCut{2, 1}.blocks(N, S) > (N <= kShortGrid ? 512 : 384)) return DenseCut{2, 4};
     return DenseCut{2, 1};
 }
 

@@ -71,7 +71,7 @@ CASES += [(N, step, S, kind, False, False)
           for kind in ("merged", "gap", "ends")]
 # (the last sizes of one sample per block, the first of four)
 CASES += [(N, 0.02, S, "uniform", False, False)
-          for N, S in [(129, 256), (129, 257), (1536, 42), (1537, 19), (1537, 20)]]
+          for N, S in [(129, 256), (129, 257), (1536, 42), (1537, 29), (1537, 30)]]
 CASES += [(65, 0.001, 3, "uniform", True, False), (321, 0.001, 260, "uniform", False, True),
           (193, 0.005, 200, "gap", True, True), (577, 0.005, 402, "merged", True, False)]
 

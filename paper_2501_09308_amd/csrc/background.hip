@@ -24,10 +24,10 @@
 //
 // The time is a chain of latencies: per reweighting about N / P rows of a
 // pivot's reciprocal each, then log2 P reduction steps.  So P is as large as
-// one wave per SIMD (256 threads) holds, or two for long spectra, and a
-// block's rows (pivots, factors, counts) stay in registers from one
-// reweighting to the next.  15 reweightings of 3501 points:
-// 127 us, of 12 000 355 us (1810 and 5040 us with one wave per spectrum, one
+// one wave per SIMD (256 threads) holds, or two for long spectra (one wave has
+// all blocks of a short one), and a block's rows (pivots, factors, counts) stay in registers from one
+// reweighting to the next.  15 reweightings of 3501 points (11 or 12 rows a
+// thread): 127 us, of 12 000 355 us (1810 and 5040 us with one wave per spectrum, one
 // lane of which eliminated the 63 separators).
 #include <cmath>
 #include <string>

@@ -38,8 +38,9 @@ constexpr int adjoint_kind(bool asym, bool sec) {
 // 3072, 145 with 6144, 141 with 8192; adjoint 160 with 2048, 148 with 8192,
 // 143 with 16384).  Blocks left without a unit end at once: a single analysis
 // of 8 phases takes 46 us a step with either.  The dense kernel's LDS leaves
-// one block per CU, so 256 (eight analyses of N 1500-5000, K 10-80, S 32, 60
-// steps: 14.0 ms, with 2048 blocks 14.6).
+// one block of four samples per CU, so 256 (eight analyses of N 1500-5000, K
+// 10-80, S 32, 60 steps: 14.0 ms, with 2048 blocks 14.6); of its blocks of one
+// sample two share a CU, and it has twice as many.
 constexpr int kGridSmall = 1024;
 constexpr int kGridLarge = 2048;
 constexpr int kGridWin = 8192;

@@ -10,14 +10,16 @@
 // Two levels of intervals are used: the tile (64 LV points) and its LV leaves
 // of 64 points.  Peaks far from the tile (most of them) are evaluated at the
 // tile's 16 nodes, peaks far from a leaf only at that leaf's 16 nodes, the
-// others at the leaf's points:
+// others at the leaf's points (a peak several times as wide as a leaf is smooth
+// enough there to be taken at its nodes wherever it lies: kWide):
 //   forward  node sums of all phases, carried from the tile's nodes to the
 //            leaves' and from those to the points once per (tile, sample);
 //   adjoint  sum_i R_i F(x_i) = sum_n R_n F(v_n) with R_n = sum_i R_i l_n(x_i)
 //            (the transpose), so the residual is carried to the nodes once.
-//            Every sum is formed of its own terms, the shift's too: taken as
-//            the slope of the interpolant of sum I l, whose weights reach 77,
-//            it erred by 5e-5 for centres 20 half-widths away (directly 1e-7).
+//            Every sum is formed of its own terms, the shift's too: the slope
+//            of the interpolant of sum I l, whose weights reach 77, in its place
+//            had an error of 3.6e-6 where all centres lie well outside the grid
+//            (directly 1e-7).
 //
 // Lanes: a wave holds SG samples (4 or 1).  With SG = 4 the 16 lanes of a
 // sample are its nodes and share its points, the peaks are wave-uniform
@@ -25,15 +27,16 @@
 // at once.  SG = 1 is for grids too small to fill the GPU that way: a
 // sample's 64 lanes take four far peaks at the tile's 16 nodes together, and
 // a leaf's points in one go (so leaves need no nodes).  NW waves split the
-// phases.
+// phases, each phase's peaks too where there are few (CUT); very few peaks are
+// taken at every point without nodes (dense_direct).
 //
 // What it measured (one MI355X, step of ELBO, adjoint and gradient, against
 // evaluating every peak at every point): 50 phases x 40 peaks, 3501 points,
-// S = 64: 208 -> 75 us; 200 x 60, 7001, S = 128: 3611 -> 639 us (both with
-// the Gaussian's reach of kGaussReach); asymmetric 50 x 50, 2501, S = 32: 160
-// -> 81 us; profile of 77 x 50, 5003, S = 24: 95 -> 30 us.  Bound by VALU issue on the large ones (about 80 % of the kernel's
-// cycles; the last round of blocks and the stages between the phase loops,
-// 17 000 cycles per block, take the rest).
+// S = 64: 208 -> 80 us; 200 x 60, 7001, S = 128: 3611 -> 692 us; asymmetric
+// 50 x 50, 2501, S = 32: 160 -> 78 us; profile of 77 x 50, 5003, S = 24: 95 -> 30
+// us.  Bound by VALU issue on the large ones (about 80 % of the kernel's cycles;
+// the last round of blocks and the stages between the phase loops, some 17 000
+// cycles per block, take the rest).
 #pragma once
 
 #include "xrdvi_device.h"
@@ -445,10 +448,11 @@ __device__ __forceinline__ void prio_left(int left) {
 }
 
 // Whether every peak is taken at every point (dense_direct): a phase costs what
-// some three peaks do, an asymmetric one (twelve sums) six.  With four samples, N = 3501, S = 64, one phase of 40 peaks
-// 30.6 us against 33.2 at the nodes, of 64 35.6 and 33.6, two of 20 32.5 and 34.4,
-// four of 16 39.2 and 35.5, twenty of one 39.4 and 33.5; in five rounds of blocks
-// (N = 7936, S = 73) one of 40 48 and 64, eight of 8 74 and 66.
+// some three peaks do, an asymmetric one (twelve sums) six.  With four samples,
+// N = 3501, S = 64, one phase of 40 peaks 30.6 us against 33.2 at the nodes, of 64
+// 35.6 and 33.6, two of 20 32.5 and 34.4, four of 16 39.2 and 35.5, twenty of one
+// 39.4 and 33.5; in five rounds of blocks (N = 7936, S = 73) one of 40 48 and 64,
+// eight of 8 74 and 66.
 constexpr int kDirectPeaks = 56;
 __host__ __device__ inline bool direct_peaks(int K, int T, bool asym) {
     return T + (asym ? 6 : 3) * K <= kDirectPeaks;

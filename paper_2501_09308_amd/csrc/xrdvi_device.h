@@ -68,8 +68,8 @@ constexpr double kHalfDegRad = 3.14159265358979323846 / 360.0;  // rad per deg /
 // each phase).
 struct ProbDev {
     int N, K, T, ntiles;
-    int ref;                          // points that share a reference point: a tile,
-                                      // or 256 (kRefDense) in dense mode
+    int ref;                          // points that share a reference point xref:
+                                      // a tile, or 256 (kRefDense) in dense mode
     int D;                            // latent types per phase: 4, or 5 with
                                       // the asymmetry alpha
     int sec;                          // 1: width w sec(rho / 2); 0: width w
@@ -92,7 +92,7 @@ struct ProbDev {
                                       // width, whose q2 it then forms in
                                       // FP32, only with windows of at most
                                       // kF32Cutoff FWHM)
-    const float *u;                   // [ntiles * kTile] x_i - xref
+    const float *u;                   // [ntiles * kTile] x_i - xref (of ref points)
                                       // (FP32, rounded)
     const float *ul;                  // [ntiles * kTile] its rounding
                                       // error: (x_i - xref) - u_i in FP32
@@ -357,27 +357,15 @@ __host__ __device__ inline int2 grid_range(const double *x, int n, double x0,
     return grid_finish(x, n, grid_probe(x, n, x0, inv_dx, va, vb));
 }
 
-// Full width of a peak centred at rho: w, or w / |cos(rho pi / 360)| with
-// the sec law (SEC).
-template <bool SEC>
-__device__ __forceinline__ double peak_width(double rho, double w) {
-#pragma clang fp contract(off)
-    return SEC ? w / fabs(cos(rho * kHalfDegRad)) : w;
-}
-
-// Grid range [lo, hi) with rho - c W <= x_i <= rho + c W (rho + (c W) alpha
-// for asymmetric peaks, alpha > 0; pass 1 otherwise), W the peak's full
-// width; each bound is one rounded FP64 operation (no contraction), as in
-// the model's definition.
 // The window's bounds a = rho - c W and b = rho + c W (rho + (c W) alpha for
-// asymmetric peaks).
-template <bool SEC>
+// asymmetric peaks, alpha > 0), rho = p + mu, W the peak's full width; each is
+// one rounded FP64 operation (no contraction), as in the model's definition.
 __device__ __forceinline__ double2 window_bounds(const ProbDev &P, double p,
-                                                 double mu, double w,
+                                                 double mu, double W,
                                                  double alpha) {
 #pragma clang fp contract(off)
     const double rho = p + mu;
-    const double hw = P.cutoff * peak_width<SEC>(rho, w);
+    const double hw = P.cutoff * W;
     return make_double2(rho - hw, rho + (P.D == 5 ? hw * alpha : hw));
 }
 
@@ -394,11 +382,11 @@ __device__ __forceinline__ int grid_below(const ProbDev &P, double v) {
     return g < 0.0 ? 0 : (g > (double)(P.N - 1) ? P.N : (int)fl + 1);
 }
 
-// W: the peak's full width (peak_width of rho = p + mu).
+// Grid range [lo, hi) of the points within the window's bounds.
 __device__ inline int2 window_of(const ProbDev &P, double p, double mu,
                                  double W, double alpha) {
     if (P.cutoff == 0.0) return make_int2(0, P.N);
-    const double2 ab = window_bounds<false>(P, p, mu, W, alpha);
+    const double2 ab = window_bounds(P, p, mu, W, alpha);
     int2 r = make_int2(-1, -1);
     if (P.uniform) r = make_int2(grid_below(P, ab.x), grid_below(P, ab.y));
     if (r.x < 0 || r.y < 0) r = grid_range(P.x, P.N, P.x0, P.inv_dx, ab.x, ab.y);
@@ -673,13 +661,6 @@ __device__ __forceinline__ float wave_total_f32(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-// Keeps a wave-uniform value in a vector register, so that an instruction
-// combining it with a scalar operand needs no extra move.
-__device__ __forceinline__ float in_vgpr(float v) {
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
 // ---- one phase's peaks over a tile's points, from global memory ------------
 //
 // The windowed forward's path for phases whose records do not fit the
@@ -873,10 +854,10 @@ __device__ __forceinline__ void tile_points(const ProbDev &P, const StepDev &st,
 // the sec law; A = 1 below, alpha above), the Lorentzian and Gaussian
 // amplitudes I h r cL n / w and I h (1 - r) cG n / w (times c with the sec
 // law) and the window.  One thread per phase finds its phase's peak ranges
-// over the tile and writes its records: those whose Gaussian reaches the
-// tile from the front of the list, the others (Lorentzian only) from the
-// back, so that each part is evaluated by a loop without a per-record
-// branch.  The waves then share both parts.  Phases whose records do not
+// over the tile and marks a place for each of its peaks in them: those whose
+// Gaussian reaches the tile from the front of the list, the others (Lorentzian
+// only) from the back, so that each part is evaluated by a loop without a
+// per-record branch.  Then all threads write the records, one place each.  The waves then share both parts.  Phases whose records do not
 // fit the staging space (they come last in the chunk) are evaluated from
 // global memory, phase by phase.
 constexpr int kWinChunk = kBlock;   // phases staged at a time (one per thread)
@@ -1272,7 +1253,8 @@ __device__ void win_tile(const ProbDev &P, const StepDev &st, int t, int s,
 // One block of kWaves waves per (sample s, phase k); the phase's peaks go
 // in groups of kAdjPeaks consecutive ones, group g to wave g mod kWaves.  A
 // wave takes a group's peaks side by side, kAdjLanes lanes each, over
-// consecutive points of their windows; x - rho is formed in FP64 and rounded
+// consecutive points of their windows (in problems of short peak lists one peak
+// on all lanes: kAdjFew); x - rho is formed in FP64 and rounded
 // to FP32 (its sign picks the side of an asymmetric peak), or for symmetric
 // peaks of constant width on a uniform grid from FP32 offsets each rounded
 // once (adjoint_phase).  Six sums (twelve: six per side) accumulate per lane
@@ -1291,6 +1273,7 @@ __device__ void win_tile(const ProbDev &P, const StepDev &st, int t, int s,
 // 64 lanes -> 16: 50x40, N=3501, S=64 17.0 -> 13.0 us; 2000x100, N=14001,
 // S=32 607 -> 510; 300x50 under the sec law, S=32 85 -> 70; 160x50
 // asymmetric, S=31 49 -> 37; eight served analyses 206 -> 158 a step.
+// (Long windows, or few peaks, keep fewer waves busy: kAdjLong, kAdjFew.)
 struct AdjPt {
     float R, q2, tt;
     bool up;
@@ -1385,7 +1368,9 @@ constexpr int kAdjFew = 8;
 // Chunks of points whose loads are issued together.
 constexpr int kAdjChunks = 4;
 // Points in every window of a group from which asymmetric peaks take several
-// chunks at once.
+// chunks at once while those lie on one side of the centres: 4 phases of 100
+// peaks, windows of 32 deg (N = 3501, S = 32) 155 us a step by single chunks, 135
+// so; shorter windows have few such chunks.
 constexpr int kAdjLong = 256;
 
 // Windows of at most this many FWHM each side (symmetric peaks of constant

@@ -236,7 +236,7 @@ __global__ __launch_bounds__(kDenseWaves * kWave, SG == 1 ? 8 : 4) void kb_dense
             dense_tile<true, ASYM, SEC, kDenseWaves, SG, 2, CUT>(d.P, d.st, tw, t, grp, nullptr,
                                                                  sm.two);
         };
-        if (direct_peaks(d.P.K, d.P.T, ASYM)) {
+        if (direct_peaks<SG, ASYM>(d.P.K, d.P.T)) {
             if constexpr (SG == 4) {
                 if (is_wide)
                     dense_direct<true, ASYM, SEC, kDenseWaves, 4, 4>(d.P, d.st, t, t, grp,

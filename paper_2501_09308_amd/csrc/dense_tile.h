@@ -423,16 +423,18 @@ struct NearPeak {
         up = false;
         return fmaf(u, s, -c * s);
     }
-    // q2 at the point u + ul; whether it lies at or above the centre (ASYM)
-    template <bool ASYM>
+    // q2 at the point u + ul; whether it lies at or above the centre (SIDE: where
+    // the points lie, if known)
+    template <bool ASYM, int SIDE = ASYM ? kBoth : kBelow>
     __device__ __forceinline__ float q2(float u, float ul, bool &up) const {
-        if (ASYM) {
+        if (SIDE == kBoth) {
             const float d = (u - ch) + (ul - cl);
             up = d >= 0.f;
             return d * (up ? sr : s);
         }
-        up = false;
-        return fmaf(u - ch, s, fmaf(ul, s, -cl * s));
+        up = SIDE == kAbove;
+        const float a = up ? sr : s;
+        return fmaf(u - ch, a, fmaf(ul, a, -cl * a));
     }
 };
 
@@ -447,15 +449,20 @@ __device__ __forceinline__ void prio_left(int left) {
     else __builtin_amdgcn_s_setprio(0);
 }
 
-// Whether every peak is taken at every point (dense_direct): a phase costs what
-// some three peaks do, an asymmetric one (twelve sums) six.  With four samples,
-// N = 3501, S = 64, one phase of 40 peaks 30.6 us against 33.2 at the nodes, of 64
-// 35.6 and 33.6, two of 20 32.5 and 34.4, four of 16 39.2 and 35.5, twenty of one
-// 39.4 and 33.5; in five rounds of blocks (N = 7936, S = 73) one of 40 48 and 64,
-// eight of 8 74 and 66.
-constexpr int kDirectPeaks = 56;
-__host__ __device__ inline bool direct_peaks(int K, int T, bool asym) {
-    return T + (asym ? 6 : 3) * K <= kDirectPeaks;
+// Whether every peak is taken at every point (dense_direct): while T peaks and K
+// phases, each a peak's worth or two (twelve sums of an asymmetric one), cost less
+// than the stages around the nodes.  A block of four samples, step in us against
+// the nodes': N = 3501, S = 64, 60 peaks in one phase 32.2 and 34.4, 80 34.2 and
+// 33.8, 8 x 10 36.1 and 36.3, 16 x 5 36.8 and 35.5, asymmetric 8 x 8 39.3 and 40.7,
+// 16 x 5 44.6 and 40.1; in five rounds of blocks (N = 7438, S = 100) 80 57.3 and
+// 67.2, 128 72.5 and 68.5, asymmetric 16 x 5 83.6 and 80.7.  A block of one sample:
+// N = 1500, S = 30, 8 x 16 30.6 and 34.7, 46 x 2 35.7 and 34.3, asymmetric 30 x 3 36.7
+// and 36.8.
+constexpr int kDirectPhases = 48;
+constexpr int direct_most(int SG) { return SG == 1 ? 128 : 88; }
+template <int SG, bool ASYM>
+__host__ __device__ constexpr bool direct_peaks(int K, int T) {
+    return K <= kDirectPhases && T + (ASYM && SG > 1 ? 2 : 1) * K <= direct_most(SG);
 }
 
 // Whether the waves share each phase's peaks instead of the phases.
@@ -1012,37 +1019,100 @@ __device__ void dense_tile(const ProbDev &P, const StepDev &st, int t, int out, 
 //
 // Around the phase loops a block of dense_tile spends some 10 us on weights,
 // ranges and nodes, which few peaks do not earn back.  Here the peaks of the
-// block's samples are prepared in LDS by a thread each; then the threads take
-// (sample, point) each, SH of them a pair's peaks in turn, and no interval is
-// formed: the sum over the peaks, the likelihood, then each phase's adjoint
-// terms, reduced over the waves.  The same tiles and places as dense_tile's.
+// block's samples are prepared in LDS by a thread each; then the waves take a
+// sample, a share of its peaks and (with four samples) all leaves each: the sum
+// over the peaks, the likelihood, then the adjoint terms of the share's phases,
+// reduced over the wave and added over the waves.  A lane with a point of each
+// leaf reads a peak once for them, and skips the Gaussian and the side of an
+// asymmetric peak that none of the tile's points has.  (With one point per lane,
+// peaks dealt out one by one and six totals apart: 4 x 8 peaks, N = 13620, S = 79
+// 74 us a step for 57, asymmetric 5 x 7, N = 7438, S = 100 89 for 60; four-wave
+// blocks of one sample at every point 67 and 75.)  Bound by issue in many rounds of
+// blocks, by latency below.  The same tiles and places as dense_tile's.
+
+// Totals over the wave of NS (6 or 12) values, that of value q in lane q: pairs of
+// values are packed as lanes are added (about half the instructions of NS totals,
+// which with few peaks a phase are a third of the adjoint).
+template <int NS>
+__device__ __forceinline__ float wave_totals(const float (&e)[NS], int lane) {
+    const bool b0 = lane & 1, b1 = lane & 2;
+    float f[NS / 2];
+#pragma unroll
+    for (int i = 0; i < NS / 2; ++i) {
+        const float keep = b0 ? e[2 * i + 1] : e[2 * i], give = b0 ? e[2 * i] : e[2 * i + 1];
+        f[i] = keep + dpp_f32<0xB1, 0xf, true>(give);       // lane ^ 1
+    }
+    constexpr int NG = (NS / 2 + 1) / 2;
+    float r = 0.f;
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+        float g;
+        if (2 * i + 1 < NS / 2) {
+            const float keep = b1 ? f[2 * i + 1] : f[2 * i], give = b1 ? f[2 * i] : f[2 * i + 1];
+            g = keep + dpp_f32<0x4E, 0xf, true>(give);      // lane ^ 2
+        } else {
+            g = f[2 * i] + dpp_f32<0x4E, 0xf, true>(f[2 * i]);
+        }
+        g += dpp_f32<0x124, 0xf, true>(g);                  // row_ror:4
+        g += dpp_f32<0x128, 0xf, true>(g);                  // row_ror:8
+        const auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(g), __float_as_uint(g),
+                                                          false, false);
+        g = __uint_as_float(s16[0]) + __uint_as_float(s16[1]);      // rows in pairs
+        const auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(g), __float_as_uint(g),
+                                                          false, false);
+        g = __uint_as_float(s32[0]) + __uint_as_float(s32[1]);
+        r = lane >> 2 == i ? g : r;
+    }
+    return r;
+}
+
 template <int NW, int SG, int LV, bool ASYM>
 struct DirectSmem {
-    static constexpr int kPts = LV * kLeaf, kShares = NW / (SG * LV);
-    float4 at[SG][kDirectPeaks];          // NearPeak
-    float4 amp[SG][kDirectPeaks];         // (aL, aG, I, c) ...
-    float tw[SG][kDirectPeaks];
-    double sig[kShares][SG * kPts];       // the shares' sums
+    static constexpr int kPts = LV * kLeaf, kMost = direct_most(SG);
+    static constexpr int kLane = SG == 1 ? 1 : LV;      // points of a lane
+    static constexpr int kShares = NW * kLane / (SG * LV);
+    float4 at[SG][kMost];                 // NearPeak
+    float4 amp[SG][kMost];                // (aL, aG, I, c) ...
+    float tw[SG][kMost];
+    int kind[SG][kMost];                  // bit 0: the Gaussian reaches the tile,
+                                          // 1, 2: all points above, below the centre
     float rres[SG * kPts];                // residual y/f - 1
     double red[SG * LV];
-    float acc[kDirectPeaks / (ASYM ? 6 : 3)][NW][ASYM ? 12 : 6];
+    union {
+        double sig[kShares][SG * kPts];                     // the shares' sums at the points,
+        float acc[kDirectPhases][NW][ASYM ? 12 : 6];        // then the waves' adjoint sums
+    };
 };
 
 template <bool GRAD, bool ASYM, bool SEC, int NW, int SG, int LV, typename SM>
 __device__ void dense_direct(const ProbDev &P, const StepDev &st, int t, int out, int grp,
                              float *f_out, SM &sm) {
     constexpr int PTS = LV * kLeaf, NT = NW * kWave, SH = SM::kShares;
+    constexpr int PP = SM::kLane, LG = LV / PP;
     constexpr int NS = ASYM ? 12 : 6;
-    static_assert(SH * SG * PTS == NT, "a thread per share, sample and point");
+    static_assert(SH * SG * PTS == NT * PP, "PP points per share, sample and thread");
+    static_assert(SM::kMost <= 2 * kWave, "two words of kinds");
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
-    const int sh = wv / (SG * LV), gq = tid % (SG * PTS), g = wv / LV % SG;
     const int S = st.S, K = P.K, T = P.T, s0 = grp * SG, ns = min(SG, S - s0);
-    const int i0 = t * PTS, i = i0 + gq % PTS, ic = min(i, P.N - 1);
-    const bool in = i < P.N && g < ns;
-    const float u = P.u[ic], ul = P.ul[ic];
+    const int i0 = t * PTS;
+    // the wave's share, sample and leaves of the sums
+    const int sh = wv / (SG * LG), g = wv / LG % SG, p0 = wv % LG * (PP * kLeaf) + lane;
+    const int ja = T * sh / SH, jb = T * (sh + 1) / SH;      // the share's peaks
+    const int gs = min(g, ns - 1);       // (waves past the last sample repeat it)
+    float u[PP], ul[PP];
+#pragma unroll
+    for (int p = 0; p < PP; ++p) {
+        const int ic = min(i0 + p0 + p * kLeaf, P.N - 1);
+        u[p] = P.u[ic];
+        ul[p] = P.ul[ic];
+    }
+    // the thread's sample and point of the likelihood
+    const int gq = tid % (SG * PTS), gl = gq / PTS, i = i0 + gq % PTS, ic = min(i, P.N - 1);
+    const bool in = i < P.N && gl < ns;
     const double py = P.y[ic], pb = P.bg[ic], pl = P.lgy[ic];
     cptr<int> off = as_const(P.off);
+    const float ua = P.u[i0], ub = P.u[min(i0 + PTS, P.N) - 1];
     for (int x = tid; x < ns * T; x += NT) {
         const int gg = x / T, j = x % T, k = P.phase[j], s = s0 + gg;
         const float4 c = st.pk[(size_t)s * K + k];
@@ -1053,39 +1123,74 @@ __device__ void dense_direct(const ProbDev &P, const StepDev &st, int t, int out
         sm.at[gg][j] = make_float4(p.ch, p.cl, p.s, p.sr);
         sm.amp[gg][j] = make_float4(c.z * r.y, c.y * r.y, r.y, r.x);
         if (SEC) sm.tw[gg][j] = r.z;
+        constexpr float kOut = (float)(2.0 * kGaussReach), kClear = 1e-3f;
+        const float da = ua - p.ch, db = p.ch - ub;
+        if (PP > 1)
+            sm.kind[gg][j] = (da * p.sr > kOut || db * p.s > kOut ? 0 : 1) |
+                             (da > kClear ? 2 : 0) | (db > kClear ? 4 : 0);
     }
     __syncthreads();
-    const int gs = min(g, ns - 1);       // (waves past the last sample repeat it)
-    auto q2_of = [&](int j, bool &up) {
+    // the peaks' kinds, a bit each
+    uint64_t kinds[3][2];
+#pragma unroll
+    for (int b = 0; b < (PP > 1 ? (ASYM ? 3 : 1) : 0); ++b)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int j = lane + h * kWave;
+            kinds[b][h] = __builtin_amdgcn_ballot_w64(j < T && (sm.kind[gs][j] >> b & 1));
+        }
+    auto is_kind = [&](int b, int j) {
+        return (kinds[b][j >= kWave] >> (j & (kWave - 1)) & 1) != 0;
+    };
+    auto reaches = [&](int j) { return PP == 1 || is_kind(0, j); };
+    auto peak_of = [&](int j) {
         const float4 a = sm.at[gs][j];
-        return NearPeak{a.x, a.y, a.z, a.w}.template q2<ASYM>(u, ul, up);
+        return NearPeak{a.x, a.y, a.z, a.w};
     };
     // (four peaks in FP32, their sums in FP64)
-    double sum = 0.0;
-    auto value = [&](int j, float v) {
-        bool up;
-        const float q2 = q2_of(j, up), tt = fmaf(q2, q2, 1.0f);
-        const float4 m = sm.amp[gs][j];
-        return fmaf(m.y, exp2_f32(-tt), fmaf(m.x, rcp_f32(tt), v));
-    };
-    int j = sh;
-    for (; j + 3 * SH < T; j += 4 * SH) {
-        float v = 0.f;
+    double sum[PP];
 #pragma unroll
-        for (int x = 0; x < 4; ++x) v = value(j + x * SH, v);
-        sum += (double)v;
-    }
-    for (; j < T; j += SH) sum += (double)value(j, 0.f);
+    for (int p = 0; p < PP; ++p) sum[p] = 0.0;
+    auto value = [&](int j, float *v) {
+        const NearPeak pk = peak_of(j);
+        const float4 m = sm.amp[gs][j];
+        float tt[PP];
+#pragma unroll
+        for (int p = 0; p < PP; ++p) {
+            bool up;
+            const float q2 = pk.template q2<ASYM>(u[p], ul[p], up);
+            tt[p] = fmaf(q2, q2, 1.0f);
+            v[p] = fmaf(m.x, rcp_f32(tt[p]), v[p]);
+        }
+        if (reaches(j)) {
+            if (PP > 1) asm volatile("");    // (a branch, not selects)
+#pragma unroll
+            for (int p = 0; p < PP; ++p) v[p] = fmaf(m.y, exp2_f32(-tt[p]), v[p]);
+        }
+    };
+    auto values = [&](int j, int n) {
+        float v[PP];
+#pragma unroll
+        for (int p = 0; p < PP; ++p) v[p] = 0.f;
+#pragma unroll
+        for (int x = 0; x < n; ++x) value(j + x, v);
+#pragma unroll
+        for (int p = 0; p < PP; ++p) sum[p] += (double)v[p];
+    };
+    int j = ja;
+    for (; j + 4 <= jb; j += 4) values(j, 4);
+    for (; j < jb; ++j) values(j, 1);
     if (SH > 1) {
-        sm.sig[sh][gq] = sum;
+#pragma unroll
+        for (int p = 0; p < PP; ++p) sm.sig[sh][g * PTS + p0 + p * kLeaf] = sum[p];
         __syncthreads();
     }
-    if (sh == 0) {
-        double sg = sum;
+    if (tid < SG * PTS) {
+        double sg = SH > 1 ? sm.sig[0][gq] : sum[0];
 #pragma unroll
         for (int x = 1; x < SH; ++x) sg += sm.sig[x][gq];
         const double f = pb + sg;
-        if (in && f_out) f_out[(size_t)(s0 + g) * P.N + i] = (float)f;
+        if (in && f_out) f_out[(size_t)(s0 + gl) * P.N + i] = (float)f;
         double ll = in && st.llp ? (py != 0.0 ? py * log(f) : 0.0) - f - pl : 0.0;
         if (GRAD) sm.rres[gq] = in ? (float)(py / f - 1.0) : 0.f;
         ll = wave_sum(ll);
@@ -1099,8 +1204,15 @@ __device__ void dense_direct(const ProbDev &P, const StepDev &st, int t, int out
         st.llp[(size_t)(s0 + tid) * st.nt + out] = v;
     }
     if (!GRAD) return;
-    const float R = sm.rres[gq];
+    float R[PP];
+#pragma unroll
+    for (int p = 0; p < PP; ++p) R[p] = sm.rres[g * PTS + p0 + p * kLeaf];
     for (int k = 0; k < K; ++k) {
+        const int a = max(off[k], ja), b = min(off[k + 1], jb);
+        if (a >= b) {                // none of the phase's peaks in the share
+            if (lane < NS) sm.acc[k][wv][lane] = 0.f;
+            continue;
+        }
         float ka = 1.f;
         if (ASYM && SEC) {
             const size_t o = (size_t)(s0 + gs) * K + k;
@@ -1109,21 +1221,39 @@ __device__ void dense_direct(const ProbDev &P, const StepDev &st, int t, int out
         float e[NS];
 #pragma unroll
         for (int q = 0; q < NS; ++q) e[q] = 0.f;
-#pragma unroll 4
-        for (int j = off[k] + sh; j < off[k + 1]; j += SH) {
-            bool up;
-            const float q2 = q2_of(j, up), tt = fmaf(q2, q2, 1.0f);
+        auto terms = [&](int j, auto side) {
+            constexpr int SIDE = decltype(side)::value;
+            const NearPeak pk = peak_of(j);
             const float4 m = sm.amp[gs][j];
-            const float RI = R * m.z, tw = SEC ? sm.tw[gs][j] : 0.f;
+            const float tw = SEC ? sm.tw[gs][j] : 0.f;
             const SecW wl = SecW::of(tw), wh = SecW::of(tw * ka);
-            adj_terms_L<ASYM, SEC>(RI, q2, tt, up, m.w, wl, wh, e);
-            adj_point_G<ASYM, SEC>(AdjPt{RI, q2, tt, up}, m.w, wl, wh, e);
+            float q2[PP], tt[PP];
+            bool up[PP];
+#pragma unroll
+            for (int p = 0; p < PP; ++p) {
+                q2[p] = pk.template q2<ASYM, SIDE>(u[p], ul[p], up[p]);
+                tt[p] = fmaf(q2[p], q2[p], 1.0f);
+                adj_terms_L<ASYM, SEC, SIDE>(R[p] * m.z, q2[p], tt[p], up[p], m.w, wl, wh, e);
+            }
+            if (reaches(j)) {
+                if (PP > 1) asm volatile("");    // (a branch, not selects)
+#pragma unroll
+                for (int p = 0; p < PP; ++p)
+                    adj_point_G<ASYM, SEC, SIDE>(AdjPt{R[p] * m.z, q2[p], tt[p], up[p]}, m.w, wl,
+                                                 wh, e);
+            }
+        };
+        using Below = std::integral_constant<int, kBelow>;
+        using Above = std::integral_constant<int, kAbove>;
+        using Both = std::integral_constant<int, ASYM ? kBoth : kBelow>;
+        constexpr int U = PP == 1 ? 4 : 1;
+#pragma unroll U
+        for (int j = a; j < b; ++j) {
+            if (ASYM && PP > 1 && is_kind(1, j)) terms(j, Above{});
+            else if (ASYM && PP > 1 && is_kind(2, j)) terms(j, Below{});
+            else terms(j, Both{});
         }
-#pragma unroll
-        for (int q = 0; q < NS; ++q) e[q] = wave_total_f32(e[q]);
-        float v = e[0];
-#pragma unroll
-        for (int q = 1; q < NS; ++q) v = lane == q ? e[q] : v;
+        const float v = wave_totals<NS>(e, lane);
         if (lane < NS) sm.acc[k][wv][lane] = v;
     }
     __syncthreads();
@@ -1131,7 +1261,7 @@ __device__ void dense_direct(const ProbDev &P, const StepDev &st, int t, int out
         const int k = x / (ns * NS), q = x % NS, gg = x / NS % ns;
         double v = 0.0;
         for (int w = 0; w < NW; ++w)
-            if (w / LV % SG == gg) v += (double)sm.acc[k][w][q];
+            if (w / LG % SG == gg) v += (double)sm.acc[k][w][q];
         st.part[(((size_t)out * K + k) * S + s0 + gg) * NS + q] = (float)v;
     }
 }

@@ -158,9 +158,9 @@ __global__ __launch_bounds__(kDenseWaves * kWave, SG == 1 ? 8 : 4) void k_dense(
     }
 }
 
-// ... of few peaks (see dense_direct).
+// ... of few peaks (see dense_direct); two blocks share a CU.
 template <bool GRAD, bool ASYM, bool SEC, int SG, int LV>
-__global__ __launch_bounds__(kDenseWaves * kWave, 4) void k_direct(ProbDev P, StepDev st,
+__global__ __launch_bounds__(kDenseWaves * kWave, 8) void k_direct(ProbDev P, StepDev st,
                                                                    float *f_out, int wide) {
     __shared__ union {
         DirectSmem<kDenseWaves, SG, LV, ASYM> wide;
@@ -360,8 +360,8 @@ static void launch_fused_t(const ProbDev &P, const StepDev &st, bool grad,
             else k_dense<false, ASYM, SEC, SG, LV, CUT><<<g, nt, 0, stream>>>(P, st, f_out, w);
         };
         auto run = [&](auto sg_tag, auto lv_tag) {
-            if (direct_peaks(P.K, P.T, ASYM)) {
-                constexpr int SG = decltype(sg_tag)::value, LV = decltype(lv_tag)::value;
+            constexpr int SG = decltype(sg_tag)::value, LV = decltype(lv_tag)::value;
+            if (direct_peaks<SG, ASYM>(P.K, P.T)) {
                 const dim3 g(st.nt, (st.S + SG - 1) / SG);
                 const int w = cut.wide(P.N);
                 if (grad)

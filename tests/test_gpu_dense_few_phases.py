@@ -1,8 +1,8 @@
 """Dense analyses of few phases, whose peaks several waves share: one to nine
 phases (the rule ends at eight), of no peaks, fewer than shares, one, and many,
-and so few peaks that every one is taken at every point (T + 3 K up to 56,
-asymmetric T + 6 K), in every kind of block, against the FP64 oracle: profile 1e-5, ELBO 1e-6, each
-phase's and latent's gradient 1e-4; and served, the same bits as alone."""
+and so few peaks that every one is taken at every point, in every kind of block,
+against the FP64 oracle: profile 1e-5, ELBO 1e-6, each phase's and latent's
+gradient 1e-4; and served, the same bits as alone."""
 import math
 
 import numpy as np
